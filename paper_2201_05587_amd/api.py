@@ -154,6 +154,7 @@ def _load():
 
 
 lib = _load()
+from . import _ttcall  # noqa: E402  (after torch and libtt: the operator calls, marshalled in native code)
 
 
 class TTError(RuntimeError):
@@ -263,7 +264,7 @@ def _ptr(t):
 
 
 def _stream():
-    return c_void_p(_torch().cuda.current_stream().cuda_stream)
+    return _ttcall.stream()
 
 
 def torch_dtype(dtype):
@@ -276,28 +277,15 @@ def workspace_bytes(sched, cls, shape) -> int:
     return int(plan.workspace_bytes) if plan.status == TT_OK else 0
 
 
-def _ws_for(sched, cls, shape, ws):
-    if ws is not None:
-        return ws
-    need = workspace_bytes(sched, cls, shape)
-    if need == 0:
-        return None
-    return _torch().empty(need, dtype=_torch().uint8, device="cuda")
+def _result(out, where):
+    """What the native call returned: the output tensor, or the status of a call that failed."""
+    if type(out) is int:
+        raise TTError(out, where)
+    return out
 
 
 def tt_conv2d_bias_relu(x, w, bias, residual, shape, cls, sched=None, ws=None, y=None):
-    torch = _torch()
-    cs = to_c_shape(shape)
-    ho = (cs.h + 2 * cs.pad_h - cs.r) // cs.stride_h + 1
-    wo = (cs.w + 2 * cs.pad_w - cs.s) // cs.stride_w + 1
-    if y is None:
-        y = torch.empty((cs.n, cs.k, ho, wo), dtype=x.dtype, device=x.device)
-    ws = _ws_for(sched, cls, cs, ws)
-    rc = lib.tt_conv2d_bias_relu(_ptr(x), _ptr(w), _ptr(bias), _ptr(residual), _ptr(y), byref(cs), cls,
-                                 byref(sched) if sched is not None else None, _ptr(ws),
-                                 0 if ws is None else ws.numel() * ws.element_size(), _stream())
-    _check(rc, "tt_conv2d_bias_relu")
-    return y
+    return _result(_ttcall.conv2d(x, w, bias, residual, to_c_shape(shape), cls, sched, ws, y), "tt_conv2d_bias_relu")
 
 
 TT_STATIC_WORKSPACE_BYTES = 16 * 1024 * 1024
@@ -312,41 +300,15 @@ def tt_conv2d_bias_relu_noalloc(x, w, bias, residual, y, shape, cls, sched=None)
 
 
 def tt_dense_bias_relu(x, w, bias, shape, cls, sched=None, ws=None, y=None):
-    torch = _torch()
-    gs = to_c_shape(shape)
-    if y is None:
-        y = torch.empty((gs.m, gs.n), dtype=x.dtype, device=x.device)
-    ws = _ws_for(sched, cls, gs, ws)
-    rc = lib.tt_dense_bias_relu(_ptr(x), _ptr(w), _ptr(bias), _ptr(y), byref(gs), cls,
-                                byref(sched) if sched is not None else None, _ptr(ws),
-                                0 if ws is None else ws.numel() * ws.element_size(), _stream())
-    _check(rc, "tt_dense_bias_relu")
-    return y
+    return _result(_ttcall.dense(x, w, bias, to_c_shape(shape), cls, sched, ws, y), "tt_dense_bias_relu")
 
 
 def tt_batch_matmul(a, b, shape, sched=None, ws=None, c=None):
-    torch = _torch()
-    gs = to_c_shape(shape)
-    if c is None:
-        c = torch.empty((gs.batch, gs.m, gs.n), dtype=a.dtype, device=a.device)
-    ws = _ws_for(sched, TT_BATCH_MATMUL, gs, ws)
-    rc = lib.tt_batch_matmul(_ptr(a), _ptr(b), _ptr(c), byref(gs), byref(sched) if sched is not None else None,
-                             _ptr(ws), 0 if ws is None else ws.numel() * ws.element_size(), _stream())
-    _check(rc, "tt_batch_matmul")
-    return c
+    return _result(_ttcall.matmul(a, b, to_c_shape(shape), sched, ws, c), "tt_batch_matmul")
 
 
 def tt_dwconv(x, w, bias, shape, sched=None, y=None):
-    torch = _torch()
-    cs = to_c_shape(shape)
-    ho = (cs.h + 2 * cs.pad_h - cs.r) // cs.stride_h + 1
-    wo = (cs.w + 2 * cs.pad_w - cs.s) // cs.stride_w + 1
-    if y is None:
-        y = torch.empty((cs.n, cs.c, ho, wo), dtype=x.dtype, device=x.device)
-    rc = lib.tt_dwconv(_ptr(x), _ptr(w), _ptr(bias), _ptr(y), byref(cs), byref(sched) if sched is not None else None,
-                       _stream())
-    _check(rc, "tt_dwconv")
-    return y
+    return _result(_ttcall.dwconv(x, w, bias, to_c_shape(shape), sched, y), "tt_dwconv")
 
 
 def tt_debug_tile_map(plan):

@@ -29,23 +29,7 @@ namespace {
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline int conv_out(int in, int f, int stride, int pad) { return (in + 2 * pad - f) / stride + 1; }
 
-// Resolve the record (NULL = default), re-apply it to the shape, check the workspace.
-int make_plan(const tt_schedule *sched, int cls, const void *shape, const void *ws, size_t ws_bytes, tt_plan *plan)
-{
-    tt_schedule def;
-    if (!sched) {
-        const int rc = tt_schedule_default(cls, shape, &def);
-        if (rc != TT_OK) return rc;
-        sched = &def;
-    }
-    const int rc = tt_schedule_apply(sched, cls, shape, 0, plan);
-    if (rc != TT_OK) return rc;
-    if (plan->workspace_bytes > 0 && (!ws || (int64_t)ws_bytes < plan->workspace_bytes || !aligned16(ws)))
-        return TT_ERR_WORKSPACE;
-    return TT_OK;
-}
-
-void fill_common(ContractArgs &g, const tt_plan &plan, const tt_schedule *sched, int cls, int dtype)
+void fill_common(ContractArgs &g, const tt_plan &plan, int cls, int dtype)
 {
     g.map = tile_map_of(plan);
     g.batch = plan.batch;
@@ -59,10 +43,9 @@ void fill_common(ContractArgs &g, const tt_plan &plan, const tt_schedule *sched,
     g.unroll = plan.eff_unroll;
     g.act = act_of_class(cls);
     g.dtype = dtype;
-    (void)sched;
 }
 
-int run_contraction(ContractArgs &g, const tt_plan &plan, int family, void *stream)
+int run_contraction(const ContractArgs &g, const tt_plan &plan, int family, void *stream)
 {
     switch (plan.sketch) {
     case TT_SK_DIRECT:
@@ -79,6 +62,148 @@ int run_contraction(ContractArgs &g, const tt_plan &plan, int family, void *stre
     default:
         return TT_ERR_UNSUPPORTED;
     }
+}
+
+void prepare_conv(const tt_conv_shape &s, PreparedOp *op)
+{
+    const tt_plan &plan = op->plan;
+    // the matrix-core kernels address both tensors with 32-bit byte offsets below 2^31 and keep one
+    // bit per filter row
+    const int elem = s.dtype == TT_F32 ? 4 : 2;
+    const int64_t x_bytes = (int64_t)s.n * s.h * s.w * s.c * elem;
+    const int64_t w_bytes = (int64_t)s.k * s.r * s.s * s.c * elem;
+    op->supported = !(plan.sketch == TT_SK_MFMA && (x_bytes >= (1ll << 31) || w_bytes >= (1ll << 31) || s.r > 32));
+    ContractArgs &g = op->g;
+    fill_common(g, plan, op->cls, s.dtype);
+    g.C = s.c;
+    g.H = s.h;
+    g.W = s.w;
+    g.R = s.r;
+    g.S = s.s;
+    g.stride_h = s.stride_h;
+    g.stride_w = s.stride_w;
+    g.pad_h = s.pad_h;
+    g.pad_w = s.pad_w;
+    g.Ho = conv_out(s.h, s.r, s.stride_h, s.pad_h);
+    g.Wo = conv_out(s.w, s.s, s.stride_w, s.pad_w);
+    const int per_item = 16 / elem;
+    g.run = s.s * s.c;
+    g.runp = (g.run + per_item - 1) / per_item * per_item;
+    g.k_walk = s.r * g.runp;
+    g.div_hw = make_fastdiv((uint32_t)(g.Ho * g.Wo));
+    g.div_wo = make_fastdiv((uint32_t)g.Wo);
+    g.PW = s.w + 2 * s.pad_w;
+    g.PHW = (s.h + 2 * s.pad_h) * g.PW;
+    g.div_phw = make_fastdiv((uint32_t)g.PHW);
+    g.div_pw = make_fastdiv((uint32_t)g.PW);
+    g.a_bytes = (uint32_t)x_bytes;
+    g.b_bytes = (uint32_t)w_bytes;
+    op->family = FAM_CONV;
+    if (plan.sketch == TT_SK_MFMA && plan.variant_id >= 0 && plan.variant_id < kNumVariants)
+        op->family = kVariants[plan.variant_id].family; // the dense family for unit-stride 1x1 filters
+}
+
+void prepare_dw(const tt_conv_shape &s, PreparedOp *op)
+{
+    const tt_plan &plan = op->plan;
+    op->supported = s.dtype == TT_F32 && s.r == 3 && s.s == 3;
+    DwArgs &g = op->d;
+    g.map = tile_map_of(plan);
+    g.planes = s.n * s.c;
+    g.C = s.c;
+    g.H = s.h;
+    g.W = s.w;
+    g.Ho = plan.M;
+    g.Wo = plan.N;
+    g.stride_h = s.stride_h;
+    g.stride_w = s.stride_w;
+    g.pad_h = s.pad_h;
+    g.pad_w = s.pad_w;
+    g.wave_m = plan.wave_m;
+    g.wave_n = plan.wave_n;
+    g.stages = plan.stages;
+    g.unroll = plan.eff_unroll;
+    g.eff_vec = plan.eff_vec_a;
+    const int64_t x_bytes = (int64_t)s.n * s.h * s.w * s.c * 4;
+    g.x_bytes = x_bytes < (1ll << 31) ? (uint32_t)x_bytes : 0u;
+}
+
+} // namespace
+
+namespace tt {
+
+int prepare_op(const tt_schedule *sched, int cls, const void *shape, PreparedOp *op)
+{
+    tt_schedule def;
+    if (!sched) {
+        const int rc = tt_schedule_default(cls, shape, &def);
+        if (rc != TT_OK) return rc;
+        sched = &def;
+    }
+    const int rc = tt_schedule_apply(sched, cls, shape, 0, &op->plan);
+    if (rc != TT_OK) return rc;
+    op->cls = cls;
+    op->supported = true;
+    std::memset(&op->g, 0, sizeof op->g);
+    if (cls == TT_DWCONV_BIAS_RELU6) {
+        std::memset(&op->d, 0, sizeof op->d);
+        prepare_dw(*static_cast<const tt_conv_shape *>(shape), op);
+    } else if (is_conv_class(cls)) {
+        prepare_conv(*static_cast<const tt_conv_shape *>(shape), op);
+    } else {
+        const tt_gemm_shape &s = *static_cast<const tt_gemm_shape *>(shape);
+        fill_common(op->g, op->plan, cls, s.dtype);
+        op->g.Ho = op->g.Wo = 1;
+        op->family = family_of(cls, s.trans_b);
+    }
+    return TT_OK;
+}
+
+int check_op_pointers(int cls, const OpPointers &p)
+{
+    if (!p.a || !p.b || !p.out) return TT_ERR_BAD_ARG;
+    if (!aligned16(p.a) || !aligned16(p.b) || !aligned16(p.out) || !aligned16(p.bias) || !aligned16(p.res))
+        return TT_ERR_BAD_ARG;
+    if (is_conv_class(cls) && (cls == TT_CONV2D_BIAS_ADD_RELU) != (p.res != nullptr)) return TT_ERR_BAD_ARG;
+    return TT_OK;
+}
+
+int launch_op(PreparedOp &op, const OpPointers &p, void *stream)
+{
+    if (op.plan.workspace_bytes > 0 && (!p.ws || (int64_t)p.ws_bytes < op.plan.workspace_bytes || !aligned16(p.ws)))
+        return TT_ERR_WORKSPACE;
+    if (!op.supported) return TT_ERR_UNSUPPORTED;
+    if (op.cls == TT_DWCONV_BIAS_RELU6) {
+        DwArgs &g = op.d;
+        g.x = static_cast<const float *>(p.a);
+        g.w = static_cast<const float *>(p.b);
+        g.bias = static_cast<const float *>(p.bias);
+        g.y = static_cast<float *>(p.out);
+        if (op.plan.sketch == TT_SK_DIRECT) return launch_dw_direct(g, op.plan.grid, stream);
+        return launch_dwconv(g, op.plan, stream);
+    }
+    ContractArgs &g = op.g;
+    g.a = p.a;
+    g.b = p.b;
+    g.bias = p.bias;
+    g.res = p.res;
+    g.out = p.out;
+    g.ws = static_cast<float *>(p.ws);
+    g.has_bias = p.bias != nullptr;
+    g.has_res = p.res != nullptr;
+    return run_contraction(g, op.plan, op.family, stream);
+}
+
+} // namespace tt
+
+namespace {
+
+int run_op(const tt_schedule *sched, int cls, const void *shape, const OpPointers &p, void *stream)
+{
+    if (const int rc = check_op_pointers(cls, p); rc != TT_OK) return rc;
+    PreparedOp op;
+    if (const int rc = prepare_op(sched, cls, shape, &op); rc != TT_OK) return rc;
+    return launch_op(op, p, stream);
 }
 
 } // namespace
@@ -132,130 +257,30 @@ extern "C" int tt_conv2d_bias_relu(const void *x, const void *w, const void *bia
                                    const tt_conv_shape *shape, int cls, const tt_schedule *sched, void *ws,
                                    size_t ws_bytes, void *stream)
 {
-    if (!x || !w || !y || !shape || !is_conv_class(cls)) return TT_ERR_BAD_ARG;
-    if (!aligned16(x) || !aligned16(w) || !aligned16(y) || !aligned16(bias) || !aligned16(residual))
-        return TT_ERR_BAD_ARG;
-    if ((cls == TT_CONV2D_BIAS_ADD_RELU) != (residual != nullptr)) return TT_ERR_BAD_ARG;
-    tt_plan plan;
-    const int rc = make_plan(sched, cls, shape, ws, ws_bytes, &plan);
-    if (rc != TT_OK) return rc;
-    // the matrix-core kernels address both tensors with 32-bit byte offsets below 2^31 and keep one
-    // bit per filter row
-    const int elem = shape->dtype == TT_F32 ? 4 : 2;
-    const int64_t x_bytes = (int64_t)shape->n * shape->h * shape->w * shape->c * elem;
-    const int64_t w_bytes = (int64_t)shape->k * shape->r * shape->s * shape->c * elem;
-    if (plan.sketch == TT_SK_MFMA && (x_bytes >= (1ll << 31) || w_bytes >= (1ll << 31) || shape->r > 32))
-        return TT_ERR_UNSUPPORTED;
-    ContractArgs g;
-    std::memset(&g, 0, sizeof g);
-    fill_common(g, plan, sched, cls, shape->dtype);
-    g.a = x;
-    g.b = w;
-    g.bias = bias;
-    g.res = residual;
-    g.out = y;
-    g.ws = static_cast<float *>(ws);
-    g.has_bias = bias != nullptr;
-    g.has_res = residual != nullptr;
-    g.C = shape->c;
-    g.H = shape->h;
-    g.W = shape->w;
-    g.R = shape->r;
-    g.S = shape->s;
-    g.stride_h = shape->stride_h;
-    g.stride_w = shape->stride_w;
-    g.pad_h = shape->pad_h;
-    g.pad_w = shape->pad_w;
-    g.Ho = conv_out(shape->h, shape->r, shape->stride_h, shape->pad_h);
-    g.Wo = conv_out(shape->w, shape->s, shape->stride_w, shape->pad_w);
-    const int per_item = 16 / elem;
-    g.run = shape->s * shape->c;
-    g.runp = (g.run + per_item - 1) / per_item * per_item;
-    g.k_walk = shape->r * g.runp;
-    g.div_hw = make_fastdiv((uint32_t)(g.Ho * g.Wo));
-    g.div_wo = make_fastdiv((uint32_t)g.Wo);
-    g.PW = shape->w + 2 * shape->pad_w;
-    g.PHW = (shape->h + 2 * shape->pad_h) * g.PW;
-    g.div_phw = make_fastdiv((uint32_t)g.PHW);
-    g.div_pw = make_fastdiv((uint32_t)g.PW);
-    g.a_bytes = (uint32_t)x_bytes;
-    g.b_bytes = (uint32_t)w_bytes;
-    int family = FAM_CONV;
-    if (plan.sketch == TT_SK_MFMA && plan.variant_id >= 0 && plan.variant_id < kNumVariants)
-        family = kVariants[plan.variant_id].family; // the dense family for unit-stride 1x1 filters
-    return run_contraction(g, plan, family, stream);
-}
-
-static int gemm_entry(const void *a, const void *b, const void *bias, void *c, const tt_gemm_shape *shape, int cls,
-                      const tt_schedule *sched, void *ws, size_t ws_bytes, void *stream)
-{
-    if (!a || !b || !c || !shape) return TT_ERR_BAD_ARG;
-    if (!aligned16(a) || !aligned16(b) || !aligned16(c) || !aligned16(bias)) return TT_ERR_BAD_ARG;
-    tt_plan plan;
-    const int rc = make_plan(sched, cls, shape, ws, ws_bytes, &plan);
-    if (rc != TT_OK) return rc;
-    ContractArgs g;
-    std::memset(&g, 0, sizeof g);
-    fill_common(g, plan, sched, cls, shape->dtype);
-    g.a = a;
-    g.b = b;
-    g.bias = bias;
-    g.out = c;
-    g.ws = static_cast<float *>(ws);
-    g.has_bias = bias != nullptr;
-    g.Ho = g.Wo = 1;
-    return run_contraction(g, plan, family_of(cls, shape->trans_b), stream);
+    if (!shape || !is_conv_class(cls)) return TT_ERR_BAD_ARG;
+    return run_op(sched, cls, shape, {x, w, bias, residual, y, ws, ws_bytes}, stream);
 }
 
 extern "C" int tt_dense_bias_relu(const void *x, const void *w, const void *bias, void *y,
                                   const tt_gemm_shape *shape, int cls, const tt_schedule *sched, void *ws,
                                   size_t ws_bytes, void *stream)
 {
-    if (!is_dense_class(cls)) return TT_ERR_BAD_ARG;
-    return gemm_entry(x, w, bias, y, shape, cls, sched, ws, ws_bytes, stream);
+    if (!shape || !is_dense_class(cls)) return TT_ERR_BAD_ARG;
+    return run_op(sched, cls, shape, {x, w, bias, nullptr, y, ws, ws_bytes}, stream);
 }
 
 extern "C" int tt_batch_matmul(const void *a, const void *b, void *c, const tt_gemm_shape *shape,
                                const tt_schedule *sched, void *ws, size_t ws_bytes, void *stream)
 {
-    return gemm_entry(a, b, nullptr, c, shape, TT_BATCH_MATMUL, sched, ws, ws_bytes, stream);
+    if (!shape) return TT_ERR_BAD_ARG;
+    return run_op(sched, TT_BATCH_MATMUL, shape, {a, b, nullptr, nullptr, c, ws, ws_bytes}, stream);
 }
 
 extern "C" int tt_dwconv(const void *x, const void *w, const void *bias, void *y, const tt_conv_shape *shape,
                          const tt_schedule *sched, void *stream)
 {
-    if (!x || !w || !y || !shape) return TT_ERR_BAD_ARG;
-    if (!aligned16(x) || !aligned16(w) || !aligned16(y) || !aligned16(bias)) return TT_ERR_BAD_ARG;
-    tt_plan plan;
-    const int rc = make_plan(sched, TT_DWCONV_BIAS_RELU6, shape, nullptr, 0, &plan);
-    if (rc != TT_OK) return rc;
-    if (shape->dtype != TT_F32 || shape->r != 3 || shape->s != 3) return TT_ERR_UNSUPPORTED;
-    DwArgs g;
-    std::memset(&g, 0, sizeof g);
-    g.x = static_cast<const float *>(x);
-    g.w = static_cast<const float *>(w);
-    g.bias = static_cast<const float *>(bias);
-    g.y = static_cast<float *>(y);
-    g.map = tile_map_of(plan);
-    g.planes = shape->n * shape->c;
-    g.C = shape->c;
-    g.H = shape->h;
-    g.W = shape->w;
-    g.Ho = plan.M;
-    g.Wo = plan.N;
-    g.stride_h = shape->stride_h;
-    g.stride_w = shape->stride_w;
-    g.pad_h = shape->pad_h;
-    g.pad_w = shape->pad_w;
-    g.wave_m = plan.wave_m;
-    g.wave_n = plan.wave_n;
-    g.stages = plan.stages;
-    g.unroll = plan.eff_unroll;
-    g.eff_vec = plan.eff_vec_a;
-    const int64_t x_bytes = (int64_t)shape->n * shape->h * shape->w * shape->c * 4;
-    g.x_bytes = x_bytes < (1ll << 31) ? (uint32_t)x_bytes : 0u;
-    if (plan.sketch == TT_SK_DIRECT) return launch_dw_direct(g, plan.grid, stream);
-    return launch_dwconv(g, plan, stream);
+    if (!shape) return TT_ERR_BAD_ARG;
+    return run_op(sched, TT_DWCONV_BIAS_RELU6, shape, {x, w, bias, nullptr, y, nullptr, 0}, stream);
 }
 
 extern "C" int tt_debug_tile_map(const tt_plan *plan, int32_t *out_dev, void *stream)
@@ -269,37 +294,53 @@ extern "C" int tt_debug_tile_map(const tt_plan *plan, int32_t *out_dev, void *st
 
 namespace {
 
-// `turn` picks the tensor set: 0 = bufs, then the alternatives in order, round and round.
-int launch_kernel_desc(const tt_kernel_desc &k, const tt_schedule *sched, void *stream, int64_t turn = 0)
+// The pointers of tensor set `turn`: 0 = bufs, then the alternatives in order, round and round.
+OpPointers pointers_of(const tt_kernel_desc &k, int64_t turn = 0)
 {
     void *const *b = k.bufs;
     if (k.n_alt > 0) {
         const int set = (int)(turn % (k.n_alt + 1));
         if (set > 0) b = k.alt_bufs + (size_t)(set - 1) * 5;
     }
-    if (is_conv_class(k.cls))
-        return tt_conv2d_bias_relu(b[0], b[1], b[2], b[3], b[4], static_cast<const tt_conv_shape *>(k.shape), k.cls, sched,
-                                   k.ws, k.ws_bytes, stream);
-    if (is_dense_class(k.cls))
-        return tt_dense_bias_relu(b[0], b[1], b[2], b[3], static_cast<const tt_gemm_shape *>(k.shape), k.cls, sched, k.ws,
-                                  k.ws_bytes, stream);
-    if (k.cls == TT_BATCH_MATMUL)
-        return tt_batch_matmul(b[0], b[1], b[2], static_cast<const tt_gemm_shape *>(k.shape), sched, k.ws, k.ws_bytes,
-                               stream);
-    if (k.cls == TT_DWCONV_BIAS_RELU6)
-        return tt_dwconv(b[0], b[1], b[2], b[3], static_cast<const tt_conv_shape *>(k.shape), sched, stream);
-    return TT_ERR_BAD_ARG;
+    if (is_conv_class(k.cls)) return {b[0], b[1], b[2], b[3], b[4], k.ws, k.ws_bytes};
+    if (k.cls == TT_BATCH_MATMUL) return {b[0], b[1], nullptr, nullptr, b[2], k.ws, k.ws_bytes};
+    return {b[0], b[1], b[2], nullptr, b[3], k.ws, k.ws_bytes}; // dense, depthwise
 }
 
-struct Timer {
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    bool ok = false;
-    Timer() { ok = hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess; }
+inline bool op_class(int cls) { return cls >= 0 && cls < TT_NUM_CLASSES; }
+
+// A kernel's plan and launch arguments are laid out once (prepare_op) and launched as often as needed.
+int launch_desc(PreparedOp &op, const tt_kernel_desc &k, void *stream, int64_t turn = 0)
+{
+    const OpPointers p = pointers_of(k, turn);
+    if (const int rc = check_op_pointers(k.cls, p); rc != TT_OK) return rc;
+    return launch_op(op, p, stream);
+}
+
+// Events of the timing functions, created as they are first asked for and kept while the sweep lasts.
+class Timer {
+public:
+    Timer() = default;
+    Timer(const Timer &) = delete;
+    Timer &operator=(const Timer &) = delete;
     ~Timer()
     {
-        if (e0) (void)hipEventDestroy(e0);
-        if (e1) (void)hipEventDestroy(e1);
+        for (hipEvent_t e : events_) (void)hipEventDestroy(e);
     }
+    bool record(size_t i, hipStream_t s)
+    {
+        while (events_.size() <= i) {
+            hipEvent_t e = nullptr;
+            if (hipEventCreate(&e) != hipSuccess) return false;
+            events_.push_back(e);
+        }
+        return hipEventRecord(events_[i], s) == hipSuccess;
+    }
+    bool wait(size_t i) { return hipEventSynchronize(events_[i]) == hipSuccess; }
+    bool elapsed_ms(size_t from, size_t to, float *ms) { return hipEventElapsedTime(ms, events_[from], events_[to]) == hipSuccess; }
+
+private:
+    std::vector<hipEvent_t> events_;
 };
 
 tt_sweep_opts resolve(const tt_sweep_opts *o)
@@ -348,30 +389,37 @@ int time_pair(const tt_kernel_desc &k, const tt_schedule *sched, const tt_sweep_
     // and the few sets a short measurement touches, still in the memory-side cache from the pair before).
     static std::atomic<int64_t> turns{0};
     auto next_turn = [&]() { return turns.fetch_add(1, std::memory_order_relaxed); };
+    // The plan is laid out once for all launches of the pair: planning a launch took longer than a small kernel
+    // runs, so such a pair was timed, and the search waited for, at the host's pace.
+    PreparedOp op;
+    rc = prepare_op(rec, k.cls, k.shape, &op);
+    if (rc != TT_OK) return rc;
     for (int i = 0; i < std::max(1, o.warmup); ++i) {
-        rc = launch_kernel_desc(k, rec, s, next_turn());
+        rc = launch_desc(op, k, s, next_turn());
         if (rc != TT_OK) return rc;
     }
     // Size a sample: time one launch, then batch enough launches to fill min_sample_us.
     float ms = 0.0f;
-    if (hipEventRecord(t.e0, s) != hipSuccess) return TT_ERR_HIP;
-    rc = launch_kernel_desc(k, rec, s, next_turn());
+    if (!t.record(0, s)) return TT_ERR_HIP;
+    rc = launch_desc(op, k, s, next_turn());
     if (rc != TT_OK) return rc;
-    if (hipEventRecord(t.e1, s) != hipSuccess || hipEventSynchronize(t.e1) != hipSuccess ||
-        hipEventElapsedTime(&ms, t.e0, t.e1) != hipSuccess)
-        return TT_ERR_HIP;
+    if (!t.record(1, s) || !t.wait(1) || !t.elapsed_ms(0, 1, &ms)) return TT_ERR_HIP;
     const double one_us = std::max(1.0, (double)ms * 1000.0);
     const int launches = (int)std::min<double>(o.max_launches, std::max(1.0, o.min_sample_us / one_us + 0.999));
-    std::vector<double> us(o.samples);
+    // All samples are enqueued back to back with one event between two of them, and waited for once: a wait per
+    // sample drained the stream each time and added its latency to the search.
+    if (!t.record(0, s)) return TT_ERR_HIP;
     for (int smp = 0; smp < o.samples; ++smp) {
-        if (hipEventRecord(t.e0, s) != hipSuccess) return TT_ERR_HIP;
         for (int l = 0; l < launches; ++l) {
-            rc = launch_kernel_desc(k, rec, s, next_turn());
+            rc = launch_desc(op, k, s, next_turn());
             if (rc != TT_OK) return rc;
         }
-        if (hipEventRecord(t.e1, s) != hipSuccess || hipEventSynchronize(t.e1) != hipSuccess ||
-            hipEventElapsedTime(&ms, t.e0, t.e1) != hipSuccess)
-            return TT_ERR_HIP;
+        if (!t.record(smp + 1, s)) return TT_ERR_HIP;
+    }
+    if (!t.wait(o.samples)) return TT_ERR_HIP;
+    std::vector<double> us(o.samples);
+    for (int smp = 0; smp < o.samples; ++smp) {
+        if (!t.elapsed_ms(smp, smp + 1, &ms)) return TT_ERR_HIP;
         us[smp] = (double)ms * 1000.0 / launches;
     }
     std::sort(us.begin(), us.end());
@@ -388,7 +436,6 @@ extern "C" int tt_time_pair(const tt_kernel_desc *kernel, const tt_schedule *sch
 {
     if (!kernel || !kernel->shape) return TT_ERR_BAD_ARG;
     Timer t;
-    if (!t.ok) return TT_ERR_HIP;
     return time_pair(*kernel, sched, resolve(opts), static_cast<hipStream_t>(stream), t, median_us, min_us);
 }
 
@@ -398,11 +445,16 @@ extern "C" int tt_run_kernels(const tt_kernel_desc *kernels, const tt_schedule *
     if (nk < 0 || repeat < 0 || (nk && !kernels)) return TT_ERR_BAD_ARG;
     for (int r = 0; r < repeat; ++r)
         for (int k = 0; k < nk; ++k) {
-            if (!kernels[k].shape) return TT_ERR_BAD_ARG;
-            for (int u = 0; u < kernels[k].use_count; ++u) {
-                const int rc = launch_kernel_desc(kernels[k], scheds ? scheds[k] : nullptr, stream);
-                if (rc != TT_OK) return rc;
-            }
+            const tt_kernel_desc &d = kernels[k];
+            if (!d.shape) return TT_ERR_BAD_ARG;
+            if (d.use_count < 1) continue;
+            const OpPointers p = pointers_of(d);
+            if (!op_class(d.cls)) return TT_ERR_BAD_ARG;
+            if (const int rc = check_op_pointers(d.cls, p); rc != TT_OK) return rc;
+            PreparedOp op; // one plan for all use_count launches
+            if (const int rc = prepare_op(scheds ? scheds[k] : nullptr, d.cls, d.shape, &op); rc != TT_OK) return rc;
+            for (int u = 0; u < d.use_count; ++u)
+                if (const int rc = launch_op(op, p, stream); rc != TT_OK) return rc;
         }
     return TT_OK;
 }
@@ -416,7 +468,6 @@ extern "C" int tt_transfer_sweep(const tt_kernel_desc *kernels, int nk, const tt
     const tt_sweep_opts o = resolve(opts);
     hipStream_t s = static_cast<hipStream_t>(stream);
     Timer timer;
-    if (!timer.ok) return TT_ERR_HIP;
     std::vector<double> local((size_t)nk * np, -2.0), defaults(nk, 0.0), weight(nk, 0.0);
     std::vector<int32_t> kcls(nk), pcls(np);
     for (int p = 0; p < np; ++p) pcls[p] = pool[p].cls;
@@ -469,7 +520,6 @@ extern "C" int tt_refine(const tt_kernel_desc *kernel, const tt_schedule *base, 
     const tt_sweep_opts o = resolve(opts);
     hipStream_t s = static_cast<hipStream_t>(stream);
     Timer timer;
-    if (!timer.ok) return TT_ERR_HIP;
     double cur_us = 0.0;
     int rc = time_pair(*kernel, base, o, s, timer, &cur_us, nullptr);
     if (rc != TT_OK) return rc;
@@ -528,7 +578,6 @@ extern "C" int tt_native_sweep(const tt_kernel_desc *kernel, int level, int fina
     tt_schedule_space(kernel->cls, dtype, level, space.data(), count);
     hipStream_t s = static_cast<hipStream_t>(stream);
     Timer timer;
-    if (!timer.ok) return TT_ERR_HIP;
 
     // the `keep` fastest records of a list under one protocol, fastest first (ties: list order)
     struct Timed {

@@ -168,15 +168,55 @@ int family_of(int cls, int trans_b)
     return FAM_GEMM_TN;
 }
 
+namespace {
+
+// The eleven small integers that name a compiled instance, packed into one key.
+uint64_t variant_key(int dtype, int family, int tm, int tn, int tk, int wm, int wn, int mf, int amode, int pipe, int stride)
+{
+    uint64_t k = 0;
+    for (int v : {tm, tn, tk, wm, wn}) k = k << 9 | (uint64_t)(v & 511);
+    for (int v : {dtype, family, pipe, stride}) k = k << 2 | (uint64_t)(v & 3);
+    return k << 11 | (uint64_t)(mf & 63) << 5 | (uint64_t)(amode & 31);
+}
+
+// Every operator call derives a plan, and a plan asks for one to three instances: walking the table of some
+// 1700 entries was 2 to 4 us of host time per launch, as long as a small kernel runs.  An open-addressing index
+// over the packed key, built once, answers in a few nanoseconds.
+class VariantIndex {
+public:
+    VariantIndex()
+    {
+        while (slots_.size() < 4u * (size_t)kNumVariants) slots_.resize(slots_.size() * 2);
+        for (int i = 0; i < kNumVariants; ++i) {
+            const Variant &v = kVariants[i];
+            const uint64_t key = variant_key(v.dtype, v.family, v.tile_m, v.tile_n, v.tile_k, v.wave_m, v.wave_n, v.mfma,
+                                             v.amode, v.pipe, v.stride);
+            size_t at = home(key);
+            while (slots_[at].id >= 0 && slots_[at].key != key) at = (at + 1) & (slots_.size() - 1);
+            if (slots_[at].id < 0) slots_[at] = {key, i}; // the first instance of a key stands for it
+        }
+    }
+    int find(uint64_t key) const
+    {
+        for (size_t at = home(key);; at = (at + 1) & (slots_.size() - 1)) // at most a quarter of the slots are taken
+            if (slots_[at].id < 0 || slots_[at].key == key) return slots_[at].id;
+    }
+
+private:
+    struct Slot {
+        uint64_t key = 0;
+        int id = -1;
+    };
+    size_t home(uint64_t key) const { return (size_t)((key * 0x9E3779B97F4A7C15ull) >> 32) & (slots_.size() - 1); }
+    std::vector<Slot> slots_ = std::vector<Slot>(1024);
+};
+
+} // namespace
+
 int find_variant(int dtype, int family, int tm, int tn, int tk, int wm, int wn, int mf, int amode, int pipe, int stride)
 {
-    for (int i = 0; i < kNumVariants; ++i) {
-        const Variant &v = kVariants[i];
-        if (v.dtype == dtype && v.family == family && v.tile_m == tm && v.tile_n == tn && v.tile_k == tk &&
-            v.wave_m == wm && v.wave_n == wn && v.mfma == mf && v.amode == amode && v.pipe == pipe && v.stride == stride)
-            return i;
-    }
-    return -1;
+    static const VariantIndex index;
+    return index.find(variant_key(dtype, family, tm, tn, tk, wm, wn, mf, amode, pipe, stride));
 }
 
 } // namespace tt

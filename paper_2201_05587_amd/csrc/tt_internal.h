@@ -180,6 +180,30 @@ struct DwArgs {
     uint32_t x_bytes;  // size of the input tensor when it is below 2 GiB, else 0
 };
 
+// The device tensors of one operator call (conv: x, w, bias, residual, y; dense and depthwise without a residual;
+// batch matmul without bias and residual) and the split-K workspace.
+struct OpPointers {
+    const void *a, *b, *bias, *res;
+    void *out, *ws;
+    size_t ws_bytes;
+};
+
+// A kernel under a record, laid out once: the plan and the launch arguments without the pointers.
+struct PreparedOp {
+    tt_plan plan;
+    int32_t cls, family;
+    bool supported; // false: a valid plan that the entry point refuses (TT_ERR_UNSUPPORTED)
+    ContractArgs g; // every class but the depthwise one
+    DwArgs d;
+};
+
+// The operator entry points in three steps (ops.hip): argument check, plan and launch arguments (record NULL = the
+// default), launch.  A caller that launches a kernel repeatedly, or needs the plan's workspace size, does the
+// second step once.
+int check_op_pointers(int cls, const OpPointers &p);
+int prepare_op(const tt_schedule *sched, int cls, const void *shape, PreparedOp *op);
+int launch_op(PreparedOp &op, const OpPointers &p, void *stream);
+
 struct Variant {
     int32_t dtype, family, tile_m, tile_n, tile_k, wave_m, wave_n, mfma;
     int32_t amode; // conv family: bytes per gathered load (16 or the element size); 0 otherwise
