@@ -1,0 +1,60 @@
+// Launchers of the contraction kernels, one per compiled instance: the kernel the record names, or the one that
+// splits the reduction inside the workgroup where the record's launch would leave most of the chip idle.
+#pragma once
+
+#include "contract.hip.h"
+#include "contract_groups.hip.h"
+
+namespace tt {
+
+template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF, int AM>
+int launch_contract(const ContractArgs &args, int grid, int lds_bytes, void *stream)
+{
+    if constexpr (FAM == FAM_GEMM_TN || (FAM == FAM_CONV && AM == 16))
+        if (groups_apply<DT, FAM, TM, TN, WM, WN, MF>(args, grid)) return launch_groups<DT, FAM, TM, TN, WM, WN, MF>(args, grid, stream);
+    auto kern = contract_kernel<DT, FAM, TM, TN, TK, WM, WN, MF, AM>;
+    // the epilogue stages one band of MF rows per wave in the same LDS
+    constexpr int EPI_BYTES = (TM / WM) * (TN / WN) * MF * (WN + (MF == 32 ? 8 : 4)) * 4;
+    if (lds_bytes < EPI_BYTES) lds_bytes = EPI_BYTES;
+    static DynamicLdsLimit limit; // per kernel instance
+    if (const int rc = limit.raise_to(reinterpret_cast<const void *>(kern), lds_bytes); rc != TT_OK) return rc;
+    constexpr int THREADS = (TM / WM) * (TN / WN) * 64;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(THREADS), lds_bytes, static_cast<hipStream_t>(stream), args);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? TT_OK : note_hip_error((int)e, "contract_kernel launch");
+}
+
+// What the host's resource check multiplies by the number of stages.
+template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF, int AM> int stage_bytes_contract()
+{
+    return StageLayout<DT, FAM, TM, TN, TK, MF>::STAGE_BYTES;
+}
+template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF> int stage_bytes_contract_async()
+{
+    return RingLayout<DT, TM, TN, TK>::STAGE_BYTES;
+}
+template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF, int AM> int lds_bytes_contract(int stages)
+{
+    return stages * StageLayout<DT, FAM, TM, TN, TK, MF>::STAGE_BYTES;
+}
+template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF> int lds_bytes_contract_async(int stages)
+{
+    return stages * RingLayout<DT, TM, TN, TK>::STAGE_BYTES;
+}
+
+template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF>
+int launch_contract_async(const ContractArgs &args, int grid, int lds_bytes, void *stream)
+{
+    if (groups_apply<DT, FAM, TM, TN, WM, WN, MF>(args, grid)) return launch_groups<DT, FAM, TM, TN, WM, WN, MF>(args, grid, stream);
+    auto kern = contract_async_kernel<DT, FAM, TM, TN, TK, WM, WN, MF>;
+    constexpr int EPI_BYTES = (TM / WM) * (TN / WN) * MF * (WN + (MF == 32 ? 8 : 4)) * 4;
+    if (lds_bytes < EPI_BYTES) lds_bytes = EPI_BYTES;
+    static DynamicLdsLimit limit; // per kernel instance
+    if (const int rc = limit.raise_to(reinterpret_cast<const void *>(kern), lds_bytes); rc != TT_OK) return rc;
+    constexpr int THREADS = (TM / WM) * (TN / WN) * 64;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(THREADS), lds_bytes, static_cast<hipStream_t>(stream), args);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? TT_OK : note_hip_error((int)e, "contract_async_kernel launch");
+}
+
+} // namespace tt

@@ -137,11 +137,14 @@ def main():
     which = sys.argv[3] if len(sys.argv) > 3 else "full"
     os.makedirs(out_dir, exist_ok=True)
     vs = variants(which)
+    # instances of one tile go to one slice: they share the kernel that splits the reduction inside a workgroup
     slices = [[] for _ in range(n_slices)]
+    home = {}
     for i, v in enumerate(vs):
-        slices[i % n_slices].append((i, v))
+        key = (v[0], v[1], v[2], v[3], v[5], v[6], v[7])
+        slices[home.setdefault(key, len(home) % n_slices)].append((i, v))
     for s, items in enumerate(slices):
-        lines = ['// generated by gen_variants.py - do not edit', '#include "../contract.hip.h"',
+        lines = ['// generated by gen_variants.py - do not edit', '#include "../contract_launch.hip.h"',
                  '#include "../conv_patch.hip.h"', '#include "../stream_gemm.hip.h"', "namespace tt {"]
         for i, v in items:
             if v[9] == 2:

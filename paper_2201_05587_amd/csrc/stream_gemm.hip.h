@@ -115,19 +115,6 @@ __global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) gemm_stream_kernel
     }
 }
 
-// Compute units of the current device (asked once; one device per process).
-inline int compute_units()
-{
-    static const int cus = [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
-            n = 256;
-        return n;
-    }();
-    return cus;
-}
-
 // `tiles` is the plan's grid (one entry per output tile); the launch itself is persistent: as many
 // workgroups as fit the chip (at most four per CU, as the LDS allows), a whole number per panel of B.
 template <int DT, int TM, int TN, int TK, int WM, int WN, int MF>

@@ -596,3 +596,25 @@ def test_timing_rotates_through_the_alternative_tensor_sets(api, P):
     cold.desc.alt_bufs = None
     st, _, _ = api.tt_time_pair(cold, None, opts)
     assert st == api.TT_ERR_BAD_ARG
+
+
+# ---- reduction split inside the workgroup (launches of at most one workgroup per CU) --------------------------------
+@pytest.mark.parametrize("name,cls,shape,rec", [
+    # dense: reductions of exactly three slices, with a ragged last one, ragged M and N, rows that are not whole vectors
+    ("three_slices", 4, wl.GemmShape(1, 64, 64, 384, 1, wl.BF16), dict(tm=64, tn=64, tk=64, wm=32, wn=32, mf=32, stages=3)),
+    ("tails", 6, wl.GemmShape(1, 100, 88, 456, 1, wl.BF16), dict(tm=64, tn=64, tk=64, wm=32, wn=32, mf=16, stages=2)),
+    ("odd_rows", 5, wl.GemmShape(1, 70, 61, 640, 1, wl.BF16), dict(tm=32, tn=32, tk=32, wm=16, wn=16, mf=16, stages=3)),
+    ("four_waves_64x32", 4, wl.GemmShape(1, 130, 66, 516, 1, wl.F32), dict(tm=128, tn=64, tk=32, wm=64, wn=32, mf=32, stages=2)),
+    ("eight_waves", 4, wl.GemmShape(1, 96, 160, 776, 1, wl.BF16), dict(tm=64, tn=64, tk=128, wm=16, wn=32, mf=16, stages=3)),
+    # one workgroup per CU, and one more than that (the plain kernel)
+    ("grid_256", 4, wl.GemmShape(1, 32 * 256, 32, 384, 1, wl.F32), dict(tm=32, tn=32, tk=32, wm=16, wn=16, mf=16, stages=3)),
+    ("grid_257", 4, wl.GemmShape(1, 32 * 256 + 1, 32, 384, 1, wl.F32), dict(tm=32, tn=32, tk=32, wm=16, wn=16, mf=16, stages=3)),
+    ("batches", 7, wl.GemmShape(5, 65, 48, 400, 1, wl.BF16), dict(tm=64, tn=32, tk=64, wm=32, wn=32, mf=32, stages=4)),
+    # convolutions: gathers at padded borders, a residual, a split across workgroups that ends inside a slice
+    ("conv", 1, wl.ConvShape(2, 40, 15, 11, 72, 3, 3, 1, 1, 1, 1, wl.BF16), dict(tm=64, tn=64, tk=32, wm=32, wn=32, mf=16, stages=2)),
+    ("conv_res_s2", 2, wl.ConvShape(1, 64, 17, 17, 64, 3, 3, 2, 2, 1, 1, wl.F32), dict(tm=32, tn=32, tk=32, wm=16, wn=16, mf=16, stages=3)),
+    ("conv_split", 2, wl.ConvShape(2, 128, 9, 9, 64, 3, 3, 1, 1, 1, 1, wl.BF16), dict(tm=64, tn=64, tk=64, wm=32, wn=32, mf=32, split_k=2, stages=3)),
+    ("conv_split_f32", 1, wl.ConvShape(1, 100, 12, 12, 40, 3, 3, 1, 1, 1, 1, wl.F32), dict(tm=32, tn=32, tk=32, wm=16, wn=16, mf=16, split_k=2, stages=4)),
+])
+def test_reduction_split_inside_the_workgroup(api, P, name, cls, shape, rec):
+    P.check_kernel(wl.Kernel(cls, shape, 1, name), [mfma(api, cls, **rec), mfma(api, cls, order=4, **rec)], seed=4321)
