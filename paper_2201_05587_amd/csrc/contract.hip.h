@@ -803,8 +803,9 @@ template <int DT, int FAM, int TM, int TN, int TK, int MF> struct StageLayout {
 
 // AM = bytes per gathered load of the conv family (16 or the element size); 0 for the others.
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF, int AM>
-__global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) contract_kernel(const ContractArgs g)
+__global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) contract_kernel(const ContractArgs args, const PointerSets sets)
 {
+    const ContractArgs g = with_set(args, sets, blockIdx.y);
     using E = typename ElemOf<DT>::type;
     using L = StageLayout<DT, FAM, TM, TN, TK, MF>;
     constexpr int CH = ElemOf<DT>::CH, ES = (int)sizeof(E);
@@ -1127,8 +1128,9 @@ template <int DT, int TM, int TN, int TK> struct RingLayout {
 
 // Conv (16-byte gathers) and dense family with the asynchronous pipeline; g.stages = 3 or 4 buffers.
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF>
-__global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) contract_async_kernel(const ContractArgs g)
+__global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) contract_async_kernel(const ContractArgs args, const PointerSets sets)
 {
+    const ContractArgs g = with_set(args, sets, blockIdx.y);
     static_assert(FAM == FAM_CONV || FAM == FAM_GEMM_TN, "family without an asynchronous loader");
     using E = typename ElemOf<DT>::type;
     constexpr int CH = ElemOf<DT>::CH, ES = (int)sizeof(E);

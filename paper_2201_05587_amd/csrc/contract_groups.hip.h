@@ -46,8 +46,9 @@ template <int DT, int TM, int TN, int WM, int WN, int MF> struct GroupShape {
 };
 
 template <int DT, int FAM, int TM, int TN, int WM, int WN, int MF>
-__global__ void __launch_bounds__((GroupShape<DT, TM, TN, WM, WN, MF>::THREADS)) contract_groups_kernel(const ContractArgs g)
+__global__ void __launch_bounds__((GroupShape<DT, TM, TN, WM, WN, MF>::THREADS)) contract_groups_kernel(const ContractArgs args, const PointerSets sets)
 {
+    const ContractArgs g = with_set(args, sets, blockIdx.y);
     using S = GroupShape<DT, TM, TN, WM, WN, MF>;
     using E = typename ElemOf<DT>::type;
     constexpr int CH = S::CH, ES = S::ES, KG = S::KG, TKI = S::TKI, CPR = S::CPR, THREADS = S::THREADS, NST = S::STAGES;
@@ -237,14 +238,14 @@ template <int DT, int FAM, int TM, int TN, int WM, int WN, int MF> bool groups_a
            (FAM == FAM_CONV || ((int64_t)a.M * a.K * S::ES < (1ll << 31) && (int64_t)a.N * a.K * S::ES < (1ll << 31)));
 }
 
-template <int DT, int FAM, int TM, int TN, int WM, int WN, int MF> int launch_groups(const ContractArgs &args, int grid, void *stream)
+template <int DT, int FAM, int TM, int TN, int WM, int WN, int MF> int launch_groups(const ContractArgs &args, const PointerSets &sets, int grid, void *stream)
 {
     using S = GroupShape<DT, TM, TN, WM, WN, MF>;
     if constexpr (S::KG > 1) {
         auto kern = contract_groups_kernel<DT, FAM, TM, TN, WM, WN, MF>;
         static DynamicLdsLimit limit; // per kernel instance
         if (const int rc = limit.raise_to(reinterpret_cast<const void *>(kern), S::LDS); rc != TT_OK) return rc;
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(S::THREADS), S::LDS, static_cast<hipStream_t>(stream), args);
+        hipLaunchKernelGGL(kern, dim3(grid, sets.count), dim3(S::THREADS), S::LDS, static_cast<hipStream_t>(stream), args, sets);
         const hipError_t e = hipGetLastError();
         return e == hipSuccess ? TT_OK : note_hip_error((int)e, "contract_groups_kernel launch");
     }

@@ -8,10 +8,10 @@
 namespace tt {
 
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF, int AM>
-int launch_contract(const ContractArgs &args, int grid, int lds_bytes, void *stream)
+int launch_contract(const ContractArgs &args, const PointerSets &sets, int grid, int lds_bytes, void *stream)
 {
     if constexpr (FAM == FAM_GEMM_TN || (FAM == FAM_CONV && AM == 16))
-        if (groups_apply<DT, FAM, TM, TN, WM, WN, MF>(args, grid)) return launch_groups<DT, FAM, TM, TN, WM, WN, MF>(args, grid, stream);
+        if (groups_apply<DT, FAM, TM, TN, WM, WN, MF>(args, grid * sets.count)) return launch_groups<DT, FAM, TM, TN, WM, WN, MF>(args, sets, grid, stream);
     auto kern = contract_kernel<DT, FAM, TM, TN, TK, WM, WN, MF, AM>;
     // the epilogue stages one band of MF rows per wave in the same LDS
     constexpr int EPI_BYTES = (TM / WM) * (TN / WN) * MF * (WN + (MF == 32 ? 8 : 4)) * 4;
@@ -19,7 +19,7 @@ int launch_contract(const ContractArgs &args, int grid, int lds_bytes, void *str
     static DynamicLdsLimit limit; // per kernel instance
     if (const int rc = limit.raise_to(reinterpret_cast<const void *>(kern), lds_bytes); rc != TT_OK) return rc;
     constexpr int THREADS = (TM / WM) * (TN / WN) * 64;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(THREADS), lds_bytes, static_cast<hipStream_t>(stream), args);
+    hipLaunchKernelGGL(kern, dim3(grid, sets.count), dim3(THREADS), lds_bytes, static_cast<hipStream_t>(stream), args, sets);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? TT_OK : note_hip_error((int)e, "contract_kernel launch");
 }
@@ -43,16 +43,16 @@ template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF> int l
 }
 
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF>
-int launch_contract_async(const ContractArgs &args, int grid, int lds_bytes, void *stream)
+int launch_contract_async(const ContractArgs &args, const PointerSets &sets, int grid, int lds_bytes, void *stream)
 {
-    if (groups_apply<DT, FAM, TM, TN, WM, WN, MF>(args, grid)) return launch_groups<DT, FAM, TM, TN, WM, WN, MF>(args, grid, stream);
+    if (groups_apply<DT, FAM, TM, TN, WM, WN, MF>(args, grid * sets.count)) return launch_groups<DT, FAM, TM, TN, WM, WN, MF>(args, sets, grid, stream);
     auto kern = contract_async_kernel<DT, FAM, TM, TN, TK, WM, WN, MF>;
     constexpr int EPI_BYTES = (TM / WM) * (TN / WN) * MF * (WN + (MF == 32 ? 8 : 4)) * 4;
     if (lds_bytes < EPI_BYTES) lds_bytes = EPI_BYTES;
     static DynamicLdsLimit limit; // per kernel instance
     if (const int rc = limit.raise_to(reinterpret_cast<const void *>(kern), lds_bytes); rc != TT_OK) return rc;
     constexpr int THREADS = (TM / WM) * (TN / WN) * 64;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(THREADS), lds_bytes, static_cast<hipStream_t>(stream), args);
+    hipLaunchKernelGGL(kern, dim3(grid, sets.count), dim3(THREADS), lds_bytes, static_cast<hipStream_t>(stream), args, sets);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? TT_OK : note_hip_error((int)e, "contract_async_kernel launch");
 }

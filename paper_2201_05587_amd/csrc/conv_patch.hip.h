@@ -74,8 +74,9 @@ template <int CK, int STRIDE, int PL, int THREADS> struct PatchLayout {
 
 // (CK, WM x WN wave tile of 32-blocks, PL patch items per thread and slice)
 template <int TM, int TN, int CK, int WM, int WN, int STRIDE, int PL>
-__global__ void __launch_bounds__((TM / WM) * (TN / WN) * 128) conv3x3_patch_kernel(const ContractArgs g)
+__global__ void __launch_bounds__((TM / WM) * (TN / WN) * 128) conv3x3_patch_kernel(const ContractArgs args, const PointerSets sets)
 {
+    const ContractArgs g = with_set(args, sets, blockIdx.y);
     constexpr int DT = TT_BF16, MF = 32, KG = 2, TAPS = 9;
     constexpr int POS = (TM / WM) * (TN / WN), THREADS = POS * KG * 64;
     constexpr int NWR = TM / WM;
@@ -366,14 +367,14 @@ template <int TM, int TN, int CK, int WM, int WN, int STRIDE, int PL> struct Pat
 };
 
 template <int TM, int TN, int CK, int WM, int WN, int STRIDE, int PL>
-int launch_conv_patch(const ContractArgs &args, int grid, int lds_bytes, void *stream)
+int launch_conv_patch(const ContractArgs &args, const PointerSets &sets, int grid, int lds_bytes, void *stream)
 {
     auto kern = conv3x3_patch_kernel<TM, TN, CK, WM, WN, STRIDE, PL>;
     using L = PatchKernelLds<TM, TN, CK, WM, WN, STRIDE, PL>;
     if (lds_bytes < L::bytes(args.stages)) lds_bytes = L::bytes(args.stages);
     static DynamicLdsLimit limit; // per kernel instance
     if (const int rc = limit.raise_to(reinterpret_cast<const void *>(kern), lds_bytes); rc != TT_OK) return rc;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(L::THREADS), lds_bytes, static_cast<hipStream_t>(stream), args);
+    hipLaunchKernelGGL(kern, dim3(grid, sets.count), dim3(L::THREADS), lds_bytes, static_cast<hipStream_t>(stream), args, sets);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? TT_OK : note_hip_error((int)e, "conv3x3_patch_kernel launch");
 }

@@ -162,15 +162,15 @@ def main():
             else:
                 args = ", ".join(str(x) for x in v[:9])
                 call, size, lds = f"launch_contract<{args}>", f"stage_bytes_contract<{args}>", f"lds_bytes_contract<{args}>"
-            lines.append(f"int ttv_{i}(const ContractArgs &a, int grid, int lds, void *s) "
-                         f"{{ return {call}(a, grid, lds, s); }}")
+            lines.append(f"int ttv_{i}(const ContractArgs &a, const PointerSets &p, int grid, int lds, void *s) "
+                         f"{{ return {call}(a, p, grid, lds, s); }}")
             lines.append(f"int tts_{i}() {{ return {size}(); }}")
             lines.append(f"int ttl_{i}(int stages) {{ return {lds}(stages); }}")
         lines.append("} // namespace tt")
         write_if_changed(os.path.join(out_dir, f"inst_{s:02d}.hip"), "\n".join(lines) + "\n")
     lines = ['// generated by gen_variants.py - do not edit', '#include "../tt_internal.h"', "namespace tt {"]
     for i, _ in enumerate(vs):
-        lines.append(f"int ttv_{i}(const ContractArgs &, int, int, void *);")
+        lines.append(f"int ttv_{i}(const ContractArgs &, const PointerSets &, int, int, void *);")
         lines.append(f"int tts_{i}();")
         lines.append(f"int ttl_{i}(int);")
     lines.append("const Variant kVariants[] = {")

@@ -45,18 +45,18 @@ void fill_common(ContractArgs &g, const tt_plan &plan, int cls, int dtype)
     g.dtype = dtype;
 }
 
-int run_contraction(const ContractArgs &g, const tt_plan &plan, int family, void *stream)
+int run_contraction(const ContractArgs &g, const PointerSets &sets, const tt_plan &plan, int family, void *stream)
 {
     switch (plan.sketch) {
     case TT_SK_DIRECT:
-        return launch_direct(g, family, plan.grid, stream);
+        return launch_direct(g, sets, family, plan.grid, stream);
     case TT_SK_GEMV:
-        return launch_gemv(g, plan, stream);
+        return launch_gemv(g, sets, plan, stream);
     case TT_SK_MFMA: {
         if (plan.variant_id < 0 || plan.variant_id >= kNumVariants) return TT_ERR_UNSUPPORTED;
-        const int rc = kVariants[plan.variant_id].launch(g, plan.grid, plan.lds_bytes, stream);
+        const int rc = kVariants[plan.variant_id].launch(g, sets, plan.grid, plan.lds_bytes, stream);
         if (rc != TT_OK) return rc;
-        if (plan.eff_split_k > 1) return launch_splitk_reduce(g, family, stream);
+        if (plan.eff_split_k > 1) return launch_splitk_reduce(g, sets, family, stream);
         return TT_OK;
     }
     default:
@@ -70,8 +70,7 @@ void prepare_conv(const tt_conv_shape &s, PreparedOp *op)
     // the matrix-core kernels address both tensors with 32-bit byte offsets below 2^31 and keep one
     // bit per filter row
     const int elem = s.dtype == TT_F32 ? 4 : 2;
-    const int64_t x_bytes = (int64_t)s.n * s.h * s.w * s.c * elem;
-    const int64_t w_bytes = (int64_t)s.k * s.r * s.s * s.c * elem;
+    const int64_t x_bytes = op->a_bytes, w_bytes = op->b_bytes;
     op->supported = !(plan.sketch == TT_SK_MFMA && (x_bytes >= (1ll << 31) || w_bytes >= (1ll << 31) || s.r > 32));
     ContractArgs &g = op->g;
     fill_common(g, plan, op->cls, s.dtype);
@@ -124,8 +123,7 @@ void prepare_dw(const tt_conv_shape &s, PreparedOp *op)
     g.stages = plan.stages;
     g.unroll = plan.eff_unroll;
     g.eff_vec = plan.eff_vec_a;
-    const int64_t x_bytes = (int64_t)s.n * s.h * s.w * s.c * 4;
-    g.x_bytes = x_bytes < (1ll << 31) ? (uint32_t)x_bytes : 0u;
+    g.x_bytes = op->supported && op->a_bytes < (1ll << 31) ? (uint32_t)op->a_bytes : 0u;
 }
 
 } // namespace
@@ -144,17 +142,33 @@ int prepare_op(const tt_schedule *sched, int cls, const void *shape, PreparedOp 
     if (rc != TT_OK) return rc;
     op->cls = cls;
     op->supported = true;
+    const bool image = is_conv_class(cls) || cls == TT_DWCONV_BIAS_RELU6;
+    const tt_conv_shape *cs = static_cast<const tt_conv_shape *>(shape);
+    const tt_gemm_shape *gs = static_cast<const tt_gemm_shape *>(shape);
+    const int64_t elem = (image ? cs->dtype : gs->dtype) == TT_F32 ? 4 : 2;
+    if (image) {
+        const int64_t pixels = (int64_t)cs->n * conv_out(cs->h, cs->r, cs->stride_h, cs->pad_h) *
+                               conv_out(cs->w, cs->s, cs->stride_w, cs->pad_w);
+        op->a_bytes = (int64_t)cs->n * cs->h * cs->w * cs->c * elem;
+        op->b_bytes = (int64_t)cs->k * cs->r * cs->s * (cls == TT_DWCONV_BIAS_RELU6 ? 1 : cs->c) * elem;
+        op->bias_bytes = cs->k * elem;
+        op->out_bytes = pixels * cs->k * elem;
+    } else {
+        op->a_bytes = (int64_t)gs->batch * gs->m * gs->k * elem;
+        op->b_bytes = (int64_t)gs->batch * gs->n * gs->k * elem;
+        op->bias_bytes = gs->n * elem;
+        op->out_bytes = (int64_t)gs->batch * gs->m * gs->n * elem;
+    }
     std::memset(&op->g, 0, sizeof op->g);
     if (cls == TT_DWCONV_BIAS_RELU6) {
         std::memset(&op->d, 0, sizeof op->d);
-        prepare_dw(*static_cast<const tt_conv_shape *>(shape), op);
+        prepare_dw(*cs, op);
     } else if (is_conv_class(cls)) {
-        prepare_conv(*static_cast<const tt_conv_shape *>(shape), op);
+        prepare_conv(*cs, op);
     } else {
-        const tt_gemm_shape &s = *static_cast<const tt_gemm_shape *>(shape);
-        fill_common(op->g, op->plan, cls, s.dtype);
+        fill_common(op->g, op->plan, cls, gs->dtype);
         op->g.Ho = op->g.Wo = 1;
-        op->family = family_of(cls, s.trans_b);
+        op->family = family_of(cls, gs->trans_b);
     }
     return TT_OK;
 }
@@ -168,30 +182,37 @@ int check_op_pointers(int cls, const OpPointers &p)
     return TT_OK;
 }
 
-int launch_op(PreparedOp &op, const OpPointers &p, void *stream)
+int launch_op(PreparedOp &op, const OpPointers *calls, int count, void *stream)
 {
-    if (op.plan.workspace_bytes > 0 && (!p.ws || (int64_t)p.ws_bytes < op.plan.workspace_bytes || !aligned16(p.ws)))
-        return TT_ERR_WORKSPACE;
+    PointerSets sets;
+    sets.count = count;
+    for (int i = 0; i < count; ++i) {
+        const OpPointers &p = calls[i];
+        if (op.plan.workspace_bytes > 0 && (!p.ws || (int64_t)p.ws_bytes < op.plan.workspace_bytes || !aligned16(p.ws)))
+            return TT_ERR_WORKSPACE;
+        if (i > 0) sets.more[i - 1] = {p.a, p.b, p.bias, p.res, p.out, static_cast<float *>(p.ws)};
+    }
     if (!op.supported) return TT_ERR_UNSUPPORTED;
+    const OpPointers &first = calls[0];
     if (op.cls == TT_DWCONV_BIAS_RELU6) {
-        DwArgs &g = op.d;
-        g.x = static_cast<const float *>(p.a);
-        g.w = static_cast<const float *>(p.b);
-        g.bias = static_cast<const float *>(p.bias);
-        g.y = static_cast<float *>(p.out);
-        if (op.plan.sketch == TT_SK_DIRECT) return launch_dw_direct(g, op.plan.grid, stream);
-        return launch_dwconv(g, op.plan, stream);
+        DwArgs &d = op.d;
+        d.x = static_cast<const float *>(first.a);
+        d.w = static_cast<const float *>(first.b);
+        d.bias = static_cast<const float *>(first.bias);
+        d.y = static_cast<float *>(first.out);
+        if (op.plan.sketch == TT_SK_DIRECT) return launch_dw_direct(d, sets, op.plan.grid, stream);
+        return launch_dwconv(d, sets, op.plan, stream);
     }
     ContractArgs &g = op.g;
-    g.a = p.a;
-    g.b = p.b;
-    g.bias = p.bias;
-    g.res = p.res;
-    g.out = p.out;
-    g.ws = static_cast<float *>(p.ws);
-    g.has_bias = p.bias != nullptr;
-    g.has_res = p.res != nullptr;
-    return run_contraction(g, op.plan, op.family, stream);
+    g.a = first.a;
+    g.b = first.b;
+    g.bias = first.bias;
+    g.res = first.res;
+    g.out = first.out;
+    g.ws = static_cast<float *>(first.ws);
+    g.has_bias = first.bias != nullptr;
+    g.has_res = first.res != nullptr;
+    return run_contraction(g, sets, op.plan, op.family, stream);
 }
 
 } // namespace tt
@@ -203,7 +224,7 @@ int run_op(const tt_schedule *sched, int cls, const void *shape, const OpPointer
     if (const int rc = check_op_pointers(cls, p); rc != TT_OK) return rc;
     PreparedOp op;
     if (const int rc = prepare_op(sched, cls, shape, &op); rc != TT_OK) return rc;
-    return launch_op(op, p, stream);
+    return launch_op(op, &p, 1, stream);
 }
 
 } // namespace
@@ -307,14 +328,12 @@ OpPointers pointers_of(const tt_kernel_desc &k, int64_t turn = 0)
     return {b[0], b[1], b[2], nullptr, b[3], k.ws, k.ws_bytes}; // dense, depthwise
 }
 
-inline bool op_class(int cls) { return cls >= 0 && cls < TT_NUM_CLASSES; }
-
 // A kernel's plan and launch arguments are laid out once (prepare_op) and launched as often as needed.
 int launch_desc(PreparedOp &op, const tt_kernel_desc &k, void *stream, int64_t turn = 0)
 {
     const OpPointers p = pointers_of(k, turn);
     if (const int rc = check_op_pointers(k.cls, p); rc != TT_OK) return rc;
-    return launch_op(op, p, stream);
+    return launch_op(op, &p, 1, stream);
 }
 
 // Events of the timing functions, created as they are first asked for and kept while the sweep lasts.
@@ -439,22 +458,81 @@ extern "C" int tt_time_pair(const tt_kernel_desc *kernel, const tt_schedule *sch
     return time_pair(*kernel, sched, resolve(opts), static_cast<hipStream_t>(stream), t, median_us, min_us);
 }
 
+namespace {
+
+struct Range {
+    const char *at;
+    int64_t bytes;
+};
+inline bool overlap(const Range &x, const Range &y) { return x.at && y.at && x.at < y.at + y.bytes && y.at < x.at + x.bytes; }
+
+// Whether two calls of one plan may run at the same time: neither writes what the other reads or writes.
+bool independent(const PreparedOp &op, const OpPointers &p, const OpPointers &q)
+{
+    const auto writes = [&](const OpPointers &c, Range (&r)[2]) {
+        r[0] = {static_cast<const char *>(c.out), op.out_bytes};
+        r[1] = {static_cast<const char *>(op.plan.workspace_bytes > 0 ? c.ws : nullptr), op.plan.workspace_bytes};
+    };
+    const auto reads = [&](const OpPointers &c, Range (&r)[4]) {
+        r[0] = {static_cast<const char *>(c.a), op.a_bytes};
+        r[1] = {static_cast<const char *>(c.b), op.b_bytes};
+        r[2] = {static_cast<const char *>(c.bias), op.bias_bytes};
+        r[3] = {static_cast<const char *>(c.res), op.out_bytes};
+    };
+    Range wp[2], wq[2], rp[4], rq[4];
+    writes(p, wp), writes(q, wq), reads(p, rp), reads(q, rq);
+    for (int i = 0; i < 2; ++i) {
+        for (int j = 0; j < 2; ++j)
+            if (overlap(wp[i], wq[j])) return false;
+        for (int j = 0; j < 4; ++j)
+            if (overlap(wp[i], rq[j]) || overlap(rp[j], wq[i])) return false;
+    }
+    return true;
+}
+
+// Same class, shape and record: one plan.
+bool same_plan(const tt_kernel_desc &x, const tt_schedule *sx, const tt_kernel_desc &y, const tt_schedule *sy)
+{
+    if (x.cls != y.cls || (sx == nullptr) != (sy == nullptr)) return false;
+    if (sx && sx != sy && std::memcmp(sx, sy, sizeof(int32_t) * 13) != 0) return false; // the thirteen knobs lead the record
+    const bool image = is_conv_class(x.cls) || x.cls == TT_DWCONV_BIAS_RELU6;
+    return x.shape == y.shape || std::memcmp(x.shape, y.shape, image ? sizeof(tt_conv_shape) : sizeof(tt_gemm_shape)) == 0;
+}
+
+} // namespace
+
+// Consecutive entries of one plan that do not touch each other's tensors (the repeated layers of a network on
+// independent data, the projections of one activation by several weights) go out as ONE launch of up to kMaxSets
+// pointer sets: a launch costs the GPU 2 to 4 us of filling and draining the chip, and a layer of 200 workgroups
+// leaves part of it idle in between.  Entries that do depend on each other are launched one by one, in order.
 extern "C" int tt_run_kernels(const tt_kernel_desc *kernels, const tt_schedule *const *scheds, int nk, int repeat,
                               void *stream)
 {
     if (nk < 0 || repeat < 0 || (nk && !kernels)) return TT_ERR_BAD_ARG;
     for (int r = 0; r < repeat; ++r)
-        for (int k = 0; k < nk; ++k) {
+        for (int k = 0; k < nk;) {
             const tt_kernel_desc &d = kernels[k];
-            if (!d.shape) return TT_ERR_BAD_ARG;
-            if (d.use_count < 1) continue;
-            const OpPointers p = pointers_of(d);
-            if (!op_class(d.cls)) return TT_ERR_BAD_ARG;
-            if (const int rc = check_op_pointers(d.cls, p); rc != TT_OK) return rc;
-            PreparedOp op; // one plan for all use_count launches
-            if (const int rc = prepare_op(scheds ? scheds[k] : nullptr, d.cls, d.shape, &op); rc != TT_OK) return rc;
+            const tt_schedule *rec = scheds ? scheds[k] : nullptr;
+            if (!d.shape || d.cls < 0 || d.cls >= TT_NUM_CLASSES) return TT_ERR_BAD_ARG;
+            OpPointers calls[kMaxSets];
+            calls[0] = pointers_of(d);
+            if (const int rc = check_op_pointers(d.cls, calls[0]); rc != TT_OK) return rc;
+            PreparedOp op; // one plan for all launches of the entry and of those that go out with it
+            if (const int rc = prepare_op(rec, d.cls, d.shape, &op); rc != TT_OK) return rc;
+            int count = 1;
+            for (; d.use_count == 1 && count < kMaxSets && k + count < nk; ++count) {
+                const tt_kernel_desc &e = kernels[k + count];
+                if (e.use_count != 1 || !e.shape || !same_plan(d, rec, e, scheds ? scheds[k + count] : nullptr)) break;
+                const OpPointers p = pointers_of(e);
+                if (check_op_pointers(e.cls, p) != TT_OK || (p.bias == nullptr) != (calls[0].bias == nullptr)) break;
+                bool apart = true;
+                for (int i = 0; i < count && apart; ++i) apart = independent(op, calls[i], p);
+                if (!apart) break;
+                calls[count] = p;
+            }
             for (int u = 0; u < d.use_count; ++u)
-                if (const int rc = launch_op(op, p, stream); rc != TT_OK) return rc;
+                if (const int rc = launch_op(op, calls, count, stream); rc != TT_OK) return rc;
+            k += count;
         }
     return TT_OK;
 }

@@ -87,7 +87,7 @@ PyObject *call(int cls, const void *shape, PyObject *sched, OpPointers p, PyObje
     }
     if (rc == TT_OK) {
         void *const stream = current_stream();
-        Py_BEGIN_ALLOW_THREADS rc = launch_op(op, p, stream); // (a full queue makes a launch wait)
+        Py_BEGIN_ALLOW_THREADS rc = launch_op(op, &p, 1, stream); // (a full queue makes a launch wait)
         Py_END_ALLOW_THREADS
     }
     if (rc != TT_OK) return PyLong_FromLong(rc);

@@ -18,8 +18,9 @@ inline int launched()
 }
 
 // ---- direct sketch: one thread per output element ------------------------------------------------
-template <int DT, int FAM> __global__ void __launch_bounds__(256) direct_kernel(const ContractArgs g)
+template <int DT, int FAM> __global__ void __launch_bounds__(256) direct_kernel(const ContractArgs args, const PointerSets sets)
 {
+    const ContractArgs g = with_set(args, sets, blockIdx.y);
     using E = typename ElemOf<DT>::type;
     const int64_t total = (int64_t)g.batch * g.M * g.N;
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -62,8 +63,9 @@ template <int DT, int FAM> __global__ void __launch_bounds__(256) direct_kernel(
 }
 
 // ---- split-K: sum the partial tiles in split order, then the fused epilogue -----------------------
-template <int DT> __global__ void __launch_bounds__(256) splitk_reduce_kernel(const ContractArgs g)
+template <int DT> __global__ void __launch_bounds__(256) splitk_reduce_kernel(const ContractArgs args, const PointerSets sets)
 {
+    const ContractArgs g = with_set(args, sets, blockIdx.y);
     const int64_t total = (int64_t)g.batch * g.M * g.N;
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= total) return;
@@ -76,8 +78,9 @@ template <int DT> __global__ void __launch_bounds__(256) splitk_reduce_kernel(co
 }
 
 // ---- GEMV sketch: a wave owns WN outputs of TMR rows; lanes split K; butterfly reduction ---------
-template <int DT> __global__ void __launch_bounds__(1024) gemv_kernel(const ContractArgs g, int tile_m, int wave_n, int chunk)
+template <int DT> __global__ void __launch_bounds__(1024) gemv_kernel(const ContractArgs args, const PointerSets sets, int tile_m, int wave_n, int chunk)
 {
+    const ContractArgs g = with_set(args, sets, blockIdx.y);
     using E = typename ElemOf<DT>::type;
     const TileCoord tc = decode_tile(g.map, (int32_t)blockIdx.x);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -137,8 +140,9 @@ template <int DT> __global__ void __launch_bounds__(1024) gemv_kernel(const Cont
 // A plane is one (image, channel) pair, numbered image * C + channel.  Threads are laid out planes
 // fastest, then cols, then rows, so the lanes of a wave read and write neighbouring channels of one
 // pixel.  With two stages the input patch of the tile is first copied to LDS (planes fastest too).
-template <int WM, int WN, int MAXT> __global__ void __launch_bounds__(MAXT) dwconv3x3_kernel(const DwArgs g)
+template <int WM, int WN, int MAXT> __global__ void __launch_bounds__(MAXT) dwconv3x3_kernel(const DwArgs args, const PointerSets sets)
 {
+    const DwArgs g = with_set(args, sets, blockIdx.y);
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     float *patch = reinterpret_cast<float *>(smem_raw);
     const TileCoord tc = decode_tile(g.map, (int32_t)blockIdx.x);
@@ -218,8 +222,9 @@ template <int WM, int WN, int MAXT> __global__ void __launch_bounds__(MAXT) dwco
 // then forms its WN outputs.  Lanes of a wave hold neighbouring channel groups of one pixel, so
 // every load and store instruction covers one contiguous run of memory.
 template <int WM, int WN, int VC, int STR, int MAXT>
-__global__ void __launch_bounds__(MAXT) dwconv3x3_rows_kernel(const DwArgs g)
+__global__ void __launch_bounds__(MAXT) dwconv3x3_rows_kernel(const DwArgs args, const PointerSets sets)
 {
+    const DwArgs g = with_set(args, sets, blockIdx.y);
     typedef __attribute__((ext_vector_type(VC))) float vec_t;
     constexpr int COLS = (WN - 1) * STR + 3;
     const TileCoord tc = decode_tile(g.map, (int32_t)blockIdx.x);
@@ -302,8 +307,9 @@ __global__ void __launch_bounds__(MAXT) dwconv3x3_rows_kernel(const DwArgs g)
     }
 }
 
-__global__ void __launch_bounds__(256) dw_direct_kernel(const DwArgs g)
+__global__ void __launch_bounds__(256) dw_direct_kernel(const DwArgs args, const PointerSets sets)
 {
+    const DwArgs g = with_set(args, sets, blockIdx.y);
     // idx walks the NHWC output: (image, p, q, channel)
     const int64_t total = (int64_t)g.planes * g.Ho * g.Wo;
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -342,47 +348,47 @@ __global__ void __launch_bounds__(256) tile_map_dump_kernel(const TileMap map, i
     o[7] = c.k_ext;
 }
 
-template <int DT> int launch_direct_dt(const ContractArgs &a, int family, int grid, hipStream_t s)
+template <int DT> int launch_direct_dt(const ContractArgs &a, const PointerSets &sets, int family, int grid, hipStream_t s)
 {
     switch (family) {
-    case FAM_CONV: hipLaunchKernelGGL((direct_kernel<DT, FAM_CONV>), dim3(grid), dim3(256), 0, s, a); break;
-    case FAM_GEMM_TN: hipLaunchKernelGGL((direct_kernel<DT, FAM_GEMM_TN>), dim3(grid), dim3(256), 0, s, a); break;
-    default: hipLaunchKernelGGL((direct_kernel<DT, FAM_GEMM_NN>), dim3(grid), dim3(256), 0, s, a); break;
+    case FAM_CONV: hipLaunchKernelGGL((direct_kernel<DT, FAM_CONV>), dim3(grid, sets.count), dim3(256), 0, s, a, sets); break;
+    case FAM_GEMM_TN: hipLaunchKernelGGL((direct_kernel<DT, FAM_GEMM_TN>), dim3(grid, sets.count), dim3(256), 0, s, a, sets); break;
+    default: hipLaunchKernelGGL((direct_kernel<DT, FAM_GEMM_NN>), dim3(grid, sets.count), dim3(256), 0, s, a, sets); break;
     }
     return launched();
 }
 
 } // namespace
 
-int launch_direct(const ContractArgs &args, int family, int grid, void *stream)
+int launch_direct(const ContractArgs &args, const PointerSets &sets, int family, int grid, void *stream)
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
-    return args.dtype == TT_F32 ? launch_direct_dt<TT_F32>(args, family, grid, s)
-                                : launch_direct_dt<TT_BF16>(args, family, grid, s);
+    return args.dtype == TT_F32 ? launch_direct_dt<TT_F32>(args, sets, family, grid, s)
+                                : launch_direct_dt<TT_BF16>(args, sets, family, grid, s);
 }
 
-int launch_splitk_reduce(const ContractArgs &args, int family, void *stream)
+int launch_splitk_reduce(const ContractArgs &args, const PointerSets &sets, int family, void *stream)
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t total = (int64_t)args.batch * args.M * args.N;
     const int grid = (int)((total + 255) / 256);
     (void)family; // every family writes a row-major [M][N] output
     if (args.dtype == TT_F32)
-        hipLaunchKernelGGL((splitk_reduce_kernel<TT_F32>), dim3(grid), dim3(256), 0, s, args);
+        hipLaunchKernelGGL((splitk_reduce_kernel<TT_F32>), dim3(grid, sets.count), dim3(256), 0, s, args, sets);
     else
-        hipLaunchKernelGGL((splitk_reduce_kernel<TT_BF16>), dim3(grid), dim3(256), 0, s, args);
+        hipLaunchKernelGGL((splitk_reduce_kernel<TT_BF16>), dim3(grid, sets.count), dim3(256), 0, s, args, sets);
     return launched();
 }
 
-int launch_gemv(const ContractArgs &args, const tt_plan &plan, void *stream)
+int launch_gemv(const ContractArgs &args, const PointerSets &sets, const tt_plan &plan, void *stream)
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int chunk = plan.tile_k / 64;
     if (args.dtype == TT_F32)
-        hipLaunchKernelGGL((gemv_kernel<TT_F32>), dim3(plan.grid), dim3(plan.block), 0, s, args, plan.tile_m,
+        hipLaunchKernelGGL((gemv_kernel<TT_F32>), dim3(plan.grid, sets.count), dim3(plan.block), 0, s, args, sets, plan.tile_m,
                            plan.wave_n, chunk);
     else
-        hipLaunchKernelGGL((gemv_kernel<TT_BF16>), dim3(plan.grid), dim3(plan.block), 0, s, args, plan.tile_m,
+        hipLaunchKernelGGL((gemv_kernel<TT_BF16>), dim3(plan.grid, sets.count), dim3(plan.block), 0, s, args, sets, plan.tile_m,
                            plan.wave_n, chunk);
     return launched();
 }
@@ -410,7 +416,7 @@ int dw_max_block(int wave_m, int wave_n, int planes_per_lane, int stride, bool r
 
 namespace {
 
-template <int WM, int WN> int launch_dw_rows(const DwArgs &a, dim3 grid, dim3 block, hipStream_t s)
+template <int WM, int WN> int launch_dw_rows(const DwArgs &a, const PointerSets &sets, dim3 grid, dim3 block, hipStream_t s)
 {
     const int str = a.stride_h;
 #define TT_DW_ROWS(VC_, STR_)                                                                                        \
@@ -418,13 +424,13 @@ template <int WM, int WN> int launch_dw_rows(const DwArgs &a, dim3 grid, dim3 bl
         constexpr int LIMIT = dw_block_limit(WM, WN, VC_, STR_, true);                                               \
         if ((int)block.x > LIMIT) return TT_ERR_UNSUPPORTED;                                                         \
         if (block.x <= 256) {                                                                                        \
-            hipLaunchKernelGGL((dwconv3x3_rows_kernel<WM, WN, VC_, STR_, 256>), grid, block, 0, s, a);               \
+            hipLaunchKernelGGL((dwconv3x3_rows_kernel<WM, WN, VC_, STR_, 256>), grid, block, 0, s, a, sets);         \
         } else if (block.x <= 512) {                                                                                 \
             if constexpr (LIMIT >= 512)                                                                              \
-                hipLaunchKernelGGL((dwconv3x3_rows_kernel<WM, WN, VC_, STR_, 512>), grid, block, 0, s, a);           \
+                hipLaunchKernelGGL((dwconv3x3_rows_kernel<WM, WN, VC_, STR_, 512>), grid, block, 0, s, a, sets);     \
         } else {                                                                                                     \
             if constexpr (LIMIT >= 1024)                                                                             \
-                hipLaunchKernelGGL((dwconv3x3_rows_kernel<WM, WN, VC_, STR_, 1024>), grid, block, 0, s, a);          \
+                hipLaunchKernelGGL((dwconv3x3_rows_kernel<WM, WN, VC_, STR_, 1024>), grid, block, 0, s, a, sets);    \
         }                                                                                                            \
         return launched();                                                                                           \
     }
@@ -435,10 +441,10 @@ template <int WM, int WN> int launch_dw_rows(const DwArgs &a, dim3 grid, dim3 bl
 
 } // namespace
 
-int launch_dwconv(const DwArgs &a, const tt_plan &plan, void *stream)
+int launch_dwconv(const DwArgs &a, const PointerSets &sets, const tt_plan &plan, void *stream)
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const dim3 grid(plan.grid), block(plan.block);
+    const dim3 grid(plan.grid, sets.count), block(plan.block);
     const int lds = plan.lds_bytes;
     // One stage, strides 1 or 2 and a tensor within the 2 GiB offset range: the register kernel.
     // Everything else (the LDS patch of two stages, other strides): the general kernel, one plane per lane.
@@ -447,7 +453,7 @@ int launch_dwconv(const DwArgs &a, const tt_plan &plan, void *stream)
     if (!rows_kernel && a.eff_vec != 1) return TT_ERR_UNSUPPORTED;
 #define TT_DW_CASE(WM_, WN_)                                                                                         \
     if (a.wave_m == WM_ && a.wave_n == WN_) {                                                                        \
-        if (rows_kernel) return launch_dw_rows<WM_, WN_>(a, grid, block, s);                                         \
+        if (rows_kernel) return launch_dw_rows<WM_, WN_>(a, sets, grid, block, s);                                   \
         constexpr int LIMIT = dw_block_limit(WM_, WN_, 1, 1, false);                                                 \
         if ((int)block.x > LIMIT) return TT_ERR_UNSUPPORTED;                                                         \
         const int bc = block.x <= 256 ? 0 : block.x <= 512 ? 1 : 2;                                                  \
@@ -458,7 +464,7 @@ int launch_dwconv(const DwArgs &a, const tt_plan &plan, void *stream)
             if (bc == 2) kern = dwconv3x3_kernel<WM_, WN_, 1024>;                                                    \
         static DynamicLdsLimit limits[3]; /* per kernel instance; host threads may launch concurrently */           \
         if (const int rc = limits[bc].raise_to(reinterpret_cast<const void *>(kern), lds); rc != TT_OK) return rc;   \
-        hipLaunchKernelGGL(kern, grid, block, lds, s, a);                                                            \
+        hipLaunchKernelGGL(kern, grid, block, lds, s, a, sets);                                                      \
         return launched();                                                                                           \
     }
     TT_DW_CASE(1, 1) TT_DW_CASE(1, 2) TT_DW_CASE(1, 4) TT_DW_CASE(1, 7)
@@ -469,9 +475,9 @@ int launch_dwconv(const DwArgs &a, const tt_plan &plan, void *stream)
     return TT_ERR_UNSUPPORTED;
 }
 
-int launch_dw_direct(const DwArgs &a, int grid, void *stream)
+int launch_dw_direct(const DwArgs &a, const PointerSets &sets, int grid, void *stream)
 {
-    hipLaunchKernelGGL(dw_direct_kernel, dim3(grid), dim3(256), 0, static_cast<hipStream_t>(stream), a);
+    hipLaunchKernelGGL(dw_direct_kernel, dim3(grid, sets.count), dim3(256), 0, static_cast<hipStream_t>(stream), a, sets);
     return launched();
 }
 

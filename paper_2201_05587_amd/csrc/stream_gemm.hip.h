@@ -23,8 +23,9 @@ template <int DT, int TM, int TN, int TK, int WM, int WN, int MF> struct StreamL
 };
 
 template <int DT, int TM, int TN, int TK, int WM, int WN, int MF>
-__global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) gemm_stream_kernel(const ContractArgs g)
+__global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) gemm_stream_kernel(const ContractArgs args, const PointerSets sets)
 {
+    const ContractArgs g = with_set(args, sets, blockIdx.y);
     using E = typename ElemOf<DT>::type;
     constexpr int CH = ElemOf<DT>::CH, ES = (int)sizeof(E);
     constexpr int THREADS = (TM / WM) * (TN / WN) * 64;
@@ -116,9 +117,9 @@ __global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) gemm_stream_kernel
 }
 
 // `tiles` is the plan's grid (one entry per output tile); the launch itself is persistent: as many
-// workgroups as fit the chip (at most four per CU, as the LDS allows), a whole number per panel of B.
+// workgroups as fit the chip (at most four per CU, as the LDS allows), a whole number per panel of B and pointer set.
 template <int DT, int TM, int TN, int TK, int WM, int WN, int MF>
-int launch_gemm_stream(const ContractArgs &args, int tiles, int lds_bytes, void *stream)
+int launch_gemm_stream(const ContractArgs &args, const PointerSets &sets, int tiles, int lds_bytes, void *stream)
 {
     auto kern = gemm_stream_kernel<DT, TM, TN, TK, WM, WN, MF>;
     (void)tiles;
@@ -129,8 +130,8 @@ int launch_gemm_stream(const ContractArgs &args, int tiles, int lds_bytes, void 
     if (const int rc = limit.raise_to(reinterpret_cast<const void *>(kern), lds_bytes); rc != TT_OK) return rc;
     constexpr int THREADS = (TM / WM) * (TN / WN) * 64;
     const int fit = std::min(4, 160 * 1024 / lds_bytes);
-    const int per = std::max(1, std::min(args.map.tiles_m, compute_units() * fit / args.map.tiles_n));
-    hipLaunchKernelGGL(kern, dim3(per * args.map.tiles_n), dim3(THREADS), lds_bytes, static_cast<hipStream_t>(stream), args);
+    const int per = std::max(1, std::min(args.map.tiles_m, compute_units() * fit / (args.map.tiles_n * sets.count)));
+    hipLaunchKernelGGL(kern, dim3(per * args.map.tiles_n, sets.count), dim3(THREADS), lds_bytes, static_cast<hipStream_t>(stream), args, sets);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? TT_OK : note_hip_error((int)e, "gemm_stream_kernel launch");
 }

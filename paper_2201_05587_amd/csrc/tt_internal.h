@@ -147,6 +147,20 @@ enum Family {
     FAM_GEMM_NN = 2  // A = [M][K], B = [K][N] (batch matmul with trans_b = 0)
 };
 
+// The tensors of one operator call as a kernel sees them, and the sets a launch carries beyond the first: workgroups
+// (x, y) work on set y, so that several calls of one plan go out as one launch (see tt_run_kernels).  The first set's
+// pointers stay with the other arguments: a lone call reads no further lines of them.
+struct PointerSet {
+    const void *a, *b, *bias, *res;
+    void *out;
+    float *ws;
+};
+constexpr int kMaxSets = 8;
+struct PointerSets {
+    PointerSet more[kMaxSets - 1];
+    int32_t count;
+};
+
 // Everything a contraction kernel (matrix-core, direct or split-K reduce) needs, passed by value.
 struct ContractArgs {
     const void *a, *b, *bias, *res;
@@ -180,6 +194,29 @@ struct DwArgs {
     uint32_t x_bytes;  // size of the input tensor when it is below 2 GiB, else 0
 };
 
+TT_HD ContractArgs with_set(ContractArgs g, const PointerSets &sets, uint32_t set)
+{
+    if (set == 0) return g;
+    const PointerSet &p = sets.more[set - 1];
+    g.a = p.a;
+    g.b = p.b;
+    g.bias = p.bias;
+    g.res = p.res;
+    g.out = p.out;
+    g.ws = p.ws;
+    return g;
+}
+TT_HD DwArgs with_set(DwArgs g, const PointerSets &sets, uint32_t set)
+{
+    if (set == 0) return g;
+    const PointerSet &p = sets.more[set - 1];
+    g.x = static_cast<const float *>(p.a);
+    g.w = static_cast<const float *>(p.b);
+    g.bias = static_cast<const float *>(p.bias);
+    g.y = static_cast<float *>(p.out);
+    return g;
+}
+
 // The device tensors of one operator call (conv: x, w, bias, residual, y; dense and depthwise without a residual;
 // batch matmul without bias and residual) and the split-K workspace.
 struct OpPointers {
@@ -193,16 +230,17 @@ struct PreparedOp {
     tt_plan plan;
     int32_t cls, family;
     bool supported; // false: a valid plan that the entry point refuses (TT_ERR_UNSUPPORTED)
+    int64_t a_bytes, b_bytes, bias_bytes, out_bytes; // sizes of the tensors (a residual is as large as the output)
     ContractArgs g; // every class but the depthwise one
     DwArgs d;
 };
 
 // The operator entry points in three steps (ops.hip): argument check, plan and launch arguments (record NULL = the
-// default), launch.  A caller that launches a kernel repeatedly, or needs the plan's workspace size, does the
-// second step once.
+// default), launch of 1..kMaxSets calls (all with a bias or all without).  A caller that launches a kernel
+// repeatedly, or needs the plan's workspace size, does the second step once.
 int check_op_pointers(int cls, const OpPointers &p);
 int prepare_op(const tt_schedule *sched, int cls, const void *shape, PreparedOp *op);
-int launch_op(PreparedOp &op, const OpPointers &p, void *stream);
+int launch_op(PreparedOp &op, const OpPointers *calls, int count, void *stream);
 
 struct Variant {
     int32_t dtype, family, tile_m, tile_n, tile_k, wave_m, wave_n, mfma;
@@ -211,7 +249,7 @@ struct Variant {
                    // 2: 3x3 conv with the padded input patch in LDS and a filter ring of 3 or 4 (stages 5 or 6)
                    // 3: persistent dense kernel, the B panel resident in LDS and two A buffers (stages 7)
     int32_t stride; // pipe 2: the convolution stride the kernel is compiled for; 0 otherwise
-    int (*launch)(const ContractArgs &args, int grid, int lds_bytes, void *stream);
+    int (*launch)(const ContractArgs &args, const PointerSets &sets, int grid, int lds_bytes, void *stream);
     int (*stage_bytes)();        // pipes 0, 1: LDS bytes of one pipeline stage; pipe 2: pixels a patch buffer holds;
                                  // pipe 3: request instructions per lane and K slice
     int (*lds_bytes)(int stages); // LDS bytes for a plan's number of stages (pipe 3: for its number of K slices), as
@@ -230,12 +268,12 @@ int find_variant(int dtype, int family, int tm, int tn, int tk, int wm, int wn, 
 int family_of(int cls, int trans_b);
 
 // launchers of the non-matrix-core kernels (simple_kernels.hip)
-int launch_direct(const ContractArgs &args, int family, int grid, void *stream);
-int launch_splitk_reduce(const ContractArgs &args, int family, void *stream);
-int launch_gemv(const ContractArgs &args, const tt_plan &plan, void *stream);
+int launch_direct(const ContractArgs &args, const PointerSets &sets, int family, int grid, void *stream);
+int launch_splitk_reduce(const ContractArgs &args, const PointerSets &sets, int family, void *stream);
+int launch_gemv(const ContractArgs &args, const PointerSets &sets, const tt_plan &plan, void *stream);
 int dw_max_block(int wave_m, int wave_n, int planes_per_lane, int stride, bool rows_kernel);
-int launch_dwconv(const DwArgs &args, const tt_plan &plan, void *stream);
-int launch_dw_direct(const DwArgs &args, int grid, void *stream);
+int launch_dwconv(const DwArgs &args, const PointerSets &sets, const tt_plan &plan, void *stream);
+int launch_dw_direct(const DwArgs &args, const PointerSets &sets, int grid, void *stream);
 int launch_tile_map_dump(const TileMap &map, int32_t *out_dev, void *stream);
 
 // Remember the text of a failed HIP call for tt_last_error(); returns TT_ERR_HIP.

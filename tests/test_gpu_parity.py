@@ -618,3 +618,40 @@ def test_timing_rotates_through_the_alternative_tensor_sets(api, P):
 ])
 def test_reduction_split_inside_the_workgroup(api, P, name, cls, shape, rec):
     P.check_kernel(wl.Kernel(cls, shape, 1, name), [mfma(api, cls, **rec), mfma(api, cls, order=4, **rec)], seed=4321)
+
+
+# ---- entries of one plan that a list sends out as one launch ---------------------------------------------------------
+@pytest.mark.parametrize("name,kernel,rec", [
+    ("ring", wl.Kernel(4, wl.GemmShape(1, 96, 96, 96, 1, wl.BF16)), dict(tm=32, tn=32, tk=32, wm=16, wn=16, mf=16, stages=3)),
+    ("split", wl.Kernel(4, wl.GemmShape(1, 128, 128, 128, 1, wl.F32)), dict(tm=64, tn=64, tk=32, wm=32, wn=32, mf=32, split_k=2)),
+    ("stream", wl.Kernel(4, wl.GemmShape(1, 192, 192, 192, 1, wl.BF16)), dict(tm=64, tn=64, tk=64, wm=32, wn=32, mf=16, stages=7)),
+    ("conv", conv_kernel(wl.CLS_CONV2D_BIAS_ADD_RELU, 1, 16, 14, 16, 3, 1), dict(tm=32, tn=16, tk=16, wm=32, wn=16, mf=16)),
+    ("patch", conv_kernel(wl.CLS_CONV2D_BIAS_RELU, 2, 64, 10, 64, 3, 1, dtype=wl.BF16), dict(tm=64, tn=64, tk=64, wm=64, wn=32, mf=32, stages=5)),
+    ("default_gemv", wl.Kernel(4, wl.GemmShape(1, 3, 256, 256, 1, wl.F32)), None),
+    ("depthwise", wl.Kernel(8, wl.ConvShape(1, 24, 13, 13, 24, 3, 3, 1, 1, 1, 1)), None),
+])
+def test_list_of_one_plan_runs_every_entry_and_keeps_dependent_ones_in_order(api, P, name, kernel, rec):
+    """More entries than one launch carries; entries 3 and 7 read what the entry before them writes."""
+    import torch
+    from paper_2201_05587_amd import harness
+    sched = None if rec is None else mfma(api, kernel.cls, **rec)
+    dks = [harness.device_kernel(kernel, 500 + i, max_split=4) for i in range(11)]
+    shared = dks[5].tensors["w"]
+    tensors = [dict(dk.tensors) for dk in dks]
+    tensors[6]["w"] = shared
+    for i in (3, 7):  # the operators keep the shape, so an output can be the next one's input
+        tensors[i]["x"] = tensors[i - 1]["y"]
+    dks = [api.DeviceKernel(kernel.cls, kernel.shape, t, 1, name, dk.ws.numel()) for t, dk in zip(tensors, dks)]
+
+    def outputs(run):
+        for dk in dks:
+            dk.output().fill_(float("nan"))
+        run()
+        torch.cuda.synchronize()
+        return [dk.output().float().cpu().numpy() for dk in dks]
+
+    want = outputs(lambda: [dk.run(sched) for dk in dks])
+    for got in (outputs(lambda: api.KernelList(dks, [sched] * len(dks)).run()),
+                outputs(lambda: api.KernelList(dks, [sched] * len(dks)).run(2))):
+        for i, (g, w) in enumerate(zip(got, want)):
+            P.assert_close(g, w, kernel.shape.dtype, f"{name} {i}")
