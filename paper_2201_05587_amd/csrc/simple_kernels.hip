@@ -63,77 +63,132 @@ template <int DT, int FAM> __global__ void __launch_bounds__(256) direct_kernel(
 }
 
 // ---- split-K: sum the partial tiles in split order, then the fused epilogue -----------------------
-template <int DT> __global__ void __launch_bounds__(256) splitk_reduce_kernel(const ContractArgs args, const PointerSets sets)
+// Bound by latency: a few hundred KB that the contraction has just left in the caches.  A thread takes VEC
+// consecutive outputs of one row (N is a multiple of VEC) and asks for the partial sums of up to eight splits before
+// it adds the first; workgroups of one wave spread a small output over the CUs.
+template <int DT, int VEC> __global__ void __launch_bounds__(256) splitk_reduce_kernel(const ContractArgs args, const PointerSets sets)
 {
     const ContractArgs g = with_set(args, sets, blockIdx.y);
+    typedef __attribute__((ext_vector_type(VEC))) float vec_t;
     const int64_t total = (int64_t)g.batch * g.M * g.N;
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t idx = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * VEC;
     if (idx >= total) return;
-    float acc = 0.0f;
-    for (int z = 0; z < g.map.eff_split_k; ++z) acc += g.ws[(int64_t)z * total + idx];
-    const int n = (int)(idx % g.N);
-    if (g.has_bias) acc += load_as_float<DT>(g.bias, n);
-    if (g.has_res) acc += load_as_float<DT>(g.res, idx);
-    store_from_float<DT>(g.out, idx, apply_act(acc, g.act));
+    const int n = (int)(idx % g.N), splits = g.map.eff_split_k;
+    const float *ws = g.ws + idx;
+    float res[VEC] = {}, bias[VEC] = {};
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+        if (g.has_bias) bias[e] = load_as_float<DT>(g.bias, n + e);
+        if (g.has_res) res[e] = load_as_float<DT>(g.res, idx + e);
+    }
+    vec_t acc = vec_t(0.0f);
+    for (int z0 = 0; z0 < splits; z0 += 8) {
+        vec_t part[8];
+#pragma unroll
+        for (int z = 0; z < 8; ++z) // (past the last split: the last one again, not added)
+            part[z] = *reinterpret_cast<const vec_t *>(ws + (int64_t)min(z0 + z, splits - 1) * total);
+#pragma unroll
+        for (int z = 0; z < 8; ++z)
+            if (z0 + z < splits) acc += part[z];
+    }
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) store_from_float<DT>(g.out, idx + e, apply_act(acc[e] + bias[e] + res[e], g.act));
 }
 
-// ---- GEMV sketch: a wave owns WN outputs of TMR rows; lanes split K; butterfly reduction ---------
-template <int DT> __global__ void __launch_bounds__(1024) gemv_kernel(const ContractArgs args, const PointerSets sets, int tile_m, int wave_n, int chunk)
+// ---- GEMV sketch: a wave owns W outputs of R rows; lanes split K ---------------------------------
+// Bound by latency (a classifier reads 2 MB): every lane asks for four pieces of EV elements of each row and each
+// weight vector before it multiplies the first, so a reduction of 256 EV elements pays the memory once, and the
+// lanes' sums are added by data-parallel moves (DPP) instead of six trips through the LDS crossbar.  A first
+// version loaded element by element: 1 x 512 x 1000 in f32 took 5.7 us, now 2.8.  A call is then bound by the host's
+// launch, which takes 3.1 us with up to 64 bytes of kernel arguments and 4.5 us from 256 bytes on: the arguments are
+// this kernel's own, in 64 bytes.
+struct GemvArgs {
+    const void *x, *w, *bias; // bias may be null
+    void *out;
+    int32_t M, N, K, tiles_n;
+    FastDiv div_n;                          // by tiles_n
+    uint8_t tile_m, wave_n, waves, act;     // rows of a workgroup, outputs per wave, waves per workgroup
+};
+static_assert(sizeof(GemvArgs) <= 64, "");
+
+template <int CTRL, int ROWS> __device__ __forceinline__ float dpp_add(float v)
 {
-    const ContractArgs g = with_set(args, sets, blockIdx.y);
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, false));
+}
+__device__ __forceinline__ float wave_sum(float v) // the sum of all lanes, in lane 63
+{
+    v = dpp_add<0x111, 0xf>(v); // row_shr:1
+    v = dpp_add<0x112, 0xf>(v); // row_shr:2
+    v = dpp_add<0x114, 0xf>(v); // row_shr:4
+    v = dpp_add<0x118, 0xf>(v); // row_shr:8: lane 15 of every row of 16 has the row's sum
+    v = dpp_add<0x142, 0xa>(v); // row_bcast:15 into rows 1 and 3
+    return dpp_add<0x143, 0xc>(v); // row_bcast:31 into rows 2 and 3
+}
+
+template <int DT, int EV> struct GemvPiece { // EV consecutive elements as floats
     using E = typename ElemOf<DT>::type;
-    const TileCoord tc = decode_tile(g.map, (int32_t)blockIdx.x);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n_first = tc.n0 + wave * wave_n;
-    const E *x = static_cast<const E *>(g.a), *w = static_cast<const E *>(g.b);
-    const int ev = g.eff_vec_a;
-    // Every array below is indexed by unrolled loop counters only (rows and outputs beyond tile_m and
-    // wave_n are skipped by wave-uniform tests), so all of it stays in registers.
-    float acc[8][8];
+    E e[EV];
+    __device__ __forceinline__ void load(const E *p) { __builtin_memcpy(e, __builtin_assume_aligned(p, EV * sizeof(E)), sizeof e); }
+    __device__ __forceinline__ float at(int i) const
+    {
+        if constexpr (DT == TT_F32)
+            return e[i];
+        else
+            return bf16_bits_to_float(e[i]);
+    }
+};
+
+template <int DT, int R, int W, int EV> __global__ void __launch_bounds__(1024) gemv_kernel(const GemvArgs g)
+{
+    using E = typename ElemOf<DT>::type;
+    constexpr int U = R * W >= 64 ? 1 : R * W >= 16 ? 2 : 4; // pieces in flight per vector
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tile_m = g.tile_m, wave_n = g.wave_n;
+    const int im = (int)fast_div(blockIdx.x, g.div_n), in = (int)blockIdx.x - im * g.tiles_n;
+    const int m_first = im * tile_m, n_first = (in * g.waves + wave) * wave_n;
+    // rows and outputs beyond tile_m, wave_n or the matrix read the last one again and are not written
+    const E *x[R], *w[W];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < R; ++i) x[i] = static_cast<const E *>(g.x) + (int64_t)min(m_first + min(i, tile_m - 1), g.M - 1) * g.K;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = 0.0f;
-    const int step = 64 * chunk;
-    for (int kb = 0; kb < g.K; kb += step) {
-        const int k = kb + lane * chunk;
-        for (int c0 = 0; c0 < chunk; c0 += ev) {
-            // ev consecutive K per access; K % ev == 0 so a group is all in or all out
-            if (k + c0 >= g.K) break;
-            for (int e = 0; e < ev; ++e) {
-                const int64_t kk = k + c0 + e;
-                float xv[8], wv[8];
+    for (int j = 0; j < W; ++j) w[j] = static_cast<const E *>(g.w) + (int64_t)min(n_first + min(j, wave_n - 1), g.N - 1) * g.K;
+    float acc[R][W];
 #pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    xv[i] = (i < tile_m && tc.m0 + i < g.M) ? load_as_float<DT>(x, (int64_t)(tc.m0 + i) * g.K + kk) : 0.0f;
+    for (int i = 0; i < R; ++i)
 #pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    wv[j] = (j < wave_n && n_first + j < g.N) ? load_as_float<DT>(w, (int64_t)(n_first + j) * g.K + kk) : 0.0f;
+        for (int j = 0; j < W; ++j) acc[i][j] = 0.0f;
+    for (int kb = lane * EV; kb < g.K; kb += 64 * EV * U) { // K is a multiple of EV: a piece is all in or all out
+        GemvPiece<DT, EV> xp[U][R], wp[U][W];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    if (i >= tile_m) break;
+        for (int u = 0; u < U; ++u) {
+            const int k = min(kb + u * 64 * EV, g.K - EV);
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) acc[i][j] = fmaf(xv[i], wv[j], acc[i][j]);
-                }
-            }
+            for (int i = 0; i < R; ++i) xp[u][i].load(x[i] + k);
+#pragma unroll
+            for (int j = 0; j < W; ++j) wp[u][j].load(w[j] + k);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (kb + u * 64 * EV >= g.K) break;
+#pragma unroll
+            for (int e = 0; e < EV; ++e)
+#pragma unroll
+                for (int i = 0; i < R; ++i)
+#pragma unroll
+                    for (int j = 0; j < W; ++j) acc[i][j] = fmaf(xp[u][i].at(e), wp[u][j].at(e), acc[i][j]);
         }
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        if (i >= tile_m) break;
+    for (int i = 0; i < R; ++i)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            if (j >= wave_n) break;
-            float v = acc[i][j];
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-            const int m = tc.m0 + i, n = n_first + j;
-            if (lane == 0 && m < g.M && n < g.N && n < tc.n0 + tc.n_ext) {
-                if (g.has_bias) v += load_as_float<DT>(g.bias, n);
+        for (int j = 0; j < W; ++j) {
+            float v = wave_sum(acc[i][j]);
+            const int m = m_first + i, n = n_first + j;
+            if (lane == 63 && i < tile_m && j < wave_n && m < g.M && n < g.N) {
+                if (g.bias) v += load_as_float<DT>(g.bias, n);
                 store_from_float<DT>(g.out, (int64_t)m * g.N + n, apply_act(v, g.act));
             }
         }
-    }
 }
 
 // ---- depthwise 3x3 over NHWC: (rows, cols, planes) tile per workgroup, WM x WN outputs per thread ---
@@ -370,27 +425,60 @@ int launch_direct(const ContractArgs &args, const PointerSets &sets, int family,
 int launch_splitk_reduce(const ContractArgs &args, const PointerSets &sets, int family, void *stream)
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int64_t total = (int64_t)args.batch * args.M * args.N;
-    const int grid = (int)((total + 255) / 256);
     (void)family; // every family writes a row-major [M][N] output
-    if (args.dtype == TT_F32)
-        hipLaunchKernelGGL((splitk_reduce_kernel<TT_F32>), dim3(grid, sets.count), dim3(256), 0, s, args, sets);
-    else
-        hipLaunchKernelGGL((splitk_reduce_kernel<TT_BF16>), dim3(grid, sets.count), dim3(256), 0, s, args, sets);
+    const int vec = args.N % 4 == 0 ? 4 : 1;
+    const int64_t threads = (int64_t)args.batch * args.M * args.N / vec;
+    const int block = threads <= 256 * 256 ? 64 : 256; // up to a workgroup of one wave for each SIMD of the chip
+    const dim3 grid((unsigned)((threads + block - 1) / block), sets.count);
+    auto kern = vec == 4 ? splitk_reduce_kernel<TT_F32, 4> : splitk_reduce_kernel<TT_F32, 1>;
+    if (args.dtype == TT_BF16) kern = vec == 4 ? splitk_reduce_kernel<TT_BF16, 4> : splitk_reduce_kernel<TT_BF16, 1>;
+    hipLaunchKernelGGL(kern, grid, dim3(block), 0, s, args, sets);
     return launched();
 }
+
+namespace {
+
+template <int DT, int R, int W> void launch_gemv_rw(const GemvArgs &g, const tt_plan &plan, hipStream_t s)
+{
+    auto kern = gemv_kernel<DT, R, W, 1>;
+    if (plan.eff_vec_a == 2) kern = gemv_kernel<DT, R, W, 2>;
+    if (plan.eff_vec_a == 4) kern = gemv_kernel<DT, R, W, 4>;
+    if constexpr (DT == TT_BF16) // (8 x 8 sums leave registers for pieces of 4)
+        if (plan.eff_vec_a == 8) kern = gemv_kernel<DT, R, W, R * W < 64 ? 8 : 4>;
+    hipLaunchKernelGGL(kern, dim3(plan.grid), dim3(plan.block), 0, s, g);
+}
+// instances for 1, 2, 4 and 8 rows and outputs per wave; others run on the next larger one
+template <int DT, int R> void launch_gemv_r(const GemvArgs &g, const tt_plan &plan, hipStream_t s)
+{
+    if (plan.wave_n <= 1) return launch_gemv_rw<DT, R, 1>(g, plan, s);
+    if (plan.wave_n <= 2) return launch_gemv_rw<DT, R, 2>(g, plan, s);
+    if (plan.wave_n <= 4) return launch_gemv_rw<DT, R, 4>(g, plan, s);
+    return launch_gemv_rw<DT, R, 8>(g, plan, s);
+}
+template <int DT> void launch_gemv_dt(const GemvArgs &g, const tt_plan &plan, hipStream_t s)
+{
+    if (plan.tile_m <= 1) return launch_gemv_r<DT, 1>(g, plan, s);
+    if (plan.tile_m <= 2) return launch_gemv_r<DT, 2>(g, plan, s);
+    if (plan.tile_m <= 4) return launch_gemv_r<DT, 4>(g, plan, s);
+    return launch_gemv_r<DT, 8>(g, plan, s);
+}
+
+} // namespace
 
 int launch_gemv(const ContractArgs &args, const PointerSets &sets, const tt_plan &plan, void *stream)
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int chunk = plan.tile_k / 64;
-    if (args.dtype == TT_F32)
-        hipLaunchKernelGGL((gemv_kernel<TT_F32>), dim3(plan.grid, sets.count), dim3(plan.block), 0, s, args, sets, plan.tile_m,
-                           plan.wave_n, chunk);
-    else
-        hipLaunchKernelGGL((gemv_kernel<TT_BF16>), dim3(plan.grid, sets.count), dim3(plan.block), 0, s, args, sets, plan.tile_m,
-                           plan.wave_n, chunk);
-    return launched();
+    for (int i = 0; i < sets.count; ++i) { // (one launch each: the table of sets would not fit the 64 bytes)
+        const ContractArgs a = with_set(args, sets, (uint32_t)i);
+        const GemvArgs g = {a.a, a.b, a.bias, a.out, a.M, a.N, a.K, plan.tiles_n, a.map.div_n,
+                            (uint8_t)plan.tile_m, (uint8_t)plan.wave_n, (uint8_t)(plan.block / 64), (uint8_t)a.act};
+        if (args.dtype == TT_F32)
+            launch_gemv_dt<TT_F32>(g, plan, s);
+        else
+            launch_gemv_dt<TT_BF16>(g, plan, s);
+        if (const int rc = launched(); rc != TT_OK) return rc;
+    }
+    return TT_OK;
 }
 
 // The depthwise kernels are compiled for workgroups of at most 256, 512 and 1024 threads, which leaves a
