@@ -81,7 +81,16 @@ __device__ __forceinline__ float apply_act(float v, int act)
     }
 }
 
-// The same on N values with one (uniform) branch for all of them.
+// Four GELUs out of line: the expansion of erff is some 60 instructions with two branches, and an epilogue of 32 unrolled
+// vectors held 256 of them, most of the kernel's code, which every other activation had to fetch its way around.
+__device__ __noinline__ f32x4 gelu4(f32x4 v)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = 0.5f * v[e] * (1.0f + erff(v[e] * 0.70710678118654752f));
+    return v;
+}
+
+// The same on N values (a multiple of 4) with one (uniform) branch for all of them.
 template <int N> __device__ __forceinline__ void apply_act_all(float (&v)[N], int act)
 {
     switch (act) {
@@ -95,7 +104,10 @@ template <int N> __device__ __forceinline__ void apply_act_all(float (&v)[N], in
         break;
     case ACT_GELU:
 #pragma unroll
-        for (int e = 0; e < N; ++e) v[e] = 0.5f * v[e] * (1.0f + erff(v[e] * 0.70710678118654752f));
+        for (int e = 0; e < N; e += 4) {
+            const f32x4 r = gelu4(f32x4{v[e], v[e + 1], v[e + 2], v[e + 3]});
+            v[e] = r[0], v[e + 1] = r[1], v[e + 2] = r[2], v[e + 3] = r[3];
+        }
         break;
     default: break;
     }
@@ -702,7 +714,8 @@ template <int N> __device__ __forceinline__ void wait_loads_outstanding(); // (d
 
 // WAIT_LOADS: the caller has asynchronous requests in flight that must have landed before the first store
 // is issued (a persistent kernel's next tile); the wait sits behind the staging of the first band.
-template <int DT, int TM, int WM, int WN, int MF, typename Acc, bool ALLOW, bool WAIT_LOADS = false>
+// ANY_ROWS: false where the host has checked that rows are whole 16-byte vectors long.
+template <int DT, int TM, int WM, int WN, int MF, typename Acc, bool ALLOW, bool WAIT_LOADS = false, bool ANY_ROWS = true>
 __device__ __forceinline__ void write_tile(Acc (&acc)[WM / MF][WN / MF], const ContractArgs &g, const TileCoord &tc,
                                            unsigned char *smem, int wave, int lane, const BiasRegs<DT> &bias,
                                            const ResRegs<DT, TM, WM, WN, MF, ALLOW> &early)
@@ -717,7 +730,7 @@ __device__ __forceinline__ void write_tile(Acc (&acc)[WM / MF][WN / MF], const C
     const int64_t mn = (int64_t)g.M * g.N;
     float *ws = g.ws + ((int64_t)tc.lo * g.batch) * mn;
     const int vc = g.eff_vec_c; // consecutive outputs of a row that are all inside or all outside the matrix
-    const bool whole = DT == TT_BF16 ? vc == 8 : vc >= 4; // rows are whole 16-byte vectors long
+    const bool whole = !ANY_ROWS || (DT == TT_BF16 ? vc == 8 : vc >= 4); // rows are whole 16-byte vectors long
     const int64_t out_base = (int64_t)bidx * mn;
     const int cg = lane % CG;
     const int first = tc.n0 + T::col(wave, lane);
@@ -756,25 +769,31 @@ __device__ __forceinline__ void write_tile(Acc (&acc)[WM / MF][WN / MF], const C
         asm volatile("" ::: "memory"); // and the reads below stay behind them
         if constexpr (WAIT_LOADS)
             if (i == 0) wait_loads_outstanding<0>();
+        if (whole) {
+            // Rows are whole vectors long: the lane's 8 columns (fp32: its two groups of 4) need no
+            // further checks and no loop.
 #pragma unroll
-        for (int ps = 0; ps < PASSES; ++ps) {
-            if (!T::pass_live(lane, ps)) continue;
-            const int row_l = ps * T::ROWS_PER_PASS + lane / CG;
-            const f32x4 lo = *reinterpret_cast<const f32x4 *>(stage + row_l * ESTRIDE + cg * 8);
-            const f32x4 hi = *reinterpret_cast<const f32x4 *>(stage + row_l * ESTRIDE + cg * 8 + 4);
-            const int m = tc.m0 + T::row(wave, lane, i, ps);
-            if (m >= g.M || first >= g.N) continue;
-            const int64_t row_at = out_base + (int64_t)m * g.N + first;
-            if (whole) {
-                // Rows are whole vectors long: the lane's 8 columns (fp32: its two groups of 4) need no
-                // further checks and no loop.
-                write_row_vector<DT>(g, ws, partial, row_at, first, lo, hi, biasf, resv[ps]);
-                continue;
+            for (int ps = 0; ps < PASSES; ++ps) {
+                const int row_l = ps * T::ROWS_PER_PASS + lane / CG;
+                const int m = tc.m0 + T::row(wave, lane, i, ps);
+                if (!T::pass_live(lane, ps) || m >= g.M || first >= g.N) continue;
+                const f32x4 lo = *reinterpret_cast<const f32x4 *>(stage + row_l * ESTRIDE + cg * 8);
+                const f32x4 hi = *reinterpret_cast<const f32x4 *>(stage + row_l * ESTRIDE + cg * 8 + 4);
+                write_row_vector<DT>(g, ws, partial, out_base + (int64_t)m * g.N + first, first, lo, hi, biasf, resv[ps]);
             }
+        } else if constexpr (ANY_ROWS) {
             // any other row length: element by element, out of line (rare, and it must not cost the
-            // path above registers)
-            write_row_elements<DT>(ws, g.out, g.bias, g.res, partial, g.has_bias, g.has_res, g.act, row_at, first,
-                                   min(8, g.N - first), lo, hi);
+            // path above registers or code)
+#pragma unroll 1
+            for (int ps = 0; ps < PASSES; ++ps) {
+                const int row_l = ps * T::ROWS_PER_PASS + lane / CG;
+                const int m = tc.m0 + T::row(wave, lane, i, ps);
+                if (!T::pass_live(lane, ps) || m >= g.M || first >= g.N) continue;
+                const f32x4 lo = *reinterpret_cast<const f32x4 *>(stage + row_l * ESTRIDE + cg * 8);
+                const f32x4 hi = *reinterpret_cast<const f32x4 *>(stage + row_l * ESTRIDE + cg * 8 + 4);
+                write_row_elements<DT>(ws, g.out, g.bias, g.res, partial, g.has_bias, g.has_res, g.act,
+                                       out_base + (int64_t)m * g.N + first, first, min(8, g.N - first), lo, hi);
+            }
         }
     }
 }
