@@ -1100,21 +1100,24 @@ template <int DT, int ROWS, int TK, int THREADS> struct AsyncGather {
         st.row_stride = g.W * g.C;
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
-            const int m = row0 + first + i * (THREADS / CPR);
-            const bool live = m < g.M;
-            const uint32_t um = live ? (uint32_t)m : 0u;
-            const uint32_t img = fast_div(um, g.div_hw);
-            const uint32_t rem = um - img * (uint32_t)(g.Ho * g.Wo);
-            const uint32_t p = fast_div(rem, g.div_wo), q = rem - p * (uint32_t)g.Wo;
-            const int ih0 = (int)p * g.stride_h - g.pad_h, iw0 = (int)q * g.stride_w - g.pad_w;
-            st.origin[i] = (((int)img * g.H + ih0) * g.W + iw0) * g.C;
-            const int lo = max(0, -ih0), hi = min(g.R, g.H - ih0);
-            const uint32_t below_hi = hi >= 32 ? 0xffffffffu : ((1u << max(hi, 0)) - 1u);
-            const uint32_t below_lo = (1u << min(lo, 31)) - 1u;
-            st.rmask[i] = (live && hi > lo) ? (below_hi & ~below_lo) : 0u;
-            st.jlo[i] = max(0, -iw0) * g.C;
-            st.jhi[i] = min(g.S, g.W - iw0) * g.C;
+            init_row(st, i, g, row0 + first + i * (THREADS / CPR));
         }
+    }
+    static __device__ __forceinline__ void init_row(State &st, int i, const ContractArgs &g, int m)
+    {
+        const bool live = m < g.M;
+        const uint32_t um = live ? (uint32_t)m : 0u;
+        const uint32_t img = fast_div(um, g.div_hw);
+        const uint32_t rem = um - img * (uint32_t)(g.Ho * g.Wo);
+        const uint32_t p = fast_div(rem, g.div_wo), q = rem - p * (uint32_t)g.Wo;
+        const int ih0 = (int)p * g.stride_h - g.pad_h, iw0 = (int)q * g.stride_w - g.pad_w;
+        st.origin[i] = (((int)img * g.H + ih0) * g.W + iw0) * g.C;
+        const int lo = max(0, -ih0), hi = min(g.R, g.H - ih0);
+        const uint32_t below_hi = hi >= 32 ? 0xffffffffu : ((1u << max(hi, 0)) - 1u);
+        const uint32_t below_lo = (1u << min(lo, 31)) - 1u;
+        st.rmask[i] = (live && hi > lo) ? (below_hi & ~below_lo) : 0u;
+        st.jlo[i] = max(0, -iw0) * g.C;
+        st.jhi[i] = min(g.S, g.W - iw0) * g.C;
     }
     // Request the current slice, then step (r, j) to the next one.  `inside`: false if this thread's chunk of the
     // slice lies past the end of its split of the reduction (it then reads as zeros).
