@@ -1339,19 +1339,6 @@ __global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) contract_async_ker
     write_tile<DT, TM, WM, WN, MF>(acc, g, tc, smem, wave, lane, bias, res_early);
 }
 
-// Compute units of the current device (asked once; one device per process).
-inline int compute_units()
-{
-    static const int cus = [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
-            n = 256;
-        return n;
-    }();
-    return cus;
-}
-
 // More than 48 KB of dynamic LDS has to be enabled per kernel.  Remembers the largest size enabled so far
 // (one device per process); host threads may launch the same kernel concurrently.
 struct DynamicLdsLimit {

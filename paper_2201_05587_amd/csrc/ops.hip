@@ -3,6 +3,7 @@
 
 #include <algorithm>
 #include <chrono>
+#include <cmath>
 #include <cstdio>
 #include <atomic>
 #include <cstring>
@@ -22,12 +23,72 @@ int note_hip_error(int code, const char *where)
 }
 } // namespace tt
 
+namespace tt {
+// Compute units of the current device (asked once; one device per process).
+int compute_units()
+{
+    static const int cus = [] {
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
+            n = 256;
+        return n;
+    }();
+    return cus;
+}
+} // namespace tt
+
 extern "C" const char *tt_last_error(void) { return tt::g_last_error; }
 
 namespace {
 
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline int conv_out(int in, int f, int stride, int pad) { return (in + 2 * pad - f) / stride + 1; }
+
+// Estimated time (us) of a launch in tiles of tm x tn: a CU takes in 80 GB/s of operand rows and multiplies at 1/256 of
+// the rate a large product reaches (bf16 1450, f32 147 TFLOP/s); workgroups beyond one per CU share both.  Tiles of 32 x 32
+// take a quarter longer than that (16 x 16 wave tiles read two LDS fragments per product).
+double tile_estimate(const tt_plan &p, int dtype, int tm, int tn)
+{
+    const double tiles = (double)p.batch * ((p.M + tm - 1) / tm) * ((p.N + tn - 1) / tn);
+    const double rows = (tm + tn) * (dtype == TT_F32 ? 4.0 : 2.0) / 80e3;
+    const double products = 2.0 * tm * tn / (dtype == TT_F32 ? 0.57e6 : 5.65e6);
+    return std::ceil(tiles / compute_units()) * p.K * std::max(rows, products) * (tm * tn <= 1024 ? 1.25 : 1.0);
+}
+
+// The plan that is launched for a record's plan.  A record of the register pipeline (one or two stages: the default
+// schedule above all) whose operands the asynchronous ring can load is run on ring instances, in the tile that the
+// estimate above likes best for this shape; everything else about the operator, and what the plan reports, stays as the
+// record says.  Splits of the reduction keep their own kernel: their partial sums are cut where the record says.
+// The register pipeline holds one slice in flight, in registers.  Default records, before -> after (us): bf16 dense
+// 73x168x3152 46.9 -> 7.1, f32 dense 77x40x1040 42.7 -> 9.4, f32 3x3 392 -> 104 channels on 2 x 15x15 133 -> 25.7, bf16 1x1
+// 152 -> 440 on 13x13 5.4 -> 3.5; the geometric mean over 60 shapes drawn between 2 MFLOP and 60 GFLOP is 2.1 times.
+tt_plan launch_plan_of(const tt_plan &plan, int cls, const void *shape, int dtype)
+{
+    if (plan.sketch != TT_SK_MFMA || plan.variant_id < 0 || plan.stages > 2 || plan.eff_split_k != 1) return plan;
+    static const int tiles[2][6][6] = {
+        // tile_m, tile_n, tile_k, wave_m, wave_n, mfma
+        {{32, 32, 32, 16, 16, 16}, {64, 64, 32, 32, 32, 16}, {128, 64, 32, 32, 32, 16}, {64, 128, 32, 32, 32, 16}, {128, 128, 32, 32, 64, 16}, {}},
+        {{32, 32, 64, 16, 16, 16}, {64, 64, 64, 32, 32, 16}, {128, 64, 64, 32, 32, 16}, {64, 128, 128, 32, 32, 16}, {128, 128, 64, 32, 64, 32}, {128, 256, 64, 32, 64, 16}},
+    };
+    tt_plan best = plan;
+    double best_us = 1e30;
+    for (const auto &t : tiles[dtype == TT_F32 ? 0 : 1]) {
+        if (!t[0]) continue;
+        const double us = tile_estimate(plan, dtype, t[0], t[1]);
+        if (us >= best_us) continue;
+        tt_schedule r;
+        std::memset(&r, 0, sizeof r);
+        r.cls = cls, r.sketch = TT_SK_MFMA;
+        r.tile_m = t[0], r.tile_n = t[1], r.tile_k = t[2], r.wave_m = t[3], r.wave_n = t[4], r.mfma = t[5];
+        r.split_k = 1, r.order = 4, r.vec = dtype == TT_F32 ? 4 : 8, r.unroll = 8, r.stages = 3;
+        tt_plan p;
+        if (tt_schedule_apply(&r, cls, shape, 0, &p) != TT_OK || p.stages != 3 || p.variant_id < 0) continue;
+        best = p;
+        best_us = us;
+    }
+    return best;
+}
 
 void fill_common(ContractArgs &g, const tt_plan &plan, int cls, int dtype)
 {
@@ -66,7 +127,7 @@ int run_contraction(const ContractArgs &g, const PointerSets &sets, const tt_pla
 
 void prepare_conv(const tt_conv_shape &s, PreparedOp *op)
 {
-    const tt_plan &plan = op->plan;
+    const tt_plan &plan = op->launch;
     // the matrix-core kernels address both tensors with 32-bit byte offsets below 2^31 and keep one
     // bit per filter row
     const int elem = s.dtype == TT_F32 ? 4 : 2;
@@ -142,6 +203,7 @@ int prepare_op(const tt_schedule *sched, int cls, const void *shape, PreparedOp 
     if (rc != TT_OK) return rc;
     op->cls = cls;
     op->supported = true;
+    op->launch = op->plan;
     const bool image = is_conv_class(cls) || cls == TT_DWCONV_BIAS_RELU6;
     const tt_conv_shape *cs = static_cast<const tt_conv_shape *>(shape);
     const tt_gemm_shape *gs = static_cast<const tt_gemm_shape *>(shape);
@@ -164,9 +226,11 @@ int prepare_op(const tt_schedule *sched, int cls, const void *shape, PreparedOp 
         std::memset(&op->d, 0, sizeof op->d);
         prepare_dw(*cs, op);
     } else if (is_conv_class(cls)) {
+        op->launch = launch_plan_of(op->plan, cls, shape, cs->dtype);
         prepare_conv(*cs, op);
     } else {
-        fill_common(op->g, op->plan, cls, gs->dtype);
+        op->launch = launch_plan_of(op->plan, cls, shape, gs->dtype);
+        fill_common(op->g, op->launch, cls, gs->dtype);
         op->g.Ho = op->g.Wo = 1;
         op->family = family_of(cls, gs->trans_b);
     }
@@ -212,7 +276,7 @@ int launch_op(PreparedOp &op, const OpPointers *calls, int count, void *stream)
     g.ws = static_cast<float *>(first.ws);
     g.has_bias = first.bias != nullptr;
     g.has_res = first.res != nullptr;
-    return run_contraction(g, sets, op.plan, op.family, stream);
+    return run_contraction(g, sets, op.launch, op.family, stream);
 }
 
 } // namespace tt

@@ -227,7 +227,8 @@ struct OpPointers {
 
 // A kernel under a record, laid out once: the plan and the launch arguments without the pointers.
 struct PreparedOp {
-    tt_plan plan;
+    tt_plan plan;   // of the record
+    tt_plan launch; // what is launched for it (ops.hip, launch_plan_of)
     int32_t cls, family;
     bool supported; // false: a valid plan that the entry point refuses (TT_ERR_UNSUPPORTED)
     int64_t a_bytes, b_bytes, bias_bytes, out_bytes; // sizes of the tensors (a residual is as large as the output)
@@ -278,6 +279,9 @@ int dw_max_block(int wave_m, int wave_n, int planes_per_lane, int stride, bool r
 int launch_dwconv(const DwArgs &args, const PointerSets &sets, const tt_plan &plan, void *stream);
 int launch_dw_direct(const DwArgs &args, const PointerSets &sets, int grid, void *stream);
 int launch_tile_map_dump(const TileMap &map, int32_t *out_dev, void *stream);
+
+// Compute units of the current device (asked once; one device per process).
+int compute_units();
 
 // Remember the text of a failed HIP call for tt_last_error(); returns TT_ERR_HIP.
 int note_hip_error(int hip_error_code, const char *where);

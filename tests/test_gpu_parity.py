@@ -671,3 +671,17 @@ def test_list_of_one_plan_runs_every_entry_and_keeps_dependent_ones_in_order(api
 ])
 def test_large_bf16_launches_run_in_blocks(api, P, name, cls, shape):
     P.check_kernel(wl.Kernel(cls, shape, 1, name), [None], seed=99)
+
+
+# ---- register-pipeline records run on ring instances in a tile chosen by size ----------------------------------------
+@pytest.mark.parametrize("dt", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("m,n,k", [
+    (32, 32, 64), (33, 40, 72),       # one tile and a ragged edge of the smallest
+    (65, 520, 136), (300, 1032, 96),  # small tiles on part of the chip
+    (2000, 776, 264), (4100, 640, 520),  # 64 and 128 rows or columns, ragged
+    (47, 90, 130), (64, 61, 65),      # rows that are not whole items: the record's own kernel
+])
+def test_register_pipeline_records_in_the_tile_their_size_asks_for(api, P, m, n, k, dt):
+    cls = wl.CLS_DENSE_BIAS_RELU
+    one_stage = mfma(api, cls, 32, 32, 32, 16, 16, 16, vec=2, unroll=1, stages=1)
+    P.check_kernel(wl.Kernel(cls, wl.GemmShape(1, m, n, k, 1, dt), 1, f"dense_{m}_{n}_{k}"), [None, one_stage], seed=7)
