@@ -577,7 +577,12 @@ extern "C" int tt_run_kernels(const tt_kernel_desc *kernels, const tt_schedule *
         for (int k = 0; k < nk;) {
             const tt_kernel_desc &d = kernels[k];
             const tt_schedule *rec = scheds ? scheds[k] : nullptr;
-            if (!d.shape || d.cls < 0 || d.cls >= TT_NUM_CLASSES) return TT_ERR_BAD_ARG;
+            if (!d.shape) return TT_ERR_BAD_ARG;
+            if (d.use_count <= 0) { // nothing to launch: neither record nor tensors are looked at
+                ++k;
+                continue;
+            }
+            if (d.cls < 0 || d.cls >= TT_NUM_CLASSES) return TT_ERR_BAD_ARG;
             OpPointers calls[kMaxSets];
             calls[0] = pointers_of(d);
             if (const int rc = check_op_pointers(d.cls, calls[0]); rc != TT_OK) return rc;

@@ -1,4 +1,5 @@
 """Host logic of libtt against the integer oracle, bit for bit (no GPU needed)."""
+import ctypes
 import os
 import random
 import re
@@ -504,3 +505,16 @@ def test_refine_space_matches_oracle():
         assert len(set(map(key, got))) == len(got)
         checked += 1
     assert checked > 200
+
+
+def test_list_entry_that_is_launched_no_times_is_passed_over():
+    """Neither its tensors nor its record are looked at; a missing shape is still an error."""
+    d = (api.tt_kernel_desc * 2)()
+    shape = api.to_c_shape(wl.GemmShape(1, 64, 64, 64, 1, wl.F32))
+    for e in d:
+        e.cls, e.use_count, e.shape = wl.CLS_DENSE_ADD, 0, ctypes.addressof(shape)
+    assert api.lib.tt_run_kernels(d, None, 2, 1, None) == api.TT_OK
+    d[1].cls = -1
+    assert api.lib.tt_run_kernels(d, None, 2, 1, None) == api.TT_OK
+    d[1].shape = None
+    assert api.lib.tt_run_kernels(d, None, 2, 1, None) == api.TT_ERR_BAD_ARG
