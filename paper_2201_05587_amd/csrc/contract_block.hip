@@ -15,8 +15,9 @@ namespace tt {
 //   share 1.00 (4096 x 4096 x 1024)  64x64 48.3, 128x64 54.6, 128x128 49.4, 128x256 34.8   blocks 35.9
 //   share 0.75, two rounds (8192 x 3072 x 3072)  the best record of all 135.3              blocks 140.9
 // and 4096 x 4096 x 4096: 128x64 166, blocks 105 (1.31 PFLOP/s; operands of zeros: 78, the chip's power sets the
-// clock).  Register-pipeline records (64x64 default: 4096 x 4096 x 1024 82 us) give way at a quarter.
-bool block_applies(const ContractArgs &a, int family, int count, int tile_outputs, bool register_pipeline)
+// clock).  A record of the register pipeline comes here as the ring record that runs it (launch_plan_of): where operands are
+// whole items and the reduction is not split, which blocks need too, it has one.
+bool block_applies(const ContractArgs &a, int family, int count, int tile_outputs)
 {
     if (a.dtype != TT_BF16 || a.batch != 1 || a.map.eff_split_k != 1 || a.K < 1024) return false;
     if (a.eff_vec_a != 8 || a.eff_vec_b != 8 || a.eff_vec_c != 8) return false;
@@ -24,7 +25,6 @@ bool block_applies(const ContractArgs &a, int family, int count, int tile_output
     const int64_t blocks = (int64_t)((a.M + 255) / 256) * ((a.N + 255) / 256) * count;
     const int64_t cus = compute_units(), rounds = (blocks + cus - 1) / cus;
     const double share = (double)a.M * a.N * count / (65536.0 * (double)(cus * rounds));
-    if (register_pipeline) return share >= 0.25;
     if (tile_outputs <= 64 * 128) return share >= 0.5;
     if (tile_outputs <= 128 * 128) return share >= 0.55;
     return share >= (rounds == 1 ? 0.55 : 0.95);

@@ -10,8 +10,6 @@ namespace tt {
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF, int AM>
 int launch_contract(const ContractArgs &args, const PointerSets &sets, int grid, int lds_bytes, void *stream)
 {
-    if constexpr (DT == TT_BF16 && (FAM == FAM_GEMM_TN || (FAM == FAM_CONV && AM == 16)))
-        if (block_applies(args, FAM, sets.count, TM * TN, true)) return launch_blocks(args, sets, FAM, stream);
     if constexpr (FAM == FAM_GEMM_TN || (FAM == FAM_CONV && AM == 16))
         if (groups_apply<DT, FAM, TM, TN, WM, WN, MF>(args, grid * sets.count)) return launch_groups<DT, FAM, TM, TN, WM, WN, MF>(args, sets, grid, stream);
     auto kern = contract_kernel<DT, FAM, TM, TN, TK, WM, WN, MF, AM>;
@@ -48,7 +46,7 @@ template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF>
 int launch_contract_async(const ContractArgs &args, const PointerSets &sets, int grid, int lds_bytes, void *stream)
 {
     if constexpr (DT == TT_BF16)
-        if (block_applies(args, FAM, sets.count, TM * TN, false)) return launch_blocks(args, sets, FAM, stream);
+        if (block_applies(args, FAM, sets.count, TM * TN)) return launch_blocks(args, sets, FAM, stream);
     if (groups_apply<DT, FAM, TM, TN, WM, WN, MF>(args, grid * sets.count)) return launch_groups<DT, FAM, TM, TN, WM, WN, MF>(args, sets, grid, stream);
     auto kern = contract_async_kernel<DT, FAM, TM, TN, TK, WM, WN, MF>;
     constexpr int EPI_BYTES = (TM / WM) * (TN / WN) * MF * (WN + (MF == 32 ? 8 : 4)) * 4;

@@ -273,7 +273,7 @@ int launch_direct(const ContractArgs &args, const PointerSets &sets, int family,
 int launch_splitk_reduce(const ContractArgs &args, const PointerSets &sets, int family, void *stream);
 int launch_gemv(const ContractArgs &args, const PointerSets &sets, const tt_plan &plan, void *stream);
 // the 256 x 256 block kernel (contract_block.hip): whether a launch of `count` sets runs on it, and its launch
-bool block_applies(const ContractArgs &args, int family, int count, int tile_outputs, bool register_pipeline);
+bool block_applies(const ContractArgs &args, int family, int count, int tile_outputs);
 int launch_blocks(const ContractArgs &args, const PointerSets &sets, int family, void *stream);
 int dw_max_block(int wave_m, int wave_n, int planes_per_lane, int stride, bool rows_kernel);
 int launch_dwconv(const DwArgs &args, const PointerSets &sets, const tt_plan &plan, void *stream);
