@@ -659,18 +659,24 @@ def test_list_of_one_plan_runs_every_entry_and_keeps_dependent_ones_in_order(api
 
 # ---- 256 x 256 blocks (large bf16 launches, whatever tile the record names) ------------------------------------------
 @pytest.mark.parametrize("name,cls,shape", [
-    # a quarter of the chip's blocks and more: ragged M, N and last slice; a band of fewer than four block rows
-    ("gemm", wl.CLS_DENSE_BIAS_GELU, wl.GemmShape(1, 2100, 2056, 1032, 1, wl.BF16)),
-    ("gemm_one_column", wl.CLS_DENSE_ADD, wl.GemmShape(1, 16500, 256, 1024, 1, wl.BF16)),
+    # half of the chip's blocks and more: ragged M, N and last slice; a band of fewer than four block rows
+    ("gemm", wl.CLS_DENSE_BIAS_GELU, wl.GemmShape(1, 3000, 2904, 1032, 1, wl.BF16)),
+    ("gemm_one_column", wl.CLS_DENSE_ADD, wl.GemmShape(1, 33000, 256, 1024, 1, wl.BF16)),
     ("gemm_two_rounds", wl.CLS_DENSE_BIAS_RELU, wl.GemmShape(1, 4200, 4104, 1024, 1, wl.BF16)),
     # gathers: padded borders, images that end inside a block, a residual, strides, slices that straddle filter rows
-    ("conv", wl.CLS_CONV2D_BIAS_RELU, wl.ConvShape(3, 120, 85, 71, 264, 3, 3, 1, 1, 1, 1, wl.BF16)),
-    ("conv_res", wl.CLS_CONV2D_BIAS_ADD_RELU, wl.ConvShape(2, 128, 96, 96, 256, 3, 3, 1, 1, 1, 1, wl.BF16)),
-    ("conv_s2", wl.CLS_CONV2D_ADD, wl.ConvShape(8, 128, 97, 95, 264, 3, 3, 2, 2, 1, 1, wl.BF16)),
-    ("conv5x5", wl.CLS_CONV2D_BIAS_RELU, wl.ConvShape(5, 48, 63, 61, 256, 5, 5, 1, 1, 2, 2, wl.BF16)),
+    ("conv", wl.CLS_CONV2D_BIAS_RELU, wl.ConvShape(3, 120, 107, 99, 264, 3, 3, 1, 1, 1, 1, wl.BF16)),
+    ("conv_res", wl.CLS_CONV2D_BIAS_ADD_RELU, wl.ConvShape(4, 128, 91, 91, 256, 3, 3, 1, 1, 1, 1, wl.BF16)),
+    ("conv_s2", wl.CLS_CONV2D_ADD, wl.ConvShape(8, 128, 127, 125, 264, 3, 3, 2, 2, 1, 1, wl.BF16)),
+    ("conv5x5", wl.CLS_CONV2D_BIAS_RELU, wl.ConvShape(9, 48, 63, 61, 256, 5, 5, 1, 1, 2, 2, wl.BF16)),
 ])
 def test_large_bf16_launches_run_in_blocks(api, P, name, cls, shape):
-    P.check_kernel(wl.Kernel(cls, shape, 1, name), [None], seed=99)
+    # a ring record of 64 x 64 tiles gives way to blocks from half of the chip's outputs on
+    ring = mfma(api, cls, 64, 64, 64, 32, 32, 16, stages=3)
+    kernel = wl.Kernel(cls, shape, 1, name)
+    _, m, n, k = kernel.gemm_extents()
+    rounds = -(-(-(-m // 256) * -(-n // 256)) // 256)
+    assert k >= 1024 and m * n >= 65536 * 256 * rounds // 2
+    P.check_kernel(kernel, [None, ring], seed=99)
 
 
 # ---- register-pipeline records run on ring instances in a tile chosen by size ----------------------------------------
