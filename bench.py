@@ -357,9 +357,8 @@ def main():
 
     # ---- per-kernel durations with HIP events on the launch stream, cold: a kernel is launched in turn on
     # enough tensor sets that a set has left the caches (256 MB memory-side cache, 32 MB of L2) before its
-    # turn comes again.  Every launch this process makes is entered in a ledger per kernel symbol, so the
-    # average duration reported for the dominant symbol is the one a kernel trace of this same command
-    # (with --no-live-sweep) shows.
+    # turn comes again.  Every launch this process asks for is entered in a ledger per symbol its record names;
+    # a kernel trace shows fewer dispatches, since up to eight entries of one plan go out together.
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     ledger = {}
 

@@ -494,7 +494,9 @@ def tt_variant_info(variant_id: int):
 
 
 def variant_name(plan: tt_plan, shape=None) -> str:
-    """Name of the kernel a plan launches, spelled like the demangled symbol rocprofv3 reports.
+    """Name of the kernel a plan names, spelled like the demangled symbol rocprofv3 reports.  (A launch of at most one
+    workgroup per CU, a large bf16 one, or one of a register-pipeline record may run on contract_groups_kernel,
+    contract_block_kernel or a ring instance in its place.)
 
     `shape` (a conv shape) is needed only to tell the two depthwise kernels apart.
     """
