@@ -230,11 +230,18 @@ __global__ void __launch_bounds__((GroupShape<DT, TM, TN, WM, WN, MF>::THREADS))
 // 25.2 -> 17.8; K = 1152: 100 workgroups 14.9 -> 11.2; K = 960: 125 workgroups 13.2 -> 9.3; K = 576: 196 workgroups
 // 8.9 -> 7.7.  bf16 64x64 tiles: K = 4608: 200 workgroups 23.1 -> 19.7; K = 2048: 16.1 -> 11.8; 64x64 default record
 // (register pipeline), K = 1152: 17.4 -> 7.3.
-template <int DT, int FAM, int TM, int TN, int WM, int WN, int MF> bool groups_apply(const ContractArgs &a, int grid)
+// Larger launches: a record whose ring takes more than half of the LDS (plain_lds; 0: not a ring) runs one workgroup of
+// at most four waves per CU whatever its grid, and groups help there too once the reduction has twelve slices.  Plain ->
+// groups (us), 64x64 bf16 tiles on 3136 x 1024: K = 384 13.0 -> 14.9, 768 17.9 -> 18.5, 1536 26.9 -> 25.7, 4608
+// 67.0 -> 60.2; 64x64 fp32 on 1600 x 800: K = 384 19.4 -> 19.5, 768 32.8 -> 31.8, 4608 169 -> 155; 7x7 3x3 convolutions
+// of 512 channels, batch 32, in lists: 21.4 -> 18.8 an entry.
+template <int DT, int FAM, int TM, int TN, int WM, int WN, int MF> bool groups_apply(const ContractArgs &a, int grid, int plain_lds)
 {
     using S = GroupShape<DT, TM, TN, WM, WN, MF>;
     if constexpr (S::KG == 1) return false;
-    return grid <= compute_units() && a.map.k_iters * a.map.tile_k >= 3 * S::TKI && a.eff_vec_a * S::ES == 16 && a.eff_vec_b * S::ES == 16 &&
+    const int reduction = a.map.k_iters * a.map.tile_k;
+    const bool alone = grid <= compute_units() || (S::WAVES <= 4 && 2 * plain_lds > kLdsBudget && reduction >= 12 * S::TKI);
+    return alone && reduction >= 3 * S::TKI && a.eff_vec_a * S::ES == 16 && a.eff_vec_b * S::ES == 16 &&
            (FAM == FAM_CONV || ((int64_t)a.M * a.K * S::ES < (1ll << 31) && (int64_t)a.N * a.K * S::ES < (1ll << 31)));
 }
 

@@ -11,7 +11,7 @@ template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF, int A
 int launch_contract(const ContractArgs &args, const PointerSets &sets, int grid, int lds_bytes, void *stream)
 {
     if constexpr (FAM == FAM_GEMM_TN || (FAM == FAM_CONV && AM == 16))
-        if (groups_apply<DT, FAM, TM, TN, WM, WN, MF>(args, grid * sets.count)) return launch_groups<DT, FAM, TM, TN, WM, WN, MF>(args, sets, grid, stream);
+        if (groups_apply<DT, FAM, TM, TN, WM, WN, MF>(args, grid * sets.count, 0)) return launch_groups<DT, FAM, TM, TN, WM, WN, MF>(args, sets, grid, stream);
     auto kern = contract_kernel<DT, FAM, TM, TN, TK, WM, WN, MF, AM>;
     // the epilogue stages one band of MF rows per wave in the same LDS
     constexpr int EPI_BYTES = (TM / WM) * (TN / WN) * MF * (WN + (MF == 32 ? 8 : 4)) * 4;
@@ -47,7 +47,7 @@ int launch_contract_async(const ContractArgs &args, const PointerSets &sets, int
 {
     if constexpr (DT == TT_BF16)
         if (block_applies(args, FAM, sets.count, TM * TN)) return launch_blocks(args, sets, FAM, stream);
-    if (groups_apply<DT, FAM, TM, TN, WM, WN, MF>(args, grid * sets.count)) return launch_groups<DT, FAM, TM, TN, WM, WN, MF>(args, sets, grid, stream);
+    if (groups_apply<DT, FAM, TM, TN, WM, WN, MF>(args, grid * sets.count, lds_bytes)) return launch_groups<DT, FAM, TM, TN, WM, WN, MF>(args, sets, grid, stream);
     auto kern = contract_async_kernel<DT, FAM, TM, TN, TK, WM, WN, MF>;
     constexpr int EPI_BYTES = (TM / WM) * (TN / WN) * MF * (WN + (MF == 32 ? 8 : 4)) * 4;
     if (lds_bytes < EPI_BYTES) lds_bytes = EPI_BYTES;

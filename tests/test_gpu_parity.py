@@ -610,6 +610,9 @@ def test_timing_rotates_through_the_alternative_tensor_sets(api, P):
     ("grid_256", 4, wl.GemmShape(1, 32 * 256, 32, 384, 1, wl.F32), dict(tm=32, tn=32, tk=32, wm=16, wn=16, mf=16, stages=3)),
     ("grid_257", 4, wl.GemmShape(1, 32 * 256 + 1, 32, 384, 1, wl.F32), dict(tm=32, tn=32, tk=32, wm=16, wn=16, mf=16, stages=3)),
     ("batches", 7, wl.GemmShape(5, 65, 48, 400, 1, wl.BF16), dict(tm=64, tn=32, tk=64, wm=32, wn=32, mf=32, stages=4)),
+    # more workgroups than CUs on a ring that leaves room for one: eleven slices (the plain kernel) and twelve, ragged
+    ("large_11", 4, wl.GemmShape(1, 1090, 1010, 1408, 1, wl.BF16), dict(tm=64, tn=64, tk=128, wm=32, wn=32, mf=32, stages=3)),
+    ("large_12", 4, wl.GemmShape(1, 1090, 1016, 1416, 1, wl.BF16), dict(tm=64, tn=64, tk=128, wm=32, wn=32, mf=32, stages=3)),
     # convolutions: gathers at padded borders, a residual, a split across workgroups that ends inside a slice
     ("conv", 1, wl.ConvShape(2, 40, 15, 11, 72, 3, 3, 1, 1, 1, 1, wl.BF16), dict(tm=64, tn=64, tk=32, wm=32, wn=32, mf=16, stages=2)),
     ("conv_res_s2", 2, wl.ConvShape(1, 64, 17, 17, 64, 3, 3, 2, 2, 1, 1, wl.F32), dict(tm=32, tn=32, tk=32, wm=16, wn=16, mf=16, stages=3)),
