@@ -611,7 +611,7 @@ template <int DT, int TM, int WM, int WN, int MF, bool ALLOW = true> struct ResR
     static constexpr bool EARLY = ALLOW && T::NI * T::PASSES * W <= 4;
     u32x4 v[EARLY ? T::NI : 1][EARLY ? T::PASSES : 1][W];
 };
-// One pass's residual items of a lane (rows past the matrix read the tile's first row: any valid address).
+// One pass's residual items of a lane (lanes past the matrix read the tile's first item, see residual_element).
 template <int DT, int TM, int WM, int WN, int MF>
 __device__ __forceinline__ void load_res_pass(u32x4 (&dst)[DT == TT_BF16 ? 1 : 2], const ContractArgs &g, const TileCoord &tc,
                                               int wave, int lane, int i, int ps)
@@ -620,7 +620,7 @@ __device__ __forceinline__ void load_res_pass(u32x4 (&dst)[DT == TT_BF16 ? 1 : 2
     const int first = tc.n0 + T::col(wave, lane);
     const int m = tc.m0 + T::row(wave, lane, i, ps);
     const bool live = T::pass_live(lane, ps) && m < g.M && first < g.N;
-    const int64_t row_at = (int64_t)tc.hi * g.M * g.N + (int64_t)(live ? m : tc.m0) * g.N + (live ? first : tc.n0);
+    const int64_t row_at = residual_element(tc, g.M, g.N, live, m, first);
     if constexpr (DT == TT_BF16) {
         dst[0] = *reinterpret_cast<const u32x4 *>(static_cast<const uint16_t *>(g.res) + row_at);
     } else {

@@ -261,9 +261,10 @@ __global__ void __launch_bounds__(512) contract_block_kernel(const ContractArgs 
         const BiasRegs<DT> bias = load_bias_columns<DT>(g, tc.n0 + k * 128 + T::col(epi_wave, lane));
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            TileCoord q = tc;
-            q.m0 = tc.m0 + h * 128;
-            q.n0 = tc.n0 + k * 128;
+            TileCoord q;
+            // nothing to write outside the matrix, and no valid address there (the first quadrant is always inside: its
+            // barrier separates the operands from the staging of all four)
+            if (!block_quadrant(tc, g.M, g.N, h, k, &q)) continue;
             write_tile<DT, 128, 64, 32, MF, typename M::Acc, false, false, false>(acc[h][k], g, q, smem, epi_wave, lane, bias, no_res);
         }
     }

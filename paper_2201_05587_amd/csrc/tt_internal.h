@@ -114,6 +114,24 @@ TT_HD TileCoord decode_tile(const TileMap &p, int32_t wg)
     return c;
 }
 
+// Element of the residual (and the output) at which a lane fetches its vector of a pass: its own where the lane is
+// `live` (row m, columns from `first`, inside the matrix), else the first one of its tile, whose value nobody uses: the
+// tile must start inside the matrix.
+TT_HD int64_t residual_element(const TileCoord &tc, int32_t M, int32_t N, bool live, int32_t m, int32_t first)
+{
+    return (int64_t)tc.hi * M * N + (int64_t)(live ? m : tc.m0) * N + (live ? first : tc.n0);
+}
+
+// Quadrant (h, k) of a 256 x 256 block, as a tile of its own; false where it lies outside the matrix (a last block of at
+// most 128 rows or columns).
+TT_HD bool block_quadrant(const TileCoord &block, int32_t M, int32_t N, int32_t h, int32_t k, TileCoord *quadrant)
+{
+    *quadrant = block;
+    quadrant->m0 = block.m0 + h * 128;
+    quadrant->n0 = block.n0 + k * 128;
+    return quadrant->m0 < M && quadrant->n0 < N;
+}
+
 inline TileMap tile_map_of(const tt_plan &pl)
 {
     TileMap m;
