@@ -277,6 +277,15 @@ def workspace_bytes(sched, cls, shape) -> int:
     return int(plan.workspace_bytes) if plan.status == TT_OK else 0
 
 
+def _refuse_struct(obj, expected):
+    """A structure argument of another type: the error ctypes gives for it."""
+    byref(obj)  # TypeError for anything that is no ctypes object at all
+    raise ctypes.ArgumentError(f"expected {expected.__name__} instance instead of {type(obj).__name__}")
+
+
+_ttcall.bind(tt_conv_shape, tt_gemm_shape, tt_schedule, _refuse_struct)
+
+
 def _result(out, where):
     """What the native call returned: the output tensor, or the status of a call that failed."""
     if type(out) is int:

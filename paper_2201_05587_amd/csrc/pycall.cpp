@@ -20,27 +20,46 @@ using namespace tt;
 
 namespace {
 
-// The memory of a ctypes structure of at least `size` bytes, held while the call lasts.
-class StructView {
+// What the binding hands over once.
+PyObject *conv_shape_type, *gemm_shape_type, *schedule_type;
+PyObject *refuse_struct;  // (object, expected type): raises what ctypes raises for such an argument
+
+// A reference that ends with the scope.
+class Owned {
 public:
-    StructView(PyObject *obj, size_t size, const char *what)
+    explicit Owned(PyObject *o) : o_(o)
     {
-        if (PyObject_GetBuffer(obj, &view_, PyBUF_SIMPLE) != 0) throw python_error();
-        held_ = true;
-        TORCH_CHECK_TYPE((size_t)view_.len >= size, what, " expected");
+        if (!o) throw python_error();
     }
-    ~StructView()
-    {
-        if (held_) PyBuffer_Release(&view_);
-    }
-    StructView(const StructView &) = delete;
-    StructView &operator=(const StructView &) = delete;
-    template <class T> const T &as() const { return *static_cast<const T *>(view_.buf); }
+    ~Owned() { Py_DECREF(o_); }
+    Owned(const Owned &) = delete;
+    Owned &operator=(const Owned &) = delete;
+    PyObject *get() const { return o_; }
 
 private:
-    Py_buffer view_;
-    bool held_ = false;
+    PyObject *o_;
 };
+
+// The contents of a ctypes structure of one type (or a type derived from it): a buffer of the right size alone could be a
+// structure of another layout.
+template <class T> T struct_of(PyObject *obj, PyObject *type)
+{
+    int ok = (PyObject *)Py_TYPE(obj) == type;
+    if (!ok) ok = PyObject_IsInstance(obj, type);
+    if (ok < 0) throw python_error();
+    if (!ok) {
+        Owned unreachable(PyObject_CallFunctionObjArgs(refuse_struct, obj, type, nullptr));
+        TORCH_CHECK_TYPE(false, "wrong type");
+    }
+    Py_buffer view;
+    if (PyObject_GetBuffer(obj, &view, PyBUF_SIMPLE) != 0) throw python_error();
+    const bool whole = (size_t)view.len >= sizeof(T);
+    T out{};
+    if (whole) out = *static_cast<const T *>(view.buf);
+    PyBuffer_Release(&view);
+    TORCH_CHECK_TYPE(whole, "structure without its contents");
+    return out;
+}
 
 const at::Tensor *tensor_or_null(PyObject *o, const char *name)
 {
@@ -71,7 +90,7 @@ PyObject *call(int cls, const void *shape, PyObject *sched, OpPointers p, PyObje
     PreparedOp op;
     {
         tt_schedule rec;
-        if (sched != Py_None) rec = StructView(sched, sizeof(tt_schedule), "a tt_schedule record").as<tt_schedule>();
+        if (sched != Py_None) rec = struct_of<tt_schedule>(sched, schedule_type);
         const at::Tensor *given = tensor_or_null(ws, "ws");
         if (given) {
             p.ws = given->data_ptr();
@@ -105,7 +124,7 @@ PyObject *py_conv2d(PyObject *, PyObject *const *a, Py_ssize_t n)
     TORCH_CHECK_TYPE(n == 9, "conv2d takes nine arguments");
     const at::Tensor *x = tensor_or_null(a[0], "x"), *w = tensor_or_null(a[1], "w"), *b = tensor_or_null(a[2], "bias"),
                      *r = tensor_or_null(a[3], "residual"), *y = tensor_or_null(a[8], "y");
-    const tt_conv_shape s = StructView(a[4], sizeof(tt_conv_shape), "a tt_conv_shape").as<tt_conv_shape>();
+    const tt_conv_shape s = struct_of<tt_conv_shape>(a[4], conv_shape_type);
     const long cls = PyLong_AsLong(a[5]);
     if (cls == -1 && PyErr_Occurred()) throw python_error();
     TORCH_CHECK_TYPE(x, "x must be a tensor");
@@ -125,7 +144,7 @@ PyObject *py_dense(PyObject *, PyObject *const *a, Py_ssize_t n)
     TORCH_CHECK_TYPE(n == 8, "dense takes eight arguments");
     const at::Tensor *x = tensor_or_null(a[0], "x"), *w = tensor_or_null(a[1], "w"), *b = tensor_or_null(a[2], "bias"),
                      *y = tensor_or_null(a[7], "y");
-    const tt_gemm_shape s = StructView(a[3], sizeof(tt_gemm_shape), "a tt_gemm_shape").as<tt_gemm_shape>();
+    const tt_gemm_shape s = struct_of<tt_gemm_shape>(a[3], gemm_shape_type);
     const long cls = PyLong_AsLong(a[4]);
     if (cls == -1 && PyErr_Occurred()) throw python_error();
     TORCH_CHECK_TYPE(x, "x must be a tensor");
@@ -143,7 +162,7 @@ PyObject *py_matmul(PyObject *, PyObject *const *a, Py_ssize_t n)
     HANDLE_TH_ERRORS
     TORCH_CHECK_TYPE(n == 6, "matmul takes six arguments");
     const at::Tensor *x = tensor_or_null(a[0], "a"), *w = tensor_or_null(a[1], "b"), *y = tensor_or_null(a[5], "c");
-    const tt_gemm_shape s = StructView(a[2], sizeof(tt_gemm_shape), "a tt_gemm_shape").as<tt_gemm_shape>();
+    const tt_gemm_shape s = struct_of<tt_gemm_shape>(a[2], gemm_shape_type);
     TORCH_CHECK_TYPE(x, "a must be a tensor");
     at::Tensor out;
     if (!y) out = at::empty({s.batch, s.m, s.n}, x->options());
@@ -159,7 +178,7 @@ PyObject *py_dwconv(PyObject *, PyObject *const *a, Py_ssize_t n)
     TORCH_CHECK_TYPE(n == 6, "dwconv takes six arguments");
     const at::Tensor *x = tensor_or_null(a[0], "x"), *w = tensor_or_null(a[1], "w"), *b = tensor_or_null(a[2], "bias"),
                      *y = tensor_or_null(a[5], "y");
-    const tt_conv_shape s = StructView(a[3], sizeof(tt_conv_shape), "a tt_conv_shape").as<tt_conv_shape>();
+    const tt_conv_shape s = struct_of<tt_conv_shape>(a[3], conv_shape_type);
     TORCH_CHECK_TYPE(x, "x must be a tensor");
     at::Tensor out;
     const int64_t ho = out_extent(s.h, s.pad_h, s.r, s.stride_h), wo = out_extent(s.w, s.pad_w, s.s, s.stride_w);
@@ -167,6 +186,20 @@ PyObject *py_dwconv(PyObject *, PyObject *const *a, Py_ssize_t n)
     return call(TT_DWCONV_BIAS_RELU6, &s, a[4],
                 {x->data_ptr(), data_of(w), data_of(b), nullptr, y ? y->data_ptr() : out.data_ptr(), nullptr, 0}, Py_None, out, a[5]);
     END_HANDLE_TH_ERRORS
+}
+
+// bind(conv shape type, gemm shape type, schedule type, refuse_struct): once, by the binding
+PyObject *py_bind(PyObject *, PyObject *args)
+{
+    PyObject *o[4];
+    if (!PyArg_ParseTuple(args, "OOOO", &o[0], &o[1], &o[2], &o[3])) return nullptr;
+    PyObject **const slots[4] = {&conv_shape_type, &gemm_shape_type, &schedule_type, &refuse_struct};
+    for (int i = 0; i < 4; ++i) {
+        PyObject *const before = *slots[i];
+        *slots[i] = Py_NewRef(o[i]);
+        Py_XDECREF(before);
+    }
+    Py_RETURN_NONE;
 }
 
 // The handle of the current stream of the current device.
@@ -178,6 +211,7 @@ PyObject *py_stream(PyObject *, PyObject *)
 }
 
 PyMethodDef methods[] = {
+    {"bind", py_bind, METH_VARARGS, nullptr},
     {"conv2d", (PyCFunction)(void (*)())py_conv2d, METH_FASTCALL, nullptr},
     {"dense", (PyCFunction)(void (*)())py_dense, METH_FASTCALL, nullptr},
     {"matmul", (PyCFunction)(void (*)())py_matmul, METH_FASTCALL, nullptr},
