@@ -283,7 +283,12 @@ def _refuse_struct(obj, expected):
     raise ctypes.ArgumentError(f"expected {expected.__name__} instance instead of {type(obj).__name__}")
 
 
-_ttcall.bind(tt_conv_shape, tt_gemm_shape, tt_schedule, _refuse_struct)
+def _empty_tensor(x, sizes):
+    """An output beside an `x` that is no plain tensor."""
+    return _torch().empty(sizes, dtype=x.dtype, device=x.device)
+
+
+_ttcall.bind(tt_conv_shape, tt_gemm_shape, tt_schedule, _refuse_struct, _empty_tensor)
 
 
 def _result(out, where):

@@ -20,9 +20,10 @@ using namespace tt;
 
 namespace {
 
-// What the binding hands over once.
+// What the binding hands over once: its structure types, and functions for what is rare enough for Python.
 PyObject *conv_shape_type, *gemm_shape_type, *schedule_type;
 PyObject *refuse_struct;  // (object, expected type): raises what ctypes raises for such an argument
+PyObject *empty_tensor;   // (x, sizes): an output of x's type and place
 
 // A reference that ends with the scope.
 class Owned {
@@ -35,6 +36,7 @@ public:
     Owned(const Owned &) = delete;
     Owned &operator=(const Owned &) = delete;
     PyObject *get() const { return o_; }
+    PyObject *new_reference() const { return Py_NewRef(o_); }
 
 private:
     PyObject *o_;
@@ -61,14 +63,47 @@ template <class T> T struct_of(PyObject *obj, PyObject *type)
     return out;
 }
 
-const at::Tensor *tensor_or_null(PyObject *o, const char *name)
+// Address of an argument: null for None, and for anything but a plain tensor what its own data_ptr() says.
+void *address_of(PyObject *o)
 {
     if (o == Py_None) return nullptr;
-    TORCH_CHECK_TYPE(THPVariable_Check(o), name, " must be a tensor");
-    return &THPVariable_Unpack(o);
+    if (THPVariable_CheckExact(o)) return THPVariable_Unpack(o).data_ptr();
+    Owned at(PyObject_CallMethod(o, "data_ptr", nullptr));
+    if (at.get() == Py_None) return nullptr;
+    void *const p = PyLong_AsVoidPtr(at.get());
+    if (!p && PyErr_Occurred()) throw python_error();
+    return p;
 }
 
-void *data_of(const at::Tensor *t) { return t ? t->data_ptr() : nullptr; }
+int64_t integer_from(PyObject *o, const char *method)
+{
+    Owned v(PyObject_CallMethod(o, method, nullptr));
+    const long long n = PyLong_AsLongLong(v.get());
+    if (n == -1 && PyErr_Occurred()) throw python_error();
+    return n;
+}
+size_t bytes_of(PyObject *o)
+{
+    if (THPVariable_CheckExact(o)) return THPVariable_Unpack(o).nbytes();
+    return (size_t)(integer_from(o, "numel") * integer_from(o, "element_size"));
+}
+
+// The output of a call: the caller's, or a new one of x's type and place.
+PyObject *output_for(PyObject *given, PyObject *x, at::IntArrayRef sizes)
+{
+    if (given != Py_None) return Py_NewRef(given);
+    if (THPVariable_CheckExact(x)) return THPVariable_Wrap(at::empty(sizes, THPVariable_Unpack(x).options()));
+    Owned tuple(PyTuple_New((Py_ssize_t)sizes.size()));
+    for (size_t i = 0; i < sizes.size(); ++i) PyTuple_SET_ITEM(tuple.get(), i, PyLong_FromLongLong(sizes[i]));
+    return PyObject_CallFunctionObjArgs(empty_tensor, x, tuple.get(), nullptr);
+}
+
+int class_of(PyObject *o)
+{
+    const long cls = PyLong_AsLong(o);
+    if (cls == -1 && PyErr_Occurred()) throw python_error();
+    return (int)cls;
+}
 
 int64_t out_extent(int64_t in, int64_t pad, int64_t filter, int64_t stride)
 {
@@ -82,8 +117,8 @@ int64_t out_extent(int64_t in, int64_t pad, int64_t filter, int64_t stride)
 
 void *current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
-// Plan, workspace, launch.  Returns the output tensor, or the status as a Python integer.
-PyObject *call(int cls, const void *shape, PyObject *sched, OpPointers p, PyObject *ws, const at::Tensor &out, PyObject *y)
+// Plan, workspace, launch.  Returns the output, or the status as a Python integer.
+PyObject *call(int cls, const void *shape, PyObject *sched, OpPointers p, PyObject *ws, Owned &out)
 {
     int rc = TT_OK;
     at::Tensor own_ws;
@@ -91,14 +126,14 @@ PyObject *call(int cls, const void *shape, PyObject *sched, OpPointers p, PyObje
     {
         tt_schedule rec;
         if (sched != Py_None) rec = struct_of<tt_schedule>(sched, schedule_type);
-        const at::Tensor *given = tensor_or_null(ws, "ws");
-        if (given) {
-            p.ws = given->data_ptr();
-            p.ws_bytes = given->nbytes();
+        if (ws != Py_None) {
+            p.ws = address_of(ws);
+            p.ws_bytes = bytes_of(ws);
         }
+        p.out = address_of(out.get());
         rc = check_op_pointers(cls, p);
         if (rc == TT_OK) rc = prepare_op(sched != Py_None ? &rec : nullptr, cls, shape, &op);
-        if (rc == TT_OK && !given && op.plan.workspace_bytes > 0) {
+        if (rc == TT_OK && ws == Py_None && op.plan.workspace_bytes > 0) {
             own_ws = at::empty({op.plan.workspace_bytes}, at::TensorOptions().dtype(at::kByte).device(at::kCUDA));
             p.ws = own_ws.data_ptr();
             p.ws_bytes = (size_t)op.plan.workspace_bytes;
@@ -109,12 +144,7 @@ PyObject *call(int cls, const void *shape, PyObject *sched, OpPointers p, PyObje
         Py_BEGIN_ALLOW_THREADS rc = launch_op(op, &p, 1, stream); // (a full queue makes a launch wait)
         Py_END_ALLOW_THREADS
     }
-    if (rc != TT_OK) return PyLong_FromLong(rc);
-    if (y != Py_None) {
-        Py_INCREF(y);
-        return y;
-    }
-    return THPVariable_Wrap(out);
+    return rc == TT_OK ? out.new_reference() : PyLong_FromLong(rc);
 }
 
 // conv2d(x, w, bias, residual, shape, cls, sched, ws, y)
@@ -122,18 +152,12 @@ PyObject *py_conv2d(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     HANDLE_TH_ERRORS
     TORCH_CHECK_TYPE(n == 9, "conv2d takes nine arguments");
-    const at::Tensor *x = tensor_or_null(a[0], "x"), *w = tensor_or_null(a[1], "w"), *b = tensor_or_null(a[2], "bias"),
-                     *r = tensor_or_null(a[3], "residual"), *y = tensor_or_null(a[8], "y");
     const tt_conv_shape s = struct_of<tt_conv_shape>(a[4], conv_shape_type);
-    const long cls = PyLong_AsLong(a[5]);
-    if (cls == -1 && PyErr_Occurred()) throw python_error();
-    TORCH_CHECK_TYPE(x, "x must be a tensor");
-    at::Tensor out;
+    const int cls = class_of(a[5]);
     const int64_t ho = out_extent(s.h, s.pad_h, s.r, s.stride_h), wo = out_extent(s.w, s.pad_w, s.s, s.stride_w);
-    if (!y) out = at::empty({s.n, s.k, ho, wo}, x->options());
-    if (!is_conv_class((int)cls)) return PyLong_FromLong(TT_ERR_BAD_ARG);
-    return call((int)cls, &s, a[6], {x->data_ptr(), data_of(w), data_of(b), data_of(r), y ? y->data_ptr() : out.data_ptr(), nullptr, 0},
-                a[7], out, a[8]);
+    Owned out(output_for(a[8], a[0], {s.n, s.k, ho, wo}));
+    if (!is_conv_class(cls)) return PyLong_FromLong(TT_ERR_BAD_ARG);
+    return call(cls, &s, a[6], {address_of(a[0]), address_of(a[1]), address_of(a[2]), address_of(a[3]), nullptr, nullptr, 0}, a[7], out);
     END_HANDLE_TH_ERRORS
 }
 
@@ -142,17 +166,11 @@ PyObject *py_dense(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     HANDLE_TH_ERRORS
     TORCH_CHECK_TYPE(n == 8, "dense takes eight arguments");
-    const at::Tensor *x = tensor_or_null(a[0], "x"), *w = tensor_or_null(a[1], "w"), *b = tensor_or_null(a[2], "bias"),
-                     *y = tensor_or_null(a[7], "y");
     const tt_gemm_shape s = struct_of<tt_gemm_shape>(a[3], gemm_shape_type);
-    const long cls = PyLong_AsLong(a[4]);
-    if (cls == -1 && PyErr_Occurred()) throw python_error();
-    TORCH_CHECK_TYPE(x, "x must be a tensor");
-    at::Tensor out;
-    if (!y) out = at::empty({s.m, s.n}, x->options());
-    if (!is_dense_class((int)cls)) return PyLong_FromLong(TT_ERR_BAD_ARG);
-    return call((int)cls, &s, a[5], {x->data_ptr(), data_of(w), data_of(b), nullptr, y ? y->data_ptr() : out.data_ptr(), nullptr, 0}, a[6],
-                out, a[7]);
+    const int cls = class_of(a[4]);
+    Owned out(output_for(a[7], a[0], {s.m, s.n}));
+    if (!is_dense_class(cls)) return PyLong_FromLong(TT_ERR_BAD_ARG);
+    return call(cls, &s, a[5], {address_of(a[0]), address_of(a[1]), address_of(a[2]), nullptr, nullptr, nullptr, 0}, a[6], out);
     END_HANDLE_TH_ERRORS
 }
 
@@ -161,13 +179,9 @@ PyObject *py_matmul(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     HANDLE_TH_ERRORS
     TORCH_CHECK_TYPE(n == 6, "matmul takes six arguments");
-    const at::Tensor *x = tensor_or_null(a[0], "a"), *w = tensor_or_null(a[1], "b"), *y = tensor_or_null(a[5], "c");
     const tt_gemm_shape s = struct_of<tt_gemm_shape>(a[2], gemm_shape_type);
-    TORCH_CHECK_TYPE(x, "a must be a tensor");
-    at::Tensor out;
-    if (!y) out = at::empty({s.batch, s.m, s.n}, x->options());
-    return call(TT_BATCH_MATMUL, &s, a[3], {x->data_ptr(), data_of(w), nullptr, nullptr, y ? y->data_ptr() : out.data_ptr(), nullptr, 0},
-                a[4], out, a[5]);
+    Owned out(output_for(a[5], a[0], {s.batch, s.m, s.n}));
+    return call(TT_BATCH_MATMUL, &s, a[3], {address_of(a[0]), address_of(a[1]), nullptr, nullptr, nullptr, nullptr, 0}, a[4], out);
     END_HANDLE_TH_ERRORS
 }
 
@@ -176,25 +190,20 @@ PyObject *py_dwconv(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     HANDLE_TH_ERRORS
     TORCH_CHECK_TYPE(n == 6, "dwconv takes six arguments");
-    const at::Tensor *x = tensor_or_null(a[0], "x"), *w = tensor_or_null(a[1], "w"), *b = tensor_or_null(a[2], "bias"),
-                     *y = tensor_or_null(a[5], "y");
     const tt_conv_shape s = struct_of<tt_conv_shape>(a[3], conv_shape_type);
-    TORCH_CHECK_TYPE(x, "x must be a tensor");
-    at::Tensor out;
     const int64_t ho = out_extent(s.h, s.pad_h, s.r, s.stride_h), wo = out_extent(s.w, s.pad_w, s.s, s.stride_w);
-    if (!y) out = at::empty({s.n, s.c, ho, wo}, x->options());
-    return call(TT_DWCONV_BIAS_RELU6, &s, a[4],
-                {x->data_ptr(), data_of(w), data_of(b), nullptr, y ? y->data_ptr() : out.data_ptr(), nullptr, 0}, Py_None, out, a[5]);
+    Owned out(output_for(a[5], a[0], {s.n, s.c, ho, wo}));
+    return call(TT_DWCONV_BIAS_RELU6, &s, a[4], {address_of(a[0]), address_of(a[1]), address_of(a[2]), nullptr, nullptr, nullptr, 0}, Py_None, out);
     END_HANDLE_TH_ERRORS
 }
 
-// bind(conv shape type, gemm shape type, schedule type, refuse_struct): once, by the binding
+// bind(conv shape type, gemm shape type, schedule type, refuse_struct, empty_tensor): once, by the binding
 PyObject *py_bind(PyObject *, PyObject *args)
 {
-    PyObject *o[4];
-    if (!PyArg_ParseTuple(args, "OOOO", &o[0], &o[1], &o[2], &o[3])) return nullptr;
-    PyObject **const slots[4] = {&conv_shape_type, &gemm_shape_type, &schedule_type, &refuse_struct};
-    for (int i = 0; i < 4; ++i) {
+    PyObject *o[5];
+    if (!PyArg_ParseTuple(args, "OOOOO", &o[0], &o[1], &o[2], &o[3], &o[4])) return nullptr;
+    PyObject **const slots[5] = {&conv_shape_type, &gemm_shape_type, &schedule_type, &refuse_struct, &empty_tensor};
+    for (int i = 0; i < 5; ++i) {
         PyObject *const before = *slots[i];
         *slots[i] = Py_NewRef(o[i]);
         Py_XDECREF(before);

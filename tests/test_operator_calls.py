@@ -1,4 +1,4 @@
-"""Arguments of the Python operator calls: what is refused and how.  Nothing here launches
+"""Arguments of the Python operator calls: what is refused and how, and what stands for a tensor.  Nothing here launches
 (the calls that get as far as a plan carry a record of another class)."""
 import ctypes
 
@@ -69,3 +69,30 @@ def test_structures_of_a_derived_type_are_taken(op):
 
     call = calls(shape_of=lambda s: derived(Shape, s), sched_of=lambda c: derived(Schedule, OTHER_CLASS[c]))[op]
     assert status(call) == api.TT_ERR_CLASS_MISMATCH
+
+
+@pytest.mark.parametrize("op", OPS)
+def test_missing_tensors(op):
+    assert status(calls(first=lambda x: None)[op]) == api.TT_ERR_BAD_ARG
+    with pytest.raises(AttributeError):  # nothing says what the output should be
+        calls(first=lambda x: None, y=False)[op]()
+
+
+class Memory:
+    """Device memory of a caller's own: all a call asks of an argument is where it lies."""
+
+    def __init__(self, t, shift=0):
+        self.t, self.shift = t, shift
+        self.dtype, self.device = t.dtype, t.device
+
+    def data_ptr(self):
+        return self.t.data_ptr() + self.shift
+
+
+@pytest.mark.parametrize("op", OPS)
+def test_whatever_has_a_data_ptr_is_taken(op):
+    for y in (True, False):
+        assert status(calls(first=Memory, y=y)[op]) == api.TT_ERR_CLASS_MISMATCH
+        assert status(calls(first=lambda t: Memory(t, 4), y=y)[op]) == api.TT_ERR_BAD_ARG  # not 16-byte aligned
+    with pytest.raises(AttributeError):
+        calls(first=lambda t: [1.0, 2.0])[op]()
