@@ -246,14 +246,18 @@ int check_op_pointers(int cls, const OpPointers &p)
     return TT_OK;
 }
 
+static bool workspace_fits(const PreparedOp &op, const OpPointers &p)
+{
+    return op.plan.workspace_bytes == 0 || (p.ws && (int64_t)p.ws_bytes >= op.plan.workspace_bytes && aligned16(p.ws));
+}
+
 int launch_op(PreparedOp &op, const OpPointers *calls, int count, void *stream)
 {
     PointerSets sets;
     sets.count = count;
     for (int i = 0; i < count; ++i) {
         const OpPointers &p = calls[i];
-        if (op.plan.workspace_bytes > 0 && (!p.ws || (int64_t)p.ws_bytes < op.plan.workspace_bytes || !aligned16(p.ws)))
-            return TT_ERR_WORKSPACE;
+        if (!workspace_fits(op, p)) return TT_ERR_WORKSPACE;
         if (i > 0) sets.more[i - 1] = {p.a, p.b, p.bias, p.res, p.out, static_cast<float *>(p.ws)};
     }
     if (!op.supported) return TT_ERR_UNSUPPORTED;
@@ -593,7 +597,9 @@ extern "C" int tt_run_kernels(const tt_kernel_desc *kernels, const tt_schedule *
                 const tt_kernel_desc &e = kernels[k + count];
                 if (e.use_count != 1 || !e.shape || !same_plan(d, rec, e, scheds ? scheds[k + count] : nullptr)) break;
                 const OpPointers p = pointers_of(e);
-                if (check_op_pointers(e.cls, p) != TT_OK || (p.bias == nullptr) != (calls[0].bias == nullptr)) break;
+                // (an entry that will be refused must not keep the ones before it from being launched)
+                if (check_op_pointers(e.cls, p) != TT_OK || !workspace_fits(op, p)) break;
+                if ((p.bias == nullptr) != (calls[0].bias == nullptr)) break;
                 bool apart = true;
                 for (int i = 0; i < count && apart; ++i) apart = independent(op, calls[i], p);
                 if (!apart) break;

@@ -660,6 +660,25 @@ def test_list_of_one_plan_runs_every_entry_and_keeps_dependent_ones_in_order(api
             P.assert_close(g, w, kernel.shape.dtype, f"{name} {i}")
 
 
+def test_list_launches_what_stands_before_an_entry_without_workspace(api, P):
+    import torch
+    from paper_2201_05587_amd import harness
+    kernel = wl.Kernel(wl.CLS_DENSE_ADD, wl.GemmShape(1, 64, 64, 128, 1, wl.F32))
+    sched = mfma(api, kernel.cls, 64, 64, 32, 32, 32, 32, split_k=2)
+    full = [harness.device_kernel(kernel, 40 + i, max_split=2) for i in range(3)]
+    want = [P.run_gpu(kernel, dk, sched) for dk in full[:2]]
+    dks = full[:2] + [api.DeviceKernel(kernel.cls, kernel.shape, full[2].tensors, 1, "short", 16)]
+    for dk in dks:
+        dk.output().fill_(float("nan"))
+    with pytest.raises(api.TTError) as e:
+        api.KernelList(dks, [sched] * 3).run()
+    assert e.value.status == api.TT_ERR_WORKSPACE
+    torch.cuda.synchronize()
+    for dk, w in zip(dks, want):
+        np.testing.assert_array_equal(dk.output().cpu().numpy(), w)
+    assert bool(torch.isnan(dks[2].output()).all())
+
+
 # ---- 256 x 256 blocks (large bf16 launches, whatever tile the record names) ------------------------------------------
 @pytest.mark.parametrize("name,cls,shape", [
     # half of the chip's blocks and more: ragged M, N and last slice; a band of fewer than four block rows
