@@ -94,7 +94,7 @@ class tt_sweep_row(Structure):
 
 
 EXPORTS = ("tt_version", "tt_status_name", "tt_last_error", "tt_schedule_default", "tt_schedule_apply", "tt_plan_tile",
-           "tt_debug_tile_map", "tt_debug_fast_div", "tt_debug_probe", "tt_conv2d_bias_relu", "tt_conv2d_bias_relu_noalloc", "tt_dense_bias_relu", "tt_batch_matmul", "tt_dwconv",
+           "tt_debug_tile_map", "tt_debug_launch", "tt_debug_fast_div", "tt_debug_probe", "tt_conv2d_bias_relu", "tt_conv2d_bias_relu_noalloc", "tt_dense_bias_relu", "tt_batch_matmul", "tt_dwconv",
            "tt_transfer_sweep", "tt_sweep_plan", "tt_refine_space", "tt_refine", "tt_native_sweep", "tt_time_pair", "tt_run_kernels", "tt_schedule_space", "tt_sweep_select", "tt_variant_info", "tt_num_variants", "tt_select_donor")
 
 
@@ -114,6 +114,7 @@ def _load():
     lib.tt_schedule_apply.argtypes = [POINTER(tt_schedule), ctypes.c_int, c_void_p, ctypes.c_int, POINTER(tt_plan)]
     lib.tt_plan_tile.argtypes = [POINTER(tt_plan), c_int64, POINTER(c_int32 * 8)]
     lib.tt_debug_tile_map.argtypes = [POINTER(tt_plan), c_void_p, c_void_p]
+    lib.tt_debug_launch.argtypes = [POINTER(tt_schedule), ctypes.c_int, c_void_p, ctypes.c_int, POINTER(tt_plan), POINTER(c_int32)]
     lib.tt_conv2d_bias_relu.argtypes = [c_void_p] * 5 + [POINTER(tt_conv_shape), ctypes.c_int, POINTER(tt_schedule),
                                                          c_void_p, c_size_t, c_void_p]
     lib.tt_conv2d_bias_relu_noalloc.argtypes = [c_void_p] * 5 + [POINTER(tt_conv_shape), ctypes.c_int,
@@ -333,6 +334,19 @@ def tt_debug_tile_map(plan):
     return out.cpu().numpy()
 
 
+TT_LAUNCH_RECORD, TT_LAUNCH_GROUPS, TT_LAUNCH_BLOCKS = range(3)
+TT_MAX_ENTRIES_PER_LAUNCH = 8
+
+
+def tt_debug_launch(sched, cls, shape, count=1):
+    """(plan as launched, kernel) of a launch of `count` equal entries under a record (None = default)."""
+    plan, kernel = tt_plan(), c_int32(0)
+    cs = to_c_shape(shape)
+    _check(lib.tt_debug_launch(byref(sched) if sched is not None else None, cls, ctypes.addressof(cs), count, byref(plan),
+                               byref(kernel)), "tt_debug_launch")
+    return plan, kernel.value
+
+
 TT_PROBE_LAUNCH_GAP_US, TT_PROBE_MFMA_BF16_TFLOPS, TT_PROBE_COPY_LINEAR_GBPS, TT_PROBE_COPY_TILED_GBPS, \
     TT_PROBE_L2_READ_GBPS = range(5)
 
@@ -508,9 +522,8 @@ def tt_variant_info(variant_id: int):
 
 
 def variant_name(plan: tt_plan, shape=None) -> str:
-    """Name of the kernel a plan names, spelled like the demangled symbol rocprofv3 reports.  (A launch of at most one
-    workgroup per CU, a large bf16 one, or one of a register-pipeline record may run on contract_groups_kernel,
-    contract_block_kernel or a ring instance in its place.)
+    """Name of the kernel a plan names, spelled like the demangled symbol rocprofv3 reports (launched_name: the one that a
+    launch runs on).
 
     `shape` (a conv shape) is needed only to tell the two depthwise kernels apart.
     """
@@ -536,3 +549,14 @@ def variant_name(plan: tt_plan, shape=None) -> str:
                     f"{bound}>")
         return f"tt::dwconv3x3_kernel<{plan.wave_m}, {plan.wave_n}, {bound}>"
     return {TT_SK_GEMV: "tt::gemv_kernel", TT_SK_DIRECT: "tt::direct_kernel"}[plan.sketch]
+
+
+def launched_name(sched, cls, shape, count=1) -> str:
+    """Name of the kernel that a launch of `count` equal entries under a record (None = default) runs on."""
+    plan, kernel = tt_debug_launch(sched, cls, shape, count)
+    if kernel == TT_LAUNCH_RECORD:
+        return variant_name(plan, shape)
+    dtype, family, tm, tn, _, wm, wn, mf = tt_variant_info(plan.variant_id)[:8]
+    if kernel == TT_LAUNCH_BLOCKS:
+        return f"tt::contract_block_kernel<{family}>"
+    return f"tt::contract_groups_kernel<{dtype}, {family}, {tm}, {tn}, {wm}, {wn}, {mf}>"

@@ -46,6 +46,19 @@ template <int FAM> int launch(const ContractArgs &args, const PointerSets &sets,
 
 } // namespace
 
+namespace {
+template <int FAM> LaunchShape shape_of(const ContractArgs &a)
+{
+    using S = BlockShape<FAM>;
+    return {TT_LAUNCH_BLOCKS, ((a.M + S::BM - 1) / S::BM) * ((a.N + S::BN - 1) / S::BN), S::THREADS, S::LDS};
+}
+} // namespace
+
+LaunchShape blocks_shape(const ContractArgs &args, int family)
+{
+    return family == FAM_CONV ? shape_of<FAM_CONV>(args) : shape_of<FAM_GEMM_TN>(args);
+}
+
 int launch_blocks(const ContractArgs &args, const PointerSets &sets, int family, void *stream)
 {
     return family == FAM_CONV ? launch<FAM_CONV>(args, sets, stream) : launch<FAM_GEMM_TN>(args, sets, stream);

@@ -7,14 +7,52 @@
 
 namespace tt {
 
+// LDS the epilogue stages one band of MF rows per wave in (the operands' own).
+constexpr int epilogue_bytes(int TM, int TN, int WM, int WN, int MF) { return (TM / WM) * (TN / WN) * MF * (WN + (MF == 32 ? 8 : 4)) * 4; }
+
+// What a launch of `count` sets runs on, and the shape it has there.
+template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF, int AM>
+int kernel_contract(const ContractArgs &args, int count, int grid)
+{
+    if constexpr (FAM == FAM_GEMM_TN || (FAM == FAM_CONV && AM == 16))
+        if (groups_apply<DT, FAM, TM, TN, WM, WN, MF>(args, grid * count, 0)) return TT_LAUNCH_GROUPS;
+    return TT_LAUNCH_RECORD;
+}
+template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF>
+int kernel_contract_async(const ContractArgs &args, int count, int grid, int lds_bytes)
+{
+    if constexpr (DT == TT_BF16)
+        if (block_applies(args, FAM, count, TM * TN)) return TT_LAUNCH_BLOCKS;
+    if (groups_apply<DT, FAM, TM, TN, WM, WN, MF>(args, grid * count, lds_bytes)) return TT_LAUNCH_GROUPS;
+    return TT_LAUNCH_RECORD;
+}
+template <int DT, int FAM, int TM, int TN, int WM, int WN, int MF>
+LaunchShape shape_on(int kernel, const ContractArgs &args, int grid, int lds_bytes)
+{
+    using S = GroupShape<DT, TM, TN, WM, WN, MF>;
+    if (kernel == TT_LAUNCH_BLOCKS) return blocks_shape(args, FAM);
+    if (kernel == TT_LAUNCH_GROUPS) return {TT_LAUNCH_GROUPS, grid, S::THREADS, S::LDS};
+    return {TT_LAUNCH_RECORD, grid, (TM / WM) * (TN / WN) * 64, std::max(lds_bytes, epilogue_bytes(TM, TN, WM, WN, MF))};
+}
+template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF, int AM>
+LaunchShape shape_contract(const ContractArgs &args, int count, int grid, int lds_bytes)
+{
+    return shape_on<DT, FAM, TM, TN, WM, WN, MF>(kernel_contract<DT, FAM, TM, TN, TK, WM, WN, MF, AM>(args, count, grid), args, grid, lds_bytes);
+}
+template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF>
+LaunchShape shape_contract_async(const ContractArgs &args, int count, int grid, int lds_bytes)
+{
+    return shape_on<DT, FAM, TM, TN, WM, WN, MF>(kernel_contract_async<DT, FAM, TM, TN, TK, WM, WN, MF>(args, count, grid, lds_bytes), args, grid, lds_bytes);
+}
+
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF, int AM>
 int launch_contract(const ContractArgs &args, const PointerSets &sets, int grid, int lds_bytes, void *stream)
 {
     if constexpr (FAM == FAM_GEMM_TN || (FAM == FAM_CONV && AM == 16))
-        if (groups_apply<DT, FAM, TM, TN, WM, WN, MF>(args, grid * sets.count, 0)) return launch_groups<DT, FAM, TM, TN, WM, WN, MF>(args, sets, grid, stream);
+        if (kernel_contract<DT, FAM, TM, TN, TK, WM, WN, MF, AM>(args, sets.count, grid) == TT_LAUNCH_GROUPS)
+            return launch_groups<DT, FAM, TM, TN, WM, WN, MF>(args, sets, grid, stream);
     auto kern = contract_kernel<DT, FAM, TM, TN, TK, WM, WN, MF, AM>;
-    // the epilogue stages one band of MF rows per wave in the same LDS
-    constexpr int EPI_BYTES = (TM / WM) * (TN / WN) * MF * (WN + (MF == 32 ? 8 : 4)) * 4;
+    constexpr int EPI_BYTES = epilogue_bytes(TM, TN, WM, WN, MF);
     if (lds_bytes < EPI_BYTES) lds_bytes = EPI_BYTES;
     static DynamicLdsLimit limit; // per kernel instance
     if (const int rc = limit.raise_to(reinterpret_cast<const void *>(kern), lds_bytes); rc != TT_OK) return rc;
@@ -45,11 +83,12 @@ template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF> int l
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF>
 int launch_contract_async(const ContractArgs &args, const PointerSets &sets, int grid, int lds_bytes, void *stream)
 {
+    const int kernel = kernel_contract_async<DT, FAM, TM, TN, TK, WM, WN, MF>(args, sets.count, grid, lds_bytes);
     if constexpr (DT == TT_BF16)
-        if (block_applies(args, FAM, sets.count, TM * TN)) return launch_blocks(args, sets, FAM, stream);
-    if (groups_apply<DT, FAM, TM, TN, WM, WN, MF>(args, grid * sets.count, lds_bytes)) return launch_groups<DT, FAM, TM, TN, WM, WN, MF>(args, sets, grid, stream);
+        if (kernel == TT_LAUNCH_BLOCKS) return launch_blocks(args, sets, FAM, stream);
+    if (kernel == TT_LAUNCH_GROUPS) return launch_groups<DT, FAM, TM, TN, WM, WN, MF>(args, sets, grid, stream);
     auto kern = contract_async_kernel<DT, FAM, TM, TN, TK, WM, WN, MF>;
-    constexpr int EPI_BYTES = (TM / WM) * (TN / WN) * MF * (WN + (MF == 32 ? 8 : 4)) * 4;
+    constexpr int EPI_BYTES = epilogue_bytes(TM, TN, WM, WN, MF);
     if (lds_bytes < EPI_BYTES) lds_bytes = EPI_BYTES;
     static DynamicLdsLimit limit; // per kernel instance
     if (const int rc = limit.raise_to(reinterpret_cast<const void *>(kern), lds_bytes); rc != TT_OK) return rc;

@@ -151,31 +151,40 @@ def main():
                 args = ", ".join(str(x) for x in (v[2], v[3], v[4], v[5], v[6], v[10], v[11]))
                 call, size, lds = (f"launch_conv_patch<{args}>", f"capacity_conv_patch<{args}>",
                                    f"lds_bytes_conv_patch<{args}>")
+                shape = None
             elif v[9] == 3:
                 args = ", ".join(str(x) for x in (v[0], v[2], v[3], v[4], v[5], v[6], v[7]))
                 call, size, lds = (f"launch_gemm_stream<{args}>", f"requests_gemm_stream<{args}>",
                                    f"lds_bytes_gemm_stream<{args}>")
+                shape = None
             elif v[9] == 1:
                 args = ", ".join(str(x) for x in v[:8])
                 call, size, lds = (f"launch_contract_async<{args}>", f"stage_bytes_contract_async<{args}>",
                                    f"lds_bytes_contract_async<{args}>")
+                shape = f"shape_contract_async<{args}>"
             else:
                 args = ", ".join(str(x) for x in v[:9])
                 call, size, lds = f"launch_contract<{args}>", f"stage_bytes_contract<{args}>", f"lds_bytes_contract<{args}>"
+                shape = f"shape_contract<{args}>"
             lines.append(f"int ttv_{i}(const ContractArgs &a, const PointerSets &p, int grid, int lds, void *s) "
                          f"{{ return {call}(a, p, grid, lds, s); }}")
+            if shape:
+                lines.append(f"LaunchShape ttk_{i}(const ContractArgs &a, int count, int grid, int lds) "
+                             f"{{ return {shape}(a, count, grid, lds); }}")
             lines.append(f"int tts_{i}() {{ return {size}(); }}")
             lines.append(f"int ttl_{i}(int stages) {{ return {lds}(stages); }}")
         lines.append("} // namespace tt")
         write_if_changed(os.path.join(out_dir, f"inst_{s:02d}.hip"), "\n".join(lines) + "\n")
     lines = ['// generated by gen_variants.py - do not edit', '#include "../tt_internal.h"', "namespace tt {"]
-    for i, _ in enumerate(vs):
+    for i, v in enumerate(vs):
         lines.append(f"int ttv_{i}(const ContractArgs &, const PointerSets &, int, int, void *);")
+        if v[9] < 2:
+            lines.append(f"LaunchShape ttk_{i}(const ContractArgs &, int, int, int);")
         lines.append(f"int tts_{i}();")
         lines.append(f"int ttl_{i}(int);")
     lines.append("const Variant kVariants[] = {")
     for i, v in enumerate(vs):
-        lines.append("    {" + ", ".join(str(x) for x in v[:11]) + f", ttv_{i}, tts_{i}, ttl_{i}}},")
+        lines.append("    {" + ", ".join(str(x) for x in v[:11]) + f", ttv_{i}, {f'ttk_{i}' if v[9] < 2 else 'nullptr'}, tts_{i}, ttl_{i}}},")
     lines.append("};")
     lines.append(f"const int kNumVariants = {len(vs)};")
     lines.append("} // namespace tt")

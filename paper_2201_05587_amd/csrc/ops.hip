@@ -297,6 +297,37 @@ int run_op(const tt_schedule *sched, int cls, const void *shape, const OpPointer
 
 } // namespace
 
+// ---- what a launch runs on -----------------------------------------------------------------------------
+
+namespace {
+
+// The kernel of a launch of `count` sets, and the plan as it is launched there.
+int launched_plan(const PreparedOp &op, int count, tt_plan *plan)
+{
+    *plan = op.launch;
+    if (plan->sketch != TT_SK_MFMA || plan->variant_id < 0 || plan->variant_id >= kNumVariants) return TT_LAUNCH_RECORD;
+    const Variant &v = kVariants[plan->variant_id];
+    if (!v.shape) return TT_LAUNCH_RECORD;
+    const LaunchShape s = v.shape(op.g, count, plan->grid, plan->lds_bytes);
+    plan->grid = s.grid;
+    plan->block = s.block;
+    plan->lds_bytes = s.lds_bytes;
+    return s.kernel;
+}
+
+} // namespace
+
+extern "C" int tt_debug_launch(const tt_schedule *sched, int cls, const void *shape, int count, tt_plan *launched, int32_t *kernel)
+{
+    if (!shape || !launched || !kernel || count < 1 || count > kMaxSets) return TT_ERR_BAD_ARG;
+    if (cls < 0 || cls >= TT_NUM_CLASSES) return TT_ERR_BAD_ARG;
+    PreparedOp op;
+    if (const int rc = prepare_op(sched, cls, shape, &op); rc != TT_OK) return rc;
+    if (!op.supported || (op.launch.sketch != TT_SK_DIRECT && op.launch.variant_id < 0)) return TT_ERR_UNSUPPORTED;
+    *kernel = launched_plan(op, count, launched);
+    return TT_OK;
+}
+
 // ---- split-K partial sums without a caller's workspace ----------------------------------------------
 // One array per GPU, part of the library's code object: it exists from the moment the library is loaded
 // on a device until the process ends.  In host code the array's name is only a handle; the address the

@@ -173,7 +173,7 @@ struct PointerSet {
     void *out;
     float *ws;
 };
-constexpr int kMaxSets = 8;
+constexpr int kMaxSets = TT_MAX_ENTRIES_PER_LAUNCH;
 struct PointerSets {
     PointerSet more[kMaxSets - 1];
     int32_t count;
@@ -261,6 +261,11 @@ int check_op_pointers(int cls, const OpPointers &p);
 int prepare_op(const tt_schedule *sched, int cls, const void *shape, PreparedOp *op);
 int launch_op(PreparedOp &op, const OpPointers *calls, int count, void *stream);
 
+// What runs a launch (tt_launch_kernel), and the grid (of one pointer set), workgroup and LDS it has.
+struct LaunchShape {
+    int32_t kernel, grid, block, lds_bytes;
+};
+
 struct Variant {
     int32_t dtype, family, tile_m, tile_n, tile_k, wave_m, wave_n, mfma;
     int32_t amode; // conv family: bytes per gathered load (16 or the element size); 0 otherwise
@@ -269,6 +274,8 @@ struct Variant {
                    // 3: persistent dense kernel, the B panel resident in LDS and two A buffers (stages 7)
     int32_t stride; // pipe 2: the convolution stride the kernel is compiled for; 0 otherwise
     int (*launch)(const ContractArgs &args, const PointerSets &sets, int grid, int lds_bytes, void *stream);
+    LaunchShape (*shape)(const ContractArgs &args, int count, int grid, int lds_bytes); // of a launch of `count` sets; pipes
+                                                                                        // 2 and 3: null, the plan's own
     int (*stage_bytes)();        // pipes 0, 1: LDS bytes of one pipeline stage; pipe 2: pixels a patch buffer holds;
                                  // pipe 3: request instructions per lane and K slice
     int (*lds_bytes)(int stages); // LDS bytes for a plan's number of stages (pipe 3: for its number of K slices), as
@@ -293,6 +300,7 @@ int launch_gemv(const ContractArgs &args, const PointerSets &sets, const tt_plan
 // the 256 x 256 block kernel (contract_block.hip): whether a launch of `count` sets runs on it, and its launch
 bool block_applies(const ContractArgs &args, int family, int count, int tile_outputs);
 int launch_blocks(const ContractArgs &args, const PointerSets &sets, int family, void *stream);
+LaunchShape blocks_shape(const ContractArgs &args, int family);
 int dw_max_block(int wave_m, int wave_n, int planes_per_lane, int stride, bool rows_kernel);
 int launch_dwconv(const DwArgs &args, const PointerSets &sets, const tt_plan &plan, void *stream);
 int launch_dw_direct(const DwArgs &args, const PointerSets &sets, int grid, void *stream);
