@@ -15,8 +15,7 @@ namespace tt {
 //   share 1.00 (4096 x 4096 x 1024)  64x64 48.3, 128x64 54.6, 128x128 49.4, 128x256 34.8   blocks 35.9
 //   share 0.75, two rounds (8192 x 3072 x 3072)  the best record of all 135.3              blocks 140.9
 // and 4096 x 4096 x 4096: 128x64 166, blocks 105 (1.31 PFLOP/s; operands of zeros: 78, the chip's power sets the
-// clock).  A record of the register pipeline comes here as the ring record that runs it (launch_plan_of): where operands are
-// whole items and the reduction is not split, which blocks need too, it has one.
+// clock).  Register-pipeline records keep their own kernel; the default schedule comes here as a ring record (launch_plan_of).
 bool block_applies(const ContractArgs &a, int family, int count, int tile_outputs)
 {
     if (a.dtype != TT_BF16 || a.batch != 1 || a.map.eff_split_k != 1 || a.K < 1024) return false;

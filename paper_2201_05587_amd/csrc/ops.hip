@@ -56,16 +56,22 @@ double tile_estimate(const tt_plan &p, int dtype, int tm, int tn)
     return std::ceil(tiles / compute_units()) * p.K * std::max(rows, products) * (tm * tn <= 1024 ? 1.25 : 1.0);
 }
 
-// The plan that is launched for a record's plan.  A record of the register pipeline (one or two stages: the default
-// schedule above all) whose operands the asynchronous ring can load is run on ring instances, in the tile that the
-// estimate above likes best for this shape; everything else about the operator, and what the plan reports, stays as the
-// record says.  Splits of the reduction keep their own kernel: their partial sums are cut where the record says.
+// Same knobs: the thirteen that lead the record.
+bool same_knobs(const tt_schedule &x, const tt_schedule &y) { return std::memcmp(&x, &y, sizeof(int32_t) * 13) == 0; }
+
+// The plan that is launched for a record's plan.  The default schedule of a kernel stands for "as the library sees fit": its
+// record names a register-pipeline tile, and where the asynchronous ring can load the operands it is run on the ring
+// instance that the estimate above likes best for this shape, whether the caller passed no record or the default's own.
+// Any other record runs in the tile, raster and pipeline that it names, so that a search times what it will store.
+// Splits of the reduction keep their own kernel: their partial sums are cut where the record says.
 // The register pipeline holds one slice in flight, in registers.  Default records, before -> after (us): bf16 dense
 // 73x168x3152 46.9 -> 7.1, f32 dense 77x40x1040 42.7 -> 9.4, f32 3x3 392 -> 104 channels on 2 x 15x15 133 -> 25.7, bf16 1x1
 // 152 -> 440 on 13x13 5.4 -> 3.5; the geometric mean over 60 shapes drawn between 2 MFLOP and 60 GFLOP is 2.1 times.
-tt_plan launch_plan_of(const tt_plan &plan, int cls, const void *shape, int dtype)
+tt_plan launch_plan_of(const tt_plan &plan, const tt_schedule &rec, int cls, const void *shape, int dtype)
 {
     if (plan.sketch != TT_SK_MFMA || plan.variant_id < 0 || plan.stages > 2 || plan.eff_split_k != 1) return plan;
+    tt_schedule def;
+    if (tt_schedule_default(cls, shape, &def) != TT_OK || !same_knobs(rec, def)) return plan;
     static const int tiles[2][6][6] = {
         // tile_m, tile_n, tile_k, wave_m, wave_n, mfma
         {{32, 32, 32, 16, 16, 16}, {64, 64, 32, 32, 32, 16}, {128, 64, 32, 32, 32, 16}, {64, 128, 32, 32, 32, 16}, {128, 128, 32, 32, 64, 16}, {}},
@@ -226,10 +232,10 @@ int prepare_op(const tt_schedule *sched, int cls, const void *shape, PreparedOp 
         std::memset(&op->d, 0, sizeof op->d);
         prepare_dw(*cs, op);
     } else if (is_conv_class(cls)) {
-        op->launch = launch_plan_of(op->plan, cls, shape, cs->dtype);
+        op->launch = launch_plan_of(op->plan, *sched, cls, shape, cs->dtype);
         prepare_conv(*cs, op);
     } else {
-        op->launch = launch_plan_of(op->plan, cls, shape, gs->dtype);
+        op->launch = launch_plan_of(op->plan, *sched, cls, shape, gs->dtype);
         fill_common(op->g, op->launch, cls, gs->dtype);
         op->g.Ho = op->g.Wo = 1;
         op->family = family_of(cls, gs->trans_b);
@@ -593,7 +599,7 @@ bool independent(const PreparedOp &op, const OpPointers &p, const OpPointers &q)
 bool same_plan(const tt_kernel_desc &x, const tt_schedule *sx, const tt_kernel_desc &y, const tt_schedule *sy)
 {
     if (x.cls != y.cls || (sx == nullptr) != (sy == nullptr)) return false;
-    if (sx && sx != sy && std::memcmp(sx, sy, sizeof(int32_t) * 13) != 0) return false; // the thirteen knobs lead the record
+    if (sx && sx != sy && !same_knobs(*sx, *sy)) return false;
     const bool image = is_conv_class(x.cls) || x.cls == TT_DWCONV_BIAS_RELU6;
     return x.shape == y.shape || std::memcmp(x.shape, y.shape, image ? sizeof(tt_conv_shape) : sizeof(tt_gemm_shape)) == 0;
 }

@@ -518,3 +518,32 @@ def test_list_entry_that_is_launched_no_times_is_passed_over():
     assert api.lib.tt_run_kernels(d, None, 2, 1, None) == api.TT_OK
     d[1].shape = None
     assert api.lib.tt_run_kernels(d, None, 2, 1, None) == api.TT_ERR_BAD_ARG
+
+
+# ---- what a launch runs on -----------------------------------------------------------------------------
+def knobs_of_plan(p):
+    return (p.tile_m, p.tile_n, p.tile_k, p.wave_m, p.wave_n, p.mfma, p.order, p.stages, p.eff_unroll, p.variant_id)
+
+
+@pytest.mark.parametrize("kernel", [
+    wl.Kernel(wl.CLS_DENSE_ADD, wl.GemmShape(1, 1024, 768, 768, 1, wl.BF16)),
+    wl.Kernel(wl.CLS_DENSE_BIAS_RELU, wl.GemmShape(1, 300, 1032, 96, 1, wl.F32)),
+    wl.Kernel(wl.CLS_CONV2D_BIAS_RELU, wl.ConvShape(8, 128, 28, 28, 128, 3, 3, 1, 1, 1, 1, wl.BF16)),
+    wl.Kernel(wl.CLS_CONV2D_ADD, wl.ConvShape(1, 64, 56, 56, 128, 1, 1, 2, 2, 0, 0, wl.F32)),
+])
+def test_records_launch_the_tile_they_name_and_only_the_default_is_the_librarys_choice(kernel):
+    cls, shape = kernel.cls, kernel.shape
+    default = api.tt_schedule_default(cls, shape)
+    chosen, _ = api.tt_debug_launch(None, cls, shape)
+    assert chosen.stages == 3 and api.tt_schedule_apply(default, cls, shape).stages == 2
+    assert knobs_of_plan(api.tt_debug_launch(default, cls, shape)[0]) == knobs_of_plan(chosen)
+    tried = 0
+    for rec in random.Random(5).sample(api.tt_schedule_space(cls, shape.dtype, 2), 400):
+        plan = api.tt_schedule_apply(rec, cls, shape)
+        if not plan.runnable() or plan.stages > 2:
+            continue
+        launched, kernel_kind = api.tt_debug_launch(rec, cls, shape)
+        assert kernel_kind in (api.TT_LAUNCH_RECORD, api.TT_LAUNCH_GROUPS)
+        assert knobs_of_plan(launched) == knobs_of_plan(plan) and launched.grid == plan.grid
+        tried += 1
+    assert tried > 20
