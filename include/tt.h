@@ -365,7 +365,8 @@ typedef struct tt_sweep_row {
  * time the default schedule, then every pool record of the kernel's class;
  * records that do not apply are recorded as -1 and skipped; the fastest wins,
  * the default is the fallback and wins ties, equal donors go to the lowest
- * index.  With opts->pair_budget > 0 every default is timed first and only the pairs
+ * index.  Records that come to the same launch on a kernel (tt_debug_launch: knobs that the kernel they
+ * run on does not have) share one time, here and in the other sweeps.  With opts->pair_budget > 0 every default is timed first and only the pairs
  * tt_sweep_plan selects (weights = default time x use count) are tried.  rows (host, nk).  pair_us
  * (host, nk * np doubles, may be NULL): median microseconds per launch, -1 for an invalid pair, -2 for
  * a record of another class, -3 for a pair the budget left out.  evaluations (host, may be NULL): number of timed pairs,

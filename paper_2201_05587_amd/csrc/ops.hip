@@ -2,11 +2,13 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <atomic>
 #include <cstring>
+#include <map>
 #include <mutex>
 #include <vector>
 
@@ -493,8 +495,39 @@ tt_sweep_opts resolve(const tt_sweep_opts *o)
     return r;
 }
 
+// Times of one kernel's launches under one protocol, for as long as a sweep lasts.  Records that differ only in knobs the
+// kernel they run on does not have (stages, tile_k and unroll of a launch in groups, everything of one in blocks) come to
+// the same launch: they share the time of the first, and the rule for ties decides among them instead of noise.
+class LaunchTimes {
+public:
+    struct Time {
+        double median_us, min_us;
+    };
+    using Key = std::array<int32_t, 20>;
+    static Key key_of(const PreparedOp &op)
+    {
+        tt_plan p;
+        const int kernel = launched_plan(op, 1, &p);
+        if (kernel == TT_LAUNCH_BLOCKS) return Key{kernel};
+        if (kernel == TT_LAUNCH_GROUPS)
+            return Key{kernel, p.tile_m, p.tile_n, p.wave_m, p.wave_n, p.mfma, p.eff_split_k,
+                       (int32_t)std::min<int64_t>((int64_t)p.k_iters * p.tile_k, p.K), p.eff_vec_c, p.order};
+        return Key{kernel, p.sketch, p.variant_id, p.tile_m, p.tile_n, p.tile_k, p.wave_m, p.wave_n, p.mfma, p.eff_split_k,
+                   p.k_iters, p.eff_vec_a, p.eff_vec_b, p.eff_vec_c, p.eff_unroll, p.stages, p.order, p.grid, p.block, p.lds_bytes};
+    }
+    const Time *find(const Key &key) const
+    {
+        const auto it = times_.find(key);
+        return it == times_.end() ? nullptr : &it->second;
+    }
+    void add(const Key &key, double median_us, double min_us) { times_[key] = {median_us, min_us}; }
+
+private:
+    std::map<Key, Time> times_;
+};
+
 int time_pair(const tt_kernel_desc &k, const tt_schedule *sched, const tt_sweep_opts &o, hipStream_t s, Timer &t,
-              double *median_us, double *min_us)
+              double *median_us, double *min_us, LaunchTimes *times = nullptr)
 {
     // Validity first: nothing is launched for a record that does not apply.
     tt_schedule def;
@@ -518,6 +551,15 @@ int time_pair(const tt_kernel_desc &k, const tt_schedule *sched, const tt_sweep_
     PreparedOp op;
     rc = prepare_op(rec, k.cls, k.shape, &op);
     if (rc != TT_OK) return rc;
+    LaunchTimes::Key key{};
+    if (times) {
+        key = LaunchTimes::key_of(op);
+        if (const LaunchTimes::Time *known = times->find(key)) {
+            if (median_us) *median_us = known->median_us;
+            if (min_us) *min_us = known->min_us;
+            return TT_OK;
+        }
+    }
     for (int i = 0; i < std::max(1, o.warmup); ++i) {
         rc = launch_desc(op, k, s, next_turn());
         if (rc != TT_OK) return rc;
@@ -548,7 +590,9 @@ int time_pair(const tt_kernel_desc &k, const tt_schedule *sched, const tt_sweep_
     }
     std::sort(us.begin(), us.end());
     const int n = (int)us.size();
-    if (median_us) *median_us = n % 2 ? us[n / 2] : 0.5 * (us[n / 2 - 1] + us[n / 2]);
+    const double median = n % 2 ? us[n / 2] : 0.5 * (us[n / 2 - 1] + us[n / 2]);
+    if (times) times->add(key, median, us[0]);
+    if (median_us) *median_us = median;
     if (min_us) *min_us = us[0];
     return TT_OK;
 }
@@ -660,13 +704,14 @@ extern "C" int tt_transfer_sweep(const tt_kernel_desc *kernels, int nk, const tt
     Timer timer;
     std::vector<double> local((size_t)nk * np, -2.0), defaults(nk, 0.0), weight(nk, 0.0);
     std::vector<int32_t> kcls(nk), pcls(np);
+    std::vector<LaunchTimes> times(nk);
     for (int p = 0; p < np; ++p) pcls[p] = pool[p].cls;
     int64_t evals = 0;
     // the default ("untuned") schedule is always evaluated: it is the baseline and the fallback
     for (int k = 0; k < nk; ++k) {
         if (!kernels[k].shape) return TT_ERR_BAD_ARG;
         kcls[k] = kernels[k].cls;
-        const int rc = time_pair(kernels[k], nullptr, o, s, timer, &defaults[k], nullptr);
+        const int rc = time_pair(kernels[k], nullptr, o, s, timer, &defaults[k], nullptr, &times[k]);
         if (rc != TT_OK) return rc;
         weight[k] = defaults[k] * std::max(1, kernels[k].use_count);
         ++evals;
@@ -686,7 +731,7 @@ extern "C" int tt_transfer_sweep(const tt_kernel_desc *kernels, int nk, const tt
             }
             ++evals;
             double us = -1.0;
-            const int rc = time_pair(kernels[k], &pool[p], o, s, timer, &us, nullptr);
+            const int rc = time_pair(kernels[k], &pool[p], o, s, timer, &us, nullptr, &times[k]);
             if (rc == TT_ERR_HIP) return rc;
             // every other failure means "this record does not fit this kernel": the paper's -1
             local[(size_t)k * np + p] = rc == TT_OK ? us : -1.0;
@@ -710,8 +755,9 @@ extern "C" int tt_refine(const tt_kernel_desc *kernel, const tt_schedule *base, 
     const tt_sweep_opts o = resolve(opts);
     hipStream_t s = static_cast<hipStream_t>(stream);
     Timer timer;
+    LaunchTimes times;
     double cur_us = 0.0;
-    int rc = time_pair(*kernel, base, o, s, timer, &cur_us, nullptr);
+    int rc = time_pair(*kernel, base, o, s, timer, &cur_us, nullptr, &times);
     if (rc != TT_OK) return rc;
     int32_t n = 1;
     tt_schedule cur = *base;
@@ -725,7 +771,7 @@ extern "C" int tt_refine(const tt_kernel_desc *kernel, const tt_schedule *base, 
         double win_us = cur_us;
         for (int i = 0; i < count; ++i) {
             double us = 0.0;
-            rc = time_pair(*kernel, &near[i], o, s, timer, &us, nullptr);
+            rc = time_pair(*kernel, &near[i], o, s, timer, &us, nullptr, &times);
             if (rc == TT_ERR_HIP) return rc;
             if (rc != TT_OK) continue; // does not apply to this kernel, or no kernel implements it
             ++n;
@@ -775,12 +821,13 @@ extern "C" int tt_native_sweep(const tt_kernel_desc *kernel, int level, int fina
         int index;
     };
     int valid = 0;
-    const auto fastest = [&](const std::vector<tt_schedule> &list, int n, const tt_sweep_opts &o, size_t keep, bool count_valid,
+    LaunchTimes ex_times, fu_times;
+    const auto fastest = [&](const std::vector<tt_schedule> &list, int n, const tt_sweep_opts &o, LaunchTimes &times, size_t keep, bool count_valid,
                              std::vector<tt_schedule> *out, std::vector<double> *out_us) -> int {
         std::vector<Timed> t;
         for (int i = 0; i < n; ++i) {
             double us = 0.0;
-            const int rc = time_pair(*kernel, &list[i], o, s, timer, &us, nullptr);
+            const int rc = time_pair(*kernel, &list[i], o, s, timer, &us, nullptr, &times);
             if (rc == TT_ERR_HIP) return rc;
             if (rc != TT_OK) continue;
             if (count_valid) ++valid;
@@ -796,7 +843,7 @@ extern "C" int tt_native_sweep(const tt_kernel_desc *kernel, int level, int fina
         return TT_OK;
     };
     std::vector<tt_schedule> top;
-    int rc = fastest(space, count, ex, (size_t)finalists, true, &top, nullptr);
+    int rc = fastest(space, count, ex, ex_times, (size_t)finalists, true, &top, nullptr);
     if (rc != TT_OK) return rc;
     if (!top.empty() && top[0].sketch == TT_SK_MFMA) {
         // the enumerated space carries one unroll setting and (below level 2) two workgroup orders: the
@@ -812,14 +859,14 @@ extern "C" int tt_native_sweep(const tt_kernel_desc *kernel, int level, int fina
                     for (const tt_schedule &w : wide) seen = seen || std::memcmp(&w, &r, sizeof(int32_t) * 13) == 0;
                     if (!seen) wide.push_back(r);
                 }
-        rc = fastest(wide, (int)wide.size(), ex, (size_t)finalists, false, &top, nullptr);
+        rc = fastest(wide, (int)wide.size(), ex, ex_times, (size_t)finalists, false, &top, nullptr);
         if (rc != TT_OK) return rc;
     }
     std::vector<double> top_us;
-    rc = fastest(top, (int)top.size(), fu, 1, false, &top, &top_us);
+    rc = fastest(top, (int)top.size(), fu, fu_times, 1, false, &top, &top_us);
     if (rc != TT_OK) return rc;
     double def_us = 0.0;
-    rc = time_pair(*kernel, nullptr, fu, s, timer, &def_us, nullptr);
+    rc = time_pair(*kernel, nullptr, fu, s, timer, &def_us, nullptr, &fu_times);
     if (rc != TT_OK) return rc;
     if (hipStreamSynchronize(s) != hipSuccess) return TT_ERR_HIP;
     if (!top.empty() && top_us[0] < def_us) { // the default wins ties

@@ -713,3 +713,22 @@ def test_register_pipeline_records_in_the_tile_their_size_asks_for(api, P, m, n,
     cls = wl.CLS_DENSE_BIAS_RELU
     one_stage = mfma(api, cls, 32, 32, 32, 16, 16, 16, vec=2, unroll=1, stages=1)
     P.check_kernel(wl.Kernel(cls, wl.GemmShape(1, m, n, k, 1, dt), 1, f"dense_{m}_{n}_{k}"), [None, one_stage], seed=7)
+
+
+# ---- records that come to the same launch --------------------------------------------------------------------------
+def test_sweeps_time_a_launch_once_whatever_records_come_to_it(api):
+    from paper_2201_05587_amd import harness
+    kernel = wl.Kernel(wl.CLS_DENSE_ADD, wl.GemmShape(1, 512, 256, 1024, 1, wl.BF16))
+    dk = harness.device_kernel(kernel, 3, max_split=2)
+    same = [mfma(api, kernel.cls, 64, 64, tk, 32, 32, 32, stages=st, unroll=un) for tk, st, un in
+            ((64, 2, 8), (32, 1, 8), (64, 3, 8), (64, 4, 1))]
+    others = [mfma(api, kernel.cls, 64, 64, 64, 32, 32, 32, stages=3, order=1), mfma(api, kernel.cls, 64, 64, 64, 32, 32, 32, stages=3, split_k=2)]
+    for r in same:
+        assert api.launched_name(r, kernel.cls, kernel.shape) == "tt::contract_groups_kernel<1, 1, 64, 64, 32, 32, 32>"
+    rows, table, evals, _ = api.tt_transfer_sweep([dk], same + others)
+    assert evals == 1 + len(same) + len(others) and rows[0]["n_valid"] == len(same) + len(others)
+    assert len(set(table[0][:4])) == 1 and len(set(table[0])) > 1
+    assert rows[0]["chosen"] not in (1, 2, 3)  # equal donors: the first
+    rc, best, best_us, base_us, tried = api.tt_refine(dk, same[2], 1)
+    assert rc == api.TT_OK and tried > 1
+    assert best.knobs() == same[2].knobs() if best_us == base_us else best_us < base_us
