@@ -60,7 +60,7 @@ def test_cfg1_conv_under_default_and_donor_tiles(api, P):
               api.make_schedule(E, api.TT_SK_DIRECT, 1, 1, 1, 1, 1, 0, 1, 0, 1, 1, 1)]
     ref, outs = P.check_kernel(k, scheds)
     assert ref.min() >= 0.0
-    # same (tile_k, split_k, block) => same summation order => identical bits, whatever the tile shape
+    # the same record on the same inputs: identical bits
     a = P.run_gpu(k, __import__("paper_2201_05587_amd.harness", fromlist=["x"]).device_kernel(k, 1234),
                   mfma(api, E, 64, 64, 32, 32, 32, 32))
     np.testing.assert_array_equal(a, outs[2])
@@ -291,7 +291,9 @@ def test_split_k_is_deterministic(api, P):
         recs = [mfma(api, k.cls, 32, 32, tk, 16, 16, 16, split_k=6), mfma(api, k.cls, 64, 64, tk, 32, 32, 16, split_k=6, stages=3),
                 mfma(api, k.cls, 64, 64, tk, 32, 16, 16, split_k=6, order=4)]
         ref, outs = P.check_kernel(k, recs, seed=5)
-        # the same (tile_k, split_k, matrix-core block) gives the same summation order whatever the tile, pipeline or raster
+        # on the records' own kernels (a split here is too short for groups) the same (tile_k, split_k, matrix-core block) gives
+        # the same summation order whatever the tile, pipeline or raster
+        assert all(api.tt_debug_launch(r, k.cls, k.shape)[1] == api.TT_LAUNCH_RECORD for r in recs)
         np.testing.assert_array_equal(outs[0], outs[1])
         np.testing.assert_array_equal(outs[0], outs[2])
         dk = harness.device_kernel(k, 5)
@@ -604,6 +606,7 @@ def test_timing_rotates_through_the_alternative_tensor_sets(api, P):
     ("three_slices", 4, wl.GemmShape(1, 64, 64, 384, 1, wl.BF16), dict(tm=64, tn=64, tk=64, wm=32, wn=32, mf=32, stages=3)),
     ("tails", 6, wl.GemmShape(1, 100, 88, 456, 1, wl.BF16), dict(tm=64, tn=64, tk=64, wm=32, wn=32, mf=16, stages=2)),
     ("odd_rows", 5, wl.GemmShape(1, 70, 61, 640, 1, wl.BF16), dict(tm=32, tn=32, tk=32, wm=16, wn=16, mf=16, stages=3)),
+    ("odd_rows_groups", 5, wl.GemmShape(1, 70, 61, 800, 1, wl.BF16), dict(tm=32, tn=32, tk=32, wm=16, wn=16, mf=16, stages=2)),
     ("four_waves_64x32", 4, wl.GemmShape(1, 130, 66, 516, 1, wl.F32), dict(tm=128, tn=64, tk=32, wm=64, wn=32, mf=32, stages=2)),
     ("eight_waves", 4, wl.GemmShape(1, 96, 160, 776, 1, wl.BF16), dict(tm=64, tn=64, tk=128, wm=16, wn=32, mf=16, stages=3)),
     # one workgroup per CU, and one more than that (the plain kernel)
@@ -620,7 +623,11 @@ def test_timing_rotates_through_the_alternative_tensor_sets(api, P):
     ("conv_split_f32", 1, wl.ConvShape(1, 100, 12, 12, 40, 3, 3, 1, 1, 1, 1, wl.F32), dict(tm=32, tn=32, tk=32, wm=16, wn=16, mf=16, split_k=2, stages=4)),
 ])
 def test_reduction_split_inside_the_workgroup(api, P, name, cls, shape, rec):
-    P.check_kernel(wl.Kernel(cls, shape, 1, name), [mfma(api, cls, **rec), mfma(api, cls, order=4, **rec)], seed=4321)
+    recs = [mfma(api, cls, **rec), mfma(api, cls, order=4, **rec)]
+    # "odd_rows" is two slices long, and the reference of "odd_rows_groups"
+    want = api.TT_LAUNCH_RECORD if name in ("odd_rows", "grid_257", "large_11") else api.TT_LAUNCH_GROUPS
+    assert all(api.tt_debug_launch(r, cls, shape)[1] == want for r in recs)
+    P.check_kernel(wl.Kernel(cls, shape, 1, name), recs, seed=4321)
 
 
 # ---- entries of one plan that a list sends out as one launch ---------------------------------------------------------
@@ -634,7 +641,7 @@ def test_reduction_split_inside_the_workgroup(api, P, name, cls, shape, rec):
     ("depthwise", wl.Kernel(8, wl.ConvShape(1, 24, 13, 13, 24, 3, 3, 1, 1, 1, 1)), None),
 ])
 def test_list_of_one_plan_runs_every_entry_and_keeps_dependent_ones_in_order(api, P, name, kernel, rec):
-    """More entries than one launch carries; entries 3 and 7 read what the entry before them writes."""
+    """Launches of three and four entries: entries 3 and 7 read what the entry before them writes."""
     import torch
     from paper_2201_05587_amd import harness
     sched = None if rec is None else mfma(api, kernel.cls, **rec)
@@ -658,6 +665,73 @@ def test_list_of_one_plan_runs_every_entry_and_keeps_dependent_ones_in_order(api
                 outputs(lambda: api.KernelList(dks, [sched] * len(dks)).run(2))):
         for i, (g, w) in enumerate(zip(got, want)):
             P.assert_close(g, w, kernel.shape.dtype, f"{name} {i}")
+
+
+R32 = wl.ConvShape(32, 256, 14, 14, 256, 3, 3, 1, 1, 1, 1, wl.BF16)  # M = 6272: the last block has a half outside
+
+
+@pytest.mark.parametrize("name,kernel,rec,alone,together", [
+    ("ring", wl.Kernel(4, wl.GemmShape(1, 96, 96, 96, 1, wl.BF16)), dict(tm=32, tn=32, tk=64, wm=16, wn=16, mf=16, stages=3), 0, 0),
+    ("split", wl.Kernel(4, wl.GemmShape(1, 128, 128, 128, 1, wl.F32)), dict(tm=64, tn=64, tk=32, wm=32, wn=32, mf=32, split_k=2), 0, 0),
+    ("stream", wl.Kernel(4, wl.GemmShape(1, 192, 192, 192, 1, wl.BF16)), dict(tm=64, tn=64, tk=64, wm=32, wn=32, mf=16, stages=7), 0, 0),
+    ("depthwise", wl.Kernel(8, wl.ConvShape(1, 24, 13, 13, 24, 3, 3, 1, 1, 1, 1)), None, 0, 0),
+    # groups: at most one workgroup per CU together; only alone; and more of them on a ring that leaves room for one
+    ("groups", conv_kernel(wl.CLS_CONV2D_BIAS_ADD_RELU, 1, 64, 14, 64, 3, 1), dict(tm=32, tn=32, tk=32, wm=16, wn=16, mf=16, stages=3), 1, 1),
+    ("groups_alone", conv_kernel(wl.CLS_CONV2D_BIAS_ADD_RELU, 1, 64, 28, 64, 3, 1), dict(tm=32, tn=32, tk=32, wm=16, wn=16, mf=16, stages=3), 1, 0),
+    ("groups_many", wl.Kernel(6, wl.GemmShape(1, 600, 600, 600, 1, wl.F32)), dict(tm=64, tn=64, tk=64, wm=32, wn=32, mf=32, stages=3), 1, 0),
+    ("groups_many_long", wl.Kernel(6, wl.GemmShape(1, 1000, 1000, 1000, 1, wl.F32)), dict(tm=64, tn=64, tk=64, wm=32, wn=32, mf=32, stages=3), 1, 1),
+    # blocks that only several entries fill the chip with
+    ("blocks", wl.Kernel(1, R32), dict(tm=64, tn=128, tk=128, wm=32, wn=32, mf=16, stages=3), 0, 2),
+    ("blocks_res", wl.Kernel(2, R32), dict(tm=64, tn=128, tk=128, wm=32, wn=32, mf=16, stages=3), 0, 2),
+    ("blocks_dense", wl.Kernel(4, wl.GemmShape(1, 1096, 1096, 1096, 1, wl.BF16)), dict(tm=64, tn=64, tk=64, wm=32, wn=32, mf=16, stages=3), 0, 2),
+])
+def test_list_that_fills_a_launch(api, P, name, kernel, rec, alone, together):
+    """Nine independent entries (a launch of eight and one more) and a tenth that reads what the ninth writes."""
+    import torch
+    from paper_2201_05587_amd import harness
+    sched = None if rec is None else mfma(api, kernel.cls, **rec)
+    assert api.tt_debug_launch(sched, kernel.cls, kernel.shape, 1)[1] == alone
+    assert api.tt_debug_launch(sched, kernel.cls, kernel.shape, 8)[1] == together
+    inputs = [wl.make_inputs(kernel, 700 + i) for i in range(10)]
+    dks = [harness.device_kernel(kernel, 0, inp, max_split=2) for inp in inputs]
+    tensors = [dict(dk.tensors) for dk in dks]
+    tensors[9]["x"] = tensors[8]["y"]
+    dks = [api.DeviceKernel(kernel.cls, kernel.shape, t, 1, name, dk.ws.numel()) for t, dk in zip(tensors, dks)]
+
+    def outputs(run):
+        for dk in dks:
+            dk.output().fill_(float("nan"))
+        run()
+        torch.cuda.synchronize()
+        return [harness.output_in_definition_order(kernel, dk.output()).float().cpu().numpy() for dk in dks]
+
+    want = outputs(lambda: [dk.run(sched) for dk in dks])
+    got = outputs(lambda: api.KernelList(dks, [sched] * len(dks)).run())
+    for i, (g, w) in enumerate(zip(got, want)):
+        P.assert_close(g, w, kernel.shape.dtype, f"{name} {i}")
+    for i in (0, 7, 8):  # the ends of the full launch, and the one behind it
+        P.assert_close(got[i], P.oracle_output(kernel, inputs[i]), kernel.shape.dtype, f"{name} {i} oracle")
+
+
+def test_list_with_and_without_a_bias(api, P):
+    """Entries of one plan with a bias and without do not go out together."""
+    import torch
+    from paper_2201_05587_amd import harness
+    kernel = wl.Kernel(wl.CLS_DENSE_BIAS_RELU, wl.GemmShape(1, 96, 96, 96, 1, wl.F32))
+    sched = mfma(api, kernel.cls, 32, 32, 32, 16, 16, 16, stages=3)
+    dks = []
+    for i, bias in enumerate((1, 1, 0, 0, 0, 1, 0, 1, 1)):
+        t = dict(harness.device_kernel(kernel, 800 + i, max_split=1).tensors)
+        if not bias:
+            del t["bias"]
+        dks.append(api.DeviceKernel(kernel.cls, kernel.shape, t, 1, f"entry{i}"))
+    want = [P.run_gpu(kernel, dk, sched) for dk in dks]
+    for dk in dks:
+        dk.output().fill_(float("nan"))
+    api.KernelList(dks, [sched] * len(dks)).run()
+    torch.cuda.synchronize()
+    for i, (dk, w) in enumerate(zip(dks, want)):
+        P.assert_close(dk.output().cpu().numpy(), w, wl.F32, f"entry {i}")
 
 
 def test_list_launches_what_stands_before_an_entry_without_workspace(api, P):
@@ -698,10 +772,11 @@ def test_large_bf16_launches_run_in_blocks(api, P, name, cls, shape):
     _, m, n, k = kernel.gemm_extents()
     rounds = -(-(-(-m // 256) * -(-n // 256)) // 256)
     assert k >= 1024 and m * n >= 65536 * 256 * rounds // 2
+    assert api.tt_debug_launch(ring, cls, shape)[1] == api.TT_LAUNCH_BLOCKS
     P.check_kernel(kernel, [None, ring], seed=99)
 
 
-# ---- register-pipeline records run on ring instances in a tile chosen by size ----------------------------------------
+# ---- the default schedule runs on ring instances in a tile chosen by size; a record of its own keeps its tile ----------
 @pytest.mark.parametrize("dt", [wl.F32, wl.BF16])
 @pytest.mark.parametrize("m,n,k", [
     (32, 32, 64), (33, 40, 72),       # one tile and a ragged edge of the smallest
