@@ -355,16 +355,15 @@ def main():
     del cold_list, launch_dks
     torch.cuda.empty_cache()
 
-    # ---- per-kernel durations with HIP events on the launch stream, cold: a kernel is launched in turn on
+    # ---- per-kernel durations with HIP events on the launch stream, cold: a kernel is launched by itself, in turn on
     # enough tensor sets that a set has left the caches (256 MB memory-side cache, 32 MB of L2) before its
-    # turn comes again.  Every launch this process asks for is entered in a ledger per symbol its record names;
-    # a kernel trace shows fewer dispatches, since up to eight entries of one plan go out together.
-    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    # turn comes again.  Every launch this process asks for is entered in a ledger per symbol that a lone launch runs
+    # on.  (In a pass up to eight equal neighbours go out as one launch, which may run on another kernel: a kernel
+    # trace shows fewer dispatches.)
     ledger = {}
 
     def symbol_of(k, rec):
-        rec = rec if rec is not None else api.tt_schedule_default(k.cls, k.shape)
-        return api.variant_name(api.tt_schedule_apply(rec, k.cls, k.shape), k.shape)
+        return api.launched_name(rec, k.cls, k.shape)
 
     def book(k, rec, launches, us):
         g = ledger.setdefault(symbol_of(k, rec), dict(us=0.0, flops=0.0, bytes=0.0, launches=0, dtype=k.shape.dtype,
@@ -375,33 +374,29 @@ def main():
         g["launches"] += launches
         g["layers"].add(k.name)
 
-    def cold_launches(k, sets, rec, rounds=3):
-        """Average duration of a launch of (kernel, record) over `rounds` turns through the tensor sets."""
-        ring = api.KernelList(sets, [rec] * len(sets))
-        ring.run(1)
-        e0.record()
-        ring.run(rounds)
-        e1.record()
-        e1.synchronize()
-        us = e0.elapsed_time(e1) * 1e3 / (rounds * len(sets))
-        book(k, rec, (rounds + 1) * len(sets), us)
+    def cold_launches(k, ring, rec, rounds=3):
+        """Duration of a launch of (kernel, record): the median over `rounds` turns through the tensor sets."""
+        n = 1 + len(ring.alternates)
+        rc, us, _ = api.tt_time_pair(ring, rec, api.make_opts(warmup=n, samples=rounds, min_sample_us=10 ** 9, max_launches=n))
+        assert rc == api.TT_OK, (k.name, api.status_name(rc))
+        book(k, rec, 1 + (rounds + 1) * n, us)
         return us
 
     per_kernel = []
     for k, dk, tr, na in zip(targets, dks, transfer, native):
         n_sets = int(min(400, max(2, -(-args.cold_mb * 1e6 // k.algorithmic_bytes()) + 1)))
-        sets = [api.DeviceKernel(k.cls, k.shape, dk.tensors, 1, k.name, dk.ws.numel())]
-        sets += [clone_kernel(api, k, dk) for _ in range(n_sets - 1)]
-        t_us = cold_launches(k, sets, tr)
+        ring = api.DeviceKernel(k.cls, k.shape, dk.tensors, 1, k.name, dk.ws.numel(),
+                                [{name: t.clone() for name, t in dk.tensors.items()} for _ in range(n_sets - 1)])
+        t_us = cold_launches(k, ring, tr)
         book(k, tr, (args.warmup + args.steps) * k.use_count, t_us)  # the cold passes of the timed region
         same = (tr is None and na is None) or (tr is not None and na is not None and tr.knobs() == na.knobs())
-        n_us = t_us if same else cold_launches(k, sets, na)
+        n_us = t_us if same else cold_launches(k, ring, na)
         e = by_name[k.name]
         per_kernel.append(dict(name=k.name, transfer_us=t_us, native_us=n_us, default_us_at_sweep=e["default_us"],
                                frac_of_native=min(n_us, t_us) / t_us, tflops=k.flops() / t_us / 1e6,
                                gbps=k.algorithmic_bytes() / t_us / 1e3, kernel=symbol_of(k, tr), tensor_sets=n_sets,
                                on_default_fallback=tr is None))
-        del sets
+        del ring
         torch.cuda.empty_cache()
     fracs = [p["frac_of_native"] for p in per_kernel]
 
@@ -432,7 +427,7 @@ def main():
         roof.update(kernel=name, avg_launch_us=in_pass["us"] / in_pass["launches"],
                     avg_launch_us_all_launches_of_this_process=led["us"] / led["launches"], launches=led["launches"],
                     layers=sorted(led["layers"]), arithmetic_intensity=ai,
-                    timing="cold: every launch on tensors that have left the caches")
+                    timing="cold: every launch by itself, on tensors that have left the caches")
         return roof
 
     by_share = sorted(share.items(), key=lambda kv: -kv[1]["us"])
