@@ -303,6 +303,17 @@ def test_split_k_is_deterministic(api, P):
         np.testing.assert_array_equal(first, outs[1])
 
 
+@pytest.mark.parametrize("dt", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("n", [64, 61])
+def test_every_number_of_splits(api, P, dt, n):
+    """The reduction asks for the partial sums of two, four and eight splits at a time: 2 to 8 splits, and past one and two
+    turns of eight.  K = 34 tiles of 32, so that the counts are what they say."""
+    kernel = wl.Kernel(wl.CLS_DENSE_BIAS_RELU, wl.GemmShape(1, 70, n, 34 * 32, 1, dt), 1, f"splits_{n}")
+    recs = [mfma(api, kernel.cls, 32, 32, 32, 16, 16, 16, split_k=sp) for sp in (2, 3, 4, 5, 6, 7, 9, 12, 17)]
+    assert [api.tt_schedule_apply(r, kernel.cls, kernel.shape).eff_split_k for r in recs] == [2, 3, 4, 5, 6, 7, 9, 12, 17]
+    P.check_kernel(kernel, recs, seed=11)
+
+
 # ---- kernels chained through shared tensors ---------------------------------------------------------
 def test_bottleneck_chain_matches_the_oracle_applied_in_sequence(api, P):
     """Three kernels per block, the output tensor of one being the input of the next, two blocks."""
