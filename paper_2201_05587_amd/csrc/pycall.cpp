@@ -36,7 +36,6 @@ public:
     Owned(const Owned &) = delete;
     Owned &operator=(const Owned &) = delete;
     PyObject *get() const { return o_; }
-    PyObject *new_reference() const { return Py_NewRef(o_); }
 
 private:
     PyObject *o_;
@@ -88,15 +87,32 @@ size_t bytes_of(PyObject *o)
     return (size_t)(integer_from(o, "numel") * integer_from(o, "element_size"));
 }
 
-// The output of a call: the caller's, or a new one of x's type and place.
-PyObject *output_for(PyObject *given, PyObject *x, at::IntArrayRef sizes)
-{
-    if (given != Py_None) return Py_NewRef(given);
-    if (THPVariable_CheckExact(x)) return THPVariable_Wrap(at::empty(sizes, THPVariable_Unpack(x).options()));
-    Owned tuple(PyTuple_New((Py_ssize_t)sizes.size()));
-    for (size_t i = 0; i < sizes.size(); ++i) PyTuple_SET_ITEM(tuple.get(), i, PyLong_FromLongLong(sizes[i]));
-    return PyObject_CallFunctionObjArgs(empty_tensor, x, tuple.get(), nullptr);
-}
+// The output of a call: the caller's, or a new one of x's type and place, which becomes a Python object behind the launch.
+class Output {
+public:
+    Output(PyObject *given, PyObject *x, at::IntArrayRef sizes)
+    {
+        if (given != Py_None) {
+            object_ = Py_NewRef(given);
+        } else if (THPVariable_CheckExact(x)) {
+            made_ = at::empty(sizes, THPVariable_Unpack(x).options());
+        } else {
+            Owned tuple(PyTuple_New((Py_ssize_t)sizes.size()));
+            for (size_t i = 0; i < sizes.size(); ++i) PyTuple_SET_ITEM(tuple.get(), i, PyLong_FromLongLong(sizes[i]));
+            object_ = PyObject_CallFunctionObjArgs(empty_tensor, x, tuple.get(), nullptr);
+            if (!object_) throw python_error();
+        }
+    }
+    ~Output() { Py_XDECREF(object_); }
+    Output(const Output &) = delete;
+    Output &operator=(const Output &) = delete;
+    void *address() const { return object_ ? address_of(object_) : made_.data_ptr(); }
+    PyObject *result() { return object_ ? Py_NewRef(object_) : THPVariable_Wrap(std::move(made_)); }
+
+private:
+    PyObject *object_ = nullptr;
+    at::Tensor made_;
+};
 
 int class_of(PyObject *o)
 {
@@ -118,7 +134,7 @@ int64_t out_extent(int64_t in, int64_t pad, int64_t filter, int64_t stride)
 void *current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
 // Plan, workspace, launch.  Returns the output, or the status as a Python integer.
-PyObject *call(int cls, const void *shape, PyObject *sched, OpPointers p, PyObject *ws, Owned &out)
+PyObject *call(int cls, const void *shape, PyObject *sched, OpPointers p, PyObject *ws, Output &out)
 {
     int rc = TT_OK;
     at::Tensor own_ws;
@@ -130,7 +146,7 @@ PyObject *call(int cls, const void *shape, PyObject *sched, OpPointers p, PyObje
             p.ws = address_of(ws);
             p.ws_bytes = bytes_of(ws);
         }
-        p.out = address_of(out.get());
+        p.out = out.address();
         rc = check_op_pointers(cls, p);
         if (rc == TT_OK) rc = prepare_op(sched != Py_None ? &rec : nullptr, cls, shape, &op);
         if (rc == TT_OK && ws == Py_None && op.plan.workspace_bytes > 0) {
@@ -144,7 +160,7 @@ PyObject *call(int cls, const void *shape, PyObject *sched, OpPointers p, PyObje
         Py_BEGIN_ALLOW_THREADS rc = launch_op(op, &p, 1, stream); // (a full queue makes a launch wait)
         Py_END_ALLOW_THREADS
     }
-    return rc == TT_OK ? out.new_reference() : PyLong_FromLong(rc);
+    return rc == TT_OK ? out.result() : PyLong_FromLong(rc);
 }
 
 // conv2d(x, w, bias, residual, shape, cls, sched, ws, y)
@@ -155,7 +171,7 @@ PyObject *py_conv2d(PyObject *, PyObject *const *a, Py_ssize_t n)
     const tt_conv_shape s = struct_of<tt_conv_shape>(a[4], conv_shape_type);
     const int cls = class_of(a[5]);
     const int64_t ho = out_extent(s.h, s.pad_h, s.r, s.stride_h), wo = out_extent(s.w, s.pad_w, s.s, s.stride_w);
-    Owned out(output_for(a[8], a[0], {s.n, s.k, ho, wo}));
+    Output out(a[8], a[0], {s.n, s.k, ho, wo});
     if (!is_conv_class(cls)) return PyLong_FromLong(TT_ERR_BAD_ARG);
     return call(cls, &s, a[6], {address_of(a[0]), address_of(a[1]), address_of(a[2]), address_of(a[3]), nullptr, nullptr, 0}, a[7], out);
     END_HANDLE_TH_ERRORS
@@ -168,7 +184,7 @@ PyObject *py_dense(PyObject *, PyObject *const *a, Py_ssize_t n)
     TORCH_CHECK_TYPE(n == 8, "dense takes eight arguments");
     const tt_gemm_shape s = struct_of<tt_gemm_shape>(a[3], gemm_shape_type);
     const int cls = class_of(a[4]);
-    Owned out(output_for(a[7], a[0], {s.m, s.n}));
+    Output out(a[7], a[0], {s.m, s.n});
     if (!is_dense_class(cls)) return PyLong_FromLong(TT_ERR_BAD_ARG);
     return call(cls, &s, a[5], {address_of(a[0]), address_of(a[1]), address_of(a[2]), nullptr, nullptr, nullptr, 0}, a[6], out);
     END_HANDLE_TH_ERRORS
@@ -180,7 +196,7 @@ PyObject *py_matmul(PyObject *, PyObject *const *a, Py_ssize_t n)
     HANDLE_TH_ERRORS
     TORCH_CHECK_TYPE(n == 6, "matmul takes six arguments");
     const tt_gemm_shape s = struct_of<tt_gemm_shape>(a[2], gemm_shape_type);
-    Owned out(output_for(a[5], a[0], {s.batch, s.m, s.n}));
+    Output out(a[5], a[0], {s.batch, s.m, s.n});
     return call(TT_BATCH_MATMUL, &s, a[3], {address_of(a[0]), address_of(a[1]), nullptr, nullptr, nullptr, nullptr, 0}, a[4], out);
     END_HANDLE_TH_ERRORS
 }
@@ -192,7 +208,7 @@ PyObject *py_dwconv(PyObject *, PyObject *const *a, Py_ssize_t n)
     TORCH_CHECK_TYPE(n == 6, "dwconv takes six arguments");
     const tt_conv_shape s = struct_of<tt_conv_shape>(a[3], conv_shape_type);
     const int64_t ho = out_extent(s.h, s.pad_h, s.r, s.stride_h), wo = out_extent(s.w, s.pad_w, s.s, s.stride_w);
-    Owned out(output_for(a[5], a[0], {s.n, s.c, ho, wo}));
+    Output out(a[5], a[0], {s.n, s.c, ho, wo});
     return call(TT_DWCONV_BIAS_RELU6, &s, a[4], {address_of(a[0]), address_of(a[1]), address_of(a[2]), nullptr, nullptr, nullptr, 0}, Py_None, out);
     END_HANDLE_TH_ERRORS
 }
