@@ -183,6 +183,7 @@ typedef struct tt_schedule {
  *            stages 5..7 report their own layouts); it is 0 when
  *            no variant implements the plan (variant_id = -1: the operator entry points then return
  *            TT_ERR_UNSUPPORTED).
+ * The library fields describe the record's own kernel; what a launch under the record runs on is tt_debug_launch's answer.
  */
 typedef struct tt_plan {
     int32_t status, reason;
@@ -215,7 +216,8 @@ const char *tt_last_error(void);
 /*
  * The default ("untuned") schedule of a kernel (Section 4.3): valid for every
  * well-formed shape of the class.  `shape` is a tt_conv_shape for the conv and
- * depthwise classes and a tt_gemm_shape otherwise (host pointers).
+ * depthwise classes and a tt_gemm_shape otherwise (host pointers).  Where the operands are whole 16-byte items, a launch
+ * under a matrix-core default runs in a tile that the library chooses by size (tt_debug_launch), passed as NULL or as this record.
  */
 int tt_schedule_default(int cls, const void *shape, tt_schedule *out);
 
@@ -438,7 +440,12 @@ int tt_time_pair(const tt_kernel_desc *kernel, const tt_schedule *sched, const t
  * Enqueue a list of kernels back to back on `stream`: kernel i runs use_count times under
  * scheds[i] (NULL entry or NULL array = default schedule), and the whole list runs `repeat` times
  * (a network-shaped pass under the schedules a sweep chose, Section 4.3).  Does not synchronise.
- * Stops at the first error and returns it.
+ * Stops at the first error and returns it; what stands before the entry that fails has been enqueued.
+ * Up to TT_MAX_ENTRIES_PER_LAUNCH consecutive entries of one class, shape and record that run once and touch none of
+ * each other's outputs or workspaces go out as one launch; an entry that depends on another one stays behind it.  What a
+ * launch runs on can depend on the number of its entries (tt_debug_launch), so the order in which an output's products are
+ * summed, and with it the last bits, can differ from those of the entry run by itself.  For a given list they are always
+ * the same.
  */
 int tt_run_kernels(const tt_kernel_desc *kernels, const tt_schedule *const *scheds, int nk, int repeat,
                    void *stream);
