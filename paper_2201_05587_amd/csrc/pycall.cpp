@@ -45,6 +45,7 @@ private:
 // structure of another layout.
 template <class T> T struct_of(PyObject *obj, PyObject *type)
 {
+    TORCH_CHECK(type, "_ttcall is used through the binding");
     int ok = (PyObject *)Py_TYPE(obj) == type;
     if (!ok) ok = PyObject_IsInstance(obj, type);
     if (ok < 0) throw python_error();
