@@ -441,9 +441,11 @@ int tt_time_pair(const tt_kernel_desc *kernel, const tt_schedule *sched, const t
  * scheds[i] (NULL entry or NULL array = default schedule), and the whole list runs `repeat` times
  * (a network-shaped pass under the schedules a sweep chose, Section 4.3).  Does not synchronise.
  * Stops at the first error and returns it; what stands before the entry that fails has been enqueued.
- * Up to TT_MAX_ENTRIES_PER_LAUNCH consecutive entries of one class, shape and record that run once and touch none of
- * each other's outputs or workspaces go out as one launch; an entry that depends on another one stays behind it.  What a
- * launch runs on can depend on the number of its entries (tt_debug_launch), so the order in which an output's products are
+ * Consecutive entries that run once and touch none of each other's outputs or workspaces share launches (tt_debug_list) and
+ * may run at the same time and in any order; an entry that depends on an earlier one stays behind it.  Contractions of
+ * different shapes that share a launch run in a tile that suits them together, whatever tile their records name (a split of
+ * the reduction stays); other entries share one of up to TT_MAX_ENTRIES_PER_LAUNCH of their own class, shape and record.
+ * What an entry runs on can therefore depend on the entries beside it, so the order in which an output's products are
  * summed, and with it the last bits, can differ from those of the entry run by itself.  For a given list they are always
  * the same.
  */
@@ -471,6 +473,18 @@ int tt_schedule_space(int cls, int dtype, int level, tt_schedule *out, int cap);
 #define TT_MAX_ENTRIES_PER_LAUNCH 8
 enum tt_launch_kernel { TT_LAUNCH_RECORD = 0, TT_LAUNCH_GROUPS = 1, TT_LAUNCH_BLOCKS = 2 };
 int tt_debug_launch(const tt_schedule *sched, int cls, const void *shape, int count, tt_plan *launched, int32_t *kernel);
+
+/*
+ * Which launch of tt_run_kernels every entry of a list goes out in (of the first pass; launches count from 0, -1: the entry
+ * runs no times), host only.  `listed`: 1 in a launch of contractions of different shapes (contract_list_kernel,
+ * contract_groups_list_kernel in deeper slices, contract_block_list_kernel in blocks of 256 x 256), 0 in one of its own plan
+ * (tt_debug_launch); the tile it runs in there,
+ * and the number of entries of that launch.  Returns what tt_run_kernels would for a list whose entry is refused.
+ */
+typedef struct tt_listed {
+    int32_t launch, listed, tile_m, tile_n, tile_k, entries;
+} tt_listed;
+int tt_debug_list(const tt_kernel_desc *kernels, const tt_schedule *const *scheds, int nk, tt_listed *out);
 
 /*
  * Template arguments of a compiled matrix-core kernel variant (tt_plan.variant_id), and what the

@@ -82,6 +82,10 @@ class tt_kernel_desc(Structure):
                 ("ws", c_void_p), ("ws_bytes", c_size_t), ("alt_bufs", POINTER(c_void_p)), ("n_alt", c_int32)]
 
 
+class tt_listed(Structure):
+    _fields_ = [(n, c_int32) for n in ("launch", "listed", "tile_m", "tile_n", "tile_k", "entries")]
+
+
 class tt_sweep_opts(Structure):
     _fields_ = [(n, c_int32) for n in ("warmup", "samples", "min_sample_us", "max_launches", "flags",
                                        "allow_slower_than_default", "pair_budget", "prioritise")]
@@ -94,7 +98,7 @@ class tt_sweep_row(Structure):
 
 
 EXPORTS = ("tt_version", "tt_status_name", "tt_last_error", "tt_schedule_default", "tt_schedule_apply", "tt_plan_tile",
-           "tt_debug_tile_map", "tt_debug_launch", "tt_debug_fast_div", "tt_debug_probe", "tt_conv2d_bias_relu", "tt_conv2d_bias_relu_noalloc", "tt_dense_bias_relu", "tt_batch_matmul", "tt_dwconv",
+           "tt_debug_tile_map", "tt_debug_launch", "tt_debug_list", "tt_debug_fast_div", "tt_debug_probe", "tt_conv2d_bias_relu", "tt_conv2d_bias_relu_noalloc", "tt_dense_bias_relu", "tt_batch_matmul", "tt_dwconv",
            "tt_transfer_sweep", "tt_sweep_plan", "tt_refine_space", "tt_refine", "tt_native_sweep", "tt_time_pair", "tt_run_kernels", "tt_schedule_space", "tt_sweep_select", "tt_variant_info", "tt_num_variants", "tt_select_donor")
 
 
@@ -139,6 +143,7 @@ def _load():
                                  POINTER(c_double), POINTER(c_double)]
     lib.tt_run_kernels.argtypes = [POINTER(tt_kernel_desc), POINTER(POINTER(tt_schedule)), ctypes.c_int, ctypes.c_int,
                                    c_void_p]
+    lib.tt_debug_list.argtypes = [POINTER(tt_kernel_desc), POINTER(POINTER(tt_schedule)), ctypes.c_int, POINTER(tt_listed)]
     lib.tt_schedule_space.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, POINTER(tt_schedule), ctypes.c_int]
     lib.tt_variant_info.argtypes = [ctypes.c_int, POINTER(c_int32 * 12)]
     lib.tt_sweep_select.argtypes = [POINTER(c_int32), ctypes.c_int, POINTER(c_int32), ctypes.c_int, POINTER(c_double),
@@ -509,6 +514,12 @@ class KernelList:
 
     def run(self, repeat=1):
         _check(lib.tt_run_kernels(self.descs, self.ptrs, self.n, repeat, _stream()), "tt_run_kernels")
+
+    def launches(self):
+        """One tt_listed per entry: which launch of a pass it goes out in, and in what tile."""
+        out = (tt_listed * max(self.n, 1))()
+        _check(lib.tt_debug_list(self.descs, self.ptrs, self.n, out), "tt_debug_list")
+        return list(out)[:self.n]
 
 
 VARIANT_INFO = ("dtype", "family", "tile_m", "tile_n", "tile_k", "wave_m", "wave_n", "mfma", "amode", "pipe",

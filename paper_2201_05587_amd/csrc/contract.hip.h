@@ -1148,11 +1148,11 @@ template <int DT, int TM, int TN, int TK> struct RingLayout {
     static constexpr int A_BYTES = TM * RB, STAGE_BYTES = (TM + TN) * RB;
 };
 
-// Conv (16-byte gathers) and dense family with the asynchronous pipeline; g.stages = 3 or 4 buffers.
+// Tile `wg` of a contraction of the conv (16-byte gathers) or dense family with the asynchronous pipeline; g.stages = 3 or
+// 4 buffers.
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF>
-__global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) contract_async_kernel(const ContractArgs args, const PointerSets sets)
+__device__ __forceinline__ void contract_async_tile(const ContractArgs &g, int32_t wg)
 {
-    const ContractArgs g = with_set(args, sets, blockIdx.y);
     static_assert(FAM == FAM_CONV || FAM == FAM_GEMM_TN, "family without an asynchronous loader");
     using E = typename ElemOf<DT>::type;
     constexpr int CH = ElemOf<DT>::CH, ES = (int)sizeof(E);
@@ -1178,7 +1178,7 @@ __global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) contract_async_ker
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const TileCoord tc = decode_tile(g.map, (int32_t)blockIdx.x);
+    const TileCoord tc = decode_tile(g.map, wg);
     const BiasRegs<DT> bias = load_bias_early<DT, TM, WM, WN, MF>(g, tc, wave, lane);
     const int k_end = tc.k0 + tc.k_ext; // (whole items only: the gather's walk is the reduction itself)
     const int kt_count = (tc.k_ext + TK - 1) / TK;
@@ -1337,6 +1337,11 @@ __global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) contract_async_ker
     else
         k_loop(std::false_type{});
     write_tile<DT, TM, WM, WN, MF>(acc, g, tc, smem, wave, lane, bias, res_early);
+}
+template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF>
+__global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) contract_async_kernel(const ContractArgs args, const PointerSets sets)
+{
+    contract_async_tile<DT, FAM, TM, TN, TK, WM, WN, MF>(with_set(args, sets, blockIdx.y), (int32_t)blockIdx.x);
 }
 
 // More than 48 KB of dynamic LDS has to be enabled per kernel.  Remembers the largest size enabled so far

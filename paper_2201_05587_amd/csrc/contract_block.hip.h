@@ -107,10 +107,9 @@ template <int FAM> struct BlockShape {
     static constexpr int BAND = 4; // block rows walked together (see block_of)
 };
 
-template <int FAM>
-__global__ void __launch_bounds__(512) contract_block_kernel(const ContractArgs args, int blocks_m, int blocks_n, const PointerSets sets)
+// Block `wg` of blocks_m x blocks_n.
+template <int FAM> __device__ __forceinline__ void contract_block(const ContractArgs &g, int blocks_m, int blocks_n, int wg)
 {
-    const ContractArgs g = with_set(args, sets, blockIdx.y);
     using S = BlockShape<FAM>;
     constexpr int DT = TT_BF16, MF = S::MF, TK = S::TK, CPR = TK / 8, THREADS = S::THREADS;
     constexpr bool CONV = FAM == FAM_CONV;
@@ -130,7 +129,7 @@ __global__ void __launch_bounds__(512) contract_block_kernel(const ContractArgs 
     // blocks an XCD works on at a time form a rectangle (its L2 serves each operand row to 4 or 8 of them).
     TileCoord tc;
     {
-        const int total = blocks_m * blocks_n, wg = (int)blockIdx.x;
+        const int total = blocks_m * blocks_n;
         const int per = total / kXcds, rem = total % kXcds, x = wg % kXcds;
         const int L = x * per + min(x, rem) + wg / kXcds;
         const int band = L / (S::BAND * blocks_n), at = L - band * S::BAND * blocks_n;
@@ -268,6 +267,11 @@ __global__ void __launch_bounds__(512) contract_block_kernel(const ContractArgs 
             write_tile<DT, 128, 64, 32, MF, typename M::Acc, false, false, false>(acc[h][k], g, q, smem, epi_wave, lane, bias, no_res);
         }
     }
+}
+template <int FAM>
+__global__ void __launch_bounds__(512) contract_block_kernel(const ContractArgs args, int blocks_m, int blocks_n, const PointerSets sets)
+{
+    contract_block<FAM>(with_set(args, sets, blockIdx.y), blocks_m, blocks_n, (int)blockIdx.x);
 }
 
 } // namespace tt

@@ -45,10 +45,9 @@ template <int DT, int TM, int TN, int WM, int WN, int MF> struct GroupShape {
     static constexpr int LDS = STAGES * stage_bytes(CPR) > sums_bytes(KG) ? STAGES * stage_bytes(CPR) : sums_bytes(KG);
 };
 
-template <int DT, int FAM, int TM, int TN, int WM, int WN, int MF>
-__global__ void __launch_bounds__((GroupShape<DT, TM, TN, WM, WN, MF>::THREADS)) contract_groups_kernel(const ContractArgs args, const PointerSets sets)
+// Tile `wg` of a contraction, in groups.
+template <int DT, int FAM, int TM, int TN, int WM, int WN, int MF> __device__ __forceinline__ void contract_groups_tile(const ContractArgs &g, int32_t wg)
 {
-    const ContractArgs g = with_set(args, sets, blockIdx.y);
     using S = GroupShape<DT, TM, TN, WM, WN, MF>;
     using E = typename ElemOf<DT>::type;
     constexpr int CH = S::CH, ES = S::ES, KG = S::KG, TKI = S::TKI, CPR = S::CPR, THREADS = S::THREADS, NST = S::STAGES;
@@ -68,7 +67,7 @@ __global__ void __launch_bounds__((GroupShape<DT, TM, TN, WM, WN, MF>::THREADS))
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int group = wave / S::WAVES, pos = wave % S::WAVES;
-    const TileCoord tc = decode_tile(g.map, (int32_t)blockIdx.x);
+    const TileCoord tc = decode_tile(g.map, wg);
     const int k_end = tc.k0 + tc.k_ext; // (whole items only: the gather's walk is the reduction itself)
     const int kt_count = (tc.k_ext + TKI - 1) / TKI;
 
@@ -89,7 +88,7 @@ __global__ void __launch_bounds__((GroupShape<DT, TM, TN, WM, WN, MF>::THREADS))
     BRows::init(b_rows, g.K, tc.n0, g.N, tid);
     auto request = [&](int kt, int stage) {
         const int k0 = tc.k0 + kt * TKI;
-        const uint32_t sa = lds0 + (uint32_t)(stage * STAGE_BYTES);
+        const uint32_t sa = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(stage * STAGE_BYTES));
         // a slice may reach past the end of this workgroup's split of the reduction: zeros on both sides there
         if constexpr (CONV)
             AGat::issue(a_gat, a_rsrc, sa, g.R, wave, k0 + b_rows.kc < k_end);
@@ -220,6 +219,11 @@ __global__ void __launch_bounds__((GroupShape<DT, TM, TN, WM, WN, MF>::THREADS))
                                    min(8, g.N - first[p]), lo, hi);
         }
     }
+}
+template <int DT, int FAM, int TM, int TN, int WM, int WN, int MF>
+__global__ void __launch_bounds__((GroupShape<DT, TM, TN, WM, WN, MF>::THREADS)) contract_groups_kernel(const ContractArgs args, const PointerSets sets)
+{
+    contract_groups_tile<DT, FAM, TM, TN, WM, WN, MF>(with_set(args, sets, blockIdx.y), (int32_t)blockIdx.x);
 }
 
 // Whether a launch is run in groups: whole 16-byte items (what the ring loads), at most one workgroup per CU, and

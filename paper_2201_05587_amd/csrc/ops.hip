@@ -58,9 +58,6 @@ double tile_estimate(const tt_plan &p, int dtype, int tm, int tn)
     return std::ceil(tiles / compute_units()) * p.K * std::max(rows, products) * (tm * tn <= 1024 ? 1.25 : 1.0);
 }
 
-// Same knobs: the thirteen that lead the record.
-bool same_knobs(const tt_schedule &x, const tt_schedule &y) { return std::memcmp(&x, &y, sizeof(int32_t) * 13) == 0; }
-
 // The plan that is launched for a record's plan.  The default schedule of a kernel stands for "as the library sees fit": its
 // record names a register-pipeline tile, and where the asynchronous ring can load the operands it is run on the ring
 // instance that the estimate above likes best for this shape, whether the caller passed no record or the default's own.
@@ -254,7 +251,7 @@ int check_op_pointers(int cls, const OpPointers &p)
     return TT_OK;
 }
 
-static bool workspace_fits(const PreparedOp &op, const OpPointers &p)
+bool workspace_fits(const PreparedOp &op, const OpPointers &p)
 {
     return op.plan.workspace_bytes == 0 || (p.ws && (int64_t)p.ws_bytes >= op.plan.workspace_bytes && aligned16(p.ws));
 }
@@ -421,19 +418,6 @@ extern "C" int tt_debug_tile_map(const tt_plan *plan, int32_t *out_dev, void *st
 // ---- standalone timing of one (kernel, schedule) pair (Section 4.3: pairs run as distinct programs) ----------
 
 namespace {
-
-// The pointers of tensor set `turn`: 0 = bufs, then the alternatives in order, round and round.
-OpPointers pointers_of(const tt_kernel_desc &k, int64_t turn = 0)
-{
-    void *const *b = k.bufs;
-    if (k.n_alt > 0) {
-        const int set = (int)(turn % (k.n_alt + 1));
-        if (set > 0) b = k.alt_bufs + (size_t)(set - 1) * 5;
-    }
-    if (is_conv_class(k.cls)) return {b[0], b[1], b[2], b[3], b[4], k.ws, k.ws_bytes};
-    if (k.cls == TT_BATCH_MATMUL) return {b[0], b[1], nullptr, nullptr, b[2], k.ws, k.ws_bytes};
-    return {b[0], b[1], b[2], nullptr, b[3], k.ws, k.ws_bytes}; // dense, depthwise
-}
 
 // A kernel's plan and launch arguments are laid out once (prepare_op) and launched as often as needed.
 int launch_desc(PreparedOp &op, const tt_kernel_desc &k, void *stream, int64_t turn = 0)
@@ -605,92 +589,6 @@ extern "C" int tt_time_pair(const tt_kernel_desc *kernel, const tt_schedule *sch
     if (!kernel || !kernel->shape) return TT_ERR_BAD_ARG;
     Timer t;
     return time_pair(*kernel, sched, resolve(opts), static_cast<hipStream_t>(stream), t, median_us, min_us);
-}
-
-namespace {
-
-struct Range {
-    const char *at;
-    int64_t bytes;
-};
-inline bool overlap(const Range &x, const Range &y) { return x.at && y.at && x.at < y.at + y.bytes && y.at < x.at + x.bytes; }
-
-// Whether two calls of one plan may run at the same time: neither writes what the other reads or writes.
-bool independent(const PreparedOp &op, const OpPointers &p, const OpPointers &q)
-{
-    const auto writes = [&](const OpPointers &c, Range (&r)[2]) {
-        r[0] = {static_cast<const char *>(c.out), op.out_bytes};
-        r[1] = {static_cast<const char *>(op.plan.workspace_bytes > 0 ? c.ws : nullptr), op.plan.workspace_bytes};
-    };
-    const auto reads = [&](const OpPointers &c, Range (&r)[4]) {
-        r[0] = {static_cast<const char *>(c.a), op.a_bytes};
-        r[1] = {static_cast<const char *>(c.b), op.b_bytes};
-        r[2] = {static_cast<const char *>(c.bias), op.bias_bytes};
-        r[3] = {static_cast<const char *>(c.res), op.out_bytes};
-    };
-    Range wp[2], wq[2], rp[4], rq[4];
-    writes(p, wp), writes(q, wq), reads(p, rp), reads(q, rq);
-    for (int i = 0; i < 2; ++i) {
-        for (int j = 0; j < 2; ++j)
-            if (overlap(wp[i], wq[j])) return false;
-        for (int j = 0; j < 4; ++j)
-            if (overlap(wp[i], rq[j]) || overlap(rp[j], wq[i])) return false;
-    }
-    return true;
-}
-
-// Same class, shape and record: one plan.
-bool same_plan(const tt_kernel_desc &x, const tt_schedule *sx, const tt_kernel_desc &y, const tt_schedule *sy)
-{
-    if (x.cls != y.cls || (sx == nullptr) != (sy == nullptr)) return false;
-    if (sx && sx != sy && !same_knobs(*sx, *sy)) return false;
-    const bool image = is_conv_class(x.cls) || x.cls == TT_DWCONV_BIAS_RELU6;
-    return x.shape == y.shape || std::memcmp(x.shape, y.shape, image ? sizeof(tt_conv_shape) : sizeof(tt_gemm_shape)) == 0;
-}
-
-} // namespace
-
-// Consecutive entries of one plan that do not touch each other's tensors (the repeated layers of a network on
-// independent data, the projections of one activation by several weights) go out as ONE launch of up to kMaxSets
-// pointer sets: a launch costs the GPU 2 to 4 us of filling and draining the chip, and a layer of 200 workgroups
-// leaves part of it idle in between.  Entries that do depend on each other are launched one by one, in order.
-extern "C" int tt_run_kernels(const tt_kernel_desc *kernels, const tt_schedule *const *scheds, int nk, int repeat,
-                              void *stream)
-{
-    if (nk < 0 || repeat < 0 || (nk && !kernels)) return TT_ERR_BAD_ARG;
-    for (int r = 0; r < repeat; ++r)
-        for (int k = 0; k < nk;) {
-            const tt_kernel_desc &d = kernels[k];
-            const tt_schedule *rec = scheds ? scheds[k] : nullptr;
-            if (!d.shape) return TT_ERR_BAD_ARG;
-            if (d.use_count <= 0) { // nothing to launch: neither record nor tensors are looked at
-                ++k;
-                continue;
-            }
-            if (d.cls < 0 || d.cls >= TT_NUM_CLASSES) return TT_ERR_BAD_ARG;
-            OpPointers calls[kMaxSets];
-            calls[0] = pointers_of(d);
-            if (const int rc = check_op_pointers(d.cls, calls[0]); rc != TT_OK) return rc;
-            PreparedOp op; // one plan for all launches of the entry and of those that go out with it
-            if (const int rc = prepare_op(rec, d.cls, d.shape, &op); rc != TT_OK) return rc;
-            int count = 1;
-            for (; d.use_count == 1 && count < kMaxSets && k + count < nk; ++count) {
-                const tt_kernel_desc &e = kernels[k + count];
-                if (e.use_count != 1 || !e.shape || !same_plan(d, rec, e, scheds ? scheds[k + count] : nullptr)) break;
-                const OpPointers p = pointers_of(e);
-                // (an entry that will be refused must not keep the ones before it from being launched)
-                if (check_op_pointers(e.cls, p) != TT_OK || !workspace_fits(op, p)) break;
-                if ((p.bias == nullptr) != (calls[0].bias == nullptr)) break;
-                bool apart = true;
-                for (int i = 0; i < count && apart; ++i) apart = independent(op, calls[i], p);
-                if (!apart) break;
-                calls[count] = p;
-            }
-            for (int u = 0; u < d.use_count; ++u)
-                if (const int rc = launch_op(op, calls, count, stream); rc != TT_OK) return rc;
-            k += count;
-        }
-    return TT_OK;
 }
 
 extern "C" int tt_transfer_sweep(const tt_kernel_desc *kernels, int nk, const tt_schedule *pool, int np,

@@ -69,21 +69,19 @@ template <int DT, int FAM> __global__ void __launch_bounds__(256) direct_kernel(
 // together, element by element / eight requests whatever the number of splits / this (us): f32 784 x 128, K = 576, two
 // splits 8.5 / 9.3 / 8.8; K = 2304, two 13.8 / 12.9 / 12.4, four 12.5 / 12.9 / 12.7, 32 18.4 / 15.5 / 15.1; bf16 4096 x 1024,
 // K = 1024, two 35.3 / 35.3 / 33.4.
-template <int DT, int VEC> __global__ void __launch_bounds__(256) splitk_reduce_kernel(const ContractArgs args, const PointerSets sets)
+template <int DT, int VEC> __device__ __forceinline__ void reduce_outputs(const ReduceEntry &g, int64_t idx)
 {
-    const ContractArgs g = with_set(args, sets, blockIdx.y);
     typedef __attribute__((ext_vector_type(VEC))) float vec_t;
-    const int64_t total = (int64_t)g.batch * g.M * g.N;
-    const int64_t idx = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * VEC;
+    const int64_t total = g.total;
     if (idx >= total) return;
     // (32-bit division where it is enough: the 64-bit one is some hundred instructions)
-    const int n = total < (1ll << 31) ? (int)((uint32_t)idx % (uint32_t)g.N) : (int)(idx % g.N), splits = g.map.eff_split_k;
+    const int n = total < (1ll << 31) ? (int)((uint32_t)idx % (uint32_t)g.N) : (int)(idx % g.N), splits = g.splits;
     const float *ws = g.ws + idx;
     float res[VEC] = {}, bias[VEC] = {};
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
-        if (g.has_bias) bias[e] = load_as_float<DT>(g.bias, n + e);
-        if (g.has_res) res[e] = load_as_float<DT>(g.res, idx + e);
+        if (g.bias) bias[e] = load_as_float<DT>(g.bias, n + e);
+        if (g.res) res[e] = load_as_float<DT>(g.res, idx + e);
     }
     vec_t acc = vec_t(0.0f);
     const auto add = [&](int z0, auto width) { // up to `width` splits from z0 on, requested together
@@ -104,6 +102,20 @@ template <int DT, int VEC> __global__ void __launch_bounds__(256) splitk_reduce_
         add(z0, std::integral_constant<int, 2>{});
 #pragma unroll
     for (int e = 0; e < VEC; ++e) store_from_float<DT>(g.out, idx + e, apply_act(acc[e] + bias[e] + res[e], g.act));
+}
+template <int DT, int VEC> __global__ void __launch_bounds__(256) splitk_reduce_kernel(const ContractArgs args, const PointerSets sets)
+{
+    const ContractArgs g = with_set(args, sets, blockIdx.y);
+    const ReduceEntry e = {g.ws, g.has_bias ? g.bias : nullptr, g.has_res ? g.res : nullptr, g.out, (int64_t)g.batch * g.M * g.N,
+                           g.N, g.map.eff_split_k, g.act, 0};
+    reduce_outputs<DT, VEC>(e, ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * VEC);
+}
+// The same for entries of different shapes in one launch, workgroups of one wave.
+template <int DT, int VEC> __global__ void __launch_bounds__(64) splitk_reduce_list_kernel(const ReduceList list)
+{
+    int e = 0;
+    while (e + 1 < kMaxReduced && (int)blockIdx.x >= list.e[e + 1].first) ++e;
+    reduce_outputs<DT, VEC>(list.e[e], ((int64_t)((int)blockIdx.x - list.e[e].first) * 64 + threadIdx.x) * VEC);
 }
 
 // ---- GEMV sketch: a wave owns W outputs of R rows; lanes split K ---------------------------------
@@ -444,6 +456,20 @@ int launch_splitk_reduce(const ContractArgs &args, const PointerSets &sets, int 
     auto kern = vec == 4 ? splitk_reduce_kernel<TT_F32, 4> : splitk_reduce_kernel<TT_F32, 1>;
     if (args.dtype == TT_BF16) kern = vec == 4 ? splitk_reduce_kernel<TT_BF16, 4> : splitk_reduce_kernel<TT_BF16, 1>;
     hipLaunchKernelGGL(kern, grid, dim3(block), 0, s, args, sets);
+    return launched();
+}
+
+int launch_reduce_list(ReduceList &list, int count, int dtype, bool fours, void *stream)
+{
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    int grid = 0;
+    for (int i = 0; i < kMaxReduced; ++i) {
+        list.e[i].first = i < count ? grid : INT32_MAX;
+        if (i < count) grid += (int)((list.e[i].total / (fours ? 4 : 1) + 63) / 64);
+    }
+    auto kern = fours ? splitk_reduce_list_kernel<TT_F32, 4> : splitk_reduce_list_kernel<TT_F32, 1>;
+    if (dtype == TT_BF16) kern = fours ? splitk_reduce_list_kernel<TT_BF16, 4> : splitk_reduce_list_kernel<TT_BF16, 1>;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64), 0, s, list);
     return launched();
 }
 

@@ -202,6 +202,51 @@ struct ContractArgs {
     int32_t eff_vec_a, eff_vec_b, eff_vec_c, stages, unroll, act, has_bias, has_res, dtype;
 };
 
+// ---- launches of entries of different shapes (contract_list.hip.h, run_list.cpp) ----------------------
+// What a contraction tile needs of its entry; the launch has the tile, the data type and the operand family.
+struct ListEntry {
+    const void *a, *b, *bias, *res; // bias, res: null where the entry has none
+    void *out;
+    float *ws;
+    int32_t M, N, K, batch;
+    int32_t grid, tiles_m, tiles_n, k_iters, k_tiles, splits;
+    FastDiv div_tiles, div_n, div_split;
+    int32_t C, H, W, R, S, Ho, Wo, stride_h, stride_w, pad_h, pad_w;
+    FastDiv div_hw, div_wo;
+    uint32_t a_bytes, b_bytes;
+    int16_t vec_c, act;
+};
+constexpr int kMaxListed = 20;  // entries of a launch: the arguments stay within 4 KB
+constexpr int kListOrder = 1;   // raster of every entry: columns fastest
+struct ContractList {
+    int32_t first[kMaxListed]; // first workgroup of every entry, a multiple of the number of XCDs; past the last: INT32_MAX
+    ListEntry e[kMaxListed];
+};
+static_assert(sizeof(ContractList) <= 4096, "");
+struct ListTile {
+    int32_t dtype, tile_m, tile_n, tile_k;
+    float fixed_us, per_k_us, alone_per_k_us; // see list_tiles
+    int (*launch[2])(const ContractList &list, int grid, void *stream); // FAM_CONV, FAM_GEMM_TN
+};
+const ListTile *list_tiles(int *count);
+
+// What the second step of a split reduction needs of its entry.
+struct ReduceEntry {
+    const float *ws;
+    const void *bias, *res; // null where the entry has none
+    void *out;
+    int64_t total;          // outputs; also the distance between the partial sums of two splits
+    int32_t N, splits, act;
+    int32_t first;          // first workgroup of the entry; past the last: INT32_MAX
+};
+constexpr int kMaxReduced = 64;
+struct ReduceList {
+    ReduceEntry e[kMaxReduced];
+};
+static_assert(sizeof(ReduceList) <= 4096, "");
+// (`count` entries of one data type; all of rows of whole fours, or all element by element)
+int launch_reduce_list(ReduceList &list, int count, int dtype, bool fours, void *stream);
+
 struct DwArgs {
     const float *x, *w, *bias;
     float *y;
@@ -260,6 +305,12 @@ struct PreparedOp {
 int check_op_pointers(int cls, const OpPointers &p);
 int prepare_op(const tt_schedule *sched, int cls, const void *shape, PreparedOp *op);
 int launch_op(PreparedOp &op, const OpPointers *calls, int count, void *stream);
+bool workspace_fits(const PreparedOp &op, const OpPointers &p);
+
+// The tensors of a kernel description, set `turn` of those it has (run_list.cpp).
+OpPointers pointers_of(const tt_kernel_desc &k, int64_t turn = 0);
+// Same knobs: the thirteen that lead the record.
+bool same_knobs(const tt_schedule &x, const tt_schedule &y);
 
 // What runs a launch (tt_launch_kernel), and the grid (of one pointer set), workgroup and LDS it has.
 struct LaunchShape {

@@ -1,0 +1,260 @@
+"""Lists of kernels: which entries share a launch (host), and that shared launches compute every entry (GPU)."""
+import ctypes
+import random
+
+import numpy as np
+import pytest
+
+from paper_2201_05587_amd import api
+from paper_2201_05587_amd import workloads as wl
+
+
+def mfma(cls, tm, tn, tk, wm, wn, mf, split_k=1, order=0, vec=8, unroll=8, stages=3):
+    return api.make_schedule(cls, api.TT_SK_MFMA, tm, tn, tk, wm, wn, mf, split_k, order, vec, unroll, stages)
+
+
+# ---- on the host: addresses are made up, nothing is launched -------------------------------------------------------
+class FakeList(api.KernelList):
+    def __init__(self, entries):
+        """entries: (kernel, record, [addresses of x, w, bias, res, y], workspace address)"""
+        self.keep, self.scheds = [], []
+        self.n = len(entries)
+        self.descs = (api.tt_kernel_desc * max(self.n, 1))()
+        self.ptrs = (ctypes.POINTER(api.tt_schedule) * max(self.n, 1))()
+        for i, (kernel, rec, at, ws) in enumerate(entries):
+            d, shape = self.descs[i], api.to_c_shape(kernel.shape)
+            self.keep.append(shape)
+            d.cls, d.use_count, d.shape = kernel.cls, kernel.use_count, ctypes.addressof(shape)
+            slots = (0, 1, 2, 3, 4) if kernel.cls in api.CONV_CLASSES else (0, 1, 4) if kernel.cls == api.TT_BATCH_MATMUL else (0, 1, 2, 4)
+            for slot, which in enumerate(slots):
+                d.bufs[slot] = at[which] or None
+            d.ws, d.ws_bytes = ws, (1 << 30) if ws else 0
+            if rec is not None:
+                self.scheds.append(rec)
+                self.ptrs[i] = ctypes.pointer(rec)
+
+
+def ranges(kernel, at, ws, ws_bytes):
+    """(ranges written, ranges read) of an entry."""
+    s = kernel.shape
+    es = 2 if s.dtype == wl.BF16 else 4
+    if kernel.cls in api.CONV_CLASSES or kernel.cls == api.TT_DWCONV_BIAS_RELU6:
+        filters = s.k * s.r * s.s * (1 if kernel.cls == api.TT_DWCONV_BIAS_RELU6 else s.c)
+        sizes = (s.n * s.h * s.w * s.c, filters, s.k, s.n * s.ho * s.wo * s.k, s.n * s.ho * s.wo * s.k)
+    else:
+        sizes = (s.batch * s.m * s.k, s.batch * s.n * s.k, s.n, 0, s.batch * s.m * s.n)
+    spans = [(a, a + z * es) for a, z in zip(at, sizes)]
+    used = [spans[i] for i in range(4) if at[i]]
+    return [spans[4]] + ([(ws, ws + ws_bytes)] if ws_bytes else []), used
+
+
+def test_windows_keep_dependent_entries_in_order():
+    """Random lists over a few overlapping tensors: an entry that touches what an earlier one writes, or writes what an
+    earlier one touches, is launched behind it; every entry is launched once, and launches hold one data type and
+    family, or one plan."""
+    conv = lambda c, k, hw, f, dt, cls=1: wl.Kernel(cls, wl.ConvShape(1, c, hw, hw, k, f, f, 1, 1, f // 2, f // 2, dt))
+    shapes = [conv(64, 64, 14, 3, wl.BF16), conv(64, 64, 14, 1, wl.BF16), conv(32, 64, 14, 3, wl.BF16, 2), conv(64, 64, 14, 3, wl.F32),
+              wl.Kernel(4, wl.GemmShape(1, 196, 64, 64, 1, wl.BF16)), wl.Kernel(7, wl.GemmShape(4, 49, 64, 64, 1, wl.BF16)),
+              wl.Kernel(7, wl.GemmShape(4, 49, 64, 64, 0, wl.BF16)), wl.Kernel(4, wl.GemmShape(1, 1, 64, 64, 1, wl.F32)),
+              wl.Kernel(8, wl.ConvShape(1, 64, 14, 14, 64, 3, 3, 1, 1, 1, 1, wl.F32)), conv(3, 64, 28, 7, wl.BF16)]
+    rng = random.Random(11)
+    shared, followed = 0, 0
+    for _ in range(200):
+        entries, spans = [], []
+        for _ in range(rng.randint(2, 40)):
+            k = rng.choice(shapes)
+            at = [(1 << 20) * rng.randint(1, 60) + 16 * rng.randint(0, 4000) for _ in range(5)]
+            if k.cls != 2:
+                at[3] = 0
+            if k.cls == api.TT_BATCH_MATMUL:
+                at[2] = 0
+            rec, ws, ws_bytes = None, 0, 0
+            if k.cls in (1, 2, 4) and rng.random() < 0.3 and k.shape.dtype == wl.F32:
+                rec = mfma(k.cls, 32, 32, 32, 16, 16, 16, split_k=2, vec=4)
+                plan = api.tt_schedule_apply(rec, k.cls, k.shape)
+                if plan.status != api.TT_OK:
+                    rec = None
+                else:
+                    ws, ws_bytes = (1 << 20) * rng.randint(1, 60), plan.workspace_bytes
+            entries.append((k, rec, at, ws))
+            spans.append(ranges(k, at, ws, ws_bytes))
+        listed = FakeList(entries).launches()
+        overlap = lambda xs, ys: any(a < d and c < b for a, b in xs for c, d in ys)
+        for j in range(len(entries)):
+            assert listed[j].launch >= 0
+            for i in range(j):
+                (wi, ri), (wj, rj) = spans[i], spans[j]
+                if overlap(wi, wj) or overlap(wi, rj) or overlap(ri, wj):
+                    assert listed[i].launch < listed[j].launch, (i, j)
+                    followed += 1
+        by_launch = {}
+        for (k, rec, _, _), l in zip(entries, listed):
+            by_launch.setdefault(l.launch, []).append((k, rec, l))
+        assert sorted(by_launch) == list(range(len(by_launch)))
+        for members in by_launch.values():
+            assert all(l.entries == len(members) for _, _, l in members) and len(members) <= 20
+            assert len({k.shape.dtype for k, _, _ in members}) == 1
+            assert len({(l.listed, l.tile_m, l.tile_n) for _, _, l in members}) == 1
+            if not members[0][2].listed:
+                assert len({(k.cls, k.shape, rec is None) for k, rec, _ in members}) == 1 and len(members) <= 8
+            shared += len(members) > 1
+    assert shared > 100 and followed > 1000
+
+
+def test_entries_that_run_several_times_or_not_at_all():
+    k = wl.Kernel(4, wl.GemmShape(1, 196, 64, 64, 1, wl.BF16))
+    at = lambda i: [(1 << 24) * (5 * i + j + 1) for j in range(5)]
+    fake = FakeList([(k, None, at(i), 0) for i in range(5)])
+    assert [l.launch for l in fake.launches()] == [0] * 5
+    fake.descs[1].use_count = 0
+    fake.descs[3].use_count = 2  # runs by itself, between the windows around it
+    assert [l.launch for l in fake.launches()] == [0, -1, 0, 1, 2]
+    fake.descs[4].bufs[0] = None
+    with pytest.raises(api.TTError):
+        fake.launches()
+
+
+# ---- on the GPU -------------------------------------------------------------------------------------------------------
+def conv(cls, n, c, h, w, k, f, stride, dtype):
+    return wl.Kernel(cls, wl.ConvShape(n, c, h, w, k, f, f, stride, stride, f // 2, f // 2, dtype))
+
+
+def gemm(cls, m, n, k, dtype, batch=1):
+    return wl.Kernel(cls, wl.GemmShape(batch, m, n, k, 1, dtype))
+
+
+SPLIT = dict(tm=64, tn=64, tk=32, wm=32, wn=32, mf=32, split_k=3, stages=2)
+LISTS = {
+    # ragged in M, N and K, rows that are not whole vectors, residuals, strides, a 5x5, one pixel, every activation
+    "bf16": [conv(1, 2, 40, 15, 11, 72, 3, 1, wl.BF16), conv(2, 1, 64, 17, 17, 61, 3, 2, wl.BF16), conv(0, 3, 8, 9, 9, 130, 1, 1, wl.BF16),
+             conv(1, 1, 136, 1, 1, 24, 3, 1, wl.BF16), conv(2, 2, 48, 21, 19, 264, 5, 1, wl.BF16), gemm(4, 100, 88, 456, wl.BF16),
+             gemm(5, 17, 16, 40, wl.BF16), gemm(6, 130, 261, 328, wl.BF16), gemm(7, 65, 48, 400, wl.BF16, 5), gemm(6, 300, 520, 1032, wl.BF16),
+             conv(1, 1, 512, 7, 7, 64, 3, 1, wl.BF16), gemm(4, 40, 40, 2048, wl.BF16)],
+    "f32": [conv(1, 2, 36, 15, 11, 72, 3, 1, wl.F32), conv(2, 1, 64, 17, 17, 61, 3, 2, wl.F32), conv(3, 3, 8, 9, 9, 130, 1, 1, wl.F32),
+            conv(0, 1, 132, 1, 1, 24, 3, 1, wl.F32), gemm(4, 100, 88, 452, wl.F32), gemm(5, 17, 16, 20, wl.F32), gemm(4, 70, 61, 640, wl.F32),
+            conv(1, 1, 512, 7, 7, 64, 3, 1, wl.F32)],
+    # large contractions beside small ones
+    "bf16_large": [conv(1, 8, 128, 28, 28, 128, 3, 1, wl.BF16)] * 3 + [gemm(6, 1024, 768, 768, wl.BF16)] * 2 +
+                  [gemm(4, 520, 3000, 776, wl.BF16), gemm(5, 64, 64, 64, wl.BF16)],
+    "f32_large": [conv(2, 2, 64, 28, 28, 128, 3, 1, wl.F32)] * 4 + [gemm(4, 4100, 136, 48, wl.F32), gemm(5, 300, 1032, 96, wl.F32)],
+    # the 256 x 256 block kernel, ragged, blocks of 128 rows and columns outside
+    "blocks": [gemm(6, 2040, 2040, 1096, wl.BF16)] * 3 + [gemm(5, 1020, 1800, 1096, wl.BF16)] * 2,
+    "conv_blocks": [conv(2, 32, 256, 14, 14, 256, 3, 1, wl.BF16)] * 9,
+    # more entries than a launch takes
+    "many": [gemm(5, 20 + 3 * i, 16 + 8 * (i % 5), 40 + 8 * i, wl.BF16) for i in range(43)],
+}
+
+
+def run_list_against_lone_calls(kernels, recs, without_bias=(), oracle_flops=2e8, check=lambda launches: None):
+    """Every entry of a list against the same kernel run by itself and, where that is quick, against the oracle."""
+    import torch
+    import parity as P
+    from paper_2201_05587_amd import harness
+    inputs = [wl.make_inputs(k, 900 + i) for i, k in enumerate(kernels)]
+    dks = [harness.device_kernel(k, 0, inp, max_split=3) for k, inp in zip(kernels, inputs)]
+    for i in without_bias:
+        tensors = dict(dks[i].tensors)
+        del tensors["bias"]
+        dks[i] = api.DeviceKernel(kernels[i].cls, kernels[i].shape, tensors, 1, "", dks[i].ws.numel())
+    want = []
+    for k, dk, r in zip(kernels, dks, recs):
+        want.append(P.run_gpu(k, dk, r))
+        dk.output().fill_(float("nan"))
+        dk.ws.fill_(255)
+    listed = api.KernelList(dks, recs)
+    launches = listed.launches()
+    check(launches)
+    listed.run()
+    torch.cuda.synchronize()
+    for i, (k, dk, w) in enumerate(zip(kernels, dks, want)):
+        got = harness.output_in_definition_order(k, dk.output()).float().cpu().numpy()
+        P.assert_close(got, w, k.shape.dtype, f"{i} {launches[i].tile_m}x{launches[i].tile_n}")
+        if k.flops() < oracle_flops and i not in without_bias:
+            P.assert_close(got, P.oracle_output(k, inputs[i]), k.shape.dtype, f"{i} oracle")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", list(LISTS))
+@pytest.mark.parametrize("split", [False, True])
+def test_entries_of_different_shapes_in_shared_launches(name, split):
+    kernels = LISTS[name]
+    recs = [None] * len(kernels)
+    for i, k in enumerate(kernels):
+        rec = mfma(k.cls, **SPLIT)
+        if split and i % 2 and api.tt_schedule_apply(rec, k.cls, k.shape).runnable():
+            recs[i] = rec
+    if split and not any(recs):
+        pytest.skip("no entry of this list is as large as the split record's tile")
+
+    def check(launches):
+        assert len({l.launch for l in launches}) < len(kernels)
+        if name.endswith("blocks") and not split:
+            assert all(l.tile_m == 256 and l.tile_n == 256 for l in launches)
+
+    run_list_against_lone_calls(kernels, recs, without_bias=(0,) if split else (), check=check)
+
+
+def lists_by_tile():
+    """The cheapest list of equal entries (ragged in every extent) of a grid of sizes that the rule runs in each of its
+    tiles: (data type, convolution?, tile) -> (kernel, count)."""
+    best = {}
+    for dt in (wl.BF16, wl.F32):
+        for is_conv in (True, False):
+            for m in (49, 300, 1000, 2000, 6300):
+                for n in (24, 136, 264, 520, 1032):
+                    for k in (40, 72, 264, 520, 1160):
+                        for count in (2, 3, 6):
+                            if m * n * k * count > (3e9 if dt == wl.BF16 else 3e8):
+                                continue
+                            if is_conv:
+                                c, hw = max(8, k // 9 // 8 * 8), 7 if m < 300 else 13 if m < 3000 else 29
+                                if c * 9 < 0.7 * k:
+                                    continue
+                                kernel = conv(2, max(1, m // hw // hw), c, hw, hw, n, 3, 1, dt)
+                            else:
+                                kernel = gemm(5, m + 3, n, k, dt)
+                            at = lambda i: [(1 << 34) * (5 * i + j + 1) if j != 3 or is_conv else 0 for j in range(5)]
+                            l = FakeList([(kernel, None, at(i), 0) for i in range(count)]).launches()[0]
+                            key = (dt, is_conv, l.tile_m, l.tile_n, l.tile_k)
+                            if l.listed and (key not in best or best[key][0].flops() * best[key][1] > kernel.flops() * count):
+                                best[key] = (kernel, count)
+    return best
+
+
+@pytest.mark.gpu
+def test_shared_launches_in_every_tile():
+    cases = lists_by_tile()
+    assert len(cases) >= 20, sorted(cases)
+    for key, (kernel, count) in sorted(cases.items()):
+        print(key, kernel.shape, count, flush=True)
+        run_list_against_lone_calls([kernel] * count, [None] * count, oracle_flops=1e9,
+                                    check=lambda ls: [None for l in ls if (l.tile_m, l.tile_n, l.tile_k) == key[2:]] or 1 / 0)
+
+
+@pytest.mark.gpu
+def test_a_list_replayed_in_a_graph():
+    """Shared launches and the second step of split reductions under capture: every replay against the eager pass."""
+    import torch
+    import parity as P
+    from paper_2201_05587_amd import harness
+    kernels = LISTS["f32"]
+    dks = [harness.device_kernel(k, 70 + i, max_split=3) for i, k in enumerate(kernels)]
+    recs = [None] * len(dks)
+    recs[0] = mfma(kernels[0].cls, **SPLIT)
+    listed = api.KernelList(dks, recs)
+    listed.run()
+    torch.cuda.synchronize()
+    want = [dk.output().cpu().numpy() for dk in dks]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        listed.run()
+    for _ in range(3):
+        for dk in dks:
+            dk.output().fill_(float("nan"))
+            dk.ws.fill_(255)
+        graph.replay()
+        torch.cuda.synchronize()
+        for i, (dk, w) in enumerate(zip(dks, want)):
+            np.testing.assert_array_equal(dk.output().cpu().numpy(), w, err_msg=str(i))
+        listed.run()
+        torch.cuda.synchronize()
