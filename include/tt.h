@@ -465,13 +465,14 @@ int tt_schedule_space(int cls, int dtype, int level, tt_schedule *out, int cap);
  * What a launch of `count` equal entries under a record runs on (count = 1: an operator call; tt_run_kernels sends up to
  * TT_MAX_ENTRIES_PER_LAUNCH entries out together); sched NULL = default.  Host only, for inspection and tests.  *kernel:
  * TT_LAUNCH_RECORD, the kernel launched->variant_id (or the sketch) names; TT_LAUNCH_GROUPS, contract_groups_kernel in the
- * same tiles; TT_LAUNCH_BLOCKS, contract_block_kernel in blocks of 256 x 256.  launched: the plan as it is launched, with
+ * same tiles; TT_LAUNCH_BLOCKS, contract_block_kernel in blocks of 256 x 256; TT_LAUNCH_ROWS, conv_rows_kernel in the
+ * same tiles.  launched: the plan as it is launched, with
  * grid, block and lds_bytes of the kernel that runs (per entry; the persistent kernel of seven stages divides its grid
  * among fewer workgroups).  Returns the apply status, TT_ERR_BAD_ARG for a count out of range, or TT_ERR_UNSUPPORTED where
  * the operator would.
  */
 #define TT_MAX_ENTRIES_PER_LAUNCH 8
-enum tt_launch_kernel { TT_LAUNCH_RECORD = 0, TT_LAUNCH_GROUPS = 1, TT_LAUNCH_BLOCKS = 2 };
+enum tt_launch_kernel { TT_LAUNCH_RECORD = 0, TT_LAUNCH_GROUPS = 1, TT_LAUNCH_BLOCKS = 2, TT_LAUNCH_ROWS = 3 };
 int tt_debug_launch(const tt_schedule *sched, int cls, const void *shape, int count, tt_plan *launched, int32_t *kernel);
 
 /*

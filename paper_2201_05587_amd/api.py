@@ -339,7 +339,7 @@ def tt_debug_tile_map(plan):
     return out.cpu().numpy()
 
 
-TT_LAUNCH_RECORD, TT_LAUNCH_GROUPS, TT_LAUNCH_BLOCKS = range(3)
+TT_LAUNCH_RECORD, TT_LAUNCH_GROUPS, TT_LAUNCH_BLOCKS, TT_LAUNCH_ROWS = range(4)
 TT_MAX_ENTRIES_PER_LAUNCH = 8
 
 
@@ -570,4 +570,6 @@ def launched_name(sched, cls, shape, count=1) -> str:
     dtype, family, tm, tn, _, wm, wn, mf = tt_variant_info(plan.variant_id)[:8]
     if kernel == TT_LAUNCH_BLOCKS:
         return f"tt::contract_block_kernel<{family}>"
+    if kernel == TT_LAUNCH_ROWS:
+        return f"tt::conv_rows_kernel<{tm}, {tn}>"
     return f"tt::contract_groups_kernel<{dtype}, {family}, {tm}, {tn}, {wm}, {wn}, {mf}>"

@@ -14,8 +14,11 @@ constexpr int epilogue_bytes(int TM, int TN, int WM, int WN, int MF) { return (T
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF, int AM>
 int kernel_contract(const ContractArgs &args, int count, int grid)
 {
-    if constexpr (FAM == FAM_GEMM_TN || (FAM == FAM_CONV && AM == 16))
+    if constexpr (FAM == FAM_GEMM_TN || (FAM == FAM_CONV && AM == 16)) {
         if (groups_apply<DT, FAM, TM, TN, WM, WN, MF>(args, grid * count, 0)) return TT_LAUNCH_GROUPS;
+    } else if constexpr (FAM == FAM_CONV) {
+        if (rows_shape(args, grid).grid > 0) return TT_LAUNCH_ROWS;
+    }
     return TT_LAUNCH_RECORD;
 }
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF>
@@ -31,6 +34,7 @@ LaunchShape shape_on(int kernel, const ContractArgs &args, int grid, int lds_byt
 {
     using S = GroupShape<DT, TM, TN, WM, WN, MF>;
     if (kernel == TT_LAUNCH_BLOCKS) return blocks_shape(args, FAM);
+    if (kernel == TT_LAUNCH_ROWS) return rows_shape(args, grid);
     if (kernel == TT_LAUNCH_GROUPS) return {TT_LAUNCH_GROUPS, grid, S::THREADS, S::LDS};
     return {TT_LAUNCH_RECORD, grid, (TM / WM) * (TN / WN) * 64, std::max(lds_bytes, epilogue_bytes(TM, TN, WM, WN, MF))};
 }
@@ -51,6 +55,9 @@ int launch_contract(const ContractArgs &args, const PointerSets &sets, int grid,
     if constexpr (FAM == FAM_GEMM_TN || (FAM == FAM_CONV && AM == 16))
         if (kernel_contract<DT, FAM, TM, TN, TK, WM, WN, MF, AM>(args, sets.count, grid) == TT_LAUNCH_GROUPS)
             return launch_groups<DT, FAM, TM, TN, WM, WN, MF>(args, sets, grid, stream);
+    if constexpr (FAM == FAM_CONV && AM != 16)
+        if (kernel_contract<DT, FAM, TM, TN, TK, WM, WN, MF, AM>(args, sets.count, grid) == TT_LAUNCH_ROWS)
+            return launch_conv_rows(args, sets, stream);
     auto kern = contract_kernel<DT, FAM, TM, TN, TK, WM, WN, MF, AM>;
     constexpr int EPI_BYTES = epilogue_bytes(TM, TN, WM, WN, MF);
     if (lds_bytes < EPI_BYTES) lds_bytes = EPI_BYTES;

@@ -493,6 +493,7 @@ public:
         tt_plan p;
         const int kernel = launched_plan(op, 1, &p);
         if (kernel == TT_LAUNCH_BLOCKS) return Key{kernel};
+        if (kernel == TT_LAUNCH_ROWS) return Key{kernel, p.tile_m, p.tile_n, p.eff_vec_c, p.order};
         if (kernel == TT_LAUNCH_GROUPS)
             return Key{kernel, p.tile_m, p.tile_n, p.wave_m, p.wave_n, p.mfma, p.eff_split_k,
                        (int32_t)std::min<int64_t>((int64_t)p.k_iters * p.tile_k, p.K), p.eff_vec_c, p.order};
