@@ -44,7 +44,7 @@ template <int FAM> int launch_block_list(const ContractList &list, int grid, voi
 
 #define TT_TILE(DT_, TM_, TN_, TK_, WM_, WN_, FIXED_, PER_K_, ALONE_)                                                                  \
     {                                                                                                                                  \
-        DT_, TM_, TN_, TK_, FIXED_, PER_K_, ALONE_,                                                                                    \
+        DT_, TM_, TN_, TK_, FIXED_, PER_K_, ALONE_, false,                                                                             \
         {                                                                                                                              \
             launch_tiles<DT_, FAM_CONV, TM_, TN_, TK_, WM_, WN_, 16>, launch_tiles<DT_, FAM_GEMM_TN, TM_, TN_, TK_, WM_, WN_, 16>      \
         }                                                                                                                              \
@@ -52,7 +52,7 @@ template <int FAM> int launch_block_list(const ContractList &list, int grid, voi
 
 #define TT_GROUPS(DT_, TM_, TN_, WM_, WN_, FIXED_, PER_K_, ALONE_)                                                                     \
     {                                                                                                                                  \
-        DT_, TM_, TN_, GroupShape<DT_, TM_, TN_, WM_, WN_, 16>::TKI, FIXED_, PER_K_, ALONE_,                                           \
+        DT_, TM_, TN_, GroupShape<DT_, TM_, TN_, WM_, WN_, 16>::TKI, FIXED_, PER_K_, ALONE_, false,                                    \
         {                                                                                                                              \
             launch_group_list<DT_, FAM_CONV, TM_, TN_, WM_, WN_, 16>, launch_group_list<DT_, FAM_GEMM_TN, TM_, TN_, WM_, WN_, 16>      \
         }                                                                                                                              \
@@ -72,15 +72,16 @@ const ListTile *list_tiles(int *count)
         TT_TILE(TT_BF16, 64, 64, 64, 32, 32, 0.85f, 0.0027f, 0.0050f),
         TT_TILE(TT_BF16, 32, 32, 64, 16, 16, 0.42f, 0.00125f, 0.0042f),
         TT_TILE(TT_F32, 64, 64, 32, 16, 32, 2.0f, 0.0180f, 0.0230f),
-        TT_TILE(TT_F32, 32, 32, 32, 16, 16, 0.55f, 0.0052f, 0.0100f),
+        TT_TILE(TT_F32, 32, 32, 32, 16, 16, 0.55f, 0.0052f, 0.0115f),
         TT_TILE(TT_F32, 16, 32, 16, 16, 32, 0.23f, 0.0036f, 0.0200f),
-        TT_TILE(TT_F32, 16, 16, 16, 16, 16, 0.13f, 0.0022f, 0.0100f),
+        TT_TILE(TT_F32, 16, 16, 16, 16, 16, 0.13f, 0.0022f, 0.0190f),
         // the reduction split inside the workgroup
-        TT_GROUPS(TT_BF16, 64, 64, 32, 32, 1.5f, 0.0030f, 0.0042f),
-        TT_GROUPS(TT_F32, 32, 32, 16, 16, 1.2f, 0.0056f, 0.0065f),
+        TT_GROUPS(TT_BF16, 64, 64, 32, 32, 3.0f, 0.0030f, 0.0042f),
+        TT_GROUPS(TT_F32, 32, 32, 16, 16, 3.2f, 0.0056f, 0.0065f),
         // the 256 x 256 block kernel
-        {TT_BF16, 256, 256, 64, 11.0f, 0.0225f, 0.0185f, {launch_block_list<FAM_CONV>, launch_block_list<FAM_GEMM_TN>}},
+        {TT_BF16, 256, 256, 64, 11.0f, 0.0225f, 0.0185f, true, {launch_block_list<FAM_CONV>, launch_block_list<FAM_GEMM_TN>}},
     };
+    static_assert(sizeof tiles / sizeof tiles[0] <= kMaxListTiles, "");
     *count = (int)(sizeof tiles / sizeof tiles[0]);
     return tiles;
 }

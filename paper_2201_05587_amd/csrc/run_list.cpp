@@ -32,9 +32,34 @@ bool same_knobs(const tt_schedule &x, const tt_schedule &y) { return std::memcmp
 namespace {
 
 struct Range {
-    const char *at, *end;
+    const char *at, *end; // empty where at is null
 };
-inline bool overlap(const Range &x, const Range &y) { return x.at && y.at && x.at < y.end && y.at < x.end; }
+
+// Address ranges, for the question whether another one touches any of them.
+class Ranges {
+public:
+    bool touches(const Range &r) const
+    {
+        if (!r.at || r.at == r.end) return false;
+        const auto it = std::lower_bound(sorted_.begin(), sorted_.end(), r.end, [](const Item &x, const char *end) { return x.at < end; });
+        return it != sorted_.begin() && (it - 1)->reach > r.at; // of those that begin before its end, the furthest end
+    }
+    void add(const Range &r)
+    {
+        if (!r.at || r.at == r.end) return;
+        auto it = std::upper_bound(sorted_.begin(), sorted_.end(), r.at, [](const char *at, const Item &x) { return at < x.at; });
+        const char *reach = it == sorted_.begin() ? r.end : std::max((it - 1)->reach, r.end);
+        it = sorted_.insert(it, {r.at, reach});
+        for (++it; it != sorted_.end() && it->reach < reach; ++it) it->reach = reach;
+    }
+    void clear() { sorted_.clear(); }
+
+private:
+    struct Item {
+        const char *at, *reach; // `reach`: the largest end up to here
+    };
+    std::vector<Item> sorted_; // by `at`
+};
 
 // An entry of a window.
 struct Entry {
@@ -58,18 +83,6 @@ Entry entry_at(int index, int op_index, const PreparedOp &op, const OpPointers &
     e.reads[2] = range(p.bias, op.bias_bytes);
     e.reads[3] = range(p.res, op.out_bytes);
     return e;
-}
-
-// Whether two entries may run at the same time: neither writes what the other reads or writes.
-bool independent(const Entry &p, const Entry &q)
-{
-    for (const Range &w : p.writes)
-        for (const Range &v : q.writes)
-            if (overlap(w, v)) return false;
-    for (int i = 0; i < 2; ++i)
-        for (int j = 0; j < 4; ++j)
-            if (overlap(p.writes[i], q.reads[j]) || overlap(p.reads[j], q.writes[i])) return false;
-    return true;
 }
 
 // Same class, shape and record: one plan.
@@ -108,6 +121,8 @@ bool block_tile_fits(const PreparedOp &op)
            (op.family == FAM_CONV || ((int64_t)pl.M * pl.K < (1ll << 30) && (int64_t)pl.N * pl.K < (1ll << 30)));
 }
 
+constexpr double kUnfit = 1e30; // the cost of a tile that a plan cannot run in
+
 // Tiles of a plan in a tile of the list rule: how many, the split of the reduction, and what one costs a compute unit.
 struct Cut {
     int64_t tiles;
@@ -130,29 +145,59 @@ Cut cut_into(const PreparedOp &op, const ListTile &t)
     return c;
 }
 
-// Estimated time (us) of the launches of a set of contractions when each takes the cheaper of two tiles.  A launch costs
-// 2.5 us; its workgroups, the longest first, are dealt to the CUs, so its end is ragged by the shortest of them; nothing is
-// faster than the longest alone, or than memory.
-double estimate(const std::vector<const PreparedOp *> &ops, const std::vector<std::vector<Cut>> &cuts, int t0, int t1, std::vector<int> *chosen)
+// A plan of a window's contractions, how many entries have it, and what their tiles cost in every tile of the rule.
+struct Kind {
+    const PreparedOp *op;
+    int count;
+    double bytes; // of all its entries
+    struct {
+        double all_us, us, alone_us; // of all its entries' tiles on one CU; of one; of one with the CU to itself
+    } in[kMaxListTiles];
+};
+
+// Estimated time (us) of the launches of a set of contractions when each takes the cheapest of some tiles (-1: none).  A
+// launch costs 2.5 us; its workgroups, the longest first, are dealt to the CUs, so its end is ragged by the shortest of them;
+// nothing is faster than the longest alone, or than memory.
+constexpr int kTilesAtOnce = 3;
+double estimate(const std::vector<Kind> &kinds, const int (&tiles)[kTilesAtOnce], int *chosen)
 {
-    double sum[2] = {}, least[2] = {1e30, 1e30}, longest[2] = {}, bytes[2] = {};
-    for (size_t i = 0; i < ops.size(); ++i) {
-        const Cut &x = cuts[i][t0], &y = cuts[i][t1];
-        const double cost[2] = {x.tiles * x.us, y.tiles * y.us};
-        const int pick = cost[1] < cost[0];
-        if (cost[pick] >= 1e30) return 1e30;
-        const Cut &c = pick ? y : x;
-        sum[pick] += cost[pick];
+    double sum[kTilesAtOnce] = {}, longest[kTilesAtOnce] = {}, bytes[kTilesAtOnce] = {}, least[kTilesAtOnce] = {1e30, 1e30, 1e30};
+    for (size_t i = 0; i < kinds.size(); ++i) {
+        const Kind &k = kinds[i];
+        int pick = -1;
+        for (int h = 0; h < kTilesAtOnce; ++h)
+            if (tiles[h] >= 0 && (pick < 0 || k.in[tiles[h]].all_us < k.in[tiles[pick]].all_us)) pick = h;
+        if (pick < 0 || k.in[tiles[pick]].us >= kUnfit) return kUnfit;
+        const auto &c = k.in[tiles[pick]];
+        sum[pick] += c.all_us;
         least[pick] = std::min(least[pick], c.us);
         longest[pick] = std::max(longest[pick], c.alone_us);
-        const PreparedOp &op = *ops[i];
-        bytes[pick] += (double)op.a_bytes + op.b_bytes + op.out_bytes * (op.cls == TT_CONV2D_BIAS_ADD_RELU ? 2 : 1);
-        if (chosen) (*chosen)[i] = pick ? t1 : t0;
+        bytes[pick] += k.bytes;
+        if (chosen) chosen[i] = tiles[pick];
     }
     double us = 0;
-    for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < kTilesAtOnce; ++h)
         if (sum[h] > 0) us += 2.5 + std::max({std::ceil(sum[h] / compute_units() / least[h]) * least[h], longest[h], bytes[h] / 5.0e6});
     return us;
+}
+
+// The tiles that suit a set of contractions: the best pair of all, and a third beside it if that helps.
+void best_tiles(const std::vector<Kind> &kinds, const ListTile *tiles, int n_tiles, int dt, int (&best)[kTilesAtOnce])
+{
+    double best_us = kUnfit;
+    const auto try_set = [&](int x, int y, int z) {
+        const int set[kTilesAtOnce] = {x, y, z};
+        const double us = estimate(kinds, set, nullptr);
+        if (us < best_us) best_us = us, std::copy(set, set + kTilesAtOnce, best);
+    };
+    for (int x = 0; x < n_tiles; ++x)
+        if (tiles[x].dtype == dt) try_set(x, -1, -1);
+    for (int x = 0; x < n_tiles; ++x)
+        for (int y = x + 1; y < n_tiles; ++y)
+            if (tiles[x].dtype == dt && tiles[y].dtype == dt) try_set(x, y, -1);
+    const int x = best[0], y = best[1];
+    for (int z = 0; z < n_tiles && y >= 0; ++z)
+        if (tiles[z].dtype == dt && z != x && z != y) try_set(x, y, z);
 }
 
 ListEntry list_entry(const PreparedOp &op, const OpPointers &p, const ListTile &t, const Cut &c)
@@ -177,7 +222,8 @@ ListEntry list_entry(const PreparedOp &op, const OpPointers &p, const ListTile &
     return e;
 }
 
-// A launch of a window: entries of one plan on pointer sets (tile -1), or listed contractions in a tile of the list rule.
+// A launch of a window: entries of one plan on pointer sets, or listed contractions in a tile of the list rule (`tile`).
+constexpr int kOnePlan = -1;
 struct Launch {
     int tile, family;
     std::vector<int> entries; // of the window
@@ -186,16 +232,24 @@ struct Launch {
 class Window {
 public:
     explicit Window(std::vector<PreparedOp> &ops) : ops_(ops) {}
+    // Whether an entry may run at the same time as all others: neither writes what the other reads or writes.
     bool admits(const Entry &e) const
     {
-        for (const Entry &f : entries_)
-            if (!independent(e, f)) return false;
+        for (const Range &w : e.writes)
+            if (written_.touches(w) || read_.touches(w)) return false;
+        for (const Range &r : e.reads)
+            if (written_.touches(r)) return false;
         return true;
     }
-    void add(const Entry &e) { entries_.push_back(e); }
+    void add(const Entry &e)
+    {
+        for (const Range &w : e.writes) written_.add(w);
+        for (const Range &r : e.reads) read_.add(r);
+        entries_.push_back(e);
+    }
     bool empty() const { return entries_.empty(); }
     const std::vector<Entry> &entries() const { return entries_; }
-    void clear() { entries_.clear(); }
+    void clear() { entries_.clear(), written_.clear(), read_.clear(); }
 
     std::vector<Launch> launches() const
     {
@@ -223,7 +277,7 @@ public:
         std::vector<Launch> plain;
         for (int i = 0; i < n; ++i) {
             if (done[i]) continue;
-            Launch l{-1, 0, {i}};
+            Launch l{kOnePlan, 0, {i}};
             for (int j = i + 1; j < n && (int)l.entries.size() < kMaxSets; ++j)
                 if (!done[j] && entries_[j].op == entries_[i].op && (entries_[j].p.bias == nullptr) == (entries_[i].p.bias == nullptr)) {
                     l.entries.push_back(j);
@@ -237,7 +291,7 @@ public:
 
     int run(const Launch &l, void *stream) const
     {
-        if (l.tile < 0) {
+        if (l.tile == kOnePlan) {
             OpPointers calls[kMaxSets];
             for (size_t i = 0; i < l.entries.size(); ++i) calls[i] = entries_[l.entries[i]].p;
             return launch_op(ops_[entries_[l.entries[0]].op], calls, (int)l.entries.size(), stream);
@@ -295,47 +349,51 @@ private:
     {
         int n_tiles = 0;
         const ListTile *tiles = list_tiles(&n_tiles);
-        std::vector<const PreparedOp *> ops;
-        std::vector<std::vector<Cut>> cuts;
-        for (int i : members) {
-            const PreparedOp &op = ops_[entries_[i].op];
-            ops.push_back(&op);
-            std::vector<Cut> c;
+        std::vector<Kind> kinds;
+        std::vector<int> kind_of(members.size());
+        for (size_t m = 0; m < members.size(); ++m) {
+            const PreparedOp &op = ops_[entries_[members[m]].op];
+            size_t at = 0;
+            while (at < kinds.size() && kinds[at].op != &op) ++at;
+            kind_of[m] = (int)at;
+            if (at == kinds.size()) {
+                kinds.emplace_back();
+                kinds[at].op = &op, kinds[at].count = 0;
+            }
+            ++kinds[at].count;
+        }
+        for (Kind &k : kinds) {
+            k.bytes = k.count * ((double)k.op->a_bytes + k.op->b_bytes + k.op->out_bytes * (k.op->cls == TT_CONV2D_BIAS_ADD_RELU ? 2.0 : 1.0));
             for (int t = 0; t < n_tiles; ++t) {
-                c.push_back(cut_into(op, tiles[t]));
-                if (tiles[t].dtype != dt || (tiles[t].tile_m == 256 && !block_tile_fits(op))) c.back().us = 1e30;
-            }
-            cuts.push_back(std::move(c));
-        }
-        int b0 = -1, b1 = -1;
-        double best = 1e30;
-        for (int t0 = 0; t0 < n_tiles; ++t0) {
-            if (tiles[t0].dtype != dt) continue;
-            for (int t1 = t0; t1 < n_tiles; ++t1) {
-                if (tiles[t1].dtype != dt) continue;
-                const double us = estimate(ops, cuts, t0, t1, nullptr);
-                if (us < best) best = us, b0 = t0, b1 = t1;
+                if (tiles[t].dtype != dt || (tiles[t].blocks && !block_tile_fits(*k.op))) {
+                    k.in[t] = {kUnfit, kUnfit, kUnfit};
+                    continue;
+                }
+                const Cut c = cut_into(*k.op, tiles[t]);
+                k.in[t] = {c.tiles * c.us * k.count, c.us, c.alone_us};
             }
         }
-        std::vector<int> chosen(members.size());
-        estimate(ops, cuts, b0, b1, &chosen);
-        for (int t : {b0, b1}) {
+        int best[kTilesAtOnce] = {-1, -1, -1};
+        best_tiles(kinds, tiles, n_tiles, dt, best);
+        std::vector<int> chosen(kinds.size());
+        estimate(kinds, best, chosen.data());
+        for (int t : best) {
             std::vector<int> at;
-            for (size_t i = 0; i < members.size(); ++i)
-                if (chosen[i] == t) at.push_back((int)i);
+            for (size_t m = 0; m < members.size(); ++m)
+                if (t >= 0 && chosen[kind_of[m]] == t) at.push_back((int)m);
             // the longest first, so that the end of the launch is not one long tile
-            std::stable_sort(at.begin(), at.end(), [&](int x, int y) { return cuts[x][t].us > cuts[y][t].us; });
+            std::stable_sort(at.begin(), at.end(), [&](int x, int y) { return kinds[kind_of[x]].in[t].us > kinds[kind_of[y]].in[t].us; });
             for (size_t i = 0; i < at.size(); i += kMaxListed) {
                 Launch l{t, family, {}};
                 for (size_t j = i; j < std::min(at.size(), i + kMaxListed); ++j) l.entries.push_back(members[at[j]]);
                 out->push_back(std::move(l));
             }
-            if (b0 == b1) break;
         }
     }
 
     std::vector<PreparedOp> &ops_;
     std::vector<Entry> entries_;
+    Ranges written_, read_;
 };
 
 int send(Window &w, void *stream)
@@ -356,7 +414,8 @@ template <typename Emit>
 int walk(const tt_kernel_desc *kernels, const tt_schedule *const *scheds, int nk, std::vector<PreparedOp> &ops, Emit &&emit)
 {
     Window w(ops);
-    int last = -1; // the entry whose plan is ops.back()
+    std::vector<int> first; // of every plan, the entry it was laid out for
+    int last = 0;           // the plan of the entry before
     for (int k = 0; k < nk; ++k) {
         const tt_kernel_desc &d = kernels[k];
         const tt_schedule *rec = scheds ? scheds[k] : nullptr;
@@ -369,18 +428,22 @@ int walk(const tt_kernel_desc *kernels, const tt_schedule *const *scheds, int nk
         if (d.cls < 0 || d.cls >= TT_NUM_CLASSES) return fail(TT_ERR_BAD_ARG);
         const OpPointers p = pointers_of(d, 0);
         if (const int rc = check_op_pointers(d.cls, p); rc != TT_OK) return fail(rc);
-        if (last < 0 || !same_plan(kernels[last], scheds ? scheds[last] : nullptr, d, rec)) {
-            ops.emplace_back();
-            if (const int rc = prepare_op(rec, d.cls, d.shape, &ops.back()); rc != TT_OK) {
-                ops.pop_back();
-                return fail(rc);
+        const auto planned = [&](int plan) { return same_plan(kernels[first[plan]], scheds ? scheds[first[plan]] : nullptr, d, rec); };
+        if (last >= (int)first.size() || !planned(last)) {
+            for (last = 0; last < (int)first.size() && !planned(last);) ++last;
+            if (last == (int)first.size()) {
+                ops.emplace_back();
+                if (const int rc = prepare_op(rec, d.cls, d.shape, &ops.back()); rc != TT_OK) {
+                    ops.pop_back();
+                    return fail(rc);
+                }
+                first.push_back(k);
             }
-            last = k;
         }
-        const PreparedOp &op = ops.back();
+        const PreparedOp &op = ops[last];
         if (!workspace_fits(op, p)) return fail(TT_ERR_WORKSPACE);
         if (refused(op)) return fail(TT_ERR_UNSUPPORTED);
-        const Entry e = entry_at(k, (int)ops.size() - 1, op, p);
+        const Entry e = entry_at(k, last, op, p);
         const bool again = d.use_count != 1;
         if (again || w.entries().size() >= kMaxWindow || !w.admits(e))
             if (const int rc = emit(w, 1); rc != TT_OK) return rc;
@@ -439,7 +502,7 @@ extern "C" int tt_debug_list(const tt_kernel_desc *kernels, const tt_schedule *c
                 for (int i : l.entries) {
                     const Entry &e = w.entries()[i];
                     const tt_plan &pl = ops[e.op].launch;
-                    out[e.index] = {launch, l.tile >= 0, l.tile >= 0 ? table[l.tile].tile_m : pl.tile_m,
+                    out[e.index] = {launch, l.tile != kOnePlan, l.tile >= 0 ? table[l.tile].tile_m : pl.tile_m,
                                     l.tile >= 0 ? table[l.tile].tile_n : pl.tile_n, l.tile >= 0 ? table[l.tile].tile_k : pl.tile_k,
                                     (int32_t)l.entries.size()};
                 }

@@ -217,7 +217,8 @@ struct ListEntry {
     int16_t vec_c, act;
 };
 constexpr int kMaxListed = 20;  // entries of a launch: the arguments stay within 4 KB
-constexpr int kListOrder = 1;   // raster of every entry: columns fastest
+constexpr int kMaxListTiles = 16; // tiles of the list rule
+constexpr int kListOrder = 4;   // raster of every entry: columns fastest, a contiguous run of tiles per XCD
 struct ContractList {
     int32_t first[kMaxListed]; // first workgroup of every entry, a multiple of the number of XCDs; past the last: INT32_MAX
     ListEntry e[kMaxListed];
@@ -226,6 +227,7 @@ static_assert(sizeof(ContractList) <= 4096, "");
 struct ListTile {
     int32_t dtype, tile_m, tile_n, tile_k;
     float fixed_us, per_k_us, alone_per_k_us; // see list_tiles
+    bool blocks;                              // the block kernel, which asks for more (block_tile_fits)
     int (*launch[2])(const ContractList &list, int grid, void *stream); // FAM_CONV, FAM_GEMM_TN
 };
 const ListTile *list_tiles(int *count);
