@@ -222,10 +222,11 @@ ListEntry list_entry(const PreparedOp &op, const OpPointers &p, const ListTile &
     return e;
 }
 
-// A launch of a window: entries of one plan on pointer sets, or listed contractions in a tile of the list rule (`tile`).
-constexpr int kOnePlan = -1;
+// A launch of a window: entries of one plan on pointer sets, listed contractions in a tile of the list rule (`tile`), or listed
+// depthwise kernels of one stride.
+constexpr int kOnePlan = -1, kDepthwise = -2;
 struct Launch {
-    int tile, family;
+    int tile, family; // (depthwise: the stride)
     std::vector<int> entries; // of the window
 };
 
@@ -273,6 +274,20 @@ public:
                 for (int i : members) done[i] = 1;
                 list(members, dt, family, &out);
             }
+        for (int stride : {1, 2}) {
+            Launch l{kDepthwise, stride, {}};
+            DwListEntry e;
+            for (int i = 0; i < n; ++i) {
+                const PreparedOp &op = ops_[entries_[i].op];
+                if (op.cls == TT_DWCONV_BIAS_RELU6 && op.d.stride_h == stride && dw_list_entry(op.d, &e)) l.entries.push_back(i);
+            }
+            if (l.entries.size() < 2) continue;
+            // the largest first
+            std::stable_sort(l.entries.begin(), l.entries.end(), [&](int x, int y) { return ops_[entries_[x].op].out_bytes > ops_[entries_[y].op].out_bytes; });
+            for (int i : l.entries) done[i] = 1;
+            for (size_t i = 0; i < l.entries.size(); i += kMaxDwListed)
+                out.push_back({kDepthwise, stride, {l.entries.begin() + i, l.entries.begin() + std::min(l.entries.size(), i + kMaxDwListed)}});
+        }
         // the rest: entries of one plan, all with a bias or all without, share a launch
         std::vector<Launch> plain;
         for (int i = 0; i < n; ++i) {
@@ -291,6 +306,17 @@ public:
 
     int run(const Launch &l, void *stream) const
     {
+        if (l.tile == kDepthwise) {
+            DwList list;
+            std::memset(&list, 0, sizeof list);
+            for (size_t i = 0; i < l.entries.size(); ++i) {
+                const Entry &e = entries_[l.entries[i]];
+                (void)dw_list_entry(ops_[e.op].d, &list.e[i]);
+                list.e[i].x = static_cast<const float *>(e.p.a), list.e[i].w = static_cast<const float *>(e.p.b);
+                list.e[i].bias = static_cast<const float *>(e.p.bias), list.e[i].y = static_cast<float *>(e.p.out);
+            }
+            return launch_dw_list(list, (int)l.entries.size(), l.family, stream);
+        }
         if (l.tile == kOnePlan) {
             OpPointers calls[kMaxSets];
             for (size_t i = 0; i < l.entries.size(); ++i) calls[i] = entries_[l.entries[i]].p;

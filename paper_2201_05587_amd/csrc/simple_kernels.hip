@@ -385,6 +385,65 @@ __global__ void __launch_bounds__(MAXT) dwconv3x3_rows_kernel(const DwArgs args,
     }
 }
 
+// ---- depthwise 3x3 entries of different shapes in one launch -------------------------------------------------------
+// Bound by memory.  A thread forms WM x WN outputs of four channels and reads every input pixel of its window once, all of
+// them before the first product: (WM + 2) (WN + 2) / (WM WN) reads an output at unit stride, 3 for 4 x 2, where the record's
+// 1 x 2 of the network's layers make 6 that miss the first cache.  The sums run in the order of the other kernels.
+template <int STR> struct DwListShape {
+    static constexpr int WM = STR == 1 ? 4 : 2, WN = 2, ROWS = (WM - 1) * STR + 3, COLS = (WN - 1) * STR + 3;
+};
+template <int STR> __global__ void __launch_bounds__(256) dwconv3x3_list_kernel(const DwList list)
+{
+    using S = DwListShape<STR>;
+    constexpr int WM = S::WM, WN = S::WN, ROWS = S::ROWS, COLS = S::COLS;
+    int at = 0;
+#pragma unroll
+    for (int i = 1; i < kMaxDwListed; ++i) at += (int)blockIdx.x >= list.e[i].first;
+    const DwListEntry &g = list.e[at];
+    // every XCD gets a contiguous run of the entry's workgroups: neighbouring windows share rows in its L2
+    const int wg = (int)blockIdx.x - g.first, wgs = (g.threads + 255) / 256, per = wgs / kXcds, rem = wgs % kXcds, xcd = wg % kXcds;
+    if (wg >= wgs) return;
+    const int t = (xcd * per + min(xcd, rem) + wg / kXcds) * 256 + (int)threadIdx.x;
+    if (t >= g.threads) return;
+    const int lanes = g.C / 4, columns = (g.Wo + WN - 1) / WN, strips = (g.Ho + WM - 1) / WM;
+    const int pix = (int)fast_div((uint32_t)t, g.div_c), ch = (t - pix * lanes) * 4;
+    const int row = (int)fast_div((uint32_t)pix, g.div_cols), q0 = (pix - row * columns) * WN;
+    const int img = (int)fast_div((uint32_t)row, g.div_rows), p0 = (row - img * strips) * WM;
+
+    const __amdgpu_buffer_rsrc_t xr = make_rsrc(g.x, g.x_bytes);
+    f32x4 in[ROWS][COLS], wgt[9];
+    const int ih0 = p0 * STR - g.pad_h, iw0 = q0 * STR - g.pad_w;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+        for (int c = 0; c < COLS; ++c) {
+            const int ih = ih0 + r, iw = iw0 + c;
+            const bool ok = ih >= 0 && ih < g.H && iw >= 0 && iw < g.W;
+            in[r][c] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, ok ? (uint32_t)(((img * g.H + ih) * g.W + iw) * g.C + ch) * 4u : kOutOfRange, 0, 0));
+        }
+#pragma unroll
+    for (int i = 0; i < 9; ++i) wgt[i] = *reinterpret_cast<const f32x4 *>(g.w + i * g.C + ch);
+    f32x4 bias = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (g.bias) bias = *reinterpret_cast<const f32x4 *>(g.bias + ch);
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j) {
+            f32x4 out = bias;
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+#pragma unroll
+                for (int s = 0; s < 3; ++s)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) out[v] = fmaf(in[i * STR + r][j * STR + s][v], wgt[r * 3 + s][v], out[v]);
+            const int p = p0 + i, q = q0 + j;
+            if (p >= g.Ho || q >= g.Wo) continue;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) out[v] = fminf(fmaxf(out[v], 0.0f), 6.0f);
+            __builtin_nontemporal_store(out, reinterpret_cast<f32x4 *>(g.y + ((int64_t)(img * g.Ho + p) * g.Wo + q) * g.C + ch)); // streamed
+        }
+}
+
 __global__ void __launch_bounds__(256) dw_direct_kernel(const DwArgs args, const PointerSets sets)
 {
     const DwArgs g = with_set(args, sets, blockIdx.y);
@@ -598,6 +657,30 @@ int launch_dwconv(const DwArgs &a, const PointerSets &sets, const tt_plan &plan,
     TT_DW_CASE(7, 1) TT_DW_CASE(7, 2) TT_DW_CASE(7, 4) TT_DW_CASE(7, 7)
 #undef TT_DW_CASE
     return TT_ERR_UNSUPPORTED;
+}
+
+bool dw_list_entry(const DwArgs &g, DwListEntry *e)
+{
+    if (g.C % 4 != 0 || g.stride_h != g.stride_w || (g.stride_h != 1 && g.stride_h != 2) || g.x_bytes == 0) return false;
+    const int wm = g.stride_h == 1 ? DwListShape<1>::WM : DwListShape<2>::WM, wn = g.stride_h == 1 ? DwListShape<1>::WN : DwListShape<2>::WN;
+    const int64_t columns = (g.Wo + wn - 1) / wn, strips = (g.Ho + wm - 1) / wm, threads = g.planes / 4 * columns * strips;
+    if (threads >= 1ll << 30) return false;
+    e->threads = (int32_t)threads;
+    e->C = g.C, e->H = g.H, e->W = g.W, e->Ho = g.Ho, e->Wo = g.Wo, e->pad_h = g.pad_h, e->pad_w = g.pad_w, e->x_bytes = g.x_bytes;
+    e->div_c = make_fastdiv((uint32_t)(g.C / 4)), e->div_cols = make_fastdiv((uint32_t)columns), e->div_rows = make_fastdiv((uint32_t)strips);
+    return true;
+}
+
+int launch_dw_list(DwList &list, int count, int stride, void *stream)
+{
+    int grid = 0;
+    for (int i = 0; i < kMaxDwListed; ++i) {
+        list.e[i].first = i < count ? grid : INT32_MAX;
+        if (i < count) grid += ((list.e[i].threads + 255) / 256 + kXcds - 1) / kXcds * kXcds;
+    }
+    auto kern = stride == 1 ? dwconv3x3_list_kernel<1> : dwconv3x3_list_kernel<2>;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, static_cast<hipStream_t>(stream), list);
+    return launched();
 }
 
 int launch_dw_direct(const DwArgs &a, const PointerSets &sets, int grid, void *stream)

@@ -259,6 +259,24 @@ struct DwArgs {
     uint32_t x_bytes;  // size of the input tensor when it is below 2 GiB, else 0
 };
 
+// Depthwise entries of different shapes in one launch (simple_kernels.hip): strides of one size, C a multiple of four.
+struct DwListEntry {
+    const float *x, *w, *bias; // bias may be null
+    float *y;
+    int32_t first;             // first workgroup, a multiple of the number of XCDs; past the last entry: INT32_MAX
+    int32_t threads, C, H, W, Ho, Wo, pad_h, pad_w;
+    uint32_t x_bytes;
+    FastDiv div_c, div_cols, div_rows; // by the threads along C, the columns and the rows of a plane
+};
+constexpr int kMaxDwListed = 36;
+struct DwList {
+    DwListEntry e[kMaxDwListed];
+};
+static_assert(sizeof(DwList) <= 4096, "");
+// Fills in the part of an entry that the launch decides on; false: the entry is not one for a list.
+bool dw_list_entry(const DwArgs &g, DwListEntry *e);
+int launch_dw_list(DwList &list, int count, int stride, void *stream);
+
 TT_HD ContractArgs with_set(ContractArgs g, const PointerSets &sets, uint32_t set)
 {
     if (set == 0) return g;

@@ -140,6 +140,11 @@ LISTS = {
     # the 256 x 256 block kernel, ragged, blocks of 128 rows and columns outside
     "blocks": [gemm(6, 2040, 2040, 1096, wl.BF16)] * 3 + [gemm(5, 1020, 1800, 1096, wl.BF16)] * 2,
     "conv_blocks": [conv(2, 32, 256, 14, 14, 256, 3, 1, wl.BF16)] * 9,
+    # depthwise: strides, windows that end outside, one pixel, padding of none and two, channels that are not whole fours
+    "depthwise": [wl.Kernel(8, wl.ConvShape(n, c, h, w, c, 3, 3, st, st, pad, pad)) for n, c, h, w, st, pad in
+                  ((2, 32, 28, 28, 1, 1), (1, 96, 15, 13, 1, 1), (3, 4, 9, 1, 1, 1), (1, 960, 7, 7, 1, 1), (2, 20, 6, 5, 1, 0), (1, 8, 3, 3, 1, 2),
+                   (2, 24, 28, 28, 2, 1), (1, 144, 57, 31, 2, 1), (5, 16, 4, 4, 2, 0), (1, 12, 1, 1, 2, 1), (2, 30, 9, 9, 1, 1), (1, 7, 10, 12, 2, 1))] +
+                 [wl.Kernel(8, wl.ConvShape(1, 16, 17, 17, 16, 3, 3, 1, 1, 1, 1))] * 40,
     # more entries than a launch takes
     "many": [gemm(5, 20 + 3 * i, 16 + 8 * (i % 5), 40 + 8 * i, wl.BF16) for i in range(43)],
 }
@@ -190,6 +195,8 @@ def test_entries_of_different_shapes_in_shared_launches(name, split):
         assert len({l.launch for l in launches}) < len(kernels)
         if name.endswith("blocks") and not split:
             assert all(l.tile_m == 256 and l.tile_n == 256 for l in launches)
+        if name == "depthwise":
+            assert [l.listed for l in launches[:12]] == [1] * 10 + [0] * 2 and len({l.launch for l in launches}) == 5
 
     run_list_against_lone_calls(kernels, recs, without_bias=(0,) if split else (), check=check)
 
