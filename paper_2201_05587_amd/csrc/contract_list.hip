@@ -5,6 +5,7 @@
 
 #include "contract_launch.hip.h"
 #include "contract_list.hip.h"
+#include "contract_thin.hip.h"
 
 namespace tt {
 
@@ -87,5 +88,39 @@ const ListTile *list_tiles(int *count)
 }
 #undef TT_TILE
 #undef TT_GROUPS
+
+// Columns: as many as 48 KB of weights hold (three workgroups on a CU), in equal chunks.  Rows: eight turns of the four waves,
+// or what gives the launch some two thousand workgroups.
+void thin_layout(ThinEntry *e)
+{
+    const int pieces = (e->K + 15) / 16, blocks = (e->N + 15) / 16, most = std::max(1, 48 * 1024 / (pieces * 1024));
+    e->chunks = (blocks + most - 1) / most;
+    e->columns = (blocks + e->chunks - 1) / e->chunks * 16;
+    e->chunks = (e->N + e->columns - 1) / e->columns;
+    e->rows = 512;
+    while (e->rows > 64 && (int64_t)e->chunks * ((e->M + e->rows - 1) / e->rows) < 384) e->rows /= 2;
+}
+
+int launch_thin_list(ThinList &list, int count, int pieces, void *stream)
+{
+    int64_t grid = 0;
+    int lds = 0;
+    for (int i = 0; i < kMaxThin; ++i) {
+        list.first[i] = i < count ? (int32_t)grid : INT32_MAX;
+        if (i >= count) continue;
+        const ThinEntry &e = list.e[i];
+        grid += (int64_t)e.chunks * ((e.M + e.rows - 1) / e.rows);
+        lds = std::max(lds, e.columns / 16 * ((e.K + 15) / 16) * 1024 + e.columns * 4);
+    }
+    auto kern = contract_thin_list_kernel<kThinPieces[0]>;
+    if (pieces == kThinPieces[1]) kern = contract_thin_list_kernel<kThinPieces[1]>;
+    if (pieces == kThinPieces[2]) kern = contract_thin_list_kernel<kThinPieces[2]>;
+    static DynamicLdsLimit limits[3];
+    DynamicLdsLimit &limit = limits[pieces == kThinPieces[0] ? 0 : pieces == kThinPieces[1] ? 1 : 2];
+    if (const int rc = limit.raise_to(reinterpret_cast<const void *>(kern), lds); rc != TT_OK) return rc;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds, static_cast<hipStream_t>(stream), list);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? TT_OK : note_hip_error((int)e, "contract_thin_list_kernel launch");
+}
 
 } // namespace tt

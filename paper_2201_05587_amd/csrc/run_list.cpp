@@ -113,6 +113,23 @@ bool listable(const PreparedOp &op)
     return (int64_t)pl.batch * pl.M * pl.N < (1ll << 31);
 }
 
+// Whether a listed contraction is a stream for the thin kernel, and the instance that holds its reduction (0: none): single
+// precision, rows of whole fours, no split of the reduction, and rows enough that a workgroup's weights, which it loads into
+// LDS first, are less than half of what it reads and writes.
+int thin_pieces(const PreparedOp &op)
+{
+    const tt_plan &pl = op.launch;
+    if (op.g.dtype != TT_F32 || op.family != FAM_GEMM_TN || pl.eff_split_k != 1 || pl.batch != 1 || op.g.act == ACT_GELU) return 0;
+    if (pl.N % 4 != 0 || pl.K % 4 != 0) return 0;
+    ThinEntry e;
+    e.M = pl.M, e.N = pl.N, e.K = pl.K;
+    thin_layout(&e);
+    if ((int64_t)std::min(e.rows, e.M) * (e.K + e.columns) < 2ll * e.K * e.columns) return 0;
+    for (int p : kThinPieces)
+        if (pl.K <= p * 16) return p;
+    return 0;
+}
+
 // What the block kernel asks for beyond that.
 bool block_tile_fits(const PreparedOp &op)
 {
@@ -222,11 +239,11 @@ ListEntry list_entry(const PreparedOp &op, const OpPointers &p, const ListTile &
     return e;
 }
 
-// A launch of a window: entries of one plan on pointer sets, listed contractions in a tile of the list rule (`tile`), or listed
-// depthwise kernels of one stride.
-constexpr int kOnePlan = -1, kDepthwise = -2;
+// A launch of a window: entries of one plan on pointer sets, listed contractions in a tile of the list rule (`tile`),
+// listed depthwise kernels of one stride, or listed streams of one instance.
+constexpr int kOnePlan = -1, kDepthwise = -2, kThin = -3;
 struct Launch {
-    int tile, family; // (depthwise: the stride)
+    int tile, family; // (depthwise: the stride; streams: the pieces of the reduction)
     std::vector<int> entries; // of the window
 };
 
@@ -267,6 +284,8 @@ public:
                     if (op.cls != TT_DWCONV_BIAS_RELU6 && op.g.dtype == dt && op.family == family && listable(op)) members.push_back(i);
                 }
                 if (members.size() < 2) continue;
+                if (dt == TT_F32 && family == FAM_GEMM_TN) stream(&members, &done, &out);
+                if (members.empty()) continue;
                 // (splits of one plan alone: nothing to share that their own launches would not)
                 const PreparedOp &first = ops_[entries_[members[0]].op];
                 const bool one_plan = std::all_of(members.begin(), members.end(), [&](int i) { return entries_[i].op == entries_[members[0]].op; });
@@ -306,6 +325,20 @@ public:
 
     int run(const Launch &l, void *stream) const
     {
+        if (l.tile == kThin) {
+            ThinList list;
+            std::memset(&list, 0, sizeof list);
+            for (size_t i = 0; i < l.entries.size(); ++i) {
+                const Entry &e = entries_[l.entries[i]];
+                const PreparedOp &op = ops_[e.op];
+                ThinEntry &t = list.e[i];
+                t.a = static_cast<const float *>(e.p.a), t.b = static_cast<const float *>(e.p.b), t.bias = static_cast<const float *>(e.p.bias);
+                t.res = static_cast<const float *>(e.p.res), t.out = static_cast<float *>(e.p.out);
+                t.M = op.launch.M, t.N = op.launch.N, t.K = op.launch.K, t.act = op.g.act;
+                thin_layout(&t);
+            }
+            return launch_thin_list(list, (int)l.entries.size(), l.family, stream);
+        }
         if (l.tile == kDepthwise) {
             DwList list;
             std::memset(&list, 0, sizeof list);
@@ -371,6 +404,19 @@ public:
     }
 
 private:
+    // Takes the streams out of the members.
+    void stream(std::vector<int> *members, std::vector<char> *done, std::vector<Launch> *out) const
+    {
+        for (int pieces : kThinPieces) {
+            Launch l{kThin, pieces, {}};
+            for (int i : *members)
+                if (thin_pieces(ops_[entries_[i].op]) == pieces) l.entries.push_back(i), (*done)[i] = 1;
+            std::stable_sort(l.entries.begin(), l.entries.end(), [&](int x, int y) { return ops_[entries_[x].op].out_bytes > ops_[entries_[y].op].out_bytes; });
+            for (size_t i = 0; i < l.entries.size(); i += kMaxThin)
+                out->push_back({kThin, pieces, {l.entries.begin() + i, l.entries.begin() + std::min(l.entries.size(), i + kMaxThin)}});
+        }
+        members->erase(std::remove_if(members->begin(), members->end(), [&](int i) { return (*done)[i]; }), members->end());
+    }
     void list(const std::vector<int> &members, int dt, int family, std::vector<Launch> *out) const
     {
         int n_tiles = 0;

@@ -232,6 +232,25 @@ struct ListTile {
 };
 const ListTile *list_tiles(int *count);
 
+// Single-precision contractions with a short reduction (contract_thin.hip.h): what the kernel needs of an entry.
+struct ThinEntry {
+    const float *a, *b, *bias, *res; // bias, res: null where the entry has none
+    float *out;
+    int32_t M, N, K;
+    int32_t rows, columns, chunks; // of a workgroup; workgroups side by side
+    int32_t act;
+};
+constexpr int kMaxThin = 48;
+struct ThinList {
+    int32_t first[kMaxThin]; // first workgroup; past the last entry: INT32_MAX
+    ThinEntry e[kMaxThin];
+};
+static_assert(sizeof(ThinList) <= 4096, "");
+constexpr int kThinPieces[] = {2, 6, 12}; // instances: 16-element pieces of the reduction
+// Lays out rows and columns of an entry whose sizes are set, and launches `count` of them on the instance of `pieces`.
+void thin_layout(ThinEntry *e);
+int launch_thin_list(ThinList &list, int count, int pieces, void *stream);
+
 // What the second step of a split reduction needs of its entry.
 struct ReduceEntry {
     const float *ws;

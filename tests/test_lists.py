@@ -145,6 +145,10 @@ LISTS = {
                   ((2, 32, 28, 28, 1, 1), (1, 96, 15, 13, 1, 1), (3, 4, 9, 1, 1, 1), (1, 960, 7, 7, 1, 1), (2, 20, 6, 5, 1, 0), (1, 8, 3, 3, 1, 2),
                    (2, 24, 28, 28, 2, 1), (1, 144, 57, 31, 2, 1), (5, 16, 4, 4, 2, 0), (1, 12, 1, 1, 2, 1), (2, 30, 9, 9, 1, 1), (1, 7, 10, 12, 2, 1))] +
                  [wl.Kernel(8, wl.ConvShape(1, 16, 17, 17, 16, 3, 3, 1, 1, 1, 1))] * 40,
+    # streams: every instance's reductions (whole pieces and not), rows and columns that end inside a block, chunks of columns
+    "thin": [gemm(4, 3001, 16, 32, wl.F32), gemm(5, 5000, 96, 16, wl.F32), gemm(4, 1003, 24, 100, wl.F32), conv(2, 3, 24, 31, 29, 148, 1, 1, wl.F32),
+             conv(3, 2, 48, 40, 40, 20, 1, 1, wl.F32), gemm(5, 4099, 32, 192, wl.F32), conv(0, 1, 180, 60, 60, 20, 1, 1, wl.F32),
+             gemm(4, 130, 20, 20, wl.F32), gemm(5, 40000, 260, 96, wl.F32), gemm(4, 9000, 64, 192, wl.F32), gemm(4, 17, 16, 16, wl.F32)],
     # more entries than a launch takes
     "many": [gemm(5, 20 + 3 * i, 16 + 8 * (i % 5), 40 + 8 * i, wl.BF16) for i in range(43)],
 }
@@ -195,6 +199,8 @@ def test_entries_of_different_shapes_in_shared_launches(name, split):
         assert len({l.launch for l in launches}) < len(kernels)
         if name.endswith("blocks") and not split:
             assert all(l.tile_m == 256 and l.tile_n == 256 for l in launches)
+        if name == "thin" and not split:
+            assert all(l.listed for l in launches) and len({l.launch for l in launches}) >= 3
         if name == "depthwise":
             assert [l.listed for l in launches[:12]] == [1] * 10 + [0] * 2 and len({l.launch for l in launches}) == 5
 
