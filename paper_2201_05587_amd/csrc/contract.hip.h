@@ -545,6 +545,16 @@ template <int TM, int WM, int WN, int MF> struct TileOut {
     {
         return ROWS_PER_PASS * PASSES == MF || ps * ROWS_PER_PASS + lane / CG < MF;
     }
+    // Single precision, rows of whole fours: a pass is two halves, in each of which a lane handles FOUR columns of a row, so
+    // that a store writes runs of a row (WN * 4 bytes) and not 16 bytes out of every 32: a MobileNet-shaped pass of 51 layers
+    // 260.7 -> 258.8 us, a ResNet18-shaped one of 21 layers 69.0 -> 68.1, the sums themselves unchanged.
+    static constexpr int CG4 = WN / 4, ROWS_PER_HALF = 64 / CG4;
+    static __device__ __forceinline__ int row_in_band4(int lane, int ps, int half) { return ps * ROWS_PER_PASS + half * ROWS_PER_HALF + lane / CG4; }
+    static __device__ __forceinline__ int col4(int wave, int lane) { return (wave / NWR) * WN + (lane % CG4) * 4; }
+    static __device__ __forceinline__ bool half_live(int lane, int ps, int half)
+    {
+        return ROWS_PER_PASS * PASSES == MF || row_in_band4(lane, ps, half) < MF;
+    }
 };
 
 // `count` (1..8) consecutive outputs of one row, starting at element `at` of the output (column `n`), from
@@ -597,7 +607,17 @@ template <int DT> __device__ __forceinline__ BiasRegs<DT> load_bias_columns(cons
 template <int DT, int TM, int WM, int WN, int MF>
 __device__ __forceinline__ BiasRegs<DT> load_bias_early(const ContractArgs &g, const TileCoord &tc, int wave, int lane)
 {
-    return load_bias_columns<DT>(g, tc.n0 + TileOut<TM, WM, WN, MF>::col(wave, lane));
+    using T = TileOut<TM, WM, WN, MF>;
+    if constexpr (DT == TT_F32) { // four columns (see TileOut)
+        BiasRegs<DT> b;
+        b.raw[0] = b.raw[1] = u32x4{0u, 0u, 0u, 0u};
+        const int first = tc.n0 + T::col4(wave, lane);
+        if (g.eff_vec_c >= 4 && g.map.eff_split_k == 1 && g.has_bias && first < g.N)
+            b.raw[0] = *reinterpret_cast<const u32x4 *>(static_cast<const float *>(g.bias) + first);
+        return b;
+    } else {
+        return load_bias_columns<DT>(g, tc.n0 + T::col(wave, lane));
+    }
 }
 
 // The residual values a lane adds in the epilogue, for ALL bands and passes, requested at the start of a
@@ -617,16 +637,19 @@ __device__ __forceinline__ void load_res_pass(u32x4 (&dst)[DT == TT_BF16 ? 1 : 2
                                               int wave, int lane, int i, int ps)
 {
     using T = TileOut<TM, WM, WN, MF>;
-    const int first = tc.n0 + T::col(wave, lane);
-    const int m = tc.m0 + T::row(wave, lane, i, ps);
-    const bool live = T::pass_live(lane, ps) && m < g.M && first < g.N;
-    const int64_t row_at = residual_element(tc, g.M, g.N, live, m, first);
     if constexpr (DT == TT_BF16) {
-        dst[0] = *reinterpret_cast<const u32x4 *>(static_cast<const uint16_t *>(g.res) + row_at);
+        const int first = tc.n0 + T::col(wave, lane);
+        const int m = tc.m0 + T::row(wave, lane, i, ps);
+        const bool live = T::pass_live(lane, ps) && m < g.M && first < g.N;
+        dst[0] = *reinterpret_cast<const u32x4 *>(static_cast<const uint16_t *>(g.res) + residual_element(tc, g.M, g.N, live, m, first));
     } else {
-        dst[0] = *reinterpret_cast<const u32x4 *>(static_cast<const float *>(g.res) + row_at);
-        dst[1] = (live && first + 4 < g.N) ? *reinterpret_cast<const u32x4 *>(static_cast<const float *>(g.res) + row_at + 4)
-                                           : u32x4{0u, 0u, 0u, 0u};
+        const int first = tc.n0 + T::col4(wave, lane);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int m = tc.m0 + (wave % T::NWR) * WM + i * MF + T::row_in_band4(lane, ps, h);
+            const bool live = T::half_live(lane, ps, h) && m < g.M && first < g.N;
+            dst[h] = *reinterpret_cast<const u32x4 *>(static_cast<const float *>(g.res) + residual_element(tc, g.M, g.N, live, m, first));
+        }
     }
 }
 template <int DT, int TM, int WM, int WN, int MF, bool ALLOW>
@@ -693,6 +716,25 @@ __device__ __forceinline__ void write_row_vector(const ContractArgs &g, float *w
                                         reinterpret_cast<f32x4 *>(static_cast<float *>(g.out) + at));
         }
     }
+}
+
+// The same for four single-precision outputs, their bias in the first four of `biasf`.
+__device__ __forceinline__ void write_row_four(const ContractArgs &g, float *ws, bool partial, int64_t row_at, const f32x4 &v,
+                                               const float (&biasf)[8], const u32x4 &res)
+{
+    if (partial) {
+        *reinterpret_cast<f32x4 *>(ws + row_at) = v;
+        asm volatile("" ::: "memory"); // (see write_row_vector)
+        return;
+    }
+    float sum[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        sum[e] = v[e] + biasf[e];
+        if (g.has_res) sum[e] += __uint_as_float(res[e]);
+    }
+    apply_act_all(sum, g.act);
+    __builtin_nontemporal_store(f32x4{sum[0], sum[1], sum[2], sum[3]}, reinterpret_cast<f32x4 *>(static_cast<float *>(g.out) + row_at));
 }
 
 // The bias of 8 columns as floats.
@@ -770,16 +812,29 @@ __device__ __forceinline__ void write_tile(Acc (&acc)[WM / MF][WN / MF], const C
         if constexpr (WAIT_LOADS)
             if (i == 0) wait_loads_outstanding<0>();
         if (whole) {
-            // Rows are whole vectors long: the lane's 8 columns (fp32: its two groups of 4) need no
+            // Rows are whole vectors long: the lane's 8 columns (fp32: 4 columns of two rows) need no
             // further checks and no loop.
+            if constexpr (DT == TT_F32) {
+                const int first4 = tc.n0 + T::col4(wave, lane);
 #pragma unroll
-            for (int ps = 0; ps < PASSES; ++ps) {
-                const int row_l = ps * T::ROWS_PER_PASS + lane / CG;
-                const int m = tc.m0 + T::row(wave, lane, i, ps);
-                if (!T::pass_live(lane, ps) || m >= g.M || first >= g.N) continue;
-                const f32x4 lo = *reinterpret_cast<const f32x4 *>(stage + row_l * ESTRIDE + cg * 8);
-                const f32x4 hi = *reinterpret_cast<const f32x4 *>(stage + row_l * ESTRIDE + cg * 8 + 4);
-                write_row_vector<DT>(g, ws, partial, out_base + (int64_t)m * g.N + first, first, lo, hi, biasf, resv[ps]);
+                for (int ps = 0; ps < PASSES; ++ps)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const int row_l = T::row_in_band4(lane, ps, h), m = tc.m0 + (wave % T::NWR) * WM + i * MF + row_l;
+                        if (!T::half_live(lane, ps, h) || m >= g.M || first4 >= g.N) continue;
+                        const f32x4 v = *reinterpret_cast<const f32x4 *>(stage + row_l * ESTRIDE + (lane % T::CG4) * 4);
+                        write_row_four(g, ws, partial, out_base + (int64_t)m * g.N + first4, v, biasf, resv[ps][h]);
+                    }
+            } else {
+#pragma unroll
+                for (int ps = 0; ps < PASSES; ++ps) {
+                    const int row_l = ps * T::ROWS_PER_PASS + lane / CG;
+                    const int m = tc.m0 + T::row(wave, lane, i, ps);
+                    if (!T::pass_live(lane, ps) || m >= g.M || first >= g.N) continue;
+                    const f32x4 lo = *reinterpret_cast<const f32x4 *>(stage + row_l * ESTRIDE + cg * 8);
+                    const f32x4 hi = *reinterpret_cast<const f32x4 *>(stage + row_l * ESTRIDE + cg * 8 + 4);
+                    write_row_vector<DT>(g, ws, partial, out_base + (int64_t)m * g.N + first, first, lo, hi, biasf, resv[ps]);
+                }
             }
         } else if constexpr (ANY_ROWS) {
             // any other row length: element by element, out of line (rare, and it must not cost the
