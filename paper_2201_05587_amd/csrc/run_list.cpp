@@ -242,6 +242,9 @@ ListEntry list_entry(const PreparedOp &op, const OpPointers &p, const ListTile &
 // A launch of a window: entries of one plan on pointer sets, listed contractions in a tile of the list rule (`tile`),
 // listed depthwise kernels of one stride, or listed streams of one instance.
 constexpr int kOnePlan = -1, kDepthwise = -2, kThin = -3;
+// Workgroups that entries of different shapes share: a launch holds less than 2^32 threads, of workgroups of at most 1024.
+// An entry beyond that goes alone.
+constexpr int64_t kMaxSharedGrid = 1 << 21;
 struct Launch {
     int tile, family; // (depthwise: the stride; streams: the pieces of the reduction)
     std::vector<int> entries; // of the window
@@ -379,9 +382,10 @@ public:
             for (bool fours : {true, false}) {
                 ReduceList list;
                 int count = 0;
+                int64_t grid = 0;
                 const auto send = [&]() {
                     const int rc = count ? launch_reduce_list(list, count, dt, fours, stream) : TT_OK;
-                    count = 0;
+                    count = 0, grid = 0;
                     return rc;
                 };
                 for (const Launch &l : launches) {
@@ -392,7 +396,11 @@ public:
                         const tt_plan &pl = op.launch;
                         const Cut c = cut_into(op, table[l.tile]);
                         if (c.splits == 1 || op.g.dtype != dt || (pl.N % 4 == 0) != fours) continue;
-                        list.e[count++] = {static_cast<float *>(e.p.ws), e.p.bias, e.p.res, e.p.out, (int64_t)pl.batch * pl.M * pl.N,
+                        const int64_t outputs = (int64_t)pl.batch * pl.M * pl.N, wgs = (outputs / (fours ? 4 : 1) + 63) / 64;
+                        if (count && grid + wgs > kMaxSharedGrid)
+                            if (const int rc = send(); rc != TT_OK) return rc;
+                        grid += wgs;
+                        list.e[count++] = {static_cast<float *>(e.p.ws), e.p.bias, e.p.res, e.p.out, outputs,
                                            pl.N, c.splits, op.g.act, 0};
                         if (count == kMaxReduced)
                             if (const int rc = send(); rc != TT_OK) return rc;
@@ -455,11 +463,17 @@ private:
                 if (t >= 0 && chosen[kind_of[m]] == t) at.push_back((int)m);
             // the longest first, so that the end of the launch is not one long tile
             std::stable_sort(at.begin(), at.end(), [&](int x, int y) { return kinds[kind_of[x]].in[t].us > kinds[kind_of[y]].in[t].us; });
-            for (size_t i = 0; i < at.size(); i += kMaxListed) {
-                Launch l{t, family, {}};
-                for (size_t j = i; j < std::min(at.size(), i + kMaxListed); ++j) l.entries.push_back(members[at[j]]);
-                out->push_back(std::move(l));
+            Launch l{t, family, {}};
+            int64_t grid = 0;
+            for (int m : at) {
+                const int64_t more = cut_into(*kinds[kind_of[m]].op, tiles[t]).tiles;
+                if (!l.entries.empty() && ((int)l.entries.size() == kMaxListed || grid + more > kMaxSharedGrid)) {
+                    out->push_back(std::move(l));
+                    l = {t, family, {}}, grid = 0;
+                }
+                l.entries.push_back(members[m]), grid += more;
             }
+            if (!l.entries.empty()) out->push_back(std::move(l));
         }
     }
 
@@ -479,7 +493,7 @@ int send(Window &w, void *stream)
     return rc;
 }
 
-constexpr size_t kMaxWindow = 128; // the check for independence looks at every pair
+constexpr size_t kMaxWindow = 128; // bounds what is planned before the first launch goes out
 
 // Walks the list and hands every window to `emit` (window, whether its one entry runs `use_count` times).
 template <typename Emit>

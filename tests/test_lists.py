@@ -114,6 +114,21 @@ def test_entries_that_run_several_times_or_not_at_all():
         fake.launches()
 
 
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F32])
+@pytest.mark.parametrize("m, k", [(1 << 20, 256), (1 << 19, 512)])
+def test_shared_launches_stay_below_the_largest_grid(dtype, m, k):
+    """A launch holds less than 2^32 threads, and a workgroup here at most 1024."""
+    kernel = wl.Kernel(4, wl.GemmShape(1, m, 768, k, 1, dtype))
+    other = wl.Kernel(4, wl.GemmShape(1, m + 1, 768, k, 1, dtype))
+    at = lambda i: [(1 << 34) * (5 * i + j + 1) for j in range(5)]
+    entries = [((kernel, other)[i % 2], None, at(i), 0) for i in range(40)]
+    listed = FakeList(entries).launches()
+    for launch in {l.launch for l in listed if l.listed}:
+        members = [(e[0].shape, l) for e, l in zip(entries, listed) if l.launch == launch]
+        grid = sum(-(-s.m // l.tile_m) * -(-s.n // l.tile_n) for s, l in members)
+        assert len(members) == 1 or grid <= 1 << 21, (len(members), grid)
+
+
 # ---- on the GPU -------------------------------------------------------------------------------------------------------
 def conv(cls, n, c, h, w, k, f, stride, dtype):
     return wl.Kernel(cls, wl.ConvShape(n, c, h, w, k, f, f, stride, stride, f // 2, f // 2, dtype))
