@@ -62,7 +62,7 @@ __global__ void __launch_bounds__((GroupShape<DT, TM, TN, WM, WN, MF>::THREADS))
     const ListEntry &e = list.e[entry_of(list, (int)blockIdx.x, &first)];
     const int wg = (int)blockIdx.x - first;
     if (wg >= e.grid) return;
-    contract_groups_tile<DT, FAM, TM, TN, WM, WN, MF>(args_of<DT, FAM, TM, TN, GroupShape<DT, TM, TN, WM, WN, MF>::TKI>(e), wg);
+    contract_groups_tile<DT, FAM, TM, TN, WM, WN, MF, true>(args_of<DT, FAM, TM, TN, GroupShape<DT, TM, TN, WM, WN, MF>::TKI>(e), wg);
 }
 
 template <int FAM> __global__ void __launch_bounds__(512) contract_block_list_kernel(const ContractList list)
