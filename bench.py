@@ -358,7 +358,7 @@ def main():
     # ---- per-kernel durations with HIP events on the launch stream, cold: a kernel is launched by itself, in turn on
     # enough tensor sets that a set has left the caches (256 MB memory-side cache, 32 MB of L2) before its
     # turn comes again.  Every launch this process asks for is entered in a ledger per symbol that a lone launch runs
-    # on.  (In a pass up to eight equal neighbours go out as one launch, which may run on another kernel: a kernel
+    # on.  (In a pass independent entries share launches, which may run on another kernel: a kernel
     # trace shows fewer dispatches.)
     ledger = {}
 
