@@ -31,6 +31,15 @@ struct RowsLayout {
     int32_t steps, filter_items;         // matrix-core steps of a filter row (whole ones); items of a filter
     int32_t filter_pitch, zone, pitch, rows, buffer; // `rows`: the most input rows that a tile touches
 };
+// The most input rows that a tile of TM pixels touches: those of its output rows, and the rows between the last of an image
+// and the first of the next.  (Int: large enough for what it is asked about.)
+template <int TM, typename Int> TT_HD Int rows_of_tile(const ContractArgs &g)
+{
+    const Int out_rows = (TM - 1 + (Int)g.Wo - 1) / g.Wo + 1;
+    const Int turn = (Int)g.H + 2 * (Int)g.pad_h - (Int)g.Ho * g.stride_h;
+    return (out_rows - 1) * g.stride_h + g.R + (g.M > g.Ho * g.Wo && turn > 0 ? (out_rows + g.Ho - 1) / g.Ho * turn : 0);
+}
+// 32 bits are enough for what rows_lds accepts.
 template <int TM, int TN> TT_HD RowsLayout rows_layout(const ContractArgs &g)
 {
     using S = RowsShape<TM, TN>;
@@ -41,10 +50,7 @@ template <int TM, int TN> TT_HD RowsLayout rows_layout(const ContractArgs &g)
     l.zone = (g.pad_w * g.C * S::ES + 15) / 16 * 16;
     // (behind the row: padding, and what the last pixel's last step and its alignment word read)
     l.pitch = l.zone + ((g.W + g.pad_w) * g.C * S::ES + S::LG * 16 + 4 + 15) / 16 * 16;
-    // output rows that TM pixels touch, and the rows between the last of an image and the first of the next
-    const int out_rows = (TM - 1 + g.Wo - 1) / g.Wo + 1;
-    const int turn = g.H + 2 * g.pad_h - g.Ho * g.stride_h;
-    l.rows = (out_rows - 1) * g.stride_h + g.R + (g.M > g.Ho * g.Wo && turn > 0 ? (out_rows + g.Ho - 1) / g.Ho * turn : 0);
+    l.rows = rows_of_tile<TM, int32_t>(g);
     l.buffer = l.rows * l.pitch > S::EPI_BYTES ? l.rows * l.pitch : S::EPI_BYTES;
     const int raw = (TN * g.R * g.run * S::ES + 20 + 15) / 16 * 16; // the filters on their way, and what the last one reads behind it
     l.buffer = l.buffer > raw ? l.buffer : raw;
@@ -94,7 +100,7 @@ __global__ void __launch_bounds__((RowsShape<TM, TN>::THREADS)) conv_rows_kernel
     const int row_items = g.W * g.C / CH, margin = (l.pitch - row_items * 16) / 16;
     const __amdgpu_buffer_rsrc_t a_rsrc = make_rsrc(g.a, g.a_bytes);
     const auto request = [&](int tile, int buffer) {
-        if (tile * TM >= g.M) return;
+        if (tile >= g.map.tiles_m) return; // (its first pixel need not be a number of 32 bits)
         const Pixel first = pixel(tile * TM);
         const int rows = pixel(tile * TM + TM - 1).row + g.R - first.row;
         const uint32_t to = __builtin_amdgcn_readfirstlane(patches0 + (uint32_t)(buffer * l.buffer));
@@ -228,9 +234,14 @@ __global__ void __launch_bounds__((RowsShape<TM, TN>::THREADS)) conv_rows_kernel
 
 // LDS of a launch, or 0 where the kernel does not apply: filters of one pixel (nothing is read twice: 6.0 -> 6.6 us over 67
 // channels on 4 x 56x56), no split of the reduction, image rows of whole items (so that they
-// begin at whole items too), and room for two workgroups on a CU.
+// begin at whole items too), and room for two workgroups on a CU.  The layout and the padded rows counted through all images
+// are computed in 32 bits, so sizes that cannot fit are turned away first, in 64.
 template <int TM, int TN> int rows_lds(const ContractArgs &g)
 {
+    const int64_t row = ((int64_t)g.W + g.pad_w) * g.C * RowsShape<TM, TN>::ES, rows = rows_of_tile<TM, int64_t>(g);
+    if (row > kLdsBudget || rows > kLdsBudget || row * rows > kLdsBudget || (int64_t)TN * g.K * RowsShape<TM, TN>::ES > kLdsBudget) return 0;
+    const int64_t images = g.M / ((int64_t)g.Ho * g.Wo), padded_rows = g.H + 2ll * g.pad_h;
+    if (images * padded_rows >= 1ll << 30 || g.stride_h >= 1 << 30) return 0;
     const RowsLayout l = rows_layout<TM, TN>(g);
     const int64_t bytes = (int64_t)TN * l.filter_pitch + 2ll * l.buffer;
     if (g.R * g.S == 1 || g.map.eff_split_k != 1 || (int64_t)g.W * g.C * RowsShape<TM, TN>::ES % 16 != 0 || bytes > kLdsBudget / 2) return 0;
