@@ -51,7 +51,7 @@ def test_lds_holds_the_rows_of_every_tile(shape):
 @pytest.mark.parametrize("shape", [
     # a row of 128 MB and more, whose layout in bytes is no number of 32 bits; padding as wide; images whose padded rows,
     # counted through all of them, are none
-    (1, 1, 1, 1 << 26, 32, 17, 7, (1, 8), (16, 3)), (1, 1, 4, 1 << 27, 32, 7, 7, (1, 1), (3, 3)), (10, 1, 3, 8, 32, 17, 7, (1, 1 << 26), (8, 1 << 27)),
+    (1, 1, 1, 1 << 26, 32, 17, 7, (1, 8), (16, 3)), (1, 1, 4, 1 << 27, 32, 7, 7, (1, 1), (3, 3)), (10, 1, 3, 8, 32, 17, 7, (1, 1 << 27), (8, 1 << 28)),
     (220000, 1, 1, 8, 32, 7, 7, (14, 1), (5000, 3))])
 def test_sizes_that_no_layout_holds_keep_their_records(shape):
     n, c, h, w, k, r, s, stride, pad = shape
