@@ -243,7 +243,6 @@ ListEntry list_entry(const PreparedOp &op, const OpPointers &p, const ListTile &
 // listed depthwise kernels of one stride, or listed streams of one instance.
 constexpr int kOnePlan = -1, kDepthwise = -2, kThin = -3;
 // Workgroups that entries of different shapes share: a launch holds less than 2^32 threads, of workgroups of at most 1024.
-// An entry beyond that goes alone.
 constexpr int64_t kMaxSharedGrid = 1 << 21;
 struct Launch {
     int tile, family; // (depthwise: the stride; streams: the pieces of the reduction)
@@ -286,29 +285,22 @@ public:
                     const PreparedOp &op = ops_[entries_[i].op];
                     if (op.cls != TT_DWCONV_BIAS_RELU6 && op.g.dtype == dt && op.family == family && listable(op)) members.push_back(i);
                 }
-                if (members.size() < 2) continue;
                 if (dt == TT_F32 && family == FAM_GEMM_TN) stream(&members, &done, &out);
-                if (members.empty()) continue;
+                if (members.size() < 2) continue;
                 // (splits of one plan alone: nothing to share that their own launches would not)
                 const PreparedOp &first = ops_[entries_[members[0]].op];
                 const bool one_plan = std::all_of(members.begin(), members.end(), [&](int i) { return entries_[i].op == entries_[members[0]].op; });
                 if (one_plan && first.launch.eff_split_k > 1) continue;
-                for (int i : members) done[i] = 1;
-                list(members, dt, family, &out);
+                list(members, dt, family, &done, &out);
             }
         for (int stride : {1, 2}) {
-            Launch l{kDepthwise, stride, {}};
+            std::vector<int> members;
             DwListEntry e;
             for (int i = 0; i < n; ++i) {
                 const PreparedOp &op = ops_[entries_[i].op];
-                if (op.cls == TT_DWCONV_BIAS_RELU6 && op.d.stride_h == stride && dw_list_entry(op.d, &e)) l.entries.push_back(i);
+                if (op.cls == TT_DWCONV_BIAS_RELU6 && op.d.stride_h == stride && dw_list_entry(op.d, &e)) members.push_back(i);
             }
-            if (l.entries.size() < 2) continue;
-            // the largest first
-            std::stable_sort(l.entries.begin(), l.entries.end(), [&](int x, int y) { return ops_[entries_[x].op].out_bytes > ops_[entries_[y].op].out_bytes; });
-            for (int i : l.entries) done[i] = 1;
-            for (size_t i = 0; i < l.entries.size(); i += kMaxDwListed)
-                out.push_back({kDepthwise, stride, {l.entries.begin() + i, l.entries.begin() + std::min(l.entries.size(), i + kMaxDwListed)}});
+            share(largest_first(members), kDepthwise, stride, kMaxDwListed, [](int) { return (int64_t)0; }, &done, &out);
         }
         // the rest: entries of one plan, all with a bias or all without, share a launch
         std::vector<Launch> plain;
@@ -412,20 +404,44 @@ public:
     }
 
 private:
+    // Cuts entries into launches of at most `most`, and of no more workgroups than a shared launch holds.  An entry that
+    // would be left with a launch to itself shares nothing: it is not done, and runs under its own record.
+    template <typename Workgroups>
+    static void share(const std::vector<int> &entries, int tile, int family, int most, Workgroups &&workgroups, std::vector<char> *done, std::vector<Launch> *out)
+    {
+        std::vector<int> launch;
+        int64_t grid = 0;
+        const auto close = [&]() {
+            if (launch.size() > 1) {
+                for (int i : launch) (*done)[i] = 1;
+                out->push_back({tile, family, launch});
+            }
+            launch.clear(), grid = 0;
+        };
+        for (int i : entries) {
+            const int64_t more = workgroups(i);
+            if ((int)launch.size() == most || grid + more > kMaxSharedGrid) close();
+            launch.push_back(i), grid += more;
+        }
+        close();
+    }
+    std::vector<int> largest_first(std::vector<int> entries) const
+    {
+        std::stable_sort(entries.begin(), entries.end(), [&](int x, int y) { return ops_[entries_[x].op].out_bytes > ops_[entries_[y].op].out_bytes; });
+        return entries;
+    }
     // Takes the streams out of the members.
     void stream(std::vector<int> *members, std::vector<char> *done, std::vector<Launch> *out) const
     {
         for (int pieces : kThinPieces) {
-            Launch l{kThin, pieces, {}};
+            std::vector<int> streams;
             for (int i : *members)
-                if (thin_pieces(ops_[entries_[i].op]) == pieces) l.entries.push_back(i), (*done)[i] = 1;
-            std::stable_sort(l.entries.begin(), l.entries.end(), [&](int x, int y) { return ops_[entries_[x].op].out_bytes > ops_[entries_[y].op].out_bytes; });
-            for (size_t i = 0; i < l.entries.size(); i += kMaxThin)
-                out->push_back({kThin, pieces, {l.entries.begin() + i, l.entries.begin() + std::min(l.entries.size(), i + kMaxThin)}});
+                if (thin_pieces(ops_[entries_[i].op]) == pieces) streams.push_back(i);
+            share(largest_first(streams), kThin, pieces, kMaxThin, [](int) { return (int64_t)0; }, done, out);
         }
         members->erase(std::remove_if(members->begin(), members->end(), [&](int i) { return (*done)[i]; }), members->end());
     }
-    void list(const std::vector<int> &members, int dt, int family, std::vector<Launch> *out) const
+    void list(const std::vector<int> &members, int dt, int family, std::vector<char> *done, std::vector<Launch> *out) const
     {
         int n_tiles = 0;
         const ListTile *tiles = list_tiles(&n_tiles);
@@ -463,17 +479,8 @@ private:
                 if (t >= 0 && chosen[kind_of[m]] == t) at.push_back((int)m);
             // the longest first, so that the end of the launch is not one long tile
             std::stable_sort(at.begin(), at.end(), [&](int x, int y) { return kinds[kind_of[x]].in[t].us > kinds[kind_of[y]].in[t].us; });
-            Launch l{t, family, {}};
-            int64_t grid = 0;
-            for (int m : at) {
-                const int64_t more = cut_into(*kinds[kind_of[m]].op, tiles[t]).tiles;
-                if (!l.entries.empty() && ((int)l.entries.size() == kMaxListed || grid + more > kMaxSharedGrid)) {
-                    out->push_back(std::move(l));
-                    l = {t, family, {}}, grid = 0;
-                }
-                l.entries.push_back(members[m]), grid += more;
-            }
-            if (!l.entries.empty()) out->push_back(std::move(l));
+            for (int &m : at) m = members[m];
+            share(at, t, family, kMaxListed, [&](int i) { return cut_into(ops_[entries_[i].op], tiles[t]).tiles; }, done, out);
         }
     }
 

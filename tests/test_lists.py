@@ -129,6 +129,35 @@ def test_shared_launches_stay_below_the_largest_grid(dtype, m, k):
         assert len(members) == 1 or grid <= 1 << 21, (len(members), grid)
 
 
+def lone_launches():
+    ring = lambda m, n, k, tile: (wl.Kernel(4, wl.GemmShape(1, m, n, k, 1, wl.BF16)), mfma(4, *tile))
+    conv21 = (wl.Kernel(1, wl.ConvShape(1, 128, 28, 28, 128, 3, 3, 1, 1, 1, 1, wl.BF16)), mfma(1, 64, 64, 64, 32, 32, 16))
+    stream = lambda m, n, k: (wl.Kernel(4, wl.GemmShape(1, m, n, k, 1, wl.F32)), mfma(4, 32, 32, 32, 16, 16, 16, vec=4))
+    dw = (wl.Kernel(8, wl.ConvShape(2, 32, 28, 28, 32, 3, 3, 1, 1, 1, 1)), None)
+    return {
+        # no tile suits both: two launches of one entry
+        "apart": [ring(4096, 4096, 4096, (128, 256, 64, 32, 64, 16)), ring(64, 64, 64, (32, 32, 64, 16, 16, 16))],
+        # one more than a launch takes: of contractions, streams (with a contraction that is none), depthwise entries
+        "tail": [conv21] * 21, "streams": [stream(9000, 64, 32)] * 49, "beside_streams": [stream(9000, 64, 32)] * 2 + [stream(64, 64, 640)],
+        "depthwise": [dw] * 37, "one": [conv21], "one_stream": [stream(9000, 64, 32)],
+    }
+
+
+@pytest.mark.parametrize("name", list(lone_launches()))
+def test_an_entry_that_shares_no_launch_keeps_its_record(name):
+    entries = lone_launches()[name]
+    at = lambda i: [(1 << 34) * (5 * i + j + 1) if j != 3 else 0 for j in range(5)]
+    listed = FakeList([(k, rec, at(i), 0) for i, (k, rec) in enumerate(entries)]).launches()
+    lone = 0
+    for (k, rec), l in zip(entries, listed):
+        assert l.entries > 1 or not l.listed
+        if l.entries == 1:
+            plan = api.tt_debug_launch(rec, k.cls, k.shape)[0]
+            assert (l.tile_m, l.tile_n, l.tile_k) == (plan.tile_m, plan.tile_n, plan.tile_k)
+            lone += 1
+    assert lone == (2 if name == "apart" else 1)
+
+
 # ---- on the GPU -------------------------------------------------------------------------------------------------------
 def conv(cls, n, c, h, w, k, f, stride, dtype):
     return wl.Kernel(cls, wl.ConvShape(n, c, h, w, k, f, f, stride, stride, f // 2, f // 2, dtype))
