@@ -244,7 +244,8 @@ def test_entries_of_different_shapes_in_shared_launches(name, split):
         if name.endswith("blocks") and not split:
             assert all(l.tile_m == 256 and l.tile_n == 256 for l in launches)
         if name == "thin" and not split:
-            assert all(l.listed for l in launches) and len({l.launch for l in launches}) >= 3
+            # (all but the contraction that no other entry shares a tile with)
+            assert [bool(l.listed) for l in launches] == [i != 9 for i in range(len(launches))] and len({l.launch for l in launches}) >= 3
         if name == "depthwise":
             assert [l.listed for l in launches[:12]] == [1] * 10 + [0] * 2 and len({l.launch for l in launches}) == 5
 
