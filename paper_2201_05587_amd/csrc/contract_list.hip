@@ -109,7 +109,7 @@ int launch_thin_list(ThinList &list, int count, int pieces, void *stream)
         list.first[i] = i < count ? (int32_t)grid : INT32_MAX;
         if (i >= count) continue;
         const ThinEntry &e = list.e[i];
-        grid += (int64_t)e.chunks * ((e.M + e.rows - 1) / e.rows);
+        grid += thin_workgroups(e);
         lds = std::max(lds, e.columns / 16 * ((e.K + 15) / 16) * 1024 + e.columns * 4);
     }
     auto kern = contract_thin_list_kernel<kThinPieces[0]>;

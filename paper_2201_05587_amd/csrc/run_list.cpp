@@ -113,6 +113,15 @@ bool listable(const PreparedOp &op)
     return (int64_t)pl.batch * pl.M * pl.N < (1ll << 31);
 }
 
+// The sizes of a stream, laid out for the thin kernel.
+ThinEntry thin_entry(const PreparedOp &op)
+{
+    ThinEntry e = {};
+    e.M = op.launch.M, e.N = op.launch.N, e.K = op.launch.K, e.act = op.g.act;
+    thin_layout(&e);
+    return e;
+}
+
 // Whether a listed contraction is a stream for the thin kernel, and the instance that holds its reduction (0: none): single
 // precision, rows of whole fours, no split of the reduction, and rows enough that a workgroup's weights, which it loads into
 // LDS first, are less than half of what it reads and writes.
@@ -121,9 +130,7 @@ int thin_pieces(const PreparedOp &op)
     const tt_plan &pl = op.launch;
     if (op.g.dtype != TT_F32 || op.family != FAM_GEMM_TN || pl.eff_split_k != 1 || pl.batch != 1 || op.g.act == ACT_GELU) return 0;
     if (pl.N % 4 != 0 || pl.K % 4 != 0) return 0;
-    ThinEntry e;
-    e.M = pl.M, e.N = pl.N, e.K = pl.K;
-    thin_layout(&e);
+    const ThinEntry e = thin_entry(op);
     if ((int64_t)std::min(e.rows, e.M) * (e.K + e.columns) < 2ll * e.K * e.columns) return 0;
     for (int p : kThinPieces)
         if (pl.K <= p * 16) return p;
@@ -300,7 +307,8 @@ public:
                 const PreparedOp &op = ops_[entries_[i].op];
                 if (op.cls == TT_DWCONV_BIAS_RELU6 && op.d.stride_h == stride && dw_list_entry(op.d, &e)) members.push_back(i);
             }
-            share(largest_first(members), kDepthwise, stride, kMaxDwListed, [](int) { return (int64_t)0; }, &done, &out);
+            share(largest_first(members), kDepthwise, stride, kMaxDwListed,
+                  [&](int i) { return dw_list_entry(ops_[entries_[i].op].d, &e) ? dw_workgroups(e) : 0; }, &done, &out);
         }
         // the rest: entries of one plan, all with a bias or all without, share a launch
         std::vector<Launch> plain;
@@ -327,10 +335,9 @@ public:
                 const Entry &e = entries_[l.entries[i]];
                 const PreparedOp &op = ops_[e.op];
                 ThinEntry &t = list.e[i];
+                t = thin_entry(op);
                 t.a = static_cast<const float *>(e.p.a), t.b = static_cast<const float *>(e.p.b), t.bias = static_cast<const float *>(e.p.bias);
                 t.res = static_cast<const float *>(e.p.res), t.out = static_cast<float *>(e.p.out);
-                t.M = op.launch.M, t.N = op.launch.N, t.K = op.launch.K, t.act = op.g.act;
-                thin_layout(&t);
             }
             return launch_thin_list(list, (int)l.entries.size(), l.family, stream);
         }
@@ -437,7 +444,7 @@ private:
             std::vector<int> streams;
             for (int i : *members)
                 if (thin_pieces(ops_[entries_[i].op]) == pieces) streams.push_back(i);
-            share(largest_first(streams), kThin, pieces, kMaxThin, [](int) { return (int64_t)0; }, done, out);
+            share(largest_first(streams), kThin, pieces, kMaxThin, [&](int i) { return thin_workgroups(thin_entry(ops_[entries_[i].op])); }, done, out);
         }
         members->erase(std::remove_if(members->begin(), members->end(), [&](int i) { return (*done)[i]; }), members->end());
     }

@@ -676,7 +676,7 @@ int launch_dw_list(DwList &list, int count, int stride, void *stream)
     int grid = 0;
     for (int i = 0; i < kMaxDwListed; ++i) {
         list.e[i].first = i < count ? grid : INT32_MAX;
-        if (i < count) grid += ((list.e[i].threads + 255) / 256 + kXcds - 1) / kXcds * kXcds;
+        if (i < count) grid += (int)dw_workgroups(list.e[i]);
     }
     auto kern = stride == 1 ? dwconv3x3_list_kernel<1> : dwconv3x3_list_kernel<2>;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, static_cast<hipStream_t>(stream), list);

@@ -249,6 +249,7 @@ static_assert(sizeof(ThinList) <= 4096, "");
 constexpr int kThinPieces[] = {2, 6, 12}; // instances: 16-element pieces of the reduction
 // Lays out rows and columns of an entry whose sizes are set, and launches `count` of them on the instance of `pieces`.
 void thin_layout(ThinEntry *e);
+inline int64_t thin_workgroups(const ThinEntry &e) { return (int64_t)e.chunks * ((e.M + e.rows - 1) / e.rows); }
 int launch_thin_list(ThinList &list, int count, int pieces, void *stream);
 
 // What the second step of a split reduction needs of its entry.
@@ -294,6 +295,7 @@ struct DwList {
 static_assert(sizeof(DwList) <= 4096, "");
 // Fills in the part of an entry that the launch decides on; false: the entry is not one for a list.
 bool dw_list_entry(const DwArgs &g, DwListEntry *e);
+inline int64_t dw_workgroups(const DwListEntry &e) { return ((e.threads + 255ll) / 256 + kXcds - 1) / kXcds * kXcds; }
 int launch_dw_list(DwList &list, int count, int stride, void *stream);
 
 TT_HD ContractArgs with_set(ContractArgs g, const PointerSets &sets, uint32_t set)

@@ -129,6 +129,30 @@ def test_shared_launches_stay_below_the_largest_grid(dtype, m, k):
         assert len(members) == 1 or grid <= 1 << 21, (len(members), grid)
 
 
+@pytest.mark.parametrize("stride", [1, 2])
+def test_shared_depthwise_launches_stay_below_the_largest_grid(stride):
+    """Maps of one pixel just below the 2 GiB that a shared launch reads: four channels a thread, and all can read one input."""
+    n, c = (1 << 15) - 1, 1 << 14
+    kernel = wl.Kernel(8, wl.ConvShape(n, c, 1, 1, c, 3, 3, stride, stride, 1, 1))
+    at = lambda i: [1 << 34, 1 << 33, 0, 0, (1 << 34) * (i + 2)]
+    listed = FakeList([(kernel, None, at(i), 0) for i in range(36)]).launches()
+    assert all(l.listed for l in listed)
+    for launch in {l.launch for l in listed}:
+        members = sum(l.launch == launch for l in listed)
+        assert members * -(-n * (c // 4) // 256) <= 1 << 21, members
+
+
+def test_shared_launches_of_streams_stay_below_the_largest_grid():
+    """Reductions of 16, 16 columns, as many rows as the loads' offsets hold: a workgroup has at most 512 of them."""
+    kernel = wl.Kernel(4, wl.GemmShape(1, (1 << 25) - 1, 16, 16, 1, wl.F32))
+    rec = mfma(4, 32, 16, 16, 32, 16, 16, vec=4)
+    at = lambda i: [1 << 34, 1 << 33, 0, 0, (1 << 34) * (i + 2)]
+    listed = FakeList([(kernel, rec, at(i), 0) for i in range(48)]).launches()
+    assert all(l.listed for l in listed)
+    for launch in {l.launch for l in listed}:
+        assert sum(l.launch == launch for l in listed) * ((1 << 25) // 512) <= 1 << 21
+
+
 def lone_launches():
     ring = lambda m, n, k, tile: (wl.Kernel(4, wl.GemmShape(1, m, n, k, 1, wl.BF16)), mfma(4, *tile))
     conv21 = (wl.Kernel(1, wl.ConvShape(1, 128, 28, 28, 128, 3, 3, 1, 1, 1, 1, wl.BF16)), mfma(1, 64, 64, 64, 32, 32, 16))
