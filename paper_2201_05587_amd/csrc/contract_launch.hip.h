@@ -17,7 +17,7 @@ int kernel_contract(const ContractArgs &args, int count, int grid)
     if constexpr (FAM == FAM_GEMM_TN || (FAM == FAM_CONV && AM == 16)) {
         if (groups_apply<DT, FAM, TM, TN, WM, WN, MF>(args, grid * count, 0)) return TT_LAUNCH_GROUPS;
     } else if constexpr (FAM == FAM_CONV) {
-        if (rows_shape(args, grid).grid > 0) return TT_LAUNCH_ROWS;
+        if (rows_shape(args, count).grid > 0) return TT_LAUNCH_ROWS;
     }
     return TT_LAUNCH_RECORD;
 }
@@ -30,23 +30,23 @@ int kernel_contract_async(const ContractArgs &args, int count, int grid, int lds
     return TT_LAUNCH_RECORD;
 }
 template <int DT, int FAM, int TM, int TN, int WM, int WN, int MF>
-LaunchShape shape_on(int kernel, const ContractArgs &args, int grid, int lds_bytes)
+LaunchShape shape_on(int kernel, const ContractArgs &args, int count, int grid, int lds_bytes)
 {
     using S = GroupShape<DT, TM, TN, WM, WN, MF>;
     if (kernel == TT_LAUNCH_BLOCKS) return blocks_shape(args, FAM);
-    if (kernel == TT_LAUNCH_ROWS) return rows_shape(args, grid);
+    if (kernel == TT_LAUNCH_ROWS) return rows_shape(args, count);
     if (kernel == TT_LAUNCH_GROUPS) return {TT_LAUNCH_GROUPS, grid, S::THREADS, S::LDS};
     return {TT_LAUNCH_RECORD, grid, (TM / WM) * (TN / WN) * 64, std::max(lds_bytes, epilogue_bytes(TM, TN, WM, WN, MF))};
 }
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF, int AM>
 LaunchShape shape_contract(const ContractArgs &args, int count, int grid, int lds_bytes)
 {
-    return shape_on<DT, FAM, TM, TN, WM, WN, MF>(kernel_contract<DT, FAM, TM, TN, TK, WM, WN, MF, AM>(args, count, grid), args, grid, lds_bytes);
+    return shape_on<DT, FAM, TM, TN, WM, WN, MF>(kernel_contract<DT, FAM, TM, TN, TK, WM, WN, MF, AM>(args, count, grid), args, count, grid, lds_bytes);
 }
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF>
 LaunchShape shape_contract_async(const ContractArgs &args, int count, int grid, int lds_bytes)
 {
-    return shape_on<DT, FAM, TM, TN, WM, WN, MF>(kernel_contract_async<DT, FAM, TM, TN, TK, WM, WN, MF>(args, count, grid, lds_bytes), args, grid, lds_bytes);
+    return shape_on<DT, FAM, TM, TN, WM, WN, MF>(kernel_contract_async<DT, FAM, TM, TN, TK, WM, WN, MF>(args, count, grid, lds_bytes), args, count, grid, lds_bytes);
 }
 
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF, int AM>

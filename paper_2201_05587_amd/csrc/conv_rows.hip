@@ -10,9 +10,10 @@ namespace {
 struct RowsTile {
     int tile_m, tile_n, threads;
     int (*lds)(const ContractArgs &);
+    int (*grid)(const ContractArgs &, int count, int lds);
     int (*launch)(const ContractArgs &, const PointerSets &, void *);
 };
-#define TT_ROWS(TM_, TN_) {TM_, TN_, RowsShape<TM_, TN_>::THREADS, rows_lds<TM_, TN_>, launch_rows<TM_, TN_>}
+#define TT_ROWS(TM_, TN_) {TM_, TN_, RowsShape<TM_, TN_>::THREADS, rows_lds<TM_, TN_>, rows_grid<TM_, TN_>, launch_rows<TM_, TN_>}
 
 // The record's tile, where it has 128 rows or more: what a workgroup does once, and the input rows that neighbouring tiles
 // share, count for less there.  Register pipeline -> this (us): 7x7 filters over 3 channels, stride 2, 32 x 224x224 to 64
@@ -31,11 +32,11 @@ const RowsTile *find_tile(const ContractArgs &g)
 
 } // namespace
 
-LaunchShape rows_shape(const ContractArgs &args, int grid)
+LaunchShape rows_shape(const ContractArgs &args, int count)
 {
     const RowsTile *t = find_tile(args);
     const int lds = t ? t->lds(args) : 0;
-    return {TT_LAUNCH_ROWS, lds > 0 ? grid : 0, t ? t->threads : 0, lds};
+    return {TT_LAUNCH_ROWS, lds > 0 ? t->grid(args, count, lds) : 0, t ? t->threads : 0, lds};
 }
 
 int launch_conv_rows(const ContractArgs &args, const PointerSets &sets, void *stream)

@@ -248,6 +248,14 @@ template <int TM, int TN> int rows_lds(const ContractArgs &g)
     return (int)bytes;
 }
 
+// Workgroups of each of `count` pointer sets: as many as the CUs hold (LDS, and 16 waves at these kernels' registers), whole
+// columns of tiles.
+template <int TM, int TN> int rows_grid(const ContractArgs &args, int count, int lds)
+{
+    const int fit = std::max(1, std::min(kLdsBudget / lds, 1024 / RowsShape<TM, TN>::THREADS));
+    return std::max(1, std::min(args.map.tiles_m, compute_units() * fit / (args.map.tiles_n * count))) * args.map.tiles_n;
+}
+
 template <int TM, int TN> int launch_rows(const ContractArgs &args, const PointerSets &sets, void *stream)
 {
     using S = RowsShape<TM, TN>;
@@ -255,10 +263,7 @@ template <int TM, int TN> int launch_rows(const ContractArgs &args, const Pointe
     const int lds = rows_lds<TM, TN>(args);
     static DynamicLdsLimit limit; // per kernel instance
     if (const int rc = limit.raise_to(reinterpret_cast<const void *>(kern), lds); rc != TT_OK) return rc;
-    // as many workgroups as the CUs hold (LDS, and 16 waves at these kernels' registers), whole columns of tiles
-    const int fit = std::max(1, std::min(kLdsBudget / lds, 1024 / S::THREADS));
-    const int per = std::max(1, std::min(args.map.tiles_m, compute_units() * fit / (args.map.tiles_n * sets.count)));
-    hipLaunchKernelGGL(kern, dim3(per * args.map.tiles_n, sets.count), dim3(S::THREADS), lds, static_cast<hipStream_t>(stream), args, sets);
+    hipLaunchKernelGGL(kern, dim3(rows_grid<TM, TN>(args, sets.count, lds), sets.count), dim3(S::THREADS), lds, static_cast<hipStream_t>(stream), args, sets);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? TT_OK : note_hip_error((int)e, "conv_rows_kernel launch");
 }

@@ -393,9 +393,9 @@ int launch_gemv(const ContractArgs &args, const PointerSets &sets, const tt_plan
 bool block_applies(const ContractArgs &args, int family, int count, int tile_outputs);
 int launch_blocks(const ContractArgs &args, const PointerSets &sets, int family, void *stream);
 LaunchShape blocks_shape(const ContractArgs &args, int family);
-// the convolution kernel with the input rows of a tile in LDS (conv_rows.hip): its launch for element-wise gathers (a grid
-// of 0: it does not apply)
-LaunchShape rows_shape(const ContractArgs &args, int grid);
+// the convolution kernel with the input rows of a tile in LDS (conv_rows.hip): its launch of `count` sets for element-wise
+// gathers (a grid of 0: it does not apply)
+LaunchShape rows_shape(const ContractArgs &args, int count);
 int launch_conv_rows(const ContractArgs &args, const PointerSets &sets, void *stream);
 int dw_max_block(int wave_m, int wave_n, int planes_per_lane, int stride, bool rows_kernel);
 int launch_dwconv(const DwArgs &args, const PointerSets &sets, const tt_plan &plan, void *stream);

@@ -48,6 +48,23 @@ def test_lds_holds_the_rows_of_every_tile(shape):
     assert seen or s.r * s.s == 1
 
 
+@pytest.mark.parametrize("shape", [(32, 3, 224, 224, 64, 7, 7, 2, 3), (1, 3, 33, 32, 64, 7, 7, 2, 3), (4, 5, 14, 16, 96, 3, 3, 2, 0), (1, 3, 17, 24, 130, 7, 7, 1, 3)])
+@pytest.mark.parametrize("count", [1, 3, 8])
+def test_the_launch_has_the_workgroups_that_the_chip_holds(shape, count):
+    """Whole columns of tiles, no more of them than there are tiles, and of all entries together no more than 256 CUs hold
+    (but a column of each)."""
+    k = conv(1, *shape, wl.BF16)
+    for tm, tn in TILES:
+        if not api.tt_schedule_apply(mfma(1, tm, tn), k.cls, k.shape).runnable():
+            continue
+        plan, kernel = api.tt_debug_launch(mfma(1, tm, tn), k.cls, k.shape, count)
+        if kernel != api.TT_LAUNCH_ROWS:
+            continue
+        fit = min(160 * 1024 // plan.lds_bytes, 1024 // plan.block)
+        columns, rows = -(-plan.N // tn), -(-plan.M // tm)
+        assert plan.grid == columns * max(1, min(rows, 256 * fit // (columns * count)))
+
+
 @pytest.mark.parametrize("shape", [
     # a row of 128 MB and more, whose layout in bytes is no number of 32 bits; padding as wide; images whose padded rows,
     # counted through all of them, are none
