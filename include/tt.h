@@ -444,7 +444,8 @@ int tt_time_pair(const tt_kernel_desc *kernel, const tt_schedule *sched, const t
  * Consecutive entries that run once and touch none of each other's outputs or workspaces share launches (tt_debug_list) and
  * may run at the same time and in any order; an entry that depends on an earlier one stays behind it.  Contractions of
  * different shapes that share a launch run in a tile that suits them together, whatever tile their records name (a split of
- * the reduction stays); other entries share one of up to TT_MAX_ENTRIES_PER_LAUNCH of their own class, shape and record.
+ * the reduction stays), and depthwise ones of a stride in windows of the launch's own; other entries share one of up to
+ * TT_MAX_ENTRIES_PER_LAUNCH of their own class, shape and record.  An entry that shares no launch runs under its record.
  * What an entry runs on can therefore depend on the entries beside it, so the order in which an output's products are
  * summed, and with it the last bits, can differ from those of the entry run by itself.  For a given list they are always
  * the same.
@@ -477,13 +478,18 @@ int tt_debug_launch(const tt_schedule *sched, int cls, const void *shape, int co
 
 /*
  * Which launch of tt_run_kernels every entry of a list goes out in (of the first pass; launches count from 0, -1: the entry
- * runs no times), host only.  `listed`: 1 in a launch of contractions of different shapes (contract_list_kernel,
- * contract_groups_list_kernel in deeper slices, contract_block_list_kernel in blocks of 256 x 256), 0 in one of its own plan
- * (tt_debug_launch); the tile it runs in there,
- * and the number of entries of that launch.  Returns what tt_run_kernels would for a list whose entry is refused.
+ * runs no times), host only.  `listed`: 1 in a launch that it shares with entries of other shapes or records, 0 in one of its
+ * own plan (tt_debug_launch); the kernel and the tile it runs in there, and the number of entries of that launch.  kernel:
+ *   TT_LISTED_RECORD     listed = 0: what tt_debug_launch reports, in the tile of the plan as launched
+ *   TT_LISTED_TILES      contract_list_kernel, contract_groups_list_kernel in deeper slices, or contract_block_list_kernel in
+ *                        blocks of 256 x 256: tile_m x tile_n x tile_k, whatever tile the record names
+ *   TT_LISTED_STREAM     contract_thin_list_kernel: blocks of 16 x 16, tile_k the longest reduction that the instance holds
+ *   TT_LISTED_DEPTHWISE  dwconv3x3_list_kernel: tile_m x tile_n outputs of tile_k channels a thread
+ * Returns what tt_run_kernels would for a list whose entry is refused.
  */
+enum tt_listed_kernel { TT_LISTED_RECORD = 0, TT_LISTED_TILES = 1, TT_LISTED_STREAM = 2, TT_LISTED_DEPTHWISE = 3 };
 typedef struct tt_listed {
-    int32_t launch, listed, tile_m, tile_n, tile_k, entries;
+    int32_t launch, listed, tile_m, tile_n, tile_k, entries, kernel;
 } tt_listed;
 int tt_debug_list(const tt_kernel_desc *kernels, const tt_schedule *const *scheds, int nk, tt_listed *out);
 

@@ -83,7 +83,7 @@ class tt_kernel_desc(Structure):
 
 
 class tt_listed(Structure):
-    _fields_ = [(n, c_int32) for n in ("launch", "listed", "tile_m", "tile_n", "tile_k", "entries")]
+    _fields_ = [(n, c_int32) for n in ("launch", "listed", "tile_m", "tile_n", "tile_k", "entries", "kernel")]
 
 
 class tt_sweep_opts(Structure):
@@ -341,6 +341,7 @@ def tt_debug_tile_map(plan):
 
 TT_LAUNCH_RECORD, TT_LAUNCH_GROUPS, TT_LAUNCH_BLOCKS, TT_LAUNCH_ROWS = range(4)
 TT_MAX_ENTRIES_PER_LAUNCH = 8
+TT_LISTED_RECORD, TT_LISTED_TILES, TT_LISTED_STREAM, TT_LISTED_DEPTHWISE = range(4)
 
 
 def tt_debug_launch(sched, cls, shape, count=1):
@@ -516,7 +517,7 @@ class KernelList:
         _check(lib.tt_run_kernels(self.descs, self.ptrs, self.n, repeat, _stream()), "tt_run_kernels")
 
     def launches(self):
-        """One tt_listed per entry: which launch of a pass it goes out in, and in what tile."""
+        """One tt_listed per entry: which launch of a pass it goes out in, on what kernel and in what tile."""
         out = (tt_listed * max(self.n, 1))()
         _check(lib.tt_debug_list(self.descs, self.ptrs, self.n, out), "tt_debug_list")
         return list(out)[:self.n]

@@ -594,18 +594,23 @@ extern "C" int tt_debug_list(const tt_kernel_desc *kernels, const tt_schedule *c
     if (nk < 0 || (nk && (!kernels || !out))) return TT_ERR_BAD_ARG;
     return without_exceptions([&]() {
         std::vector<PreparedOp> ops;
-        for (int k = 0; k < nk; ++k) out[k] = {-1, 0, 0, 0, 0, 0};
+        for (int k = 0; k < nk; ++k) out[k] = {-1, 0, 0, 0, 0, 0, 0};
         int launch = 0, tiles = 0;
         const ListTile *table = list_tiles(&tiles);
         return walk(kernels, scheds, nk, ops, [&](Window &w, int) {
             for (const Launch &l : w.launches()) {
-                for (int i : l.entries) {
-                    const Entry &e = w.entries()[i];
-                    const tt_plan &pl = ops[e.op].launch;
-                    out[e.index] = {launch, l.tile != kOnePlan, l.tile >= 0 ? table[l.tile].tile_m : pl.tile_m,
-                                    l.tile >= 0 ? table[l.tile].tile_n : pl.tile_n, l.tile >= 0 ? table[l.tile].tile_k : pl.tile_k,
-                                    (int32_t)l.entries.size()};
+                tt_listed as = {launch, l.tile != kOnePlan, 16, 16, l.family * 16, (int32_t)l.entries.size(), TT_LISTED_STREAM};
+                if (l.tile >= 0) {
+                    const ListTile &t = table[l.tile];
+                    as.tile_m = t.tile_m, as.tile_n = t.tile_n, as.tile_k = t.tile_k, as.kernel = TT_LISTED_TILES;
+                } else if (l.tile == kDepthwise) {
+                    dw_list_window(l.family, &as.tile_m, &as.tile_n);
+                    as.tile_k = 4, as.kernel = TT_LISTED_DEPTHWISE;
+                } else if (l.tile == kOnePlan) { // (one plan for all of its entries)
+                    const tt_plan &pl = ops[w.entries()[l.entries[0]].op].launch;
+                    as.tile_m = pl.tile_m, as.tile_n = pl.tile_n, as.tile_k = pl.tile_k, as.kernel = TT_LISTED_RECORD;
                 }
+                for (int i : l.entries) out[w.entries()[i].index] = as;
                 ++launch;
             }
             w.clear();

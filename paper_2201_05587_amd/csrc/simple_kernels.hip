@@ -659,10 +659,17 @@ int launch_dwconv(const DwArgs &a, const PointerSets &sets, const tt_plan &plan,
     return TT_ERR_UNSUPPORTED;
 }
 
+void dw_list_window(int stride, int32_t *rows, int32_t *columns)
+{
+    *rows = stride == 1 ? DwListShape<1>::WM : DwListShape<2>::WM;
+    *columns = stride == 1 ? DwListShape<1>::WN : DwListShape<2>::WN;
+}
+
 bool dw_list_entry(const DwArgs &g, DwListEntry *e)
 {
     if (g.C % 4 != 0 || g.stride_h != g.stride_w || (g.stride_h != 1 && g.stride_h != 2) || g.x_bytes == 0) return false;
-    const int wm = g.stride_h == 1 ? DwListShape<1>::WM : DwListShape<2>::WM, wn = g.stride_h == 1 ? DwListShape<1>::WN : DwListShape<2>::WN;
+    int32_t wm, wn;
+    dw_list_window(g.stride_h, &wm, &wn);
     const int64_t columns = (g.Wo + wn - 1) / wn, strips = (g.Ho + wm - 1) / wm, threads = g.planes / 4 * columns * strips;
     if (threads >= 1ll << 30) return false;
     e->threads = (int32_t)threads;

@@ -296,6 +296,8 @@ static_assert(sizeof(DwList) <= 4096, "");
 // Fills in the part of an entry that the launch decides on; false: the entry is not one for a list.
 bool dw_list_entry(const DwArgs &g, DwListEntry *e);
 inline int64_t dw_workgroups(const DwListEntry &e) { return ((e.threads + 255ll) / 256 + kXcds - 1) / kXcds * kXcds; }
+// Rows and columns of the outputs that a thread forms (of four channels).
+void dw_list_window(int stride, int32_t *rows, int32_t *columns);
 int launch_dw_list(DwList &list, int count, int stride, void *stream);
 
 TT_HD ContractArgs with_set(ContractArgs g, const PointerSets &sets, uint32_t set)

@@ -182,6 +182,27 @@ def test_an_entry_that_shares_no_launch_keeps_its_record(name):
     assert lone == (2 if name == "apart" else 1)
 
 
+def test_launches_name_the_kernel_and_the_tile_they_run_in():
+    """Whatever tiles the records name: depthwise windows of 4 x 2 and, at stride two, 2 x 2 outputs of four channels, streams in
+    blocks of 16 x 16 on the shortest instance that holds the reduction, contractions in a tile of the rule."""
+    dw = lambda stride: (wl.Kernel(8, wl.ConvShape(1, 32, 13, 13, 32, 3, 3, stride, stride, 1, 1)),
+                         api.make_schedule(8, api.TT_SK_DWCONV, 4, 4, 8, 1, 2, 0, 1, 0, 4, 1, 1))
+    stream = lambda k: (wl.Kernel(4, wl.GemmShape(1, 90000, 64, k, 1, wl.F32)), mfma(4, 32, 32, 16, 16, 16, 16, vec=4))
+    tiles = (wl.Kernel(5, wl.GemmShape(1, 300, 1032, 96, 1, wl.BF16)), mfma(5, 128, 256, 64, 32, 64, 16))
+    lone = (wl.Kernel(7, wl.GemmShape(3, 50, 64, 50, 0, wl.BF16)), None)
+    entries = [dw(1), dw(2), stream(32), stream(20), stream(36), stream(96), tiles, lone] + [dw(1), dw(2), stream(100), stream(192), tiles]
+    at = lambda i: [(1 << 34) * (5 * i + j + 1) if j != 3 else 0 for j in range(5)]
+    fake = FakeList([(k, rec, [a if j != 2 or k.cls != 7 else 0 for j, a in enumerate(at(i))], 0) for i, (k, rec) in enumerate(entries)])
+    got = [(l.kernel, l.listed, l.entries, l.tile_m, l.tile_n, l.tile_k) for l in fake.launches()]
+    of_lone = api.tt_debug_launch(None, lone[0].cls, lone[0].shape)[0]
+    d1, d2 = (api.TT_LISTED_DEPTHWISE, 1, 2, 4, 2, 4), (api.TT_LISTED_DEPTHWISE, 1, 2, 2, 2, 4)
+    s = lambda k: (api.TT_LISTED_STREAM, 1, 2, 16, 16, k)
+    t = got[6]
+    assert t[:3] == (api.TT_LISTED_TILES, 1, 2) and t[3:] != (128, 256, 64)
+    assert got == [d1, d2, s(32), s(32), s(96), s(96), t, (api.TT_LISTED_RECORD, 0, 1, of_lone.tile_m, of_lone.tile_n, of_lone.tile_k),
+                   d1, d2, s(192), s(192), t]
+
+
 # ---- on the GPU -------------------------------------------------------------------------------------------------------
 def conv(cls, n, c, h, w, k, f, stride, dtype):
     return wl.Kernel(cls, wl.ConvShape(n, c, h, w, k, f, f, stride, stride, f // 2, f // 2, dtype))
