@@ -2,8 +2,9 @@
 """Benchmark of the transfer-tuning hot path on one MI355X.
 
 A step is one network-shaped pass over the workload's fused kernels, each under the best
-TRANSFERRED schedule (the fastest valid donor record of its class, or the default as fallback),
-with all inputs resident in HBM and every launch of the pass on tensors of its own (a network's
+TRANSFERRED schedule (the fastest valid donor record of its class, or the default as fallback:
+KernelList.run_as_recorded; the pass in shared launches, whose tiles the library chooses, is
+reported beside it), with all inputs resident in HBM and every launch of the pass on tensors of its own (a network's
 layers do not share weights or activations; the pass touches far more than the caches hold, so
 every launch finds its operands cold).  `value` is the pass's algorithmic FLOPs over its time; the
 time of the same launches repeated on one set of tensors per kernel is reported beside it as the
@@ -163,10 +164,10 @@ def chain_leg(args, api, harness, tune, wl, targets, dks, transfer):
         independent += [single(i) for _ in range(blocks) for i in (ir, ic, ie)]
 
     def timed(klist):
-        klist.run(args.warmup)
+        klist.run_as_recorded(args.warmup)
         torch.cuda.synchronize()
         t0 = time.perf_counter()
-        klist.run(args.steps)
+        klist.run_as_recorded(args.steps)
         torch.cuda.synchronize()
         return (time.perf_counter() - t0) * 1e6 / args.steps
 
@@ -335,21 +336,28 @@ def main():
     cold_list = api.KernelList(launch_dks, launch_recs)
     pass_flops = sum(k.flops() * k.use_count for k in targets)
     pass_bytes = sum(k.algorithmic_bytes() * k.use_count for k in targets)
+    cold_list.run_as_recorded(args.warmup)
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    cold_list.run_as_recorded(args.steps)
+    torch.cuda.synchronize()
+    elapsed = time.perf_counter() - t0
+    ms_per_step = elapsed * 1e3 / args.steps
+    value = pass_flops / (elapsed / args.steps) / 1e12
+    # the same launches as a list that the library may share among launches of its own tiles
     cold_list.run(args.warmup)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     cold_list.run(args.steps)
     torch.cuda.synchronize()
-    elapsed = time.perf_counter() - t0
-    ms_per_step = elapsed * 1e3 / args.steps
-    value = pass_flops / (elapsed / args.steps) / 1e12
+    shared_ms = (time.perf_counter() - t0) * 1e3 / args.steps
     # the same launches with each kernel's use_count launches repeated on ONE set of tensors (cache-warm)
     warm_steps = max(3, args.steps // 5)
     warm_list = api.KernelList(dks, transfer)
-    warm_list.run(2)
+    warm_list.run_as_recorded(2)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
-    warm_list.run(warm_steps)
+    warm_list.run_as_recorded(warm_steps)
     torch.cuda.synchronize()
     warm_ms = (time.perf_counter() - t0) * 1e3 / warm_steps
     del cold_list, launch_dks
@@ -358,8 +366,8 @@ def main():
     # ---- per-kernel durations with HIP events on the launch stream, cold: a kernel is launched by itself, in turn on
     # enough tensor sets that a set has left the caches (256 MB memory-side cache, 32 MB of L2) before its
     # turn comes again.  Every launch this process asks for is entered in a ledger per symbol that a lone launch runs
-    # on.  (In a pass independent entries share launches, which may run on another kernel: a kernel
-    # trace shows fewer dispatches.)
+    # on.  (In a pass up to eight equal entries go out as one launch, which may run on another kernel, and in the pass of
+    # shared launches entries of different shapes: a kernel trace shows fewer dispatches.)
     ledger = {}
 
     def symbol_of(k, rec):
@@ -464,6 +472,9 @@ def main():
                    "kernels_on_default_fallback": sum(1 for t in transfer if t is None)},
         "cold": {"ms_per_step": ms_per_step, "tflops": value,
                  "what": "every launch of a pass on tensors of its own (the headline)"},
+        "shared_launches": {"ms_per_step": shared_ms, "tflops": pass_flops / shared_ms / 1e9,
+                            "what": "the cold pass through KernelList.run: independent entries share launches, in tiles that "
+                                    "suit them together whatever their records name"},
         "warm": {"ms_per_step": warm_ms, "tflops": pass_flops / warm_ms / 1e9,
                  "what": "each kernel's use_count launches repeated on one set of tensors"},
         "pct_of_native_optimum": {"mean": 100.0 * sum(fracs) / len(fracs), "min": 100.0 * min(fracs),

@@ -454,6 +454,14 @@ int tt_run_kernels(const tt_kernel_desc *kernels, const tt_schedule *const *sche
                    void *stream);
 
 /*
+ * The same list with every entry under its own record: only entries of one class, shape and record that do not depend on each
+ * other share a launch, up to TT_MAX_ENTRIES_PER_LAUNCH of them (tt_debug_launch says on what).  What a pass costs under the
+ * schedules that a sweep chose is this function's time.
+ */
+int tt_run_kernels_as_recorded(const tt_kernel_desc *kernels, const tt_schedule *const *scheds, int nk, int repeat,
+                               void *stream);
+
+/*
  * Enumerate the schedule space of a class for a data type: every compiled
  * kernel variant crossed with the run-time knobs (split_k, order, stages, vec,
  * unroll).  Writes up to `cap` records to out (host) and returns the total
@@ -463,8 +471,9 @@ int tt_run_kernels(const tt_kernel_desc *kernels, const tt_schedule *const *sche
 int tt_schedule_space(int cls, int dtype, int level, tt_schedule *out, int cap);
 
 /*
- * What a launch of `count` equal entries under a record runs on (count = 1: an operator call; tt_run_kernels sends up to
- * TT_MAX_ENTRIES_PER_LAUNCH entries out together); sched NULL = default.  Host only, for inspection and tests.  *kernel:
+ * What a launch of `count` equal entries under a record runs on (count = 1: an operator call; tt_run_kernels_as_recorded sends
+ * up to TT_MAX_ENTRIES_PER_LAUNCH entries out together, and so does tt_run_kernels with those that tt_debug_list reports as
+ * not listed); sched NULL = default.  Host only, for inspection and tests.  *kernel:
  * TT_LAUNCH_RECORD, the kernel launched->variant_id (or the sketch) names; TT_LAUNCH_GROUPS, contract_groups_kernel in the
  * same tiles; TT_LAUNCH_BLOCKS, contract_block_kernel in blocks of 256 x 256; TT_LAUNCH_ROWS, conv_rows_kernel in the
  * same tiles.  launched: the plan as it is launched, with

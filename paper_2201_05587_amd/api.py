@@ -99,7 +99,7 @@ class tt_sweep_row(Structure):
 
 EXPORTS = ("tt_version", "tt_status_name", "tt_last_error", "tt_schedule_default", "tt_schedule_apply", "tt_plan_tile",
            "tt_debug_tile_map", "tt_debug_launch", "tt_debug_list", "tt_debug_fast_div", "tt_debug_probe", "tt_conv2d_bias_relu", "tt_conv2d_bias_relu_noalloc", "tt_dense_bias_relu", "tt_batch_matmul", "tt_dwconv",
-           "tt_transfer_sweep", "tt_sweep_plan", "tt_refine_space", "tt_refine", "tt_native_sweep", "tt_time_pair", "tt_run_kernels", "tt_schedule_space", "tt_sweep_select", "tt_variant_info", "tt_num_variants", "tt_select_donor")
+           "tt_transfer_sweep", "tt_sweep_plan", "tt_refine_space", "tt_refine", "tt_native_sweep", "tt_time_pair", "tt_run_kernels", "tt_run_kernels_as_recorded", "tt_schedule_space", "tt_sweep_select", "tt_variant_info", "tt_num_variants", "tt_select_donor")
 
 
 def _load():
@@ -143,6 +143,7 @@ def _load():
                                  POINTER(c_double), POINTER(c_double)]
     lib.tt_run_kernels.argtypes = [POINTER(tt_kernel_desc), POINTER(POINTER(tt_schedule)), ctypes.c_int, ctypes.c_int,
                                    c_void_p]
+    lib.tt_run_kernels_as_recorded.argtypes = lib.tt_run_kernels.argtypes
     lib.tt_debug_list.argtypes = [POINTER(tt_kernel_desc), POINTER(POINTER(tt_schedule)), ctypes.c_int, POINTER(tt_listed)]
     lib.tt_schedule_space.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, POINTER(tt_schedule), ctypes.c_int]
     lib.tt_variant_info.argtypes = [ctypes.c_int, POINTER(c_int32 * 12)]
@@ -515,6 +516,10 @@ class KernelList:
 
     def run(self, repeat=1):
         _check(lib.tt_run_kernels(self.descs, self.ptrs, self.n, repeat, _stream()), "tt_run_kernels")
+
+    def run_as_recorded(self, repeat=1):
+        """The same pass with every entry under its own record (launches hold entries of one record and shape only)."""
+        _check(lib.tt_run_kernels_as_recorded(self.descs, self.ptrs, self.n, repeat, _stream()), "tt_run_kernels_as_recorded")
 
     def launches(self):
         """One tt_listed per entry: which launch of a pass it goes out in, on what kernel and in what tile."""

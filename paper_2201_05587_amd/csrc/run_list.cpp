@@ -258,7 +258,7 @@ struct Launch {
 
 class Window {
 public:
-    explicit Window(std::vector<PreparedOp> &ops) : ops_(ops) {}
+    Window(std::vector<PreparedOp> &ops, bool as_recorded) : ops_(ops), as_recorded_(as_recorded) {}
     // Whether an entry may run at the same time as all others: neither writes what the other reads or writes.
     bool admits(const Entry &e) const
     {
@@ -285,7 +285,7 @@ public:
         list_tiles(&tiles);
         const int n = (int)entries_.size();
         std::vector<char> done(n, 0);
-        for (int dt = 0; dt < 2; ++dt)
+        for (int dt = 0; dt < 2 && !as_recorded_; ++dt)
             for (int family : {FAM_CONV, FAM_GEMM_TN}) {
                 std::vector<int> members;
                 for (int i = 0; i < n; ++i) {
@@ -301,6 +301,7 @@ public:
                 list(members, dt, family, &done, &out);
             }
         for (int stride : {1, 2}) {
+            if (as_recorded_) break;
             std::vector<int> members;
             DwListEntry e;
             for (int i = 0; i < n; ++i) {
@@ -492,6 +493,7 @@ private:
     }
 
     std::vector<PreparedOp> &ops_;
+    const bool as_recorded_; // entries share launches of their own plan only
     std::vector<Entry> entries_;
     Ranges written_, read_;
 };
@@ -511,9 +513,9 @@ constexpr size_t kMaxWindow = 128; // bounds what is planned before the first la
 
 // Walks the list and hands every window to `emit` (window, whether its one entry runs `use_count` times).
 template <typename Emit>
-int walk(const tt_kernel_desc *kernels, const tt_schedule *const *scheds, int nk, std::vector<PreparedOp> &ops, Emit &&emit)
+int walk(const tt_kernel_desc *kernels, const tt_schedule *const *scheds, int nk, bool as_recorded, std::vector<PreparedOp> &ops, Emit &&emit)
 {
-    Window w(ops);
+    Window w(ops, as_recorded);
     std::vector<int> first; // of every plan, the entry it was laid out for
     int last = 0;           // the plan of the entry before
     for (int k = 0; k < nk; ++k) {
@@ -569,14 +571,14 @@ template <typename F> static int without_exceptions(F &&f)
     }
 }
 
-extern "C" int tt_run_kernels(const tt_kernel_desc *kernels, const tt_schedule *const *scheds, int nk, int repeat, void *stream)
+static int run_kernels(const tt_kernel_desc *kernels, const tt_schedule *const *scheds, int nk, int repeat, bool as_recorded, void *stream)
 {
     if (nk < 0 || repeat < 0 || (nk && !kernels)) return TT_ERR_BAD_ARG;
     return without_exceptions([&]() {
         std::vector<PreparedOp> ops;
         for (int r = 0; r < repeat; ++r) {
             ops.clear();
-            const int rc = walk(kernels, scheds, nk, ops, [&](Window &w, int times) {
+            const int rc = walk(kernels, scheds, nk, as_recorded, ops, [&](Window &w, int times) {
                 for (int u = 1; u < times; ++u) {
                     Window again = w;
                     if (const int rc = send(again, stream); rc != TT_OK) return rc;
@@ -589,6 +591,16 @@ extern "C" int tt_run_kernels(const tt_kernel_desc *kernels, const tt_schedule *
     });
 }
 
+extern "C" int tt_run_kernels(const tt_kernel_desc *kernels, const tt_schedule *const *scheds, int nk, int repeat, void *stream)
+{
+    return run_kernels(kernels, scheds, nk, repeat, false, stream);
+}
+
+extern "C" int tt_run_kernels_as_recorded(const tt_kernel_desc *kernels, const tt_schedule *const *scheds, int nk, int repeat, void *stream)
+{
+    return run_kernels(kernels, scheds, nk, repeat, true, stream);
+}
+
 extern "C" int tt_debug_list(const tt_kernel_desc *kernels, const tt_schedule *const *scheds, int nk, tt_listed *out)
 {
     if (nk < 0 || (nk && (!kernels || !out))) return TT_ERR_BAD_ARG;
@@ -597,7 +609,7 @@ extern "C" int tt_debug_list(const tt_kernel_desc *kernels, const tt_schedule *c
         for (int k = 0; k < nk; ++k) out[k] = {-1, 0, 0, 0, 0, 0, 0};
         int launch = 0, tiles = 0;
         const ListTile *table = list_tiles(&tiles);
-        return walk(kernels, scheds, nk, ops, [&](Window &w, int) {
+        return walk(kernels, scheds, nk, false, ops, [&](Window &w, int) {
             for (const Launch &l : w.launches()) {
                 tt_listed as = {launch, l.tile != kOnePlan, 16, 16, l.family * 16, (int32_t)l.entries.size(), TT_LISTED_STREAM};
                 if (l.tile >= 0) {

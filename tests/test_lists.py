@@ -297,6 +297,30 @@ def test_entries_of_different_shapes_in_shared_launches(name, split):
     run_list_against_lone_calls(kernels, recs, without_bias=(0,) if split else (), check=check)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", ["bf16", "f32", "thin"])
+def test_a_list_as_recorded_runs_what_lone_calls_run(name):
+    """No two of these entries have one plan, so each has a launch to itself: the same bits."""
+    import torch
+    import parity as P
+    from paper_2201_05587_amd import harness
+    kernels = LISTS[name]
+    recs = [mfma(k.cls, **SPLIT) if i % 3 == 1 else mfma(k.cls, 16, 16, 16 if k.shape.dtype == wl.F32 else 32, 16, 16, 16, stages=2) if i % 3 == 2 else None
+            for i, k in enumerate(kernels)]
+    recs = [r if r is None or api.tt_schedule_apply(r, k.cls, k.shape).runnable() else None for k, r in zip(kernels, recs)]
+    assert any(recs)
+    dks = [harness.device_kernel(k, 60 + i, max_split=3) for i, k in enumerate(kernels)]
+    want = [P.run_gpu(k, dk, r) for k, dk, r in zip(kernels, dks, recs)]
+    for dk in dks:
+        dk.output().fill_(float("nan"))
+        dk.ws.fill_(255)
+    api.KernelList(dks, recs).run_as_recorded()
+    torch.cuda.synchronize()
+    for i, (k, dk, w) in enumerate(zip(kernels, dks, want)):
+        got = harness.output_in_definition_order(k, dk.output()).float().cpu().numpy()
+        np.testing.assert_array_equal(got, w, err_msg=str(i))
+
+
 def lists_by_tile():
     """The cheapest list of equal entries (ragged in every extent) of a grid of sizes that the rule runs in each of its
     tiles: (data type, convolution?, tile) -> (kernel, count)."""
