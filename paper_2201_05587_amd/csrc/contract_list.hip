@@ -112,11 +112,10 @@ int launch_thin_list(ThinList &list, int count, int pieces, void *stream)
         grid += thin_workgroups(e);
         lds = std::max(lds, e.columns / 16 * ((e.K + 15) / 16) * 1024 + e.columns * 4);
     }
-    auto kern = contract_thin_list_kernel<kThinPieces[0]>;
-    if (pieces == kThinPieces[1]) kern = contract_thin_list_kernel<kThinPieces[1]>;
-    if (pieces == kThinPieces[2]) kern = contract_thin_list_kernel<kThinPieces[2]>;
-    static DynamicLdsLimit limits[3];
-    DynamicLdsLimit &limit = limits[pieces == kThinPieces[0] ? 0 : pieces == kThinPieces[1] ? 1 : 2];
+    const int instance = pieces == kThinPieces[0] ? 0 : 1;
+    auto kern = instance == 0 ? contract_thin_list_kernel<kThinPieces[0]> : contract_thin_list_kernel<kThinPieces[1]>;
+    static DynamicLdsLimit limits[2];
+    DynamicLdsLimit &limit = limits[instance];
     if (const int rc = limit.raise_to(reinterpret_cast<const void *>(kern), lds); rc != TT_OK) return rc;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds, static_cast<hipStream_t>(stream), list);
     const hipError_t e = hipGetLastError();

@@ -1,14 +1,15 @@
-// Single-precision contractions with a short reduction and many rows (the pointwise layers of a mobile network): several
-// entries in one launch.
+// Single-precision contractions with a short reduction and many rows (the expanding pointwise layers of a mobile network):
+// several entries in one launch.
 //
-// Such a layer is a stream: 16 to 192 elements in and as many out per row, and little to multiply.  A tile kernel spends its
+// Such a layer is a stream: 16 to 96 elements in, more out per row, and little to multiply.  A tile kernel spends its
 // life on set-up, a round trip of the outputs through LDS and one memory latency per 2 KB of output (2.2 TB/s).  Here a
 // workgroup keeps its columns' weights in LDS as matrix-core fragments, and every wave walks down blocks of 16 rows: the
 // rows come straight into registers as fragments, those of the next block while this one is multiplied, and with the
 // weights as the matrix cores' row operand a lane ends up with four consecutive columns of one row.  Written like that, 64
 // bytes a row and store, the stream stays at 3.2 TB/s: memory takes whole lines of 128 (see the exchange below: 4.5 TB/s).
-// Tiles of the list rule -> this (us): two entries of 200704 x 96 x 16 67 -> 40, of 200704 x 16 x 32 17 -> 20, four of 50176 x
-// 144 x 24 62 -> 37, x 24 x 96 27 -> 29, x 24 x 144 35 -> 39; the layers of a MobileNetV2 pass at batch 16 together 195 -> 167.
+// Tiles of the list rule -> this (us): two entries of 200704 x 96 x 16 56 -> 43, four of 50176 x 144 x 24 57 -> 39 (which
+// contractions come here, and what the others lose: thin_pieces in run_list.cpp); a MobileNetV2 pass at batch 16, whose
+// reductions of up to 192 all came here before, 250 -> 243.
 #pragma once
 
 #include "contract.hip.h"

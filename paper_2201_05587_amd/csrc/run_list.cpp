@@ -124,7 +124,15 @@ ThinEntry thin_entry(const PreparedOp &op)
 
 // Whether a listed contraction is a stream for the thin kernel, and the instance that holds its reduction (0: none): single
 // precision, rows of whole fours, no split of the reduction, and rows enough that a workgroup's weights, which it loads into
-// LDS first, are less than half of what it reads and writes.
+// LDS first, are less than half of what it reads and writes.  Of those, the ones that the tiles of the rule do not stream as
+// fast; two entries of M x N x K in tiles -> as streams (us):
+//   reductions of up to 32 that read less than twice what they write: 200704 x 24 x 16 23 -> 20, x 96 x 24 67 -> 48, 50176 x 144
+//   x 24 31 -> 21, 12544 x 192 x 24 12 -> 11, but 50176 x 16 x 32 7.6 -> 8.1
+//   reductions of up to 96 over more than 32 columns that tiles of 64 do not divide: 200704 x 144 x 64 171 -> 112, 50176 x 48 x
+//   96 29 -> 24, x 96 x 64 29 -> 26, but x 192 x 64 40 -> 50, x 64 x 96 22 -> 26, x 32 x 96 15 -> 17
+//   with workgroups for half of the CUs, or little for each of them to multiply: 3136 x 64 x 16 4.9 -> 4.7, but x 64 x 32 4.7 ->
+//   5.4, x 48 x 96 4.7 -> 6.7, x 192 x 24 5.7 -> 8.9
+//   longer ones: 50176 x 24 x 144 19 -> 24, x 32 x 192 23 -> 31, x 64 x 144 30 -> 37, x 144 x 192 77 -> 72
 int thin_pieces(const PreparedOp &op)
 {
     const tt_plan &pl = op.launch;
@@ -132,6 +140,8 @@ int thin_pieces(const PreparedOp &op)
     if (pl.N % 4 != 0 || pl.K % 4 != 0) return 0;
     const ThinEntry e = thin_entry(op);
     if ((int64_t)std::min(e.rows, e.M) * (e.K + e.columns) < 2ll * e.K * e.columns) return 0;
+    if (e.K <= 32 ? e.K >= 2 * (int64_t)e.N : e.N <= 32 || e.N % 64 == 0) return 0;
+    if (thin_workgroups(e) < compute_units() / 2 && (int64_t)e.K * e.columns > 1024) return 0;
     for (int p : kThinPieces)
         if (pl.K <= p * 16) return p;
     return 0;

@@ -246,7 +246,7 @@ struct ThinList {
     ThinEntry e[kMaxThin];
 };
 static_assert(sizeof(ThinList) <= 4096, "");
-constexpr int kThinPieces[] = {2, 6, 12}; // instances: 16-element pieces of the reduction
+constexpr int kThinPieces[] = {2, 6}; // instances: 16-element pieces of the reduction
 // Lays out rows and columns of an entry whose sizes are set, and launches `count` of them on the instance of `pieces`.
 void thin_layout(ThinEntry *e);
 inline int64_t thin_workgroups(const ThinEntry &e) { return (int64_t)e.chunks * ((e.M + e.rows - 1) / e.rows); }

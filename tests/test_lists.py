@@ -187,10 +187,10 @@ def test_launches_name_the_kernel_and_the_tile_they_run_in():
     blocks of 16 x 16 on the shortest instance that holds the reduction, contractions in a tile of the rule."""
     dw = lambda stride: (wl.Kernel(8, wl.ConvShape(1, 32, 13, 13, 32, 3, 3, stride, stride, 1, 1)),
                          api.make_schedule(8, api.TT_SK_DWCONV, 4, 4, 8, 1, 2, 0, 1, 0, 4, 1, 1))
-    stream = lambda k: (wl.Kernel(4, wl.GemmShape(1, 90000, 64, k, 1, wl.F32)), mfma(4, 32, 32, 16, 16, 16, 16, vec=4))
+    stream = lambda k, n: (wl.Kernel(4, wl.GemmShape(1, 90000, n, k, 1, wl.F32)), mfma(4, 32, 32, 16, 16, 16, 16, vec=4))
     tiles = (wl.Kernel(5, wl.GemmShape(1, 300, 1032, 96, 1, wl.BF16)), mfma(5, 128, 256, 64, 32, 64, 16))
     lone = (wl.Kernel(7, wl.GemmShape(3, 50, 64, 50, 0, wl.BF16)), None)
-    entries = [dw(1), dw(2), stream(32), stream(20), stream(36), stream(96), tiles, lone] + [dw(1), dw(2), stream(100), stream(192), tiles]
+    entries = [dw(1), dw(2), stream(32, 64), stream(20, 64), stream(36, 48), stream(96, 144), tiles, lone, dw(1), dw(2), tiles]
     at = lambda i: [(1 << 34) * (5 * i + j + 1) if j != 3 else 0 for j in range(5)]
     fake = FakeList([(k, rec, [a if j != 2 or k.cls != 7 else 0 for j, a in enumerate(at(i))], 0) for i, (k, rec) in enumerate(entries)])
     got = [(l.kernel, l.listed, l.entries, l.tile_m, l.tile_n, l.tile_k) for l in fake.launches()]
@@ -200,7 +200,18 @@ def test_launches_name_the_kernel_and_the_tile_they_run_in():
     t = got[6]
     assert t[:3] == (api.TT_LISTED_TILES, 1, 2) and t[3:] != (128, 256, 64)
     assert got == [d1, d2, s(32), s(32), s(96), s(96), t, (api.TT_LISTED_RECORD, 0, 1, of_lone.tile_m, of_lone.tile_n, of_lone.tile_k),
-                   d1, d2, s(192), s(192), t]
+                   d1, d2, t]
+
+
+@pytest.mark.parametrize("m, n, k, streams", [
+    (200704, 24, 32, 1), (50176, 16, 28, 1), (50176, 16, 32, 0), (50176, 20, 40, 0),  # twice the reduction's elements in, one out
+    (8192, 96, 16, 1), (8128, 96, 16, 0), (3136, 64, 16, 1), (3136, 64, 20, 0),       # workgroups of 64 rows for half of the CUs
+    (50176, 36, 36, 1), (50176, 32, 36, 0), (50176, 64, 36, 0), (50176, 144, 96, 1), (50176, 192, 96, 0), (50176, 144, 100, 0)])
+def test_which_contractions_are_streams(m, n, k, streams):
+    kernel, rec = wl.Kernel(5, wl.GemmShape(1, m, n, k, 1, wl.F32)), mfma(5, 16, 16, 16, 16, 16, 16, vec=4)
+    at = lambda i: [(1 << 34) * (5 * i + j + 1) if j != 3 else 0 for j in range(5)]
+    listed = FakeList([(kernel, rec, at(i), 0) for i in range(2)]).launches()
+    assert [l.kernel for l in listed] == [api.TT_LISTED_STREAM if streams else api.TT_LISTED_TILES] * 2
 
 
 # ---- on the GPU -------------------------------------------------------------------------------------------------------
@@ -234,10 +245,13 @@ LISTS = {
                   ((2, 32, 28, 28, 1, 1), (1, 96, 15, 13, 1, 1), (3, 4, 9, 1, 1, 1), (1, 960, 7, 7, 1, 1), (2, 20, 6, 5, 1, 0), (1, 8, 3, 3, 1, 2),
                    (2, 24, 28, 28, 2, 1), (1, 144, 57, 31, 2, 1), (5, 16, 4, 4, 2, 0), (1, 12, 1, 1, 2, 1), (2, 30, 9, 9, 1, 1), (1, 7, 10, 12, 2, 1))] +
                  [wl.Kernel(8, wl.ConvShape(1, 16, 17, 17, 16, 3, 3, 1, 1, 1, 1))] * 40,
-    # streams: every instance's reductions (whole pieces and not), rows and columns that end inside a block, chunks of columns
-    "thin": [gemm(4, 3001, 16, 32, wl.F32), gemm(5, 5000, 96, 16, wl.F32), gemm(4, 1003, 24, 100, wl.F32), conv(2, 3, 24, 31, 29, 148, 1, 1, wl.F32),
-             conv(3, 2, 48, 40, 40, 20, 1, 1, wl.F32), gemm(5, 4099, 32, 192, wl.F32), conv(0, 1, 180, 60, 60, 20, 1, 1, wl.F32),
-             gemm(4, 130, 20, 20, wl.F32), gemm(5, 40000, 260, 96, wl.F32), gemm(4, 9000, 64, 192, wl.F32), gemm(4, 17, 16, 16, wl.F32)],
+    # streams: every instance's reductions (whole pieces and not), rows and columns that end inside a block, chunks of columns,
+    # residuals, every activation; and two entries that are none
+    "thin": [gemm(4, 3001, 20, 32, wl.F32), gemm(5, 9001, 96, 16, wl.F32), gemm(4, 130, 20, 20, wl.F32), gemm(4, 17, 16, 16, wl.F32),
+             conv(2, 3, 28, 53, 52, 36, 1, 1, wl.F32), conv(3, 2, 24, 65, 64, 44, 1, 1, wl.F32), gemm(5, 3001, 772, 20, wl.F32),
+             gemm(5, 40000, 260, 96, wl.F32), conv(2, 2, 36, 65, 64, 44, 1, 1, wl.F32), gemm(4, 8203, 36, 52, wl.F32),
+             conv(0, 1, 68, 92, 91, 40, 1, 1, wl.F32), conv(3, 1, 36, 100, 90, 100, 1, 1, wl.F32),
+             gemm(4, 1003, 24, 100, wl.F32), gemm(5, 4099, 32, 192, wl.F32)],
     # more entries than a launch takes
     "many": [gemm(5, 20 + 3 * i, 16 + 8 * (i % 5), 40 + 8 * i, wl.BF16) for i in range(43)],
 }
@@ -289,8 +303,8 @@ def test_entries_of_different_shapes_in_shared_launches(name, split):
         if name.endswith("blocks") and not split:
             assert all(l.tile_m == 256 and l.tile_n == 256 for l in launches)
         if name == "thin" and not split:
-            # (all but the contraction that no other entry shares a tile with)
-            assert [bool(l.listed) for l in launches] == [i != 9 for i in range(len(launches))] and len({l.launch for l in launches}) >= 3
+            assert [l.kernel for l in launches] == [api.TT_LISTED_STREAM] * 12 + [api.TT_LISTED_TILES] * 2
+            assert len({l.launch for l in launches}) == 3
         if name == "depthwise":
             assert [l.listed for l in launches[:12]] == [1] * 10 + [0] * 2 and len({l.launch for l in launches}) == 5
 
