@@ -224,6 +224,7 @@ def gemm(cls, m, n, k, dtype, batch=1):
 
 
 SPLIT = dict(tm=64, tn=64, tk=32, wm=32, wn=32, mf=32, split_k=3, stages=2)
+SPLIT_SMALL = dict(tm=16, tn=16, tk=32, wm=16, wn=16, mf=16, split_k=2, stages=2)
 LISTS = {
     # ragged in M, N and K, rows that are not whole vectors, residuals, strides, a 5x5, one pixel, every activation
     "bf16": [conv(1, 2, 40, 15, 11, 72, 3, 1, wl.BF16), conv(2, 1, 64, 17, 17, 61, 3, 2, wl.BF16), conv(0, 3, 8, 9, 9, 130, 1, 1, wl.BF16),
@@ -292,11 +293,13 @@ def test_entries_of_different_shapes_in_shared_launches(name, split):
     kernels = LISTS[name]
     recs = [None] * len(kernels)
     for i, k in enumerate(kernels):
-        rec = mfma(k.cls, **SPLIT)
-        if split and i % 2 and api.tt_schedule_apply(rec, k.cls, k.shape).runnable():
-            recs[i] = rec
-    if split and not any(recs):
-        pytest.skip("no entry of this list is as large as the split record's tile")
+        for fields in (SPLIT, SPLIT_SMALL):
+            rec = mfma(k.cls, **fields)
+            if split and i % 2 and recs[i] is None and api.tt_schedule_apply(rec, k.cls, k.shape).runnable():
+                recs[i] = rec
+    if split and name == "depthwise":
+        pytest.skip("a depthwise reduction has nine elements: no record splits it")
+    assert any(recs) == split
 
     def check(launches):
         assert len({l.launch for l in launches}) < len(kernels)
@@ -309,6 +312,80 @@ def test_entries_of_different_shapes_in_shared_launches(name, split):
             assert [l.listed for l in launches[:12]] == [1] * 10 + [0] * 2 and len({l.launch for l in launches}) == 5
 
     run_list_against_lone_calls(kernels, recs, without_bias=(0,) if split else (), check=check)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", ["thin", "depthwise", "f32", "bf16"])
+def test_infinities_and_nan_in_shared_launches(name):
+    """Elements behind a reduction, outside a window or in another row must not count, whatever they are: the outputs that are
+    no numbers are those of the lone calls (an activation takes a NaN to zero there and here), the others are as close."""
+    import torch
+    import parity as P
+    from paper_2201_05587_amd import harness
+    kernels = LISTS[name][:12]
+    dks = [harness.device_kernel(k, 20 + i, max_split=1) for i, k in enumerate(kernels)]
+    for dk in dks:
+        x = next(dk.tensors[t] for t in ("x", "a") if t in dk.tensors).view(-1)
+        for at, value in ((0, float("inf")), (x.numel() // 3, float("nan")), (x.numel() - 1, float("-inf"))):
+            x[at] = value
+    want = [P.run_gpu(k, dk) for k, dk in zip(kernels, dks)]
+    for dk in dks:
+        dk.output().fill_(7.0)
+    listed = api.KernelList(dks, [None] * len(dks))
+    assert any(l.listed for l in listed.launches())
+    listed.run()
+    torch.cuda.synchronize()
+    special = 0
+    for i, (k, dk, w) in enumerate(zip(kernels, dks, want)):
+        got = harness.output_in_definition_order(k, dk.output()).float().cpu().numpy()
+        for kind in (np.isnan, np.isposinf, np.isneginf):
+            np.testing.assert_array_equal(kind(got), kind(w), err_msg=f"{name} {i} {kind.__name__}")
+        special += int((~np.isfinite(w)).sum())
+        P.assert_close(np.where(np.isfinite(got), got, 0), np.where(np.isfinite(w), w, 0), k.shape.dtype, f"{name} {i}")
+    assert special > 0 or name == "depthwise"  # (clamped to six, a NaN to zero)
+
+
+@pytest.mark.gpu
+def test_lists_on_streams_of_their_own_from_threads_of_their_own():
+    """Three threads, each with a stream, tensors and workspaces of its own, plan and send their lists at the same time."""
+    import threading
+    import torch
+    import parity as P
+    from paper_2201_05587_amd import harness
+    names = ("f32", "bf16", "thin")
+    dks = [[harness.device_kernel(k, 100 * t + i, max_split=3) for i, k in enumerate(LISTS[n])] for t, n in enumerate(names)]
+    recs = [[mfma(k.cls, **SPLIT) if i == 0 and n != "thin" else None for i, k in enumerate(LISTS[n])] for n in names]
+    lists = [api.KernelList(d, r) for d, r in zip(dks, recs)]
+    want = []
+    for l, ds in zip(lists, dks):
+        l.run()
+        torch.cuda.synchronize()
+        want.append([d.output().clone() for d in ds])
+    for ds in dks:
+        for d in ds:
+            d.output().fill_(float("nan"))
+    torch.cuda.synchronize()
+    failed = []
+
+    def work(l):
+        try:
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                for _ in range(20):
+                    l.run()
+            stream.synchronize()
+        except Exception as e:  # (an assertion in a thread would pass unseen)
+            failed.append(e)
+
+    threads = [threading.Thread(target=work, args=(l,)) for l in lists]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed, failed
+    for n, ds, ws in zip(names, dks, want):
+        for i, (d, w) in enumerate(zip(ds, ws)):
+            assert torch.equal(d.output(), w), (n, i)
 
 
 @pytest.mark.gpu
