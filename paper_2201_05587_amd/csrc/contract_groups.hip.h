@@ -5,8 +5,9 @@
 // products.  Here KG groups of waves own the SAME output tile: every slice is KG times as deep (or is shared), the
 // groups take one part of it each, and their sums meet in LDS at the end.  One barrier then covers KG times the
 // matrix work, KG times the bytes are in flight, and four waves per SIMD overlap each other's LDS reads and
-// products.  Nothing the record defines changes (tile, grid, split of the reduction across workgroups), only how
-// many waves work on a tile.
+// products.  A launch under a record keeps what the record defines (tile, grid, split of the reduction across
+// workgroups); only how many waves work on a tile changes.  In a launch of several shapes the list rule names the tile
+// (run_list.cpp).
 //
 // Operands go through the asynchronous ring of contract.hip.h (same loaders, same chunk swizzle).  The epilogue
 // is shared by all groups too: each dumps its sums to LDS as a row-major tile, then every thread finishes whole

@@ -89,8 +89,8 @@ const ListTile *list_tiles(int *count)
 #undef TT_TILE
 #undef TT_GROUPS
 
-// Columns: as many as 48 KB of weights hold (three workgroups on a CU), in equal chunks.  Rows: eight turns of the four waves,
-// or what gives the launch some two thousand workgroups.
+// Columns: as many as 48 KB of weights hold (three workgroups on a CU), in equal chunks.  Rows: eight turns of the four waves;
+// four, two or one where the entry would have less than 384 workgroups, half as many again as CUs.
 void thin_layout(ThinEntry *e)
 {
     const int pieces = (e->K + 15) / 16, blocks = (e->N + 15) / 16, most = std::max(1, 48 * 1024 / (pieces * 1024));

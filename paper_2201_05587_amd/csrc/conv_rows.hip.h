@@ -3,10 +3,10 @@
 // The gathering register pipeline fetches every item of every filter row of every output pixel from memory, each with its
 // own address, border check, alignment shift and mask: that arithmetic, not the matrix products or the memory, was its time.
 // Here a workgroup keeps its filters in LDS and walks down the tiles of its columns; the input rows that a tile of pixels
-// touches are copied into LDS ONCE, with zeros where the padding is, and those of the next tile are on their way meanwhile.
-// (asynchronously, straight into LDS).  A fragment is then one LDS read at  pixel + filter row * pitch + chunk: no borders, and one mask for the chunk that ends
-// the run of S * C elements.  Nothing the record defines changes (the tile), only how it is computed; the reduction is walked
-// in one go, so records that split it keep the register pipeline.
+// touches are copied into LDS ONCE, with zeros where the padding is, and those of the next tile are on their way meanwhile
+// (asynchronously, straight into LDS).  A fragment is then one LDS read at  pixel + filter row * pitch + chunk: no borders,
+// and one mask for the chunk that ends the run of S * C elements.  The record's tile stays, its raster, slices and stages
+// have no meaning here; the reduction is walked in one go, so records that split it keep the register pipeline.
 #pragma once
 
 #include <algorithm>

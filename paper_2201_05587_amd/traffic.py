@@ -70,7 +70,7 @@ def _symbol(name: str) -> str:
     if name.startswith("void "):
         name = name[5:]
     name = name.replace("(anonymous namespace)::", "")
-    for args in ("(tt::ContractArgs", "(tt::DwArgs"):
+    for args in ("(tt::ContractArgs", "(tt::DwArgs", "(tt::ContractList", "(tt::ThinList", "(tt::DwList", "(tt::ReduceList"):
         cut = name.find(args)
         if cut >= 0:
             return name[:cut]

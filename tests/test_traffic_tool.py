@@ -42,3 +42,9 @@ def test_summarise_scales_by_the_copy_and_lookup_follows_the_digest(tmp_path, mo
     assert traffic.lookup("cfgY", SYM) is None
     (tmp_path / "csrc" / "k.hip").write_text("kernel v2")   # the kernel changed: the figure no longer applies
     assert traffic.lookup("cfgX", SYM) is None
+
+
+def test_counters_of_shared_launches_are_named_by_their_kernels():
+    for symbol, args in (("tt::contract_list_kernel<0, 1, 64, 64, 32, 16, 32, 16>", "tt::ContractList"), ("tt::contract_thin_list_kernel<2>", "tt::ThinList"),
+                         ("tt::dwconv3x3_list_kernel<1>", "tt::DwList"), ("tt::splitk_reduce_list_kernel<0, 4>", "tt::ReduceList")):
+        assert traffic._symbol(f"void {symbol}({args})") == symbol
