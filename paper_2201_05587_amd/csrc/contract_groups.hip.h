@@ -88,7 +88,7 @@ __device__ __forceinline__ void contract_groups_tile(std::conditional_t<LISTED, 
     typename AGat::State a_gat;
     typename BRows::State b_rows;
     if constexpr (CONV)
-        AGat::init(a_gat, g, tc.m0, tc.k0, tid);
+        AGat::template init<LISTED>(a_gat, g, tc.m0, tc.k0, tid);
     else
         ARows::init(a_rows, g.K, tc.m0, g.M, tid);
     BRows::init(b_rows, g.K, tc.n0, g.N, tid);

@@ -52,7 +52,7 @@ __global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) contract_list_kern
     const ListEntry &e = list.e[entry_of(list, (int)blockIdx.x, &first)];
     const int wg = (int)blockIdx.x - first;
     if (wg >= e.grid) return; // (entries begin at multiples of the number of XCDs)
-    contract_async_tile<DT, FAM, TM, TN, TK, WM, WN, MF>(args_of<DT, FAM, TM, TN, TK>(e), wg);
+    contract_async_tile<DT, FAM, TM, TN, TK, WM, WN, MF, true>(args_of<DT, FAM, TM, TN, TK>(e), wg);
 }
 
 template <int DT, int FAM, int TM, int TN, int WM, int WN, int MF>

@@ -157,6 +157,7 @@ void prepare_conv(const tt_conv_shape &s, PreparedOp *op)
     g.k_walk = s.r * g.runp;
     g.div_hw = make_fastdiv((uint32_t)(g.Ho * g.Wo));
     g.div_wo = make_fastdiv((uint32_t)g.Wo);
+    g.div_run = make_fastdiv((uint32_t)g.runp);
     g.PW = s.w + 2 * s.pad_w;
     g.PHW = (s.h + 2 * s.pad_h) * g.PW;
     g.div_phw = make_fastdiv((uint32_t)g.PHW);

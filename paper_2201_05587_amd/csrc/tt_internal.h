@@ -195,6 +195,7 @@ struct ContractArgs {
     int32_t C, H, W, R, S, stride_h, stride_w, pad_h, pad_w, Ho, Wo;
     int32_t run, runp;
     FastDiv div_hw, div_wo; // output pixel index -> (image, row, column)
+    FastDiv div_run;        // position in the walked reduction -> (filter row, position in the run): by runp
     // padded image geometry of the patch kernel: PW = W + 2 pad_w, PHW = (H + 2 pad_h) * PW
     int32_t PW, PHW;
     FastDiv div_phw, div_pw; // flat padded pixel index -> (image, padded row, padded column)
