@@ -49,8 +49,9 @@ template <int DT, int TM, int TN, int WM, int WN, int MF> struct GroupShape {
 // Tile `wg` of a contraction, in groups.  LISTED: the arguments are looked up in the launch, and the compiler has to be told that
 // addresses in LDS are the same for all lanes; where it knows, saying so costs two instructions a request (7.35 -> 7.40 us for
 // 64 channels on 56 x 56, 3x3, single precision).  There the arguments come by value: by reference the same statements were
-// scheduled otherwise, twelve instructions longer, and 128 channels on 8 x 28 x 28, 3x3, bf16, took 7.41 us where this takes 7.36
-// (the same record with a residual, 88 to 104 channels on 5 x 31 x 45: 7.07 and 7.01).
+// scheduled otherwise, twelve instructions longer, and 128 channels on 8 x 28 x 28, 3x3, bf16, took 7.41 us where this took 7.36
+// (the same record with a residual, 88 to 104 channels on 5 x 31 x 45: 7.07 and 7.01; both with the divisions that lone
+// launches make no longer, see AsyncGather).
 template <int DT, int FAM, int TM, int TN, int WM, int WN, int MF, bool LISTED>
 __device__ __forceinline__ void contract_groups_tile(std::conditional_t<LISTED, const ContractArgs &, const ContractArgs> g, int32_t wg)
 {
