@@ -191,10 +191,13 @@ struct Kind {
 
 // Estimated time (us) of the launches of a set of contractions when each takes the cheapest of some tiles (-1: none).  A
 // launch costs 2.5 us; its workgroups, the longest first, are dealt to the CUs, so its end is ragged by the shortest of them;
-// nothing is faster than the longest alone, or than memory.
+// nothing is faster than the longest alone, or than memory.  A tile that one entry alone would take is none to share, and an
+// entry with a launch to itself runs under its record: such sets do not count (a transformer layer of 2079 tokens, whose one
+// batched product took a tile of its own: 76 us, under its record 84, beside the others 75).
 constexpr int kTilesAtOnce = 3;
 double estimate(const std::vector<Kind> &kinds, const int (&tiles)[kTilesAtOnce], int *chosen)
 {
+    int count[kTilesAtOnce] = {};
     double sum[kTilesAtOnce] = {}, longest[kTilesAtOnce] = {}, bytes[kTilesAtOnce] = {}, least[kTilesAtOnce] = {1e30, 1e30, 1e30};
     for (size_t i = 0; i < kinds.size(); ++i) {
         const Kind &k = kinds[i];
@@ -203,6 +206,7 @@ double estimate(const std::vector<Kind> &kinds, const int (&tiles)[kTilesAtOnce]
             if (tiles[h] >= 0 && (pick < 0 || k.in[tiles[h]].all_us < k.in[tiles[pick]].all_us)) pick = h;
         if (pick < 0 || k.in[tiles[pick]].us >= kUnfit) return kUnfit;
         const auto &c = k.in[tiles[pick]];
+        count[pick] += k.count;
         sum[pick] += c.all_us;
         least[pick] = std::min(least[pick], c.us);
         longest[pick] = std::max(longest[pick], c.alone_us);
@@ -210,6 +214,8 @@ double estimate(const std::vector<Kind> &kinds, const int (&tiles)[kTilesAtOnce]
         if (chosen) chosen[i] = tiles[pick];
     }
     double us = 0;
+    for (int h = 0; h < kTilesAtOnce; ++h)
+        if (count[h] == 1) return kUnfit;
     for (int h = 0; h < kTilesAtOnce; ++h)
         if (sum[h] > 0) us += 2.5 + std::max({std::ceil(sum[h] / compute_units() / least[h]) * least[h], longest[h], bytes[h] / 5.0e6});
     return us;
@@ -436,10 +442,11 @@ private:
             }
             launch.clear(), grid = 0;
         };
-        for (int i : entries) {
-            const int64_t more = workgroups(i);
-            if ((int)launch.size() == most || grid + more > kMaxSharedGrid) close();
-            launch.push_back(i), grid += more;
+        for (size_t i = 0; i < entries.size(); ++i) {
+            const int64_t more = workgroups(entries[i]);
+            const bool leaves_one = (int)launch.size() == most - 1 && entries.size() - i == 2; // the last two share one
+            if ((int)launch.size() == most || leaves_one || grid + more > kMaxSharedGrid) close();
+            launch.push_back(entries[i]), grid += more;
         }
         close();
     }

@@ -153,33 +153,34 @@ def test_shared_launches_of_streams_stay_below_the_largest_grid():
         assert sum(l.launch == launch for l in listed) * ((1 << 25) // 512) <= 1 << 21
 
 
-def lone_launches():
+def list_ends():
     ring = lambda m, n, k, tile: (wl.Kernel(4, wl.GemmShape(1, m, n, k, 1, wl.BF16)), mfma(4, *tile))
-    conv21 = (wl.Kernel(1, wl.ConvShape(1, 128, 28, 28, 128, 3, 3, 1, 1, 1, 1, wl.BF16)), mfma(1, 64, 64, 64, 32, 32, 16))
+    conv = (wl.Kernel(1, wl.ConvShape(1, 128, 28, 28, 128, 3, 3, 1, 1, 1, 1, wl.BF16)), mfma(1, 64, 64, 64, 32, 32, 16))
     stream = lambda m, n, k: (wl.Kernel(4, wl.GemmShape(1, m, n, k, 1, wl.F32)), mfma(4, 32, 32, 32, 16, 16, 16, vec=4))
     dw = (wl.Kernel(8, wl.ConvShape(2, 32, 28, 28, 32, 3, 3, 1, 1, 1, 1)), None)
     return {
-        # no tile suits both: two launches of one entry
-        "apart": [ring(4096, 4096, 4096, (128, 256, 64, 32, 64, 16)), ring(64, 64, 64, (32, 32, 64, 16, 16, 16))],
-        # one more than a launch takes: of contractions, streams (with a contraction that is none), depthwise entries
-        "tail": [conv21] * 21, "streams": [stream(9000, 64, 32)] * 49, "beside_streams": [stream(9000, 64, 32)] * 2 + [stream(64, 64, 640)],
-        "depthwise": [dw] * 37, "one": [conv21], "one_stream": [stream(9000, 64, 32)],
+        # name -> (entries, sizes of their launches); what suits each by itself is no reason for launches of one
+        "apart": ([ring(4096, 4096, 4096, (128, 256, 64, 32, 64, 16)), ring(64, 64, 64, (32, 32, 64, 16, 16, 16))], [2]),
+        # one more than a launch takes: of contractions, streams, depthwise entries
+        "tail": ([conv] * 21, [2, 19]), "streams": ([stream(9000, 64, 32)] * 49, [2, 47]), "depthwise": ([dw] * 37, [2, 35]),
+        # nothing to share with
+        "one": ([conv], [1]), "one_stream": ([stream(9000, 64, 32)], [1]), "one_depthwise": ([dw], [1]),
+        "beside_streams": ([stream(9000, 64, 32)] * 2 + [stream(64, 64, 640)], [1, 2]),
+        "two_families": ([conv, ring(64, 64, 64, (32, 32, 64, 16, 16, 16))], [1, 1]),
     }
 
 
-@pytest.mark.parametrize("name", list(lone_launches()))
+@pytest.mark.parametrize("name", list(list_ends()))
 def test_an_entry_that_shares_no_launch_keeps_its_record(name):
-    entries = lone_launches()[name]
+    entries, sizes = list_ends()[name]
     at = lambda i: [(1 << 34) * (5 * i + j + 1) if j != 3 else 0 for j in range(5)]
     listed = FakeList([(k, rec, at(i), 0) for i, (k, rec) in enumerate(entries)]).launches()
-    lone = 0
+    assert sorted(l.entries for l in {l.launch: l for l in listed}.values()) == sizes
     for (k, rec), l in zip(entries, listed):
-        assert l.entries > 1 or not l.listed
+        assert bool(l.listed) == (l.entries > 1)
         if l.entries == 1:
             plan = api.tt_debug_launch(rec, k.cls, k.shape)[0]
             assert (l.tile_m, l.tile_n, l.tile_k) == (plan.tile_m, plan.tile_n, plan.tile_k)
-            lone += 1
-    assert lone == (2 if name == "apart" else 1)
 
 
 def test_launches_name_the_kernel_and_the_tile_they_run_in():
