@@ -182,7 +182,7 @@ Cut cut_into(const PreparedOp &op, const ListTile &t)
 // A plan of a window's contractions, how many entries have it, and what their tiles cost in every tile of the rule.
 struct Kind {
     const PreparedOp *op;
-    int count;
+    int count, own_tile; // entries; the tile of the rule that is its record's (-1: none)
     double bytes; // of all its entries
     struct {
         double all_us, us, alone_us; // of all its entries' tiles on one CU; of one; of one with the CU to itself
@@ -191,13 +191,14 @@ struct Kind {
 
 // Estimated time (us) of the launches of a set of contractions when each takes the cheapest of some tiles (-1: none).  A
 // launch costs 2.5 us; its workgroups, the longest first, are dealt to the CUs, so its end is ragged by the shortest of them;
-// nothing is faster than the longest alone, or than memory.  A tile that one entry alone would take is none to share, and an
-// entry with a launch to itself runs under its record: such sets do not count (a transformer layer of 2079 tokens, whose one
-// batched product took a tile of its own: 76 us, under its record 84, beside the others 75).
+// nothing is faster than the longest alone, or than memory.  An entry with a launch to itself runs under its record, so sets
+// that leave a tile to one entry count only where its record names that tile (a transformer layer of 2079 tokens, whose one
+// batched product would have a tile to itself: under its record, of another tile, 84 us, beside the others 75; a MobileNetV2
+// pass at batch 16 with a layer that has one, 16 x 16 x 16, in its record too: 243.5 us, with that layer beside others 248).
 constexpr int kTilesAtOnce = 3;
 double estimate(const std::vector<Kind> &kinds, const int (&tiles)[kTilesAtOnce], int *chosen)
 {
-    int count[kTilesAtOnce] = {};
+    int count[kTilesAtOnce] = {}, own[kTilesAtOnce] = {};
     double sum[kTilesAtOnce] = {}, longest[kTilesAtOnce] = {}, bytes[kTilesAtOnce] = {}, least[kTilesAtOnce] = {1e30, 1e30, 1e30};
     for (size_t i = 0; i < kinds.size(); ++i) {
         const Kind &k = kinds[i];
@@ -206,7 +207,7 @@ double estimate(const std::vector<Kind> &kinds, const int (&tiles)[kTilesAtOnce]
             if (tiles[h] >= 0 && (pick < 0 || k.in[tiles[h]].all_us < k.in[tiles[pick]].all_us)) pick = h;
         if (pick < 0 || k.in[tiles[pick]].us >= kUnfit) return kUnfit;
         const auto &c = k.in[tiles[pick]];
-        count[pick] += k.count;
+        count[pick] += k.count, own[pick] = k.own_tile;
         sum[pick] += c.all_us;
         least[pick] = std::min(least[pick], c.us);
         longest[pick] = std::max(longest[pick], c.alone_us);
@@ -215,7 +216,7 @@ double estimate(const std::vector<Kind> &kinds, const int (&tiles)[kTilesAtOnce]
     }
     double us = 0;
     for (int h = 0; h < kTilesAtOnce; ++h)
-        if (count[h] == 1) return kUnfit;
+        if (count[h] == 1 && own[h] != tiles[h]) return kUnfit;
     for (int h = 0; h < kTilesAtOnce; ++h)
         if (sum[h] > 0) us += 2.5 + std::max({std::ceil(sum[h] / compute_units() / least[h]) * least[h], longest[h], bytes[h] / 5.0e6});
     return us;
@@ -485,7 +486,10 @@ private:
         }
         for (Kind &k : kinds) {
             k.bytes = k.count * ((double)k.op->a_bytes + k.op->b_bytes + k.op->out_bytes * (k.op->cls == TT_CONV2D_BIAS_ADD_RELU ? 2.0 : 1.0));
+            const tt_plan &pl = k.op->launch;
+            k.own_tile = -1;
             for (int t = 0; t < n_tiles; ++t) {
+                if (tiles[t].dtype == dt && tiles[t].tile_m == pl.tile_m && tiles[t].tile_n == pl.tile_n && tiles[t].tile_k == pl.tile_k) k.own_tile = t;
                 if (tiles[t].dtype != dt || (tiles[t].blocks && !block_tile_fits(*k.op))) {
                     k.in[t] = {kUnfit, kUnfit, kUnfit};
                     continue;

@@ -159,8 +159,9 @@ def list_ends():
     stream = lambda m, n, k: (wl.Kernel(4, wl.GemmShape(1, m, n, k, 1, wl.F32)), mfma(4, 32, 32, 32, 16, 16, 16, vec=4))
     dw = (wl.Kernel(8, wl.ConvShape(2, 32, 28, 28, 32, 3, 3, 1, 1, 1, 1)), None)
     return {
-        # name -> (entries, sizes of their launches); what suits each by itself is no reason for launches of one
-        "apart": ([ring(4096, 4096, 4096, (128, 256, 64, 32, 64, 16)), ring(64, 64, 64, (32, 32, 64, 16, 16, 16))], [2]),
+        # name -> (entries, sizes of their launches); a launch of one is a choice only where its record names the tile
+        "apart": ([ring(4096, 4096, 4096, (128, 256, 64, 32, 64, 16)), ring(64, 64, 64, (32, 32, 64, 16, 16, 16))], [1, 1]),
+        "together": ([ring(4096, 4096, 4096, (64, 64, 32, 32, 32, 16)), ring(64, 64, 64, (32, 32, 32, 16, 16, 16))], [2]),
         # one more than a launch takes: of contractions, streams, depthwise entries
         "tail": ([conv] * 21, [2, 19]), "streams": ([stream(9000, 64, 32)] * 49, [2, 47]), "depthwise": ([dw] * 37, [2, 35]),
         # nothing to share with
