@@ -1143,10 +1143,11 @@ template <int DT, int ROWS, int TK, int THREADS> struct AsyncGather {
         int32_t jlo[NL], jhi[NL];
         int32_t r, j, dr, dj, runp, row_stride;
     };
-    // LISTED: the launch holds several shapes and no reciprocal of the run.  Two emulated divisions are a fifth of the
-    // instructions before the first request: without them the lone launches of a tile a CU go 7.40 -> 7.15 us (128 channels
-    // on 8 x 28 x 28, 3x3, bf16), 7.43 -> 7.20 (64 on 56 x 56, single precision) and 7.14 -> 6.97 (88 to 104 on 5 x 31 x 45, a
-    // residual); a list of 19 single-precision layers went from 68.1 to 70.6 us with them.
+    // LISTED: the launch holds several shapes and no reciprocal of the run.  The two emulated divisions are 36 of some 320
+    // instructions before the first request, and chains of dependent ones: without them the lone launches of a tile a CU go
+    // 7.40 -> 7.15 us (128 channels on 8 x 28 x 28, 3x3, bf16), 7.43 -> 7.20 (64 on 56 x 56, single precision) and 7.14 ->
+    // 6.97 (88 to 104 on 5 x 31 x 45, a residual); a list of 19 single-precision layers went from 68.1 to 70.6 us with
+    // reciprocals, and keeps the divisions.
     template <bool LISTED> static __device__ __forceinline__ void init(State &st, const ContractArgs &g, int row0, int k0, int tid)
     {
         const int first = tid / CPR, pos = tid % CPR;
