@@ -3,13 +3,13 @@
 
 A step is one network-shaped pass over the workload's fused kernels, each under the best
 TRANSFERRED schedule (the fastest valid donor record of its class, or the default as fallback:
-KernelList.run_as_recorded; the pass in shared launches, whose tiles the library chooses, is
-reported beside it), with all inputs resident in HBM and every launch of the pass on tensors of its own (a network's
-layers do not share weights or activations; the pass touches far more than the caches hold, so
-every launch finds its operands cold).  `value` is the pass's algorithmic FLOPs over its time; the
-time of the same launches repeated on one set of tensors per kernel is reported beside it as the
-cache-warm figure.  The same run re-times, per kernel, the record an exhaustive native sweep found
-and reports the transferred schedule's speed as a fraction of it.
+KernelList.run_as_recorded), with all inputs resident in HBM and every launch of the pass on
+tensors of its own (a network's layers do not share weights or activations; the pass touches far
+more than the caches hold, so every launch finds its operands cold).  `value` is the pass's
+algorithmic FLOPs over its time.  Reported beside it: the same pass in shared launches, whose tiles
+the library chooses (KernelList.run), and the launches repeated on one set of tensors per kernel,
+the cache-warm figure.  The same run re-times, per kernel, the record an exhaustive native sweep
+found and reports the transferred schedule's speed as a fraction of it.
 
 The sweeps are the search, not the step.  The records the timed pass uses are the stored outcome of
 `--sweep` (tuned/<workload>.json, with the donor pool in tuned/<workload>.pool), the same records

@@ -641,6 +641,19 @@ def test_reduction_split_inside_the_workgroup(api, P, name, cls, shape, rec):
     P.check_kernel(wl.Kernel(cls, shape, 1, name), recs, seed=4321)
 
 
+# ---- runs of a filter row against the slices that walk them (lone gathers find their filter row by a reciprocal) -------------
+@pytest.mark.parametrize("dt", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("c,f,stride", [(8, 1, 2), (32, 1, 2), (64, 1, 2), (72, 1, 2), (8, 5, 1), (24, 3, 1), (40, 3, 2), (128, 3, 1), (200, 3, 1)])
+def test_filter_rows_shorter_and_longer_than_a_slice(api, P, c, f, stride, dt):
+    """Runs of 8 to 600 elements, several a slice, a slice each, and slices that straddle them; with and without a split."""
+    kernel = conv_kernel(wl.CLS_CONV2D_BIAS_RELU, 2, c, 11, 40, f, stride, dtype=dt)
+    shapes = [(32, 32, 32, 16, 16, 16), (64, 32, 32, 32, 32, 32), (32, 32, 64, 16, 16, 16)]
+    recs = [mfma(api, kernel.cls, *s, split_k=split, stages=3) for s in shapes for split in (1, 2)]
+    recs = [r for r in recs if api.tt_schedule_apply(r, kernel.cls, kernel.shape).runnable()]
+    assert c * f * f < 32 or recs
+    P.check_kernel(kernel, [None] + recs, seed=57)
+
+
 # ---- entries of one plan that a list sends out as one launch ---------------------------------------------------------
 @pytest.mark.parametrize("name,kernel,rec", [
     ("ring", wl.Kernel(4, wl.GemmShape(1, 96, 96, 96, 1, wl.BF16)), dict(tm=32, tn=32, tk=32, wm=16, wn=16, mf=16, stages=3)),
