@@ -557,34 +557,67 @@ template <int TM, int WM, int WN, int MF> struct TileOut {
     }
 };
 
-// `count` (1..8) consecutive outputs of one row, starting at element `at` of the output (column `n`), from
-// the 8 staged sums lo, hi: bias, residual, activation, conversion and store one element at a time, or the
-// raw sums into the split-K workspace.  Everything is passed by value so that the call needs no stack.
-template <int DT>
-__device__ __noinline__ void write_row_elements(float *ws, void *out, const void *bias, const void *res, bool partial,
-                                                bool has_bias, bool has_res, int act, int64_t at, int n, int count,
-                                                f32x4 lo, f32x4 hi)
+// Rows that are no whole vectors long begin at any element, and their last vector is one in part.  The memory takes 16-byte
+// accesses at any element's address (13 MB of bf16 in tiles of 64 columns: 4.0 us where rows are whole vectors, 4.9 where they
+// are odd; stored element by element 7.4, and streaming 7.5, since lines then leave the L2 in parts), so only that last one is
+// taken apart.  `count`: how many elements from `at` there are, 1 .. CH or more.
+template <int DT> __device__ __forceinline__ u32x4 load_piece(const void *p, int64_t at, int count)
 {
-#pragma unroll 1
-    for (int e = 0; e < count; ++e) {
-        float a = lo[0];
+    using E = typename ElemOf<DT>::type;
+    constexpr int CH = ElemOf<DT>::CH;
+    const E *const from = static_cast<const E *>(p) + at;
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (count >= CH) {
+        load16(v, from);
+    } else {
 #pragma unroll
-        for (int t = 1; t < 8; ++t) a = e == t ? (t < 4 ? lo[t] : hi[t - 4]) : a; // (registers cannot be indexed)
-        if (partial) {
-            ws[at + e] = a;
-            continue;
+        for (int e = 0; e < CH - 1; ++e)
+            if (e < count) {
+                if constexpr (DT == TT_F32)
+                    v[e] = __float_as_uint(from[e]);
+                else
+                    v[e / 2] |= (uint32_t)from[e] << (16 * (e % 2));
+            }
+    }
+    return v;
+}
+// (`e` is a constant where this is used)
+template <int DT> __device__ __forceinline__ float element_of(const u32x4 &v, int e)
+{
+    return DT == TT_F32 ? __uint_as_float(v[e % 4]) : __uint_as_float(e % 2 == 0 ? v[e / 2] << 16 : v[e / 2] & 0xffff0000u);
+}
+template <int DT> __device__ __forceinline__ void store_piece(void *p, int64_t at, u32x4 v, int count)
+{
+    using E = typename ElemOf<DT>::type;
+    E *to = static_cast<E *>(p) + at;
+    if (count >= ElemOf<DT>::CH) {
+        __builtin_memcpy(to, &v, 16);
+        return;
+    }
+    if constexpr (DT == TT_BF16) {
+        if (count & 4) {
+            __builtin_memcpy(to, &v, 8);
+            to += 4, v[0] = v[2], v[1] = v[3];
         }
-        if (has_bias) a += load_as_float<DT>(bias, n + e);
-        if (has_res) a += load_as_float<DT>(res, at + e);
-        store_from_float<DT>(out, at + e, apply_act(a, act));
+        if (count & 2) {
+            __builtin_memcpy(to, &v, 4);
+            to += 2, v[0] = v[1];
+        }
+        if (count & 1) *to = (uint16_t)v[0];
+    } else {
+        if (count & 2) {
+            __builtin_memcpy(to, &v, 8);
+            to += 2, v[0] = v[2];
+        }
+        if (count & 1) *to = __uint_as_float(v[0]);
     }
 }
 
 // The bias of the 8 output columns a lane finishes in the epilogue (the same for every row), as raw
 // bits.  Requested at the start of a kernel, so that its memory latency runs under the K loop; a load
 // inside the epilogue's loops would be repeated per pass at full latency, because the compiler cannot
-// move it across the stores.  Zero where the vector path does not apply (no bias, split-K partials,
-// rows that are not whole 16-byte vectors long: that path reads the bias element by element).
+// move it across the stores.  Zero where the vector path does not apply (no bias, split-K partials, rows
+// that are not whole 16-byte vectors long: the epilogue fetches theirs).
 template <int DT> struct BiasRegs {
     u32x4 raw[DT == TT_BF16 ? 1 : 2];
 };
@@ -737,6 +770,62 @@ __device__ __forceinline__ void write_row_four(const ContractArgs &g, float *ws,
     __builtin_nontemporal_store(f32x4{sum[0], sum[1], sum[2], sum[3]}, reinterpret_cast<f32x4 *>(static_cast<float *>(g.out) + row_at));
 }
 
+// `count` outputs (up to 8; fp32: 4, from `lo`) of a row that is no whole vectors long, in the same order: bias (the piece of its
+// columns), residual (fetched here, a round trip for every row: such layers are rare), activation.
+template <int DT>
+__device__ __forceinline__ void write_row_piece(float *ws, void *out, const void *res, bool partial, int act, int64_t at, int count, const f32x4 &lo,
+                                                const f32x4 &hi, const u32x4 &bias)
+{
+    if (partial) {
+        store_piece<TT_F32>(ws, at, __builtin_bit_cast(u32x4, lo), count);
+        if (DT == TT_BF16 && count > 4) store_piece<TT_F32>(ws, at + 4, __builtin_bit_cast(u32x4, hi), count - 4);
+        return;
+    }
+    constexpr int CH = ElemOf<DT>::CH;
+    float val[CH];
+#pragma unroll
+    for (int e = 0; e < CH; ++e) val[e] = (e < 4 ? lo[e % 4] : hi[e % 4]) + element_of<DT>(bias, e);
+    u32x4 v;
+    if (res) {
+        v = load_piece<DT>(res, at, count);
+#pragma unroll
+        for (int e = 0; e < CH; ++e) val[e] += element_of<DT>(v, e);
+    }
+    if (act == ACT_GELU) { // one at a time: called or interleaved, it would raise what the whole kernel holds in registers
+#pragma unroll 1
+        for (int e = 0; e < CH; ++e) {
+            const float done = apply_act(val[0], ACT_GELU);
+#pragma unroll
+            for (int t = 0; t + 1 < CH; ++t) val[t] = val[t + 1];
+            val[CH - 1] = done;
+        }
+    } else {
+        const float most = act == ACT_RELU6 ? 6.0f : INFINITY;
+        if (act != ACT_NONE)
+#pragma unroll
+            for (int e = 0; e < CH; ++e) val[e] = fminf(fmaxf(val[e], 0.0f), most);
+    }
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        if constexpr (DT == TT_F32)
+            v[h] = __float_as_uint(val[h]);
+        else
+            v[h] = pack_bf16x2(val[2 * h], val[2 * h + 1]);
+    }
+    store_piece<DT>(out, at, v, count);
+}
+// Up to 8 outputs of such a row, out of line and with everything by value, for kernels that write few of them a thread.
+template <int DT>
+__device__ __noinline__ void write_row_in_pieces(float *ws, void *out, const void *bias, const void *res, bool partial, int act, int64_t at, int first,
+                                                 int count, f32x4 lo, f32x4 hi)
+{
+    const bool add = bias && !partial;
+    const u32x4 none = {0u, 0u, 0u, 0u};
+    write_row_piece<DT>(ws, out, res, partial, act, at, count, lo, hi, add ? load_piece<DT>(bias, first, count) : none);
+    if (DT == TT_F32 && count > 4)
+        write_row_piece<DT>(ws, out, res, partial, act, at + 4, count - 4, hi, hi, add ? load_piece<DT>(bias, first + 4, count - 4) : none);
+}
+
 // The bias of 8 columns as floats.
 template <int DT> __device__ __forceinline__ void unpack_bias(float (&biasf)[8], const BiasRegs<DT> &bias)
 {
@@ -752,28 +841,43 @@ template <int DT> __device__ __forceinline__ void unpack_bias(float (&biasf)[8],
     }
 }
 
+__device__ __forceinline__ uint32_t lds_address(const void *p)
+{
+    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char *)p;
+}
+
 template <int N> __device__ __forceinline__ void wait_loads_outstanding(); // (defined with the asynchronous loaders)
 
-// WAIT_LOADS: the caller has asynchronous requests in flight that must have landed before the first store
-// is issued (a persistent kernel's next tile); the wait sits behind the staging of the first band.
-// ANY_ROWS: false where the host has checked that rows are whole 16-byte vectors long.
-template <int DT, int TM, int WM, int WN, int MF, typename Acc, bool ALLOW, bool WAIT_LOADS = false, bool ANY_ROWS = true>
-__device__ __forceinline__ void write_tile(Acc (&acc)[WM / MF][WN / MF], const ContractArgs &g, const TileCoord &tc,
-                                           unsigned char *smem, int wave, int lane, const BiasRegs<DT> &bias,
-                                           const ResRegs<DT, TM, WM, WN, MF, ALLOW> &early)
+// One band of a wave's sums into its staging region.
+template <int WN, int MF, typename Acc> __device__ __forceinline__ void stage_band(float *stage, const Acc (&band)[WN / MF], int lane_r, int lane_g)
+{
+    constexpr int ACC = MF * MF / 64, ESTRIDE = WN + (MF == 32 ? 8 : 4);
+    asm volatile("" ::: "memory"); // the reads of the band before stay ahead of these writes
+#pragma unroll
+    for (int j = 0; j < WN / MF; ++j)
+#pragma unroll
+        for (int v = 0; v < ACC; ++v) {
+            const int row_l = MF == 32 ? (v / 4) * 8 + lane_g * 4 + (v % 4) : lane_g * 4 + v;
+            stage[row_l * ESTRIDE + j * MF + lane_r] = band[j][v];
+        }
+    asm volatile("" ::: "memory"); // and the reads below stay behind them
+}
+
+// The tile of a matrix whose rows are whole vectors long: the lane's 8 columns (fp32: 4 columns of two rows) need no further
+// checks and no loop.
+template <int DT, int TM, int WM, int WN, int MF, typename Acc, bool ALLOW, bool WAIT_LOADS>
+__device__ __forceinline__ void write_tile_whole(Acc (&acc)[WM / MF][WN / MF], const ContractArgs &g, const TileCoord &tc,
+                                                 float *stage, int wave, int lane, const BiasRegs<DT> &bias,
+                                                 const ResRegs<DT, TM, WM, WN, MF, ALLOW> &early)
 {
     using R = ResRegs<DT, TM, WM, WN, MF, ALLOW>;
     using T = TileOut<TM, WM, WN, MF>;
-    constexpr int NI = T::NI, NJ = T::NJ, ACC = T::ACC, ESTRIDE = T::ESTRIDE, CG = T::CG, PASSES = T::PASSES;
+    constexpr int NI = T::NI, ESTRIDE = T::ESTRIDE, CG = T::CG, PASSES = T::PASSES;
     const int lane_r = lane % MF, lane_g = lane / MF;
-    const int bidx = tc.hi;
-    float *stage = reinterpret_cast<float *>(smem) + wave * (MF * ESTRIDE);
     const bool partial = g.map.eff_split_k > 1;
     const int64_t mn = (int64_t)g.M * g.N;
     float *ws = g.ws + ((int64_t)tc.lo * g.batch) * mn;
-    const int vc = g.eff_vec_c; // consecutive outputs of a row that are all inside or all outside the matrix
-    const bool whole = !ANY_ROWS || (DT == TT_BF16 ? vc == 8 : vc >= 4); // rows are whole 16-byte vectors long
-    const int64_t out_base = (int64_t)bidx * mn;
+    const int64_t out_base = (int64_t)tc.hi * mn;
     const int cg = lane % CG;
     const int first = tc.n0 + T::col(wave, lane);
 
@@ -789,7 +893,7 @@ __device__ __forceinline__ void write_tile(Acc (&acc)[WM / MF][WN / MF], const C
         // the residuals of this band's rows (where they were not requested at kernel start): all passes
         // before the staging, so that their latency runs in parallel instead of once per pass
         u32x4 resv[PASSES][R::W];
-        if (whole && !partial && g.has_res) {
+        if (!partial && g.has_res) {
 #pragma unroll
             for (int ps = 0; ps < PASSES; ++ps) {
                 if constexpr (R::EARLY) {
@@ -800,57 +904,80 @@ __device__ __forceinline__ void write_tile(Acc (&acc)[WM / MF][WN / MF], const C
                 }
             }
         }
-        asm volatile("" ::: "memory"); // the reads of the band before stay ahead of these writes
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-            for (int v = 0; v < ACC; ++v) {
-                const int row_l = MF == 32 ? (v / 4) * 8 + lane_g * 4 + (v % 4) : lane_g * 4 + v;
-                stage[row_l * ESTRIDE + j * MF + lane_r] = acc[i][j][v];
-            }
-        asm volatile("" ::: "memory"); // and the reads below stay behind them
+        stage_band<WN, MF>(stage, acc[i], lane_r, lane_g);
         if constexpr (WAIT_LOADS)
             if (i == 0) wait_loads_outstanding<0>();
-        if (whole) {
-            // Rows are whole vectors long: the lane's 8 columns (fp32: 4 columns of two rows) need no
-            // further checks and no loop.
-            if constexpr (DT == TT_F32) {
-                const int first4 = tc.n0 + T::col4(wave, lane);
+        if constexpr (DT == TT_F32) {
+            const int first4 = tc.n0 + T::col4(wave, lane);
 #pragma unroll
-                for (int ps = 0; ps < PASSES; ++ps)
+            for (int ps = 0; ps < PASSES; ++ps)
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const int row_l = T::row_in_band4(lane, ps, h), m = tc.m0 + (wave % T::NWR) * WM + i * MF + row_l;
-                        if (!T::half_live(lane, ps, h) || m >= g.M || first4 >= g.N) continue;
-                        const f32x4 v = *reinterpret_cast<const f32x4 *>(stage + row_l * ESTRIDE + (lane % T::CG4) * 4);
-                        write_row_four(g, ws, partial, out_base + (int64_t)m * g.N + first4, v, biasf, resv[ps][h]);
-                    }
-            } else {
-#pragma unroll
-                for (int ps = 0; ps < PASSES; ++ps) {
-                    const int row_l = ps * T::ROWS_PER_PASS + lane / CG;
-                    const int m = tc.m0 + T::row(wave, lane, i, ps);
-                    if (!T::pass_live(lane, ps) || m >= g.M || first >= g.N) continue;
-                    const f32x4 lo = *reinterpret_cast<const f32x4 *>(stage + row_l * ESTRIDE + cg * 8);
-                    const f32x4 hi = *reinterpret_cast<const f32x4 *>(stage + row_l * ESTRIDE + cg * 8 + 4);
-                    write_row_vector<DT>(g, ws, partial, out_base + (int64_t)m * g.N + first, first, lo, hi, biasf, resv[ps]);
+                for (int h = 0; h < 2; ++h) {
+                    const int row_l = T::row_in_band4(lane, ps, h), m = tc.m0 + (wave % T::NWR) * WM + i * MF + row_l;
+                    if (!T::half_live(lane, ps, h) || m >= g.M || first4 >= g.N) continue;
+                    const f32x4 v = *reinterpret_cast<const f32x4 *>(stage + row_l * ESTRIDE + (lane % T::CG4) * 4);
+                    write_row_four(g, ws, partial, out_base + (int64_t)m * g.N + first4, v, biasf, resv[ps][h]);
                 }
-            }
-        } else if constexpr (ANY_ROWS) {
-            // any other row length: element by element, out of line (rare, and it must not cost the
-            // path above registers or code)
-#pragma unroll 1
+        } else {
+#pragma unroll
             for (int ps = 0; ps < PASSES; ++ps) {
                 const int row_l = ps * T::ROWS_PER_PASS + lane / CG;
                 const int m = tc.m0 + T::row(wave, lane, i, ps);
                 if (!T::pass_live(lane, ps) || m >= g.M || first >= g.N) continue;
                 const f32x4 lo = *reinterpret_cast<const f32x4 *>(stage + row_l * ESTRIDE + cg * 8);
                 const f32x4 hi = *reinterpret_cast<const f32x4 *>(stage + row_l * ESTRIDE + cg * 8 + 4);
-                write_row_elements<DT>(ws, g.out, g.bias, g.res, partial, g.has_bias, g.has_res, g.act,
-                                       out_base + (int64_t)m * g.N + first, first, min(8, g.N - first), lo, hi);
+                write_row_vector<DT>(g, ws, partial, out_base + (int64_t)m * g.N + first, first, lo, hi, biasf, resv[ps]);
             }
         }
     }
+}
+
+// The tile of any other matrix: the same pieces of rows, but a piece may be one in part, and the rows of a band are taken in a
+// rolled loop (some 100 instructions; unrolled they would be most of the kernel).
+template <int DT, int TM, int WM, int WN, int MF, typename Acc, bool WAIT_LOADS>
+__device__ __forceinline__ void write_tile_pieces(Acc (&acc)[WM / MF][WN / MF], const ContractArgs &g, const TileCoord &tc, float *stage, int wave, int lane)
+{
+    using T = TileOut<TM, WM, WN, MF>;
+    constexpr int PER_ROW = DT == TT_F32 ? T::CG4 : T::CG, COLUMNS = DT == TT_F32 ? 4 : 8, STEP = 64 / PER_ROW;
+    const bool partial = g.map.eff_split_k > 1;
+    const int64_t mn = (int64_t)g.M * g.N;
+    float *ws = g.ws + ((int64_t)tc.lo * g.batch) * mn;
+    const int row = lane / PER_ROW, n = tc.n0 + (wave / T::NWR) * WN + lane % PER_ROW * COLUMNS;
+    u32x4 bias = {0u, 0u, 0u, 0u};
+    if (!partial && g.has_bias && n < g.N) bias = load_piece<DT>(g.bias, n, g.N - n);
+    __syncthreads(); // (see write_tile_whole)
+#pragma unroll
+    for (int i = 0; i < T::NI; ++i) {
+        stage_band<WN, MF>(stage, acc[i], lane % MF, lane / MF);
+        if constexpr (WAIT_LOADS)
+            if (i == 0) wait_loads_outstanding<0>();
+        const int m0 = tc.m0 + (wave % T::NWR) * WM + i * MF, rows = n < g.N ? min(MF, g.M - m0) : 0;
+#pragma unroll 1
+        for (int r = row; r < rows; r += STEP) {
+            const float *const from = stage + r * T::ESTRIDE + lane % PER_ROW * COLUMNS;
+            const f32x4 lo = *reinterpret_cast<const f32x4 *>(from);
+            const f32x4 hi = DT == TT_F32 ? lo : *reinterpret_cast<const f32x4 *>(from + 4);
+            write_row_piece<DT>(ws, g.out, g.has_res ? g.res : nullptr, partial, g.act, tc.hi * mn + (int64_t)(m0 + r) * g.N + n, g.N - n, lo, hi, bias);
+        }
+    }
+}
+
+// WAIT_LOADS: the caller has asynchronous requests in flight that must have landed before the first store
+// is issued (a persistent kernel's next tile); the wait sits behind the staging of the first band.
+// ANY_ROWS: false where the host has checked that rows are whole 16-byte vectors long.
+// The two are apart from the barrier on: with the second's loop inside the first's bands 64 x 64 x 64 bf16 tiles of whole rows
+// took 6.8 us for 6.5, and with it out of line a call had to wait for the stores before it (167 x 167 products 5.1 us, here 4.9;
+// the element loop that was there before 11.0).
+template <int DT, int TM, int WM, int WN, int MF, typename Acc, bool ALLOW, bool WAIT_LOADS = false, bool ANY_ROWS = true>
+__device__ __forceinline__ void write_tile(Acc (&acc)[WM / MF][WN / MF], const ContractArgs &g, const TileCoord &tc,
+                                           unsigned char *smem, int wave, int lane, const BiasRegs<DT> &bias,
+                                           const ResRegs<DT, TM, WM, WN, MF, ALLOW> &early)
+{
+    float *const stage = reinterpret_cast<float *>(smem) + wave * (MF * TileOut<TM, WM, WN, MF>::ESTRIDE);
+    if (__builtin_expect(!ANY_ROWS || (DT == TT_BF16 ? g.eff_vec_c == 8 : g.eff_vec_c >= 4), 1))
+        write_tile_whole<DT, TM, WM, WN, MF, Acc, ALLOW, WAIT_LOADS>(acc, g, tc, stage, wave, lane, bias, early);
+    else
+        write_tile_pieces<DT, TM, WM, WN, MF, Acc, WAIT_LOADS>(acc, g, tc, stage, wave, lane);
 }
 
 // How many consecutive steps of a slice have their fragment reads issued together, ahead of the first
@@ -1097,11 +1224,6 @@ template <int N> __device__ __forceinline__ void wait_loads_outstanding()
 {
     static_assert(N >= 0 && N < 64, "vector-memory counter range");
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
-__device__ __forceinline__ uint32_t lds_address(const void *p)
-{
-    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char *)p;
 }
 
 // Rows of a K-contiguous matrix [rows_total][K], K a multiple of the items' element count.
