@@ -478,7 +478,8 @@ int tt_schedule_space(int cls, int dtype, int level, tt_schedule *out, int cap);
  * same tiles; TT_LAUNCH_BLOCKS, contract_block_kernel in blocks of 256 x 256; TT_LAUNCH_ROWS, conv_rows_kernel in the
  * same tiles.  launched: the plan as it is launched, with
  * grid, block and lds_bytes of the kernel that runs (per entry; the persistent kernel of seven stages divides its grid
- * among fewer workgroups).  Returns the apply status, TT_ERR_BAD_ARG for a count out of range, or TT_ERR_UNSUPPORTED where
+ * among fewer workgroups), and for a depthwise record of one stage and equal strides the wave_m x wave_n outputs of eff_vec_a
+ * channels that a thread forms there, whatever the record's (dwconv3x3_window_kernel).  Returns the apply status, TT_ERR_BAD_ARG for a count out of range, or TT_ERR_UNSUPPORTED where
  * the operator would.
  */
 #define TT_MAX_ENTRIES_PER_LAUNCH 8

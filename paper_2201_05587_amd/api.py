@@ -542,7 +542,7 @@ def variant_name(plan: tt_plan, shape=None) -> str:
     """Name of the kernel a plan names, spelled like the demangled symbol rocprofv3 reports (launched_name: the one that a
     launch runs on).
 
-    `shape` (a conv shape) is needed only to tell the two depthwise kernels apart.
+    `shape` (a conv shape) is needed only for the stride of the patch kernel.
     """
     if plan.sketch == TT_SK_MFMA:
         info = tt_variant_info(plan.variant_id)
@@ -558,12 +558,7 @@ def variant_name(plan: tt_plan, shape=None) -> str:
             return "tt::contract_async_kernel<" + ", ".join(str(v) for v in info[:8]) + ">"
         return "tt::contract_kernel<" + ", ".join(str(v) for v in info[:9]) + ">"
     if plan.sketch == TT_SK_DWCONV:
-        s = shape
         bound = 256 if plan.block <= 256 else 512 if plan.block <= 512 else 1024   # the instance's thread bound
-        if (s is not None and plan.stages == 1 and s.stride_h == s.stride_w and s.stride_h in (1, 2)
-                and s.n * s.h * s.w * s.c * 4 < 2 ** 31):
-            return (f"tt::dwconv3x3_rows_kernel<{plan.wave_m}, {plan.wave_n}, {plan.eff_vec_a}, {s.stride_h}, "
-                    f"{bound}>")
         return f"tt::dwconv3x3_kernel<{plan.wave_m}, {plan.wave_n}, {bound}>"
     return {TT_SK_GEMV: "tt::gemv_kernel", TT_SK_DIRECT: "tt::direct_kernel"}[plan.sketch]
 
@@ -571,6 +566,10 @@ def variant_name(plan: tt_plan, shape=None) -> str:
 def launched_name(sched, cls, shape, count=1) -> str:
     """Name of the kernel that a launch of `count` equal entries under a record (None = default) runs on."""
     plan, kernel = tt_debug_launch(sched, cls, shape, count)
+    if (plan.sketch == TT_SK_DWCONV and plan.stages == 1 and shape.stride_h == shape.stride_w and shape.stride_h in (1, 2)
+            and shape.n * shape.h * shape.w * shape.c * 4 < 2 ** 31):
+        sets = "_sets" if count > 1 else ""
+        return f"tt::dwconv3x3_window{sets}_kernel<{shape.stride_h}, {plan.eff_vec_a}, {plan.wave_m}, {plan.wave_n}>"
     if kernel == TT_LAUNCH_RECORD:
         return variant_name(plan, shape)
     dtype, family, tm, tn, _, wm, wn, mf = tt_variant_info(plan.variant_id)[:8]

@@ -311,6 +311,14 @@ namespace {
 int launched_plan(const PreparedOp &op, int count, tt_plan *plan)
 {
     *plan = op.launch;
+    DwListEntry windows;
+    DwWindow w;
+    int vc;
+    if (plan->sketch == TT_SK_DWCONV && dw_windows(op.d, count, &windows, &w, &vc)) {
+        plan->grid = (int32_t)dw_workgroups(windows), plan->block = 256;
+        plan->wave_m = w.rows, plan->wave_n = w.columns, plan->eff_vec_a = plan->eff_vec_c = vc;
+        return TT_LAUNCH_RECORD;
+    }
     if (plan->sketch != TT_SK_MFMA || plan->variant_id < 0 || plan->variant_id >= kNumVariants) return TT_LAUNCH_RECORD;
     const Variant &v = kVariants[plan->variant_id];
     if (!v.shape) return TT_LAUNCH_RECORD;
@@ -481,7 +489,7 @@ tt_sweep_opts resolve(const tt_sweep_opts *o)
 }
 
 // Times of one kernel's launches under one protocol, for as long as a sweep lasts.  Records that differ only in knobs the
-// kernel they run on does not have (stages, tile_k and unroll of a launch in groups, everything of one in blocks) come to
+// kernel they run on does not have (stages, tile_k and unroll of a launch in groups, everything of one in blocks or windows) come to
 // the same launch: they share the time of the first, and the rule for ties decides among them instead of noise.
 class LaunchTimes {
 public:
@@ -493,6 +501,10 @@ public:
     {
         tt_plan p;
         const int kernel = launched_plan(op, 1, &p);
+        DwListEntry windows;
+        DwWindow w;
+        int vc;
+        if (p.sketch == TT_SK_DWCONV && dw_windows(op.d, 1, &windows, &w, &vc)) return Key{-1};
         if (kernel == TT_LAUNCH_BLOCKS) return Key{kernel};
         if (kernel == TT_LAUNCH_ROWS) return Key{kernel, p.tile_m, p.tile_n, p.eff_vec_c, p.order};
         if (kernel == TT_LAUNCH_GROUPS)

@@ -637,8 +637,8 @@ extern "C" int tt_debug_list(const tt_kernel_desc *kernels, const tt_schedule *c
                     const ListTile &t = table[l.tile];
                     as.tile_m = t.tile_m, as.tile_n = t.tile_n, as.tile_k = t.tile_k, as.kernel = TT_LISTED_TILES;
                 } else if (l.tile == kDepthwise) {
-                    dw_list_window(l.family, &as.tile_m, &as.tile_n);
-                    as.tile_k = 4, as.kernel = TT_LISTED_DEPTHWISE;
+                    const DwWindow w = dw_list_window(l.family);
+                    as.tile_m = w.rows, as.tile_n = w.columns, as.tile_k = 4, as.kernel = TT_LISTED_DEPTHWISE;
                 } else if (l.tile == kOnePlan) { // (one plan for all of its entries)
                     const tt_plan &pl = ops[w.entries()[l.entries[0]].op].launch;
                     as.tile_m = pl.tile_m, as.tile_n = pl.tile_n, as.tile_k = pl.tile_k, as.kernel = TT_LISTED_RECORD;

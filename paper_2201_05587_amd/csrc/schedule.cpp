@@ -361,13 +361,13 @@ extern "C" int tt_schedule_apply(const tt_schedule *sched, int cls, const void *
             lds = p.tile_k * rows * cols * elem;
         }
         if (lds > kLdsBudget) return fail(plan, TT_ERR_INVALID_SCHEDULE, TT_R_LDS);
-        // Several planes per lane exist in the register kernel only (one stage, equal strides of 1 or 2,
+        // Several planes per lane exist without an LDS patch only (one stage, equal strides of 1 or 2,
         // input below 2 GiB); elsewhere such a plan has no kernel.
-        const bool rows_kernel = r.stages == 1 && s->stride_h == s->stride_w && (s->stride_h == 1 || s->stride_h == 2) &&
+        const bool in_registers = r.stages == 1 && s->stride_h == s->stride_w && (s->stride_h == 1 || s->stride_h == 2) &&
                                  (int64_t)s->n * s->h * s->w * s->c * elem < (1ll << 31);
         const int block = r.tile_k * (r.tile_m / r.wave_m) * (r.tile_n / r.wave_n);
-        const bool fits = block <= dw_max_block(r.wave_m, r.wave_n, ev_planes, s->stride_w, rows_kernel);
-        p.variant_id = (ev_planes == 1 || rows_kernel) && s->r == 3 && s->s == 3 && dt == TT_F32 && fits ? 0 : -1;
+        const bool fits = block <= dw_max_block(r.wave_m, r.wave_n, ev_planes, s->stride_w, in_registers);
+        p.variant_id = (ev_planes == 1 || in_registers) && s->r == 3 && s->s == 3 && dt == TT_F32 && fits ? 0 : -1;
         p.eff_split_k = 1;
         p.k_iters = 1;
         p.slabs = p.k_tiles;

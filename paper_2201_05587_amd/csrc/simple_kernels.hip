@@ -293,125 +293,28 @@ template <int WM, int WN, int MAXT> __global__ void __launch_bounds__(MAXT) dwco
     }
 }
 
-// ---- depthwise 3x3, register version: VC channel-contiguous planes per lane, unit or double stride ---
-// The same tile and thread layout as above, without LDS.  For each of its WM output rows a thread
-// fetches the three input rows it needs, each input pixel once, as VC-wide vectors through
-// bounds-checked buffer loads (an offset outside the tensor reads as zero, which is the padding),
-// then forms its WN outputs.  Lanes of a wave hold neighbouring channel groups of one pixel, so
-// every load and store instruction covers one contiguous run of memory.
-template <int WM, int WN, int VC, int STR, int MAXT>
-__global__ void __launch_bounds__(MAXT) dwconv3x3_rows_kernel(const DwArgs args, const PointerSets sets)
+// ---- depthwise 3x3 in windows: one entry, or entries of different shapes in one launch ------------------------------
+// Bound by memory.  A thread forms WM x WN outputs of VC neighbouring channels and reads every input pixel of its window
+// once, all of them before the first product: (WM + 2) (WN + 2) / (WM WN) reads an output at unit stride, 3 for 4 x 2, 4 for
+// 2 x 2, where tiles of workgroups with rows of outputs per thread made 9 (1 x 1) to 3.9 (7 columns).  Padding comes from loads
+// out of range, which return zero.  The lanes of a wave hold neighbouring channels of one pixel: every access is one run of
+// memory.  The sums run in the order of the other kernels.
+template <int STR, int VC, int WM, int WN> __device__ __forceinline__ void dw_window(const DwListEntry &g, int wg)
 {
-    const DwArgs g = with_set(args, sets, blockIdx.y);
+    constexpr int ROWS = (WM - 1) * STR + 3, COLS = (WN - 1) * STR + 3;
     typedef __attribute__((ext_vector_type(VC))) float vec_t;
-    constexpr int COLS = (WN - 1) * STR + 3;
-    const TileCoord tc = decode_tile(g.map, (int32_t)blockIdx.x);
-    const int lanes_k = g.map.tile_k / VC; // lanes along the plane axis
-    const int tcols = g.map.tile_n / WN;
-    const int tid = threadIdx.x;
-    const int tp = tid % lanes_k, tx = (tid / lanes_k) % tcols, ty = tid / (lanes_k * tcols);
-    const int plane = tc.k0 + tp * VC;
-    if (plane >= tc.k0 + tc.k_ext) return;
-    const int img = plane / g.C, ch = plane - img * g.C;
-    const int p0 = tc.m0 + ty * WM, q0 = tc.n0 + tx * WN;
-    const __amdgpu_buffer_rsrc_t xr = make_rsrc(g.x, g.x_bytes);
-
-    vec_t wgt[9], bias;
-#pragma unroll
-    for (int i = 0; i < 9; ++i) wgt[i] = *reinterpret_cast<const vec_t *>(g.w + i * g.C + ch);
-#pragma unroll
-    for (int v = 0; v < VC; ++v) bias[v] = g.bias ? g.bias[ch + v] : 0.0f;
-
-    // byte offset of input column c of this thread's window, or out of range
-    const int iw0 = q0 * STR - g.pad_w;
-    uint32_t col_off[COLS];
-#pragma unroll
-    for (int c = 0; c < COLS; ++c) {
-        const int iw = iw0 + c;
-        col_off[c] = (iw >= 0 && iw < g.W) ? (uint32_t)((iw * g.C + ch) * 4) : kOutOfRange;
-    }
-    const int plim = min(g.Ho, tc.m0 + tc.m_ext), qlim = min(g.Wo, tc.n0 + tc.n_ext);
-    float *yp = g.y + (int64_t)img * g.Ho * g.Wo * g.C + ch;
-
-    auto body = [&](int i) {
-        const int p = p0 + i;
-        if (p >= plim) return;
-        vec_t out[WN];
-#pragma unroll
-        for (int j = 0; j < WN; ++j) out[j] = bias;
-#pragma unroll
-        for (int r = 0; r < 3; ++r) {
-            const int ih = p * STR + r - g.pad_h;
-            const bool row_ok = ih >= 0 && ih < g.H;
-            const uint32_t row_off = (uint32_t)((img * g.H + ih) * g.W * g.C * 4);
-            vec_t in[COLS];
-#pragma unroll
-            for (int c = 0; c < COLS; ++c) {
-                // an out-of-range column keeps its sentinel: the sum below stays out of range for every row offset
-                const uint32_t off = (row_ok && col_off[c] != kOutOfRange) ? row_off + col_off[c] : kOutOfRange;
-                if constexpr (VC == 4) {
-                    const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0);
-                    in[c] = __builtin_bit_cast(vec_t, t);
-                } else if constexpr (VC == 2) {
-                    typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-                    const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(xr, off, 0, 0);
-                    in[c] = __builtin_bit_cast(vec_t, t);
-                } else {
-                    in[c][0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xr, off, 0, 0));
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < WN; ++j)
-#pragma unroll
-                for (int s = 0; s < 3; ++s)
-#pragma unroll
-                    for (int v = 0; v < VC; ++v) out[j][v] = fmaf(in[j * STR + s][v], wgt[r * 3 + s][v], out[j][v]);
-        }
-#pragma unroll
-        for (int j = 0; j < WN; ++j) {
-            if (q0 + j >= qlim) continue;
-            vec_t o;
-#pragma unroll
-            for (int v = 0; v < VC; ++v) o[v] = fminf(fmaxf(out[j][v], 0.0f), 6.0f);
-            __builtin_nontemporal_store(o, reinterpret_cast<vec_t *>(yp + ((int64_t)p * g.Wo + q0 + j) * g.C)); // streamed
-        }
-    };
-    if (g.unroll >= WM) {
-#pragma unroll
-        for (int i = 0; i < WM; ++i) body(i);
-    } else {
-#pragma unroll 1
-        for (int i = 0; i < WM; ++i) body(i);
-    }
-}
-
-// ---- depthwise 3x3 entries of different shapes in one launch -------------------------------------------------------
-// Bound by memory.  A thread forms WM x WN outputs of four channels and reads every input pixel of its window once, all of
-// them before the first product: (WM + 2) (WN + 2) / (WM WN) reads an output at unit stride, 3 for 4 x 2, where the record's
-// 1 x 2 of the network's layers make 6 that miss the first cache.  The sums run in the order of the other kernels.
-template <int STR> struct DwListShape {
-    static constexpr int WM = STR == 1 ? 4 : 2, WN = 2, ROWS = (WM - 1) * STR + 3, COLS = (WN - 1) * STR + 3;
-};
-template <int STR> __global__ void __launch_bounds__(256) dwconv3x3_list_kernel(const DwList list)
-{
-    using S = DwListShape<STR>;
-    constexpr int WM = S::WM, WN = S::WN, ROWS = S::ROWS, COLS = S::COLS;
-    int at = 0;
-#pragma unroll
-    for (int i = 1; i < kMaxDwListed; ++i) at += (int)blockIdx.x >= list.e[i].first;
-    const DwListEntry &g = list.e[at];
     // every XCD gets a contiguous run of the entry's workgroups: neighbouring windows share rows in its L2
-    const int wg = (int)blockIdx.x - g.first, wgs = (g.threads + 255) / 256, per = wgs / kXcds, rem = wgs % kXcds, xcd = wg % kXcds;
+    const int wgs = (g.threads + 255) / 256, per = wgs / kXcds, rem = wgs % kXcds, xcd = wg % kXcds;
     if (wg >= wgs) return;
     const int t = (xcd * per + min(xcd, rem) + wg / kXcds) * 256 + (int)threadIdx.x;
     if (t >= g.threads) return;
-    const int lanes = g.C / 4, columns = (g.Wo + WN - 1) / WN, strips = (g.Ho + WM - 1) / WM;
-    const int pix = (int)fast_div((uint32_t)t, g.div_c), ch = (t - pix * lanes) * 4;
+    const int lanes = g.C / VC, columns = (g.Wo + WN - 1) / WN, strips = (g.Ho + WM - 1) / WM;
+    const int pix = (int)fast_div((uint32_t)t, g.div_c), ch = (t - pix * lanes) * VC;
     const int row = (int)fast_div((uint32_t)pix, g.div_cols), q0 = (pix - row * columns) * WN;
     const int img = (int)fast_div((uint32_t)row, g.div_rows), p0 = (row - img * strips) * WM;
 
     const __amdgpu_buffer_rsrc_t xr = make_rsrc(g.x, g.x_bytes);
-    f32x4 in[ROWS][COLS], wgt[9];
+    vec_t in[ROWS][COLS], wgt[9];
     const int ih0 = p0 * STR - g.pad_h, iw0 = q0 * STR - g.pad_w;
 #pragma unroll
     for (int r = 0; r < ROWS; ++r)
@@ -419,29 +322,61 @@ template <int STR> __global__ void __launch_bounds__(256) dwconv3x3_list_kernel(
         for (int c = 0; c < COLS; ++c) {
             const int ih = ih0 + r, iw = iw0 + c;
             const bool ok = ih >= 0 && ih < g.H && iw >= 0 && iw < g.W;
-            in[r][c] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, ok ? (uint32_t)(((img * g.H + ih) * g.W + iw) * g.C + ch) * 4u : kOutOfRange, 0, 0));
+            const uint32_t off = ok ? (uint32_t)(((img * g.H + ih) * g.W + iw) * g.C + ch) * 4u : kOutOfRange;
+            if constexpr (VC == 4)
+                in[r][c] = __builtin_bit_cast(vec_t, __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0));
+            else if constexpr (VC == 2)
+                in[r][c] = __builtin_bit_cast(vec_t, __builtin_amdgcn_raw_buffer_load_b64(xr, off, 0, 0));
+            else
+                in[r][c][0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xr, off, 0, 0));
         }
 #pragma unroll
-    for (int i = 0; i < 9; ++i) wgt[i] = *reinterpret_cast<const f32x4 *>(g.w + i * g.C + ch);
-    f32x4 bias = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (g.bias) bias = *reinterpret_cast<const f32x4 *>(g.bias + ch);
+    for (int i = 0; i < 9; ++i) wgt[i] = *reinterpret_cast<const vec_t *>(g.w + i * g.C + ch);
+    vec_t bias = 0.0f;
+    if (g.bias) bias = *reinterpret_cast<const vec_t *>(g.bias + ch);
 #pragma unroll
     for (int i = 0; i < WM; ++i)
 #pragma unroll
         for (int j = 0; j < WN; ++j) {
-            f32x4 out = bias;
+            vec_t out = bias;
 #pragma unroll
             for (int r = 0; r < 3; ++r)
 #pragma unroll
                 for (int s = 0; s < 3; ++s)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) out[v] = fmaf(in[i * STR + r][j * STR + s][v], wgt[r * 3 + s][v], out[v]);
+                    for (int v = 0; v < VC; ++v) out[v] = fmaf(in[i * STR + r][j * STR + s][v], wgt[r * 3 + s][v], out[v]);
             const int p = p0 + i, q = q0 + j;
             if (p >= g.Ho || q >= g.Wo) continue;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) out[v] = fminf(fmaxf(out[v], 0.0f), 6.0f);
-            __builtin_nontemporal_store(out, reinterpret_cast<f32x4 *>(g.y + ((int64_t)(img * g.Ho + p) * g.Wo + q) * g.C + ch)); // streamed
+            for (int v = 0; v < VC; ++v) out[v] = fminf(fmaxf(out[v], 0.0f), 6.0f);
+            __builtin_nontemporal_store(out, reinterpret_cast<vec_t *>(g.y + ((int64_t)(img * g.Ho + p) * g.Wo + q) * g.C + ch)); // streamed
         }
+}
+// Windows that a list is cut into.
+template <int STR> constexpr DwWindow kDwListWindow = {STR == 1 ? 4 : 2, 2};
+template <int STR> __global__ void __launch_bounds__(256) dwconv3x3_list_kernel(const DwList list)
+{
+    int at = 0;
+#pragma unroll
+    for (int i = 1; i < kMaxDwListed; ++i) at += (int)blockIdx.x >= list.e[i].first;
+    const DwListEntry &g = list.e[at];
+    dw_window<STR, 4, kDwListWindow<STR>.rows, kDwListWindow<STR>.columns>(g, (int)blockIdx.x - g.first);
+}
+// (96 bytes of arguments: up to there a launch costs the host 2.9 us, with 704 bytes 3.9)
+static_assert(sizeof(DwListEntry) <= 96, "");
+template <int STR, int VC, int WM, int WN> __global__ void __launch_bounds__(256) dwconv3x3_window_kernel(const DwListEntry g)
+{
+    dw_window<STR, VC, WM, WN>(g, (int)blockIdx.x);
+}
+// Several entries of one plan.
+template <int STR, int VC, int WM, int WN> __global__ void __launch_bounds__(256) dwconv3x3_window_sets_kernel(DwListEntry g, const PointerSets sets)
+{
+    if (blockIdx.y > 0) {
+        const PointerSet &p = sets.more[blockIdx.y - 1];
+        g.x = static_cast<const float *>(p.a), g.w = static_cast<const float *>(p.b);
+        g.bias = static_cast<const float *>(p.bias), g.y = static_cast<float *>(p.out);
+    }
+    dw_window<STR, VC, WM, WN>(g, (int)blockIdx.x);
 }
 
 __global__ void __launch_bounds__(256) dw_direct_kernel(const DwArgs args, const PointerSets sets)
@@ -577,67 +512,105 @@ int launch_gemv(const ContractArgs &args, const PointerSets &sets, const tt_plan
     return TT_OK;
 }
 
-// The depthwise kernels are compiled for workgroups of at most 256, 512 and 1024 threads, which leaves a
-// lane 512, 256 and 128 registers.  What a lane keeps in flight grows with the input columns of its
-// window times the planes per access (register kernel) or with its outputs per row (general kernel); the
-// bounds below are the sizes the compiler keeps in registers (the build's resource report: no instance
-// that these bounds admit uses scratch memory).
-constexpr int dw_block_limit(int wave_m, int wave_n, int planes_per_lane, int stride, bool rows_kernel)
+// Workgroups that a depthwise record may name, by what a lane of them would keep in flight: input columns of its outputs times
+// planes per access where the record asks for neither an LDS patch nor unequal strides (`in_registers`), else outputs per row.
+// The general kernel is compiled for at most 256, 512 and 1024 threads, which leaves a lane 512, 256 and 128 registers; of
+// these sizes the compiler keeps everything in registers.
+constexpr int dw_block_limit(int wave_m, int wave_n, int planes_per_lane, int stride, bool in_registers)
 {
     const auto built = [](int w) { return w == 1 || w == 2 || w == 4 || w == 7; };
     if (!built(wave_m) || !built(wave_n)) return 0; // no instance for other outputs per thread
-    if (rows_kernel) {
+    if (in_registers) {
         const int in_flight = ((wave_n - 1) * stride + 3) * planes_per_lane;
         return in_flight <= 9 || (in_flight <= 16 && wave_n < 7) ? 1024 : in_flight <= 36 ? 512 : 256;
     }
     return wave_n <= 2 ? 1024 : wave_n <= 4 ? 512 : 256;
 }
 
-int dw_max_block(int wave_m, int wave_n, int planes_per_lane, int stride, bool rows_kernel)
+int dw_max_block(int wave_m, int wave_n, int planes_per_lane, int stride, bool in_registers)
 {
-    return dw_block_limit(wave_m, wave_n, planes_per_lane, stride, rows_kernel);
+    return dw_block_limit(wave_m, wave_n, planes_per_lane, stride, in_registers);
 }
 
 namespace {
 
-template <int WM, int WN> int launch_dw_rows(const DwArgs &a, const PointerSets &sets, dim3 grid, dim3 block, hipStream_t s)
+// The part of an entry that its sizes decide; false: no windows for it.
+bool dw_entry(const DwArgs &g, int vc, DwWindow w, DwListEntry *e)
 {
-    const int str = a.stride_h;
-#define TT_DW_ROWS(VC_, STR_)                                                                                        \
-    if (a.eff_vec == VC_ && str == STR_) {                                                                           \
-        constexpr int LIMIT = dw_block_limit(WM, WN, VC_, STR_, true);                                               \
-        if ((int)block.x > LIMIT) return TT_ERR_UNSUPPORTED;                                                         \
-        if (block.x <= 256) {                                                                                        \
-            hipLaunchKernelGGL((dwconv3x3_rows_kernel<WM, WN, VC_, STR_, 256>), grid, block, 0, s, a, sets);         \
-        } else if (block.x <= 512) {                                                                                 \
-            if constexpr (LIMIT >= 512)                                                                              \
-                hipLaunchKernelGGL((dwconv3x3_rows_kernel<WM, WN, VC_, STR_, 512>), grid, block, 0, s, a, sets);     \
-        } else {                                                                                                     \
-            if constexpr (LIMIT >= 1024)                                                                             \
-                hipLaunchKernelGGL((dwconv3x3_rows_kernel<WM, WN, VC_, STR_, 1024>), grid, block, 0, s, a, sets);    \
-        }                                                                                                            \
-        return launched();                                                                                           \
-    }
-    TT_DW_ROWS(1, 1) TT_DW_ROWS(2, 1) TT_DW_ROWS(4, 1) TT_DW_ROWS(1, 2) TT_DW_ROWS(2, 2) TT_DW_ROWS(4, 2)
-#undef TT_DW_ROWS
-    return TT_ERR_UNSUPPORTED;
+    if (g.C % vc != 0 || g.stride_h != g.stride_w || (g.stride_h != 1 && g.stride_h != 2) || g.x_bytes == 0) return false;
+    const int64_t columns = (g.Wo + w.columns - 1) / w.columns, strips = (g.Ho + w.rows - 1) / w.rows, threads = g.planes / vc * columns * strips;
+    if (threads >= 1ll << 30) return false;
+    e->threads = (int32_t)threads;
+    e->C = g.C, e->H = g.H, e->W = g.W, e->Ho = g.Ho, e->Wo = g.Wo, e->pad_h = g.pad_h, e->pad_w = g.pad_w, e->x_bytes = g.x_bytes;
+    e->div_c = make_fastdiv((uint32_t)(g.C / vc)), e->div_cols = make_fastdiv((uint32_t)columns), e->div_rows = make_fastdiv((uint32_t)strips);
+    return true;
+}
+
+// The window of a launch of `pieces` outputs of one thread's channels.  A larger one reads less and a smaller one has more threads,
+// and less code to fetch before the first load: 1 x 1 up to a workgroup per CU, 1 x 2 up to six, 4 x 2 from 80 on.  Unit stride, 1x1 /
+// 1x2 / 2x2 / 4x2 in us, and in rows of the record that a search chose: 57 k pieces 2.7 / 3.0 / 3.6 / 4.8, 3.2; 71 k 3.1 / 3.0 /
+// 3.6 / 4.8, 3.7; 368 k 5.6 / 4.5 / 4.5 / 5.1, 5.3; 442 k 6.1 / 5.1 / 4.5 / 5.1, -; 1.0 M 10.9 / 7.9 / 6.4 / 6.1, 9.7; 4.1 M 41.7 / 30.2
+// / 23.4 / 24.2, 41.6; 5.4 M 56 / 39 / 29.7 / 29.2, 39.5; 6.2 M 67 / 45 / 37.9 / 34.5, 48.3.  Stride 2, 1x1 / 1x2 / 2x2: 76 k 3.1 / 3.2 / 4.1, 3.6;
+// 326 k 5.0 / 4.6 / 4.9, 8.7; 469 k 6.7 / 5.7 / 5.2, 10.9; 1.4 M 21.0 / 19.4 / 19.0, 22.4.
+DwWindow dw_window_for(int64_t pieces, int stride)
+{
+    if (pieces <= 65536) return {1, 1};
+    if (pieces <= 6 * 65536) return {1, 2};
+    if (stride == 2 || pieces <= 80 * 65536) return {2, 2};
+    return {4, 2};
+}
+
+template <int STR, int VC, int WM, int WN> int launch_windows(const DwListEntry &e, const PointerSets &sets, hipStream_t s)
+{
+    const unsigned grid = (unsigned)dw_workgroups(e);
+    if (sets.count == 1)
+        hipLaunchKernelGGL((dwconv3x3_window_kernel<STR, VC, WM, WN>), dim3(grid), dim3(256), 0, s, e);
+    else
+        hipLaunchKernelGGL((dwconv3x3_window_sets_kernel<STR, VC, WM, WN>), dim3(grid, sets.count), dim3(256), 0, s, e, sets);
+    return launched();
+}
+template <int STR, int VC> int launch_windows_of(DwWindow w, const DwListEntry &e, const PointerSets &sets, hipStream_t s)
+{
+    if constexpr (STR == 1)
+        if (w.rows == 4) return launch_windows<STR, VC, 4, 2>(e, sets, s);
+    if (w.rows == 2) return launch_windows<STR, VC, 2, 2>(e, sets, s);
+    if (w.columns == 2) return launch_windows<STR, VC, 1, 2>(e, sets, s);
+    return launch_windows<STR, VC, 1, 1>(e, sets, s);
 }
 
 } // namespace
 
+// Records of one stage over a tensor within the 2 GiB offset range, strides 1 or 2: in windows, whose size the launch's own
+// decides, since a record's outputs per thread cost reads that no tile gets back (see dw_window_for).  An LDS patch (two stages)
+// and unequal strides are what the record says.
+bool dw_windows(const DwArgs &g, int count, DwListEntry *e, DwWindow *w, int *vc)
+{
+    if (g.stages != 1) return false;
+    *vc = g.C % 4 == 0 ? 4 : g.C % 2 == 0 ? 2 : 1;
+    *w = dw_window_for((int64_t)g.planes / *vc * g.Ho * g.Wo * count, g.stride_h);
+    return dw_entry(g, *vc, *w, e);
+}
+
 int launch_dwconv(const DwArgs &a, const PointerSets &sets, const tt_plan &plan, void *stream)
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (plan.variant_id < 0) return TT_ERR_UNSUPPORTED;
+    DwListEntry e;
+    DwWindow w;
+    int vc;
+    if (dw_windows(a, sets.count, &e, &w, &vc)) {
+        e.x = a.x, e.w = a.w, e.bias = a.bias, e.y = a.y, e.first = 0;
+        if (a.stride_h == 1) return vc == 4 ? launch_windows_of<1, 4>(w, e, sets, s) : vc == 2 ? launch_windows_of<1, 2>(w, e, sets, s) : launch_windows_of<1, 1>(w, e, sets, s);
+        return vc == 4 ? launch_windows_of<2, 4>(w, e, sets, s) : vc == 2 ? launch_windows_of<2, 2>(w, e, sets, s) : launch_windows_of<2, 1>(w, e, sets, s);
+    }
     const dim3 grid(plan.grid, sets.count), block(plan.block);
     const int lds = plan.lds_bytes;
-    // One stage, strides 1 or 2 and a tensor within the 2 GiB offset range: the register kernel.
-    // Everything else (the LDS patch of two stages, other strides): the general kernel, one plane per lane.
-    const bool rows_kernel = a.stages == 1 && a.stride_h == a.stride_w && (a.stride_h == 1 || a.stride_h == 2) &&
-                             a.x_bytes != 0;
-    if (!rows_kernel && a.eff_vec != 1) return TT_ERR_UNSUPPORTED;
+    if (a.eff_vec != 1) { // more windows than they are counted in, which takes padding of many times the image
+        const int64_t wgs = ((int64_t)a.planes * a.Ho * a.Wo + 255) / 256;
+        return wgs > INT32_MAX ? TT_ERR_UNSUPPORTED : launch_dw_direct(a, sets, (int)wgs, stream);
+    }
 #define TT_DW_CASE(WM_, WN_)                                                                                         \
     if (a.wave_m == WM_ && a.wave_n == WN_) {                                                                        \
-        if (rows_kernel) return launch_dw_rows<WM_, WN_>(a, sets, grid, block, s);                                   \
         constexpr int LIMIT = dw_block_limit(WM_, WN_, 1, 1, false);                                                 \
         if ((int)block.x > LIMIT) return TT_ERR_UNSUPPORTED;                                                         \
         const int bc = block.x <= 256 ? 0 : block.x <= 512 ? 1 : 2;                                                  \
@@ -659,24 +632,9 @@ int launch_dwconv(const DwArgs &a, const PointerSets &sets, const tt_plan &plan,
     return TT_ERR_UNSUPPORTED;
 }
 
-void dw_list_window(int stride, int32_t *rows, int32_t *columns)
-{
-    *rows = stride == 1 ? DwListShape<1>::WM : DwListShape<2>::WM;
-    *columns = stride == 1 ? DwListShape<1>::WN : DwListShape<2>::WN;
-}
+DwWindow dw_list_window(int stride) { return stride == 1 ? kDwListWindow<1> : kDwListWindow<2>; }
 
-bool dw_list_entry(const DwArgs &g, DwListEntry *e)
-{
-    if (g.C % 4 != 0 || g.stride_h != g.stride_w || (g.stride_h != 1 && g.stride_h != 2) || g.x_bytes == 0) return false;
-    int32_t wm, wn;
-    dw_list_window(g.stride_h, &wm, &wn);
-    const int64_t columns = (g.Wo + wn - 1) / wn, strips = (g.Ho + wm - 1) / wm, threads = g.planes / 4 * columns * strips;
-    if (threads >= 1ll << 30) return false;
-    e->threads = (int32_t)threads;
-    e->C = g.C, e->H = g.H, e->W = g.W, e->Ho = g.Ho, e->Wo = g.Wo, e->pad_h = g.pad_h, e->pad_w = g.pad_w, e->x_bytes = g.x_bytes;
-    e->div_c = make_fastdiv((uint32_t)(g.C / 4)), e->div_cols = make_fastdiv((uint32_t)columns), e->div_rows = make_fastdiv((uint32_t)strips);
-    return true;
-}
+bool dw_list_entry(const DwArgs &g, DwListEntry *e) { return dw_entry(g, 4, dw_list_window(g.stride_h), e); }
 
 int launch_dw_list(DwList &list, int count, int stride, void *stream)
 {

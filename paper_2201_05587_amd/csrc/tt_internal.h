@@ -280,7 +280,10 @@ struct DwArgs {
     uint32_t x_bytes;  // size of the input tensor when it is below 2 GiB, else 0
 };
 
-// Depthwise entries of different shapes in one launch (simple_kernels.hip): strides of one size, C a multiple of four.
+// A depthwise entry in windows of outputs, alone or beside others of different shapes (simple_kernels.hip).
+struct DwWindow {
+    int32_t rows, columns;
+};
 struct DwListEntry {
     const float *x, *w, *bias; // bias may be null
     float *y;
@@ -294,11 +297,13 @@ struct DwList {
     DwListEntry e[kMaxDwListed];
 };
 static_assert(sizeof(DwList) <= 4096, "");
-// Fills in the part of an entry that the launch decides on; false: the entry is not one for a list.
+// Whether a launch of `count` entries runs in windows: the entry without its pointers, the window and the channels of a thread.
+bool dw_windows(const DwArgs &g, int count, DwListEntry *e, DwWindow *w, int *vc);
+// Fills in the part of an entry that the launch decides on; false: the entry is not one for a list (C not a multiple of four).
 bool dw_list_entry(const DwArgs &g, DwListEntry *e);
 inline int64_t dw_workgroups(const DwListEntry &e) { return ((e.threads + 255ll) / 256 + kXcds - 1) / kXcds * kXcds; }
-// Rows and columns of the outputs that a thread forms (of four channels).
-void dw_list_window(int stride, int32_t *rows, int32_t *columns);
+// The outputs that a thread of a list forms (of four channels).
+DwWindow dw_list_window(int stride);
 int launch_dw_list(DwList &list, int count, int stride, void *stream);
 
 TT_HD ContractArgs with_set(ContractArgs g, const PointerSets &sets, uint32_t set)
@@ -400,7 +405,7 @@ LaunchShape blocks_shape(const ContractArgs &args, int family);
 // gathers (a grid of 0: it does not apply)
 LaunchShape rows_shape(const ContractArgs &args, int count);
 int launch_conv_rows(const ContractArgs &args, const PointerSets &sets, void *stream);
-int dw_max_block(int wave_m, int wave_n, int planes_per_lane, int stride, bool rows_kernel);
+int dw_max_block(int wave_m, int wave_n, int planes_per_lane, int stride, bool in_registers);
 int launch_dwconv(const DwArgs &args, const PointerSets &sets, const tt_plan &plan, void *stream);
 int launch_dw_direct(const DwArgs &args, const PointerSets &sets, int grid, void *stream);
 int launch_tile_map_dump(const TileMap &map, int32_t *out_dev, void *stream);
