@@ -1,0 +1,77 @@
+"""Contractions over rows that are no whole 16-byte items: the walk tap by tap, at its edges."""
+import numpy as np
+import pytest
+
+from paper_2201_05587_amd import api, harness
+from paper_2201_05587_amd import workloads as wl
+
+
+def record(cls, dtype, tm, tn, tk, wm, wn, stages, split_k=1, mfma=16):
+    return api.make_schedule(cls, api.TT_SK_MFMA, tm, tn, tk, wm, wn, mfma, split_k, 1, 8 if dtype == wl.BF16 else 4, 8, stages)
+
+
+def records(cls, dtype):
+    k = 64 if dtype == wl.BF16 else 32
+    return [record(cls, dtype, 32, 32, k, 16, 16, 2), record(cls, dtype, 64, 64, k // 2, 32, 32, 1, mfma=32 if dtype == wl.F32 else 16),
+            record(cls, dtype, 64, 16, k // 2, 32, 16, 2), record(cls, dtype, 32, 32, k, 16, 16, 2, split_k=2), record(cls, dtype, 16, 64, k // 2, 16, 32, 2, split_k=3)]
+
+
+def conv(dtype, n, c, h, w, k, f, stride, pad, cls=1):
+    return wl.Kernel(cls, wl.ConvShape(n, c, h, w, k, f, f, stride, stride, pad, pad, dtype), 1, f"conv_{n}_{c}_{h}x{w}_{k}_{f}_s{stride}_p{pad}")
+
+
+def product(dtype, batch, m, n, k):
+    return wl.Kernel(7, wl.GemmShape(batch, m, n, k, 1, dtype), 1, f"product_{batch}_{m}_{n}_{k}")
+
+
+# a pixel one element longer than items and one shorter, even and odd, one slice to many (an even and an odd number of them),
+# filters larger than the image, no padding and more than the filter's half, strides, the tensor's last item, residuals;
+# 17 and 21: too much padding, the walk along the run
+CASES = [lambda d: conv(d, 1, 23, 5, 6, 33, 1, 1, 0), lambda d: conv(d, 2, 31, 7, 9, 40, 3, 1, 1), lambda d: conv(d, 1, 47, 6, 5, 66, 5, 1, 2),
+         lambda d: conv(d, 3, 34, 11, 8, 17, 3, 2, 1), lambda d: conv(d, 1, 63, 3, 2, 64, 5, 1, 4), lambda d: conv(d, 1, 55, 8, 8, 31, 3, 1, 0),
+         lambda d: conv(d, 2, 95, 4, 7, 48, 3, 1, 1, 2), lambda d: conv(d, 1, 17, 9, 9, 20, 3, 1, 1), lambda d: conv(d, 1, 21, 6, 7, 18, 5, 2, 2),
+         lambda d: conv(d, 1, 130, 6, 6, 70, 3, 3, 1), lambda d: conv(d, 1, 257, 5, 5, 16, 1, 2, 0),
+         lambda d: product(d, 3, 33, 70, 31), lambda d: product(d, 2, 65, 33, 63), lambda d: product(d, 1, 130, 17, 127), lambda d: product(d, 5, 18, 64, 201),
+         lambda d: product(d, 1, 64, 66, 515)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_walk_by_taps_against_the_oracle(case, dtype):
+    import parity as P
+    k = CASES[case](dtype)
+    P.check_kernel(k, [None] + records(k.cls, dtype), seed=31 + case)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_what_lies_behind_a_pixel_is_not_read_into_it(dtype, bad):
+    """The item that ends a pixel holds the next pixel's first elements, and a row's the next row's: of either operand."""
+    import torch
+    for k in (conv(dtype, 2, 23, 7, 9, 40, 1, 1, 0, 0), product(dtype, 2, 40, 36, 23)):
+        inp = wl.make_inputs(k, 5)
+        for rec in records(k.cls, dtype)[:2]:
+            if not api.tt_schedule_apply(rec, k.cls, k.shape).runnable():
+                continue
+            dk = harness.device_kernel(k, 5, inp)
+            a, b = (dk.tensors["a"], dk.tensors["b"]) if "a" in dk.tensors else (dk.tensors["x"], dk.tensors["w"])
+            assert dk.run(rec) == api.TT_OK
+            torch.cuda.synchronize()
+            want = dk.output().clone().view(-1, dk.output().shape[-1])
+            rows, columns = a.view(-1, 23), b.view(-1, 23)
+            rows[1::2, 0] = bad      # of every second row, and of every third column
+            columns[2::3, 0] = bad
+            assert dk.run(rec) == api.TT_OK
+            torch.cuda.synchronize()
+            got = dk.output().view(-1, dk.output().shape[-1])
+            n = got.shape[1]
+            clean_rows = torch.arange(got.shape[0], device="cuda") % 2 == 0
+            batch = columns.shape[0] // n
+            for i in range(batch):  # (a product's batches have columns of their own)
+                clean = torch.arange(i * n, (i + 1) * n, device="cuda") % 3 != 2
+                part = slice(i * got.shape[0] // batch, (i + 1) * got.shape[0] // batch)
+                keep = clean_rows[part][:, None] & clean[None, :]
+                assert torch.equal(got[part][keep], want[part][keep]), (k.name, rec)
+                assert not bool(torch.isfinite(got[part][~keep]).all())
