@@ -115,7 +115,7 @@ int run_contraction(const ContractArgs &g, const PointerSets &sets, const tt_pla
 {
     switch (plan.sketch) {
     case TT_SK_DIRECT:
-        return launch_direct(g, sets, family, plan.grid, stream);
+        return launch_direct(g, sets, family, stream);
     case TT_SK_GEMV:
         return launch_gemv(g, sets, plan, stream);
     case TT_SK_MFMA: {

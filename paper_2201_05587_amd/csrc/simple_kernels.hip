@@ -1,4 +1,4 @@
-// Kernels that do not use the matrix cores: the one-thread-per-output "direct"
+// Kernels that do not use the matrix cores: the "direct"
 // sketch (the unscheduled loop nest, always valid), the split-K reduction with
 // the fused epilogue, the wave-reduction GEMV sketch for small-M dense kernels,
 // the depthwise 3x3 tile kernel, and the index-map dump.
@@ -17,49 +17,102 @@ inline int launched()
     return e == hipSuccess ? TT_OK : note_hip_error((int)e, "kernel launch");
 }
 
-// ---- direct sketch: one thread per output element ------------------------------------------------
-template <int DT, int FAM> __global__ void __launch_bounds__(256) direct_kernel(const ContractArgs args, const PointerSets sets)
+// ---- direct sketch: the unscheduled loop nest, a thread per few outputs ------------------------------------------
+// What shapes below the matrix cores' smallest tile run on (a 1x1 convolution over 16 bf16 channels, 20 tokens), so reductions
+// are short and the instructions around them count.  A thread forms V neighbouring outputs of a row (4, or 1 in rows shorter
+// than that), which share its reads of the first operand, and reads both operands in 16-byte pieces at element alignment (a
+// [K][N] operand: one output, its elements next to those of the neighbouring lanes); every sum runs in the order of the loop nest.  Rows and columns are counted in 32 bits (I) where they fit.
+// A thread per output and element by element -> this (us): bf16 1x1 convolutions, 16 -> 624 channels on 6 x 17x17 34.7 -> 10.1,
+// 16 -> 72 on 7 x 25x22 12.0 -> 5.3, 20 -> 128 on 8 x 56x57 62 -> 18; 3x3 stride 3, 64 -> 33 on 7x7 57 -> 23; 192 products of 31 x 31 x 31
+// 9.0 -> 5.8; fp32 13 -> 64 on 4 x 30x30 6.1 -> 4.6.
+template <int DT, int V>
+__device__ __forceinline__ void add_products(float (&acc)[V], const typename ElemOf<DT>::type *x, const typename ElemOf<DT>::type *const (&w)[V], int count)
+{
+    constexpr int CH = ElemOf<DT>::CH;
+    int c = 0;
+    for (; c + CH <= count; c += CH) {
+        u32x4 xv, wv[V];
+        load16(xv, x + c);
+#pragma unroll
+        for (int v = 0; v < V; ++v) load16(wv[v], w[v] + c);
+#pragma unroll
+        for (int e = 0; e < CH; ++e)
+#pragma unroll
+            for (int v = 0; v < V; ++v) acc[v] = fmaf(element_of<DT>(xv, e), element_of<DT>(wv[v], e), acc[v]);
+    }
+    if (c < count && count >= CH) { // the rest: the last piece, shifted down to where the sum stands (zeros behind it)
+        const int back = c + CH - count;
+        u32x4 xv, wv[V];
+        load16(xv, x + count - CH);
+#pragma unroll
+        for (int v = 0; v < V; ++v) load16(wv[v], w[v] + count - CH);
+        xv = shift_elems<DT>(xv, -back);
+#pragma unroll
+        for (int v = 0; v < V; ++v) wv[v] = shift_elems<DT>(wv[v], -back);
+#pragma unroll
+        for (int e = 0; e < CH - 1; ++e)
+#pragma unroll
+            for (int v = 0; v < V; ++v) acc[v] = fmaf(element_of<DT>(xv, e), element_of<DT>(wv[v], e), acc[v]);
+        return;
+    }
+    for (; c < count; ++c)
+#pragma unroll
+        for (int v = 0; v < V; ++v) acc[v] = fmaf(load_as_float<DT>(x, c), load_as_float<DT>(w[v], c), acc[v]);
+}
+template <int DT, int FAM, int V, typename I> __global__ void __launch_bounds__(256) direct_kernel(const ContractArgs args, const PointerSets sets)
 {
     const ContractArgs g = with_set(args, sets, blockIdx.y);
     using E = typename ElemOf<DT>::type;
-    const int64_t total = (int64_t)g.batch * g.M * g.N;
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= total) return;
+    const I columns = (I)((g.N + V - 1) / V);
+    const I idx = (I)blockIdx.x * 256 + threadIdx.x;
+    const I row = idx / columns; // of all batches
+    if (row >= (I)g.batch * (I)g.M) return;
+    const int n = (int)(idx - row * columns) * V, count = min(V, g.N - n);
     const E *a = static_cast<const E *>(g.a), *b = static_cast<const E *>(g.b);
-    float acc = 0.0f;
-    int n;
+    float acc[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) acc[v] = 0.0f;
     if constexpr (FAM == FAM_CONV) {
-        // idx walks the NHWC output: (img, p, q, n); activations NHWC, filters KRSC
-        n = (int)(idx % g.N);
-        const int64_t pix = idx / g.N;
-        const int q = (int)(pix % g.Wo), p = (int)((pix / g.Wo) % g.Ho);
-        const int img = (int)(pix / ((int64_t)g.Ho * g.Wo));
+        // rows are output pixels (img, p, q); activations NHWC, filters KRSC
+        const I img = row / (I)(g.Ho * g.Wo);
+        const int rem = (int)(row - img * (I)(g.Ho * g.Wo)), p = rem / g.Wo, q = rem - p * g.Wo;
         for (int r = 0; r < g.R; ++r) {
             const int ih = p * g.stride_h + r - g.pad_h;
             if (ih < 0 || ih >= g.H) continue;
             for (int s = 0; s < g.S; ++s) {
                 const int iw = q * g.stride_w + s - g.pad_w;
                 if (iw < 0 || iw >= g.W) continue;
-                const E *xp = a + (((int64_t)img * g.H + ih) * g.W + iw) * g.C;
-                const E *wp = b + (((int64_t)n * g.R + r) * g.S + s) * g.C;
-                for (int c = 0; c < g.C; ++c) acc = fmaf(load_as_float<DT>(xp, c), load_as_float<DT>(wp, c), acc);
+                const E *w[V];
+#pragma unroll
+                for (int v = 0; v < V; ++v) w[v] = b + (((int64_t)min(n + v, g.N - 1) * g.R + r) * g.S + s) * g.C;
+                add_products<DT, V>(acc, a + (((int64_t)img * g.H + ih) * g.W + iw) * g.C, w, g.C);
             }
         }
     } else {
-        n = (int)(idx % g.N);
-        const int m = (int)((idx / g.N) % g.M);
-        const int bi = (int)(idx / ((int64_t)g.M * g.N));
-        const E *ar = a + ((int64_t)bi * g.M + m) * g.K;
-        const E *bb = b + (int64_t)bi * g.N * g.K;
-        for (int k = 0; k < g.K; ++k) {
-            const float bv = FAM == FAM_GEMM_TN ? load_as_float<DT>(bb, (int64_t)n * g.K + k)
-                                                : load_as_float<DT>(bb, (int64_t)k * g.N + n);
-            acc = fmaf(load_as_float<DT>(ar, k), bv, acc);
+        const int64_t bi = (int64_t)(row / (I)g.M);
+        const E *ar = a + (int64_t)row * g.K, *bb = b + bi * g.N * g.K;
+        if constexpr (FAM == FAM_GEMM_TN) {
+            const E *w[V];
+#pragma unroll
+            for (int v = 0; v < V; ++v) w[v] = bb + (int64_t)min(n + v, g.N - 1) * g.K;
+            add_products<DT, V>(acc, ar, w, g.K);
+        } else {
+            for (int k = 0; k < g.K; ++k) {
+                const float av = load_as_float<DT>(ar, k);
+#pragma unroll
+                for (int v = 0; v < V; ++v) acc[v] = fmaf(av, load_as_float<DT>(bb, (int64_t)k * g.N + min(n + v, g.N - 1)), acc[v]);
+            }
         }
     }
-    if (g.has_bias) acc += load_as_float<DT>(g.bias, n);
-    if (g.has_res) acc += load_as_float<DT>(g.res, idx);
-    store_from_float<DT>(g.out, idx, apply_act(acc, g.act));
+    const int64_t at = (int64_t)row * g.N + n;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        if (v >= count) break;
+        float out = acc[v];
+        if (g.has_bias) out += load_as_float<DT>(g.bias, n + v);
+        if (g.has_res) out += load_as_float<DT>(g.res, at + v);
+        store_from_float<DT>(g.out, at + v, apply_act(out, g.act));
+    }
 }
 
 // ---- split-K: sum the partial tiles in split order, then the fused epilogue -----------------------
@@ -420,23 +473,32 @@ __global__ void __launch_bounds__(256) tile_map_dump_kernel(const TileMap map, i
     o[7] = c.k_ext;
 }
 
-template <int DT> int launch_direct_dt(const ContractArgs &a, const PointerSets &sets, int family, int grid, hipStream_t s)
+template <int DT, int FAM> int launch_direct_of(const ContractArgs &a, const PointerSets &sets, hipStream_t s)
+{
+    constexpr int MOST = FAM == FAM_GEMM_NN ? 1 : 4;
+    const int v = a.N >= 4 ? MOST : 1;
+    const int64_t threads = (int64_t)a.batch * a.M * ((a.N + v - 1) / v);
+    const dim3 grid((unsigned)((threads + 255) / 256), sets.count);
+    auto kern = v > 1 ? direct_kernel<DT, FAM, MOST, uint32_t> : direct_kernel<DT, FAM, 1, uint32_t>;
+    if (threads >= 1ll << 31) kern = v > 1 ? direct_kernel<DT, FAM, MOST, uint64_t> : direct_kernel<DT, FAM, 1, uint64_t>;
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, a, sets);
+    return launched();
+}
+template <int DT> int launch_direct_dt(const ContractArgs &a, const PointerSets &sets, int family, hipStream_t s)
 {
     switch (family) {
-    case FAM_CONV: hipLaunchKernelGGL((direct_kernel<DT, FAM_CONV>), dim3(grid, sets.count), dim3(256), 0, s, a, sets); break;
-    case FAM_GEMM_TN: hipLaunchKernelGGL((direct_kernel<DT, FAM_GEMM_TN>), dim3(grid, sets.count), dim3(256), 0, s, a, sets); break;
-    default: hipLaunchKernelGGL((direct_kernel<DT, FAM_GEMM_NN>), dim3(grid, sets.count), dim3(256), 0, s, a, sets); break;
+    case FAM_CONV: return launch_direct_of<DT, FAM_CONV>(a, sets, s);
+    case FAM_GEMM_TN: return launch_direct_of<DT, FAM_GEMM_TN>(a, sets, s);
+    default: return launch_direct_of<DT, FAM_GEMM_NN>(a, sets, s);
     }
-    return launched();
 }
 
 } // namespace
 
-int launch_direct(const ContractArgs &args, const PointerSets &sets, int family, int grid, void *stream)
+int launch_direct(const ContractArgs &args, const PointerSets &sets, int family, void *stream)
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
-    return args.dtype == TT_F32 ? launch_direct_dt<TT_F32>(args, sets, family, grid, s)
-                                : launch_direct_dt<TT_BF16>(args, sets, family, grid, s);
+    return args.dtype == TT_F32 ? launch_direct_dt<TT_F32>(args, sets, family, s) : launch_direct_dt<TT_BF16>(args, sets, family, s);
 }
 
 int launch_splitk_reduce(const ContractArgs &args, const PointerSets &sets, int family, void *stream)

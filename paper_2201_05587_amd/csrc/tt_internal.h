@@ -394,7 +394,7 @@ int find_variant(int dtype, int family, int tm, int tn, int tk, int wm, int wn, 
 int family_of(int cls, int trans_b);
 
 // launchers of the non-matrix-core kernels (simple_kernels.hip)
-int launch_direct(const ContractArgs &args, const PointerSets &sets, int family, int grid, void *stream);
+int launch_direct(const ContractArgs &args, const PointerSets &sets, int family, void *stream);
 int launch_splitk_reduce(const ContractArgs &args, const PointerSets &sets, int family, void *stream);
 int launch_gemv(const ContractArgs &args, const PointerSets &sets, const tt_plan &plan, void *stream);
 // the 256 x 256 block kernel (contract_block.hip): whether a launch of `count` sets runs on it, and its launch

@@ -1,0 +1,17 @@
+"""The unscheduled loop nest: rows shorter than its pieces, reductions that end inside one, every family."""
+import pytest
+
+from paper_2201_05587_amd import api
+from paper_2201_05587_amd import workloads as wl
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("k", [1, 3, 4, 5, 7, 8, 9, 15, 16, 20, 31])
+def test_direct_against_the_oracle(k, dtype):
+    import parity as P
+    for n in (1, 3, 4, 6, 33):
+        for kernel in (wl.Kernel(7, wl.GemmShape(3, 17, n, k, 1, dtype), 1, f"qk_{n}_{k}"), wl.Kernel(7, wl.GemmShape(2, 19, n, k, 0, dtype), 1, f"pv_{n}_{k}"),
+                       wl.Kernel(2, wl.ConvShape(2, k, 5, 6, n, 3, 3, 2, 1, 1, 2, dtype), 1, f"conv_{n}_{k}"), wl.Kernel(6, wl.GemmShape(1, 40, n, k, 1, dtype), 1, f"dense_{n}_{k}")):
+            direct = api.make_schedule(kernel.cls, api.TT_SK_DIRECT, 1, 1, 1, 1, 1, 0, 1, 0, 1, 1, 1)
+            P.check_kernel(kernel, [direct], seed=3 * k + n)
