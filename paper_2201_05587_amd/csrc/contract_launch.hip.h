@@ -60,7 +60,8 @@ int launch_contract(const ContractArgs &args, const PointerSets &sets, int grid,
         if (kernel_contract<DT, FAM, TM, TN, TK, WM, WN, MF, AM>(args, sets.count, grid) == TT_LAUNCH_ROWS)
             return launch_conv_rows(args, sets, stream);
     auto kern = contract_kernel<DT, FAM, TM, TN, TK, WM, WN, MF, AM>;
-    if constexpr (((FAM == FAM_CONV && AM != 16) || FAM == FAM_GEMM_TN) && WM * WN <= 4096 && (TM / WM) * (TN / WN) <= 8) // (beyond, sums and slices do not fit the registers)
+    constexpr int WAVES = (TM / WM) * (TN / WN), ITEMS = (TM + TN) * TK / ElemOf<DT>::CH / (WAVES * 64); // of a slice, for a lane
+    if constexpr (((FAM == FAM_CONV && AM != 16) || FAM == FAM_GEMM_TN) && WM * WN <= 4096 && WAVES <= 8 && ITEMS <= 8) // (beyond, sums and slices do not fit the registers)
         if (taps_apply<DT, FAM>(args)) kern = contract_taps_kernel<DT, FAM, TM, TN, TK, WM, WN, MF>;
     constexpr int EPI_BYTES = epilogue_bytes(TM, TN, WM, WN, MF);
     if (lds_bytes < EPI_BYTES) lds_bytes = EPI_BYTES;
