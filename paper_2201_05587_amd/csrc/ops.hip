@@ -307,6 +307,13 @@ int run_op(const tt_schedule *sched, int cls, const void *shape, const OpPointer
 
 namespace {
 
+// Whether a launch of `count` sets is a depthwise one in windows: its record's stages and strides allow them, and the operator
+// takes the record.
+bool in_windows(const PreparedOp &op, int count, DwListEntry *e, DwWindow *w, int *vc)
+{
+    return op.launch.sketch == TT_SK_DWCONV && op.launch.variant_id >= 0 && dw_windows(op.d, count, e, w, vc);
+}
+
 // The kernel of a launch of `count` sets, and the plan as it is launched there.
 int launched_plan(const PreparedOp &op, int count, tt_plan *plan)
 {
@@ -314,7 +321,7 @@ int launched_plan(const PreparedOp &op, int count, tt_plan *plan)
     DwListEntry windows;
     DwWindow w;
     int vc;
-    if (plan->sketch == TT_SK_DWCONV && dw_windows(op.d, count, &windows, &w, &vc)) {
+    if (in_windows(op, count, &windows, &w, &vc)) {
         plan->grid = (int32_t)dw_workgroups(windows), plan->block = 256;
         plan->wave_m = w.rows, plan->wave_n = w.columns, plan->eff_vec_a = plan->eff_vec_c = vc;
         return TT_LAUNCH_RECORD;
@@ -504,7 +511,7 @@ public:
         DwListEntry windows;
         DwWindow w;
         int vc;
-        if (p.sketch == TT_SK_DWCONV && dw_windows(op.d, 1, &windows, &w, &vc)) return Key{-1};
+        if (in_windows(op, 1, &windows, &w, &vc)) return Key{-1}; // (a record that the operator refuses has a key of its own)
         if (kernel == TT_LAUNCH_BLOCKS) return Key{kernel};
         if (kernel == TT_LAUNCH_ROWS) return Key{kernel, p.tile_m, p.tile_n, p.eff_vec_c, p.order};
         if (kernel == TT_LAUNCH_GROUPS)

@@ -81,3 +81,19 @@ def test_entries_of_one_plan(case):
         torch.cuda.synchronize()
         assert torch.equal(dk.output(), got)
     assert not torch.equal(together[0], together[1])
+
+
+REFUSED, VALID = (16, 7, 64, 1, 7, 4), (8, 8, 16, 1, 2, 4)  # (the first names 1024 threads of seven outputs)
+
+
+@pytest.mark.gpu
+def test_a_search_counts_no_refused_record():
+    """Records that the operator refuses share no time with those that run in the same windows."""
+    k = kernel(4, 256, 56, 56, 1)
+    pool = [api.make_schedule(k.cls, api.TT_SK_DWCONV, tm, tn, tk, wm, wn, 0, 1, 0, v, 1, 1) for tm, tn, tk, wm, wn, v in (REFUSED, VALID)]
+    dk = harness.device_kernel(k, 3)
+    assert dk.run(pool[0]) == api.TT_ERR_UNSUPPORTED and dk.run(pool[1]) == api.TT_OK
+    opts = api.tt_sweep_opts(warmup=1, samples=3, min_sample_us=20, max_launches=4, allow_slower_than_default=1)
+    rows, us, _, _ = api.tt_transfer_sweep([dk], pool, opts)
+    assert us[0][0] == -1 and us[0][1] > 0
+    assert (rows[0]["chosen"], rows[0]["n_valid"], rows[0]["n_invalid"]) == (1, 1, 1)
