@@ -473,15 +473,16 @@ __global__ void __launch_bounds__(256) tile_map_dump_kernel(const TileMap map, i
     o[7] = c.k_ext;
 }
 
+// Outputs of a thread of the direct kernel.
+int direct_outputs(const ContractArgs &a, int family) { return a.N >= 4 && family != FAM_GEMM_NN ? 4 : 1; }
 template <int DT, int FAM> int launch_direct_of(const ContractArgs &a, const PointerSets &sets, hipStream_t s)
 {
     constexpr int MOST = FAM == FAM_GEMM_NN ? 1 : 4;
-    const int v = a.N >= 4 ? MOST : 1;
-    const int64_t threads = (int64_t)a.batch * a.M * ((a.N + v - 1) / v);
-    const dim3 grid((unsigned)((threads + 255) / 256), sets.count);
+    const int v = direct_outputs(a, FAM);
+    const int64_t grid = direct_workgroups(a, FAM);
     auto kern = v > 1 ? direct_kernel<DT, FAM, MOST, uint32_t> : direct_kernel<DT, FAM, 1, uint32_t>;
-    if (threads >= 1ll << 31) kern = v > 1 ? direct_kernel<DT, FAM, MOST, uint64_t> : direct_kernel<DT, FAM, 1, uint64_t>;
-    hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, a, sets);
+    if (grid * 256 >= 1ll << 31) kern = v > 1 ? direct_kernel<DT, FAM, MOST, uint64_t> : direct_kernel<DT, FAM, 1, uint64_t>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid, sets.count), dim3(256), 0, s, a, sets);
     return launched();
 }
 template <int DT> int launch_direct_dt(const ContractArgs &a, const PointerSets &sets, int family, hipStream_t s)
@@ -494,6 +495,12 @@ template <int DT> int launch_direct_dt(const ContractArgs &a, const PointerSets 
 }
 
 } // namespace
+
+int64_t direct_workgroups(const ContractArgs &a, int family)
+{
+    const int v = direct_outputs(a, family);
+    return ((int64_t)a.batch * a.M * ((a.N + v - 1) / v) + 255) / 256;
+}
 
 int launch_direct(const ContractArgs &args, const PointerSets &sets, int family, void *stream)
 {

@@ -15,3 +15,21 @@ def test_direct_against_the_oracle(k, dtype):
                        wl.Kernel(2, wl.ConvShape(2, k, 5, 6, n, 3, 3, 2, 1, 1, 2, dtype), 1, f"conv_{n}_{k}"), wl.Kernel(6, wl.GemmShape(1, 40, n, k, 1, dtype), 1, f"dense_{n}_{k}")):
             direct = api.make_schedule(kernel.cls, api.TT_SK_DIRECT, 1, 1, 1, 1, 1, 0, 1, 0, 1, 1, 1)
             P.check_kernel(kernel, [direct], seed=3 * k + n)
+
+
+def direct(cls):
+    return api.make_schedule(cls, api.TT_SK_DIRECT, 1, 1, 1, 1, 1, 0, 1, 0, 1, 1, 1)
+
+
+# kernel, outputs of a thread
+GRIDS = [(wl.Kernel(7, wl.GemmShape(65, 31, 31, 31, 1, wl.BF16)), 4), (wl.Kernel(7, wl.GemmShape(65, 31, 31, 31, 0, wl.BF16)), 1),
+         (wl.Kernel(7, wl.GemmShape(3, 100, 3, 40, 1, wl.F32)), 1), (wl.Kernel(6, wl.GemmShape(1, 300, 101, 64, 1, wl.BF16)), 4)]
+
+
+@pytest.mark.parametrize("kernel,outputs", GRIDS)
+def test_the_grid_of_a_launch(kernel, outputs):
+    """As launched, which is not the plan's (a workgroup per 256 outputs)."""
+    s = kernel.shape
+    plan, which = api.tt_debug_launch(direct(kernel.cls), kernel.cls, s)
+    assert which == api.TT_LAUNCH_RECORD and plan.block == 256
+    assert plan.grid == -(-s.batch * s.m * -(-s.n // outputs) // 256)
