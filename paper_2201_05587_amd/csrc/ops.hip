@@ -326,7 +326,7 @@ int launched_plan(const PreparedOp &op, int count, tt_plan *plan)
         plan->wave_m = w.rows, plan->wave_n = w.columns, plan->eff_vec_a = plan->eff_vec_c = vc;
         return TT_LAUNCH_RECORD;
     }
-    if (plan->sketch == TT_SK_DIRECT && op.cls != TT_DWCONV_BIAS_RELU6) plan->grid = (int32_t)direct_workgroups(op.g, op.family);
+    if (plan->sketch == TT_SK_DIRECT && op.cls != TT_DWCONV_BIAS_RELU6) plan->grid = (int32_t)direct_workgroups(op.g, op.family, count);
     if (plan->sketch != TT_SK_MFMA || plan->variant_id < 0 || plan->variant_id >= kNumVariants) return TT_LAUNCH_RECORD;
     const Variant &v = kVariants[plan->variant_id];
     if (!v.shape) return TT_LAUNCH_RECORD;

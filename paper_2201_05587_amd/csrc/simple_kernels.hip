@@ -19,16 +19,26 @@ inline int launched()
 
 // ---- direct sketch: the unscheduled loop nest, a thread per few outputs ------------------------------------------
 // What shapes below the matrix cores' smallest tile run on (a 1x1 convolution over 16 bf16 channels, 20 tokens), so reductions
-// are short and the instructions around them count.  A thread forms V neighbouring outputs of a row (4, or 1 in rows shorter
-// than that), which share its reads of the first operand, and reads both operands in 16-byte pieces at element alignment (a
-// [K][N] operand: one output, its elements next to those of the neighbouring lanes); every sum runs in the order of the loop nest.  Rows and columns are counted in 32 bits (I) where they fit.
-// A thread per output and element by element -> this (us): bf16 1x1 convolutions, 16 -> 624 channels on 6 x 17x17 34.7 -> 10.1,
-// 16 -> 72 on 7 x 25x22 12.0 -> 5.3, 20 -> 128 on 8 x 56x57 62 -> 18; 3x3 stride 3, 64 -> 33 on 7x7 57 -> 23; 192 products of 31 x 31 x 31
-// 9.0 -> 5.8; fp32 13 -> 64 on 4 x 30x30 6.1 -> 4.6.
-template <int DT, int V>
+// are short and the instructions around them count.  A thread forms V neighbouring outputs of a row (4 or 1, see direct_outputs),
+// which share its reads of the first operand, and reads both operands in 16-byte PIECES at element alignment, or element by element
+// where a run is shorter (a [K][N] operand always: its elements lie next to those of the neighbouring lanes); every sum runs in the
+// order of the loop nest.  Rows and columns are counted in 32 bits (I) where they fit.
+// A thread per output, element by element and counted in 64 bits -> this (us): bf16 1x1 convolutions, 16 -> 624 channels on 6 x
+// 17x17 34.6 -> 10.1, 16 -> 72 on 7 x 25x22 12.0 -> 3.7, 20 -> 128 on 8 x 56x57 59.7 -> 17.9; 3x3 stride 3, 64 -> 33 on 7x7 57.3 -> 12.5;
+// 5x5, 4 -> 98 on 3x9 8.6 -> 8.4; 192 products of 31 x 31 x 31 9.1 -> 5.8; fp32 13 -> 64 on 4 x 30x30 6.2 -> 3.8, 3x3 41 -> 29 on 2 x
+// 13x13 42.1 -> 16.5; the geometric mean over 750 draws is 1.74 times.
+template <int DT, int V, bool PIECES>
 __device__ __forceinline__ void add_products(float (&acc)[V], const typename ElemOf<DT>::type *x, const typename ElemOf<DT>::type *const (&w)[V], int count)
 {
     constexpr int CH = ElemOf<DT>::CH;
+    if constexpr (!PIECES) {
+        for (int c = 0; c < count; ++c) {
+            const float xv = load_as_float<DT>(x, c);
+#pragma unroll
+            for (int v = 0; v < V; ++v) acc[v] = fmaf(xv, load_as_float<DT>(w[v], c), acc[v]);
+        }
+        return;
+    }
     int c = 0;
     for (; c + CH <= count; c += CH) {
         u32x4 xv, wv[V];
@@ -40,7 +50,7 @@ __device__ __forceinline__ void add_products(float (&acc)[V], const typename Ele
 #pragma unroll
             for (int v = 0; v < V; ++v) acc[v] = fmaf(element_of<DT>(xv, e), element_of<DT>(wv[v], e), acc[v]);
     }
-    if (c < count && count >= CH) { // the rest: the last piece, shifted down to where the sum stands (zeros behind it)
+    if (c < count) { // the rest: the last piece, shifted down to where the sum stands (zeros behind it)
         const int back = c + CH - count;
         u32x4 xv, wv[V];
         load16(xv, x + count - CH);
@@ -53,13 +63,9 @@ __device__ __forceinline__ void add_products(float (&acc)[V], const typename Ele
         for (int e = 0; e < CH - 1; ++e)
 #pragma unroll
             for (int v = 0; v < V; ++v) acc[v] = fmaf(element_of<DT>(xv, e), element_of<DT>(wv[v], e), acc[v]);
-        return;
     }
-    for (; c < count; ++c)
-#pragma unroll
-        for (int v = 0; v < V; ++v) acc[v] = fmaf(load_as_float<DT>(x, c), load_as_float<DT>(w[v], c), acc[v]);
 }
-template <int DT, int FAM, int V, typename I> __global__ void __launch_bounds__(256) direct_kernel(const ContractArgs args, const PointerSets sets)
+template <int DT, int FAM, int V, bool PIECES, typename I> __global__ void __launch_bounds__(256) direct_kernel(const ContractArgs args, const PointerSets sets)
 {
     const ContractArgs g = with_set(args, sets, blockIdx.y);
     using E = typename ElemOf<DT>::type;
@@ -85,7 +91,7 @@ template <int DT, int FAM, int V, typename I> __global__ void __launch_bounds__(
                 const E *w[V];
 #pragma unroll
                 for (int v = 0; v < V; ++v) w[v] = b + (((int64_t)min(n + v, g.N - 1) * g.R + r) * g.S + s) * g.C;
-                add_products<DT, V>(acc, a + (((int64_t)img * g.H + ih) * g.W + iw) * g.C, w, g.C);
+                add_products<DT, V, PIECES>(acc, a + (((int64_t)img * g.H + ih) * g.W + iw) * g.C, w, g.C);
             }
         }
     } else {
@@ -95,7 +101,7 @@ template <int DT, int FAM, int V, typename I> __global__ void __launch_bounds__(
             const E *w[V];
 #pragma unroll
             for (int v = 0; v < V; ++v) w[v] = bb + (int64_t)min(n + v, g.N - 1) * g.K;
-            add_products<DT, V>(acc, ar, w, g.K);
+            add_products<DT, V, PIECES>(acc, ar, w, g.K);
         } else {
             for (int k = 0; k < g.K; ++k) {
                 const float av = load_as_float<DT>(ar, k);
@@ -473,17 +479,30 @@ __global__ void __launch_bounds__(256) tile_map_dump_kernel(const TileMap map, i
     o[7] = c.k_ext;
 }
 
-// Outputs of a thread of the direct kernel.
-int direct_outputs(const ContractArgs &a, int family) { return a.N >= 4 && family != FAM_GEMM_NN ? 4 : 1; }
-template <int DT, int FAM> int launch_direct_of(const ContractArgs &a, const PointerSets &sets, hipStream_t s)
+// Whether the direct kernel reads in pieces: reductions (a pixel's channels) of at least one.  Shorter ones are a loop over
+// elements, of one output a thread: that loop with four took 1.2 to 1.7 times as long at any size.
+bool direct_in_pieces(const ContractArgs &a, int family) { return family != FAM_GEMM_NN && (family == FAM_CONV ? a.C : a.K) >= (a.dtype == TT_F32 ? 4 : 8); }
+// Outputs of a thread: four read the first operand a fourth as often, one has four times the threads to wait for memory with.
+// One -> four, geometric means over draws (bf16 runs of 8 .. 31 channels, of 32 and more; fp32 of 4 .. 15, of 16 and more): 8 to 30
+// thousand outputs 1.57, 1.83, 1.29, 2.05 times as long, 30 to 100 thousand 1.50, 1.63, 1.32, 1.72, 100 to 400 thousand 1.12, 1.13,
+// 1.18, 1.08, beyond (to 3 million) 0.83, 0.66, 1.08, 0.98.
+int direct_outputs(const ContractArgs &a, int family, int count)
 {
-    constexpr int MOST = FAM == FAM_GEMM_NN ? 1 : 4;
-    const int v = direct_outputs(a, FAM);
-    const int64_t grid = direct_workgroups(a, FAM);
-    auto kern = v > 1 ? direct_kernel<DT, FAM, MOST, uint32_t> : direct_kernel<DT, FAM, 1, uint32_t>;
-    if (grid * 256 >= 1ll << 31) kern = v > 1 ? direct_kernel<DT, FAM, MOST, uint64_t> : direct_kernel<DT, FAM, 1, uint64_t>;
+    return direct_in_pieces(a, family) && a.N >= 4 && (int64_t)a.batch * a.M * a.N * count >= 400000 ? 4 : 1;
+}
+template <int DT, int FAM, int V, bool PIECES> int launch_direct_in(int64_t grid, const ContractArgs &a, const PointerSets &sets, hipStream_t s)
+{
+    const auto kern = grid < 1ll << 23 ? direct_kernel<DT, FAM, V, PIECES, uint32_t> : direct_kernel<DT, FAM, V, PIECES, uint64_t>;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid, sets.count), dim3(256), 0, s, a, sets);
     return launched();
+}
+template <int DT, int FAM> int launch_direct_of(const ContractArgs &a, const PointerSets &sets, hipStream_t s)
+{
+    const int64_t grid = direct_workgroups(a, FAM, sets.count);
+    if constexpr (FAM != FAM_GEMM_NN)
+        if (direct_in_pieces(a, FAM))
+            return direct_outputs(a, FAM, sets.count) == 4 ? launch_direct_in<DT, FAM, 4, true>(grid, a, sets, s) : launch_direct_in<DT, FAM, 1, true>(grid, a, sets, s);
+    return launch_direct_in<DT, FAM, 1, false>(grid, a, sets, s);
 }
 template <int DT> int launch_direct_dt(const ContractArgs &a, const PointerSets &sets, int family, hipStream_t s)
 {
@@ -496,9 +515,9 @@ template <int DT> int launch_direct_dt(const ContractArgs &a, const PointerSets 
 
 } // namespace
 
-int64_t direct_workgroups(const ContractArgs &a, int family)
+int64_t direct_workgroups(const ContractArgs &a, int family, int count)
 {
-    const int v = direct_outputs(a, family);
+    const int v = direct_outputs(a, family, count);
     return ((int64_t)a.batch * a.M * ((a.N + v - 1) / v) + 255) / 256;
 }
 

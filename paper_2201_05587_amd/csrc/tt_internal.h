@@ -394,7 +394,7 @@ int find_variant(int dtype, int family, int tm, int tn, int tk, int wm, int wn, 
 int family_of(int cls, int trans_b);
 
 // launchers of the non-matrix-core kernels (simple_kernels.hip)
-int64_t direct_workgroups(const ContractArgs &args, int family); // of one pointer set
+int64_t direct_workgroups(const ContractArgs &args, int family, int count); // of one of `count` pointer sets
 int launch_direct(const ContractArgs &args, const PointerSets &sets, int family, void *stream);
 int launch_splitk_reduce(const ContractArgs &args, const PointerSets &sets, int family, void *stream);
 int launch_gemv(const ContractArgs &args, const PointerSets &sets, const tt_plan &plan, void *stream);

@@ -21,15 +21,28 @@ def direct(cls):
     return api.make_schedule(cls, api.TT_SK_DIRECT, 1, 1, 1, 1, 1, 0, 1, 0, 1, 1, 1)
 
 
-# kernel, outputs of a thread
-GRIDS = [(wl.Kernel(7, wl.GemmShape(65, 31, 31, 31, 1, wl.BF16)), 4), (wl.Kernel(7, wl.GemmShape(65, 31, 31, 31, 0, wl.BF16)), 1),
-         (wl.Kernel(7, wl.GemmShape(3, 100, 3, 40, 1, wl.F32)), 1), (wl.Kernel(6, wl.GemmShape(1, 300, 101, 64, 1, wl.BF16)), 4)]
+# kernel, entries, outputs of a thread: to either side of the line, of rows shorter than four and of runs shorter than a piece
+GRIDS = [(wl.Kernel(7, wl.GemmShape(65, 31, 31, 31, 1, wl.BF16)), 1, 1), (wl.Kernel(7, wl.GemmShape(65, 31, 31, 31, 1, wl.BF16)), 7, 4),
+         (wl.Kernel(6, wl.GemmShape(1, 10000, 40, 8, 1, wl.BF16)), 1, 4), (wl.Kernel(6, wl.GemmShape(1, 9999, 40, 8, 1, wl.BF16)), 1, 1),
+         (wl.Kernel(6, wl.GemmShape(1, 20000, 37, 7, 1, wl.BF16)), 1, 1), (wl.Kernel(4, wl.GemmShape(1, 20000, 37, 7, 1, wl.F32)), 1, 4),
+         (wl.Kernel(7, wl.GemmShape(1, 150000, 3, 40, 1, wl.F32)), 1, 1), (wl.Kernel(7, wl.GemmShape(200, 50, 50, 9, 0, wl.BF16)), 1, 1),
+         (wl.Kernel(4, wl.GemmShape(1, 20000, 37, 3, 1, wl.F32)), 1, 1)]
 
 
-@pytest.mark.parametrize("kernel,outputs", GRIDS)
-def test_the_grid_of_a_launch(kernel, outputs):
+@pytest.mark.parametrize("kernel,count,outputs", GRIDS)
+def test_the_grid_of_a_launch(kernel, count, outputs):
     """As launched, which is not the plan's (a workgroup per 256 outputs)."""
     s = kernel.shape
-    plan, which = api.tt_debug_launch(direct(kernel.cls), kernel.cls, s)
+    plan, which = api.tt_debug_launch(direct(kernel.cls), kernel.cls, s, count)
     assert which == api.TT_LAUNCH_RECORD and plan.block == 256
     assert plan.grid == -(-s.batch * s.m * -(-s.n // outputs) // 256)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("k", [8, 9, 20])
+def test_four_outputs_a_thread_against_the_oracle(k, dtype):
+    import parity as P
+    for kernel in (wl.Kernel(7, wl.GemmShape(9, 1200, 39, k, 1, dtype), 1, f"qk_{k}"), wl.Kernel(2, wl.ConvShape(3, k, 45, 46, 66, 3, 3, 1, 1, 1, 1, dtype), 1, f"conv_{k}")):
+        assert api.tt_debug_launch(direct(kernel.cls), kernel.cls, kernel.shape)[0].grid < 450  # (400 thousand outputs and more)
+        P.check_kernel(kernel, [direct(kernel.cls)], seed=k)
