@@ -50,6 +50,16 @@ LaunchShape shape_contract_async(const ContractArgs &args, int count, int grid, 
     return shape_on<DT, FAM, TM, TN, WM, WN, MF>(kernel_contract_async<DT, FAM, TM, TN, TK, WM, WN, MF>(args, count, grid, lds_bytes), args, count, grid, lds_bytes);
 }
 
+// A launch of one kernel.  The LDS it has been allowed so far is the kernel's own, whatever else the record can come to.
+template <auto KERNEL> int launch_tiles(const ContractArgs &args, const PointerSets &sets, int grid, int threads, int lds_bytes, void *stream, const char *where)
+{
+    static DynamicLdsLimit limit;
+    if (const int rc = limit.raise_to(reinterpret_cast<const void *>(KERNEL), lds_bytes); rc != TT_OK) return rc;
+    hipLaunchKernelGGL(KERNEL, dim3(grid, sets.count), dim3(threads), lds_bytes, static_cast<hipStream_t>(stream), args, sets);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? TT_OK : note_hip_error((int)e, where);
+}
+
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF, int AM>
 int launch_contract(const ContractArgs &args, const PointerSets &sets, int grid, int lds_bytes, void *stream)
 {
@@ -59,18 +69,12 @@ int launch_contract(const ContractArgs &args, const PointerSets &sets, int grid,
     if constexpr (FAM == FAM_CONV && AM != 16)
         if (kernel_contract<DT, FAM, TM, TN, TK, WM, WN, MF, AM>(args, sets.count, grid) == TT_LAUNCH_ROWS)
             return launch_conv_rows(args, sets, stream);
-    auto kern = contract_kernel<DT, FAM, TM, TN, TK, WM, WN, MF, AM>;
     constexpr int WAVES = (TM / WM) * (TN / WN), ITEMS = (TM + TN) * TK / ElemOf<DT>::CH / (WAVES * 64); // of a slice, for a lane
+    lds_bytes = std::max(lds_bytes, epilogue_bytes(TM, TN, WM, WN, MF));
     if constexpr (((FAM == FAM_CONV && AM != 16) || FAM == FAM_GEMM_TN) && WM * WN <= 4096 && WAVES <= 8 && ITEMS <= 8) // (beyond, sums and slices do not fit the registers)
-        if (taps_apply<DT, FAM>(args)) kern = contract_taps_kernel<DT, FAM, TM, TN, TK, WM, WN, MF>;
-    constexpr int EPI_BYTES = epilogue_bytes(TM, TN, WM, WN, MF);
-    if (lds_bytes < EPI_BYTES) lds_bytes = EPI_BYTES;
-    static DynamicLdsLimit limit; // per kernel instance
-    if (const int rc = limit.raise_to(reinterpret_cast<const void *>(kern), lds_bytes); rc != TT_OK) return rc;
-    constexpr int THREADS = (TM / WM) * (TN / WN) * 64;
-    hipLaunchKernelGGL(kern, dim3(grid, sets.count), dim3(THREADS), lds_bytes, static_cast<hipStream_t>(stream), args, sets);
-    const hipError_t e = hipGetLastError();
-    return e == hipSuccess ? TT_OK : note_hip_error((int)e, "contract_kernel launch");
+        if (taps_apply<DT, FAM>(args))
+            return launch_tiles<contract_taps_kernel<DT, FAM, TM, TN, TK, WM, WN, MF>>(args, sets, grid, WAVES * 64, lds_bytes, stream, "contract_taps_kernel launch");
+    return launch_tiles<contract_kernel<DT, FAM, TM, TN, TK, WM, WN, MF, AM>>(args, sets, grid, WAVES * 64, lds_bytes, stream, "contract_kernel launch");
 }
 
 // What the host's resource check multiplies by the number of stages.
@@ -98,15 +102,9 @@ int launch_contract_async(const ContractArgs &args, const PointerSets &sets, int
     if constexpr (DT == TT_BF16)
         if (kernel == TT_LAUNCH_BLOCKS) return launch_blocks(args, sets, FAM, stream);
     if (kernel == TT_LAUNCH_GROUPS) return launch_groups<DT, FAM, TM, TN, WM, WN, MF>(args, sets, grid, stream);
-    auto kern = contract_async_kernel<DT, FAM, TM, TN, TK, WM, WN, MF>;
-    constexpr int EPI_BYTES = epilogue_bytes(TM, TN, WM, WN, MF);
-    if (lds_bytes < EPI_BYTES) lds_bytes = EPI_BYTES;
-    static DynamicLdsLimit limit; // per kernel instance
-    if (const int rc = limit.raise_to(reinterpret_cast<const void *>(kern), lds_bytes); rc != TT_OK) return rc;
-    constexpr int THREADS = (TM / WM) * (TN / WN) * 64;
-    hipLaunchKernelGGL(kern, dim3(grid, sets.count), dim3(THREADS), lds_bytes, static_cast<hipStream_t>(stream), args, sets);
-    const hipError_t e = hipGetLastError();
-    return e == hipSuccess ? TT_OK : note_hip_error((int)e, "contract_async_kernel launch");
+    return launch_tiles<contract_async_kernel<DT, FAM, TM, TN, TK, WM, WN, MF>>(args, sets, grid, (TM / WM) * (TN / WN) * 64,
+                                                                                std::max(lds_bytes, epilogue_bytes(TM, TN, WM, WN, MF)), stream,
+                                                                                "contract_async_kernel launch");
 }
 
 } // namespace tt

@@ -1,0 +1,29 @@
+"""What the library asks the runtime for: kernels, grids and the LDS they are allowed."""
+import pytest
+
+from launches import launches
+from paper_2201_05587_amd import api
+from paper_2201_05587_amd import workloads as wl
+
+ENABLED = 48 * 1024  # of dynamic LDS; more has to be asked for, per kernel
+
+
+def mfma(cls, tm, tn, tk, wm, wn, mf, stages, vec, split_k=1, order=1):
+    return api.make_schedule(cls, api.TT_SK_MFMA, tm, tn, tk, wm, wn, mf, split_k, order, vec, 8, stages)
+
+
+def product(m, n, k, dtype):
+    return wl.CLS_BATCH_MATMUL, wl.GemmShape(1, m, n, k, 1, dtype)
+
+
+def test_lds_is_enabled_for_the_kernel_that_runs():
+    """Two kernels under one record: rows of whole items, and not (either one first)."""
+    calls = []
+    for tile, first in (((128, 128, 64, 64, 64, 16), 0), ((128, 128, 64, 32, 64, 16), 1)):
+        for k in ((6400, 6399), (6399, 6400))[first]:
+            calls.append(product(8000, 8000, k, wl.BF16) + (mfma(wl.CLS_BATCH_MATMUL, *tile, 2, 8),))
+    done = launches(calls)
+    names = [made[0]["name"].split("<")[0] for rc, made in done]
+    assert all(rc == api.TT_OK for rc, _ in done) and len(set(names)) == 2, names
+    for rc, made in done:
+        assert made[0]["lds"] > ENABLED and made[0]["enabled"] >= made[0]["lds"], done
