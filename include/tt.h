@@ -476,14 +476,14 @@ int tt_schedule_space(int cls, int dtype, int level, tt_schedule *out, int cap);
  * not listed); sched NULL = default.  Host only, for inspection and tests.  *kernel:
  * TT_LAUNCH_RECORD, the kernel launched->variant_id (or the sketch) names; TT_LAUNCH_GROUPS, contract_groups_kernel in the
  * same tiles; TT_LAUNCH_BLOCKS, contract_block_kernel in blocks of 256 x 256; TT_LAUNCH_ROWS, conv_rows_kernel in the
- * same tiles.  launched: the plan as it is launched, with
+ * same tiles; TT_LAUNCH_TAPS, contract_taps_kernel in the same tiles.  launched: the plan as it is launched, with
  * grid, block and lds_bytes of the kernel that runs (per entry; the persistent kernel of seven stages divides its grid
  * among fewer workgroups), and for a depthwise record of one stage and equal strides the wave_m x wave_n outputs of eff_vec_a
- * channels that a thread forms there, whatever the record's (dwconv3x3_window_kernel).  Returns the apply status, TT_ERR_BAD_ARG for a count out of range, or TT_ERR_UNSUPPORTED where
- * the operator would.
+ * channels that a thread forms there, whatever the record's (dwconv3x3_window_kernel).  Returns the apply status, TT_ERR_BAD_ARG
+ * for a count out of range, or TT_ERR_UNSUPPORTED where the operator would.
  */
 #define TT_MAX_ENTRIES_PER_LAUNCH 8
-enum tt_launch_kernel { TT_LAUNCH_RECORD = 0, TT_LAUNCH_GROUPS = 1, TT_LAUNCH_BLOCKS = 2, TT_LAUNCH_ROWS = 3 };
+enum tt_launch_kernel { TT_LAUNCH_RECORD = 0, TT_LAUNCH_GROUPS = 1, TT_LAUNCH_BLOCKS = 2, TT_LAUNCH_ROWS = 3, TT_LAUNCH_TAPS = 4 };
 int tt_debug_launch(const tt_schedule *sched, int cls, const void *shape, int count, tt_plan *launched, int32_t *kernel);
 
 /*

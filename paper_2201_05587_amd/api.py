@@ -340,7 +340,7 @@ def tt_debug_tile_map(plan):
     return out.cpu().numpy()
 
 
-TT_LAUNCH_RECORD, TT_LAUNCH_GROUPS, TT_LAUNCH_BLOCKS, TT_LAUNCH_ROWS = range(4)
+TT_LAUNCH_RECORD, TT_LAUNCH_GROUPS, TT_LAUNCH_BLOCKS, TT_LAUNCH_ROWS, TT_LAUNCH_TAPS = range(5)
 TT_MAX_ENTRIES_PER_LAUNCH = 8
 TT_LISTED_RECORD, TT_LISTED_TILES, TT_LISTED_STREAM, TT_LISTED_DEPTHWISE = range(4)
 
@@ -572,9 +572,11 @@ def launched_name(sched, cls, shape, count=1) -> str:
         return f"tt::dwconv3x3_window{sets}_kernel<{shape.stride_h}, {plan.eff_vec_a}, {plan.wave_m}, {plan.wave_n}>"
     if kernel == TT_LAUNCH_RECORD:
         return variant_name(plan, shape)
-    dtype, family, tm, tn, _, wm, wn, mf = tt_variant_info(plan.variant_id)[:8]
+    dtype, family, tm, tn, tk, wm, wn, mf = tt_variant_info(plan.variant_id)[:8]
     if kernel == TT_LAUNCH_BLOCKS:
         return f"tt::contract_block_kernel<{family}>"
+    if kernel == TT_LAUNCH_TAPS:
+        return f"tt::contract_taps_kernel<{dtype}, {family}, {tm}, {tn}, {tk}, {wm}, {wn}, {mf}>"
     if kernel == TT_LAUNCH_ROWS:
         return f"tt::conv_rows_kernel<{tm}, {tn}>"
     return f"tt::contract_groups_kernel<{dtype}, {family}, {tm}, {tn}, {wm}, {wn}, {mf}>"

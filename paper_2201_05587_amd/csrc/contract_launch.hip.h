@@ -11,6 +11,13 @@ namespace tt {
 // LDS the epilogue stages one band of MF rows per wave in (the operands' own).
 constexpr int epilogue_bytes(int TM, int TN, int WM, int WN, int MF) { return (TM / WM) * (TN / WN) * MF * (WN + (MF == 32 ? 8 : 4)) * 4; }
 
+// Whether there is a walk by taps in these tiles: beyond, sums and slices do not fit the registers.
+template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int AM> constexpr bool taps_built()
+{
+    constexpr int WAVES = (TM / WM) * (TN / WN), ITEMS = (TM + TN) * TK / ElemOf<DT>::CH / (WAVES * 64); // of a slice, for a lane
+    return ((FAM == FAM_CONV && AM != 16) || FAM == FAM_GEMM_TN) && WM * WN <= 4096 && WAVES <= 8 && ITEMS <= 8;
+}
+
 // What a launch of `count` sets runs on, and the shape it has there.
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF, int AM>
 int kernel_contract(const ContractArgs &args, int count, int grid)
@@ -20,6 +27,8 @@ int kernel_contract(const ContractArgs &args, int count, int grid)
     } else if constexpr (FAM == FAM_CONV) {
         if (rows_shape(args, count).grid > 0) return TT_LAUNCH_ROWS;
     }
+    if constexpr (taps_built<DT, FAM, TM, TN, TK, WM, WN, AM>())
+        if (taps_apply<DT, FAM>(args)) return TT_LAUNCH_TAPS;
     return TT_LAUNCH_RECORD;
 }
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF>
@@ -37,7 +46,7 @@ LaunchShape shape_on(int kernel, const ContractArgs &args, int count, int grid, 
     if (kernel == TT_LAUNCH_BLOCKS) return blocks_shape(args, FAM);
     if (kernel == TT_LAUNCH_ROWS) return rows_shape(args, count);
     if (kernel == TT_LAUNCH_GROUPS) return {TT_LAUNCH_GROUPS, grid, S::THREADS, S::LDS};
-    return {TT_LAUNCH_RECORD, grid, (TM / WM) * (TN / WN) * 64, std::max(lds_bytes, epilogue_bytes(TM, TN, WM, WN, MF))};
+    return {kernel, grid, (TM / WM) * (TN / WN) * 64, std::max(lds_bytes, epilogue_bytes(TM, TN, WM, WN, MF))};
 }
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF, int AM>
 LaunchShape shape_contract(const ContractArgs &args, int count, int grid, int lds_bytes)
@@ -63,18 +72,17 @@ template <auto KERNEL> int launch_tiles(const ContractArgs &args, const PointerS
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF, int AM>
 int launch_contract(const ContractArgs &args, const PointerSets &sets, int grid, int lds_bytes, void *stream)
 {
+    constexpr int THREADS = (TM / WM) * (TN / WN) * 64;
+    const int kernel = kernel_contract<DT, FAM, TM, TN, TK, WM, WN, MF, AM>(args, sets.count, grid);
     if constexpr (FAM == FAM_GEMM_TN || (FAM == FAM_CONV && AM == 16))
-        if (kernel_contract<DT, FAM, TM, TN, TK, WM, WN, MF, AM>(args, sets.count, grid) == TT_LAUNCH_GROUPS)
-            return launch_groups<DT, FAM, TM, TN, WM, WN, MF>(args, sets, grid, stream);
+        if (kernel == TT_LAUNCH_GROUPS) return launch_groups<DT, FAM, TM, TN, WM, WN, MF>(args, sets, grid, stream);
     if constexpr (FAM == FAM_CONV && AM != 16)
-        if (kernel_contract<DT, FAM, TM, TN, TK, WM, WN, MF, AM>(args, sets.count, grid) == TT_LAUNCH_ROWS)
-            return launch_conv_rows(args, sets, stream);
-    constexpr int WAVES = (TM / WM) * (TN / WN), ITEMS = (TM + TN) * TK / ElemOf<DT>::CH / (WAVES * 64); // of a slice, for a lane
+        if (kernel == TT_LAUNCH_ROWS) return launch_conv_rows(args, sets, stream);
     lds_bytes = std::max(lds_bytes, epilogue_bytes(TM, TN, WM, WN, MF));
-    if constexpr (((FAM == FAM_CONV && AM != 16) || FAM == FAM_GEMM_TN) && WM * WN <= 4096 && WAVES <= 8 && ITEMS <= 8) // (beyond, sums and slices do not fit the registers)
-        if (taps_apply<DT, FAM>(args))
-            return launch_tiles<contract_taps_kernel<DT, FAM, TM, TN, TK, WM, WN, MF>>(args, sets, grid, WAVES * 64, lds_bytes, stream, "contract_taps_kernel launch");
-    return launch_tiles<contract_kernel<DT, FAM, TM, TN, TK, WM, WN, MF, AM>>(args, sets, grid, WAVES * 64, lds_bytes, stream, "contract_kernel launch");
+    if constexpr (taps_built<DT, FAM, TM, TN, TK, WM, WN, AM>())
+        if (kernel == TT_LAUNCH_TAPS)
+            return launch_tiles<contract_taps_kernel<DT, FAM, TM, TN, TK, WM, WN, MF>>(args, sets, grid, THREADS, lds_bytes, stream, "contract_taps_kernel launch");
+    return launch_tiles<contract_kernel<DT, FAM, TM, TN, TK, WM, WN, MF, AM>>(args, sets, grid, THREADS, lds_bytes, stream, "contract_kernel launch");
 }
 
 // What the host's resource check multiplies by the number of stages.

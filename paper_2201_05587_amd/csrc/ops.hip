@@ -497,8 +497,8 @@ tt_sweep_opts resolve(const tt_sweep_opts *o)
 }
 
 // Times of one kernel's launches under one protocol, for as long as a sweep lasts.  Records that differ only in knobs the
-// kernel they run on does not have (stages, tile_k and unroll of a launch in groups, everything of one in blocks or windows) come to
-// the same launch: they share the time of the first, and the rule for ties decides among them instead of noise.
+// kernel they run on does not have (stages, tile_k and unroll of a launch in groups, vec and unroll of a walk by taps, everything of
+// one in blocks or windows) come to the same launch: they share the time of the first, and the rule for ties decides among them instead of noise.
 class LaunchTimes {
 public:
     struct Time {
@@ -518,6 +518,7 @@ public:
         if (kernel == TT_LAUNCH_GROUPS)
             return Key{kernel, p.tile_m, p.tile_n, p.wave_m, p.wave_n, p.mfma, p.eff_split_k,
                        (int32_t)std::min<int64_t>((int64_t)p.k_iters * p.tile_k, p.K), p.eff_vec_c, p.order};
+        if (kernel == TT_LAUNCH_TAPS) p.eff_vec_a = p.eff_vec_b = p.eff_unroll = 0;
         return Key{kernel, p.sketch, p.variant_id, p.tile_m, p.tile_n, p.tile_k, p.wave_m, p.wave_n, p.mfma, p.eff_split_k,
                    p.k_iters, p.eff_vec_a, p.eff_vec_b, p.eff_vec_c, p.eff_unroll, p.stages, p.order, p.grid, p.block, p.lds_bytes};
     }

@@ -2,6 +2,7 @@
 import numpy as np
 import pytest
 
+from launches import launches
 from paper_2201_05587_amd import api, harness
 from paper_2201_05587_amd import workloads as wl
 
@@ -33,6 +34,64 @@ CASES = [lambda d: conv(d, 1, 23, 5, 6, 33, 1, 1, 0), lambda d: conv(d, 2, 31, 7
          lambda d: conv(d, 1, 130, 6, 6, 70, 3, 3, 1), lambda d: conv(d, 1, 257, 5, 5, 16, 1, 2, 0),
          lambda d: product(d, 3, 33, 70, 31), lambda d: product(d, 2, 65, 33, 63), lambda d: product(d, 1, 130, 17, 127), lambda d: product(d, 5, 18, 64, 201),
          lambda d: product(d, 1, 64, 66, 515)]
+# of these every record applies: rows and columns for all of its tiles
+CASES += [lambda d: conv(d, 2, 23, 9, 8, 66, 3, 1, 1), lambda d: conv(d, 3, 130, 17, 18, 70, 3, 3, 1), lambda d: conv(d, 2, 257, 12, 13, 66, 1, 2, 0),
+          lambda d: conv(d, 1, 34, 17, 16, 65, 5, 2, 2), lambda d: conv(d, 2, 44, 9, 9, 66, 5, 1, 2), lambda d: conv(d, 1, 7 if d == wl.F32 else 55, 11, 7, 64, 3, 1, 1, 2),
+          lambda d: product(d, 2, 66, 65, 127), lambda d: product(d, 1, 130, 70, 71)]
+
+
+def by_taps(kernel):
+    """The rule on the elements of a pixel (of a row): no whole items, more than one, and little padding."""
+    s = kernel.shape
+    item, c = (8 if s.dtype == wl.BF16 else 4), s.c if kernel.is_conv() else s.k
+    padded = -(-c // item) * item
+    if c % item == 0 or c <= item:
+        return False
+    return 7 * padded <= 8 * c if item == 4 else 5 * padded < 6 * c if c % 2 == 0 else 8 * padded <= 9 * c
+
+
+def check_names(calls, walks):
+    """Named as launched; `walks` says of a call whether it walks by taps (None: either)."""
+    for (cls, shape, rec), want, (rc, made) in zip(calls, walks, launches(calls)):
+        plan, which = api.tt_debug_launch(rec, cls, shape)
+        assert rc == api.TT_OK and want in (None, which == api.TT_LAUNCH_TAPS), (shape, rec, made)
+        assert made[0]["name"].startswith("tt::contract_taps_kernel<") == (which == api.TT_LAUNCH_TAPS)
+        if plan.sketch == api.TT_SK_MFMA:
+            assert made[0]["name"] == api.launched_name(rec, cls, shape)
+            assert [made[0][x] for x in ("grid", "block", "lds")] == [plan.grid, plan.block, plan.lds_bytes]
+
+
+def test_which_cases_walk_by_taps():
+    """The cases above under their records, and channels to either side of the rule's lines."""
+    calls, walks = [], []
+    for dtype in (wl.F32, wl.BF16):
+        lines = [conv(dtype, 8, c, 56, 56, 256, 3, 1, 1) for c in ((6, 7, 9, 13, 14, 15, 17) if dtype == wl.F32 else (10, 20, 22, 23, 35, 38, 43, 50, 63, 69))]
+        for i, k in enumerate([make(dtype) for make in CASES] + lines):
+            for rec in [None] + records(k.cls, dtype):
+                if rec is None or api.tt_schedule_apply(rec, k.cls, k.shape).runnable():
+                    calls.append((k.cls, k.shape, rec))
+                    walks.append(None if rec is None else by_taps(k))
+                else:
+                    assert i < 16 or k in lines
+    assert walks.count(True) > 120 and walks.count(False) > 40
+    check_names(calls, walks)
+
+
+def test_which_tiles_walk_by_taps():
+    """Waves of at most 64 x 64, eight of them at most, and eight items a lane at most: every tile of the register pipeline."""
+    calls, walks = [], []
+    for v in range(api.lib.tt_num_variants()):
+        dtype, family, tm, tn, tk, wm, wn, mf, bytes_, pipeline = api.tt_variant_info(v)[:10]
+        if pipeline != 0 or family == 2 or bytes_ == 16:
+            continue
+        k = conv(dtype, 8, 511, 28, 28, 256, 3, 1, 1) if family == 0 else product(dtype, 1, 3000, 520, 511)
+        rec = record(k.cls, dtype, tm, tn, tk, wm, wn, 1, mfma=mf)
+        assert api.tt_schedule_apply(rec, k.cls, k.shape).variant_id == v
+        waves = tm * tn // (wm * wn)
+        calls.append((k.cls, k.shape, rec))
+        walks.append(wm * wn <= 4096 and waves <= 8 and (tm + tn) * tk // (8 if dtype == wl.BF16 else 4) // (waves * 64) <= 8)
+    assert walks.count(True) > 100 and walks.count(False) > 10
+    check_names(calls, walks)
 
 
 @pytest.mark.gpu
