@@ -128,16 +128,17 @@ __global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) contract_taps_kern
     const TileCoord tc = decode_tile(g.map, (int32_t)blockIdx.x);
     const BiasRegs<DT> bias = load_bias_early<DT, TM, WM, WN, MF>(g, tc, wave, lane);
     const int C = CONV ? g.C : g.K, R = CONV ? g.R : 1, S = CONV ? g.S : 1, padded = (C + CH - 1) / CH * CH;
-    // the split that ends at K runs on to the end of the walk
-    const int k_end = tc.k0 + tc.k_ext == g.K ? R * S * padded : tc.k0 + tc.k_ext;
-    const int kt_count = (k_end - tc.k0 + TK - 1) / TK;
+    // Splits share the walk, padding and all, slice by slice: its padding would else be the last one's (34 channels, 5x5, in nine:
+    // eight of 3 slices and one of 8, here of 4 and 3).  There are as many slices as the record's reduction has, or more.
+    const int slices = (R * S * padded + TK - 1) / TK, share = (int)fast_div((uint32_t)slices, g.map.div_split), longer = slices - share * g.map.eff_split_k;
+    const int kt_count = share + (tc.lo < longer ? 1 : 0), first = share * tc.lo + min(tc.lo, longer);
     const E *a_base = static_cast<const E *>(g.a), *b_base = static_cast<const E *>(g.b);
     if constexpr (!CONV) {
         a_base += (int64_t)tc.hi * g.M * g.K;
         b_base += (int64_t)tc.hi * g.N * g.K;
     }
     TapWalk<DT, TK> walk;
-    walk.begin(tc.k0 + tid % (TK / CH) * CH, padded, S);
+    walk.begin(first * TK + tid % (TK / CH) * CH, padded, S);
     typename ARows::Rows a_rows;
     typename BRows::Rows b_rows;
     ARows::init(a_rows, g, tc.m0, g.M, g.K, CONV ? (int)(g.a_bytes / (uint32_t)ES) : g.M * g.K, tid);

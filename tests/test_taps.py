@@ -134,3 +134,29 @@ def test_what_lies_behind_a_pixel_is_not_read_into_it(dtype, bad):
                 keep = clean_rows[part][:, None] & clean[None, :]
                 assert torch.equal(got[part][keep], want[part][keep]), (k.name, rec)
                 assert not bool(torch.isfinite(got[part][~keep]).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,c,f,tile,splits", [(wl.BF16, 34, 5, (32, 32, 32, 16, 16), 9), (wl.BF16, 44, 5, (32, 32, 32, 16, 16), 8), (wl.F32, 7, 5, (32, 32, 32, 16, 16), 4),
+                                                   (wl.BF16, 63, 3, (64, 64, 32, 32, 32), 6), (wl.F32, 131, 1, (32, 32, 32, 16, 16), 5)])
+def test_splits_share_the_walk(dtype, c, f, tile, splits):
+    """A split adds up as many slices as any other, or one more: with ones for operands its partial sum counts the elements."""
+    import torch
+    k = conv(dtype, 1, c, 12, 12, 64, f, 2 if f == 1 else 1, f // 2)
+    rec = record(k.cls, dtype, *tile, 2, split_k=splits)
+    plan, which = api.tt_debug_launch(rec, k.cls, k.shape)
+    assert which == api.TT_LAUNCH_TAPS
+    splits, m, n = plan.eff_split_k, plan.M, plan.N
+    dk = harness.device_kernel(k, 1)
+    for t in ("x", "w"):
+        dk.tensors[t].fill_(1.0)
+    assert dk.run(rec) == api.TT_OK
+    torch.cuda.synchronize()
+    parts = dk.ws[:splits * m * n * 4].view(torch.float32).view(splits, m, n)
+    inside = parts[:, k.shape.wo * (k.shape.ho // 2) + k.shape.wo // 2, :]  # (a pixel whose taps are all in the image)
+    counts = inside[:, 0].tolist()
+    assert bool((inside == inside[:, :1]).all()) and sum(counts) == c * f * f
+    item, tk = (8 if dtype == wl.BF16 else 4), tile[2]
+    slices = -(-f * f * -(-c // item) * item // tk)
+    assert max(counts) <= -(-slices // splits) * tk, counts
+    assert min(counts) > 0
