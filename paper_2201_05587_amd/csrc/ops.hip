@@ -326,6 +326,8 @@ int launched_plan(const PreparedOp &op, int count, tt_plan *plan)
         plan->wave_m = w.rows, plan->wave_n = w.columns, plan->eff_vec_a = plan->eff_vec_c = vc;
         return TT_LAUNCH_RECORD;
     }
+    if (plan->sketch == TT_SK_DWCONV && plan->variant_id >= 0 && dw_in_registers(op.d))
+        plan->sketch = TT_SK_DIRECT, plan->grid = kDwLargestDirect, plan->block = 256;
     if (plan->sketch == TT_SK_DIRECT && op.cls != TT_DWCONV_BIAS_RELU6) plan->grid = (int32_t)direct_workgroups(op.g, op.family, count);
     if (plan->sketch != TT_SK_MFMA || plan->variant_id < 0 || plan->variant_id >= kNumVariants) return TT_LAUNCH_RECORD;
     const Variant &v = kVariants[plan->variant_id];

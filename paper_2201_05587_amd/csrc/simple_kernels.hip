@@ -443,24 +443,24 @@ __global__ void __launch_bounds__(256) dw_direct_kernel(const DwArgs args, const
     const DwArgs g = with_set(args, sets, blockIdx.y);
     // idx walks the NHWC output: (image, p, q, channel)
     const int64_t total = (int64_t)g.planes * g.Ho * g.Wo;
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= total) return;
-    const int ch = (int)(idx % g.C);
-    const int64_t pix = idx / g.C;
-    const int q = (int)(pix % g.Wo), p = (int)((pix / g.Wo) % g.Ho);
-    const int img = (int)(pix / ((int64_t)g.Ho * g.Wo));
-    float acc = 0.0f;
-    for (int r = 0; r < 3; ++r) {
-        const int ih = p * g.stride_h + r - g.pad_h;
-        if (ih < 0 || ih >= g.H) continue;
-        for (int s = 0; s < 3; ++s) {
-            const int iw = q * g.stride_w + s - g.pad_w;
-            if (iw < 0 || iw >= g.W) continue;
-            acc = fmaf(g.x[(((int64_t)img * g.H + ih) * g.W + iw) * g.C + ch], g.w[(r * 3 + s) * g.C + ch], acc);
+    for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * 256) {
+        const int ch = (int)(idx % g.C);
+        const int64_t pix = idx / g.C;
+        const int q = (int)(pix % g.Wo), p = (int)((pix / g.Wo) % g.Ho);
+        const int img = (int)(pix / ((int64_t)g.Ho * g.Wo));
+        float acc = 0.0f;
+        for (int r = 0; r < 3; ++r) {
+            const int ih = p * g.stride_h + r - g.pad_h;
+            if (ih < 0 || ih >= g.H) continue;
+            for (int s = 0; s < 3; ++s) {
+                const int iw = q * g.stride_w + s - g.pad_w;
+                if (iw < 0 || iw >= g.W) continue;
+                acc = fmaf(g.x[(((int64_t)img * g.H + ih) * g.W + iw) * g.C + ch], g.w[(r * 3 + s) * g.C + ch], acc);
+            }
         }
+        if (g.bias) acc += g.bias[ch];
+        g.y[idx] = fminf(fmaxf(acc, 0.0f), 6.0f);
     }
-    if (g.bias) acc += g.bias[ch];
-    g.y[idx] = fminf(fmaxf(acc, 0.0f), 6.0f);
 }
 
 __global__ void __launch_bounds__(256) tile_map_dump_kernel(const TileMap map, int32_t *out)
@@ -600,10 +600,11 @@ int launch_gemv(const ContractArgs &args, const PointerSets &sets, const tt_plan
     return TT_OK;
 }
 
-// Workgroups that a depthwise record may name, by what a lane of them would keep in flight: input columns of its outputs times
-// planes per access where the record asks for neither an LDS patch nor unequal strides (`in_registers`), else outputs per row.
-// The general kernel is compiled for at most 256, 512 and 1024 threads, which leaves a lane 512, 256 and 128 registers; of
-// these sizes the compiler keeps everything in registers.
+// Workgroups that a depthwise record may name.  The general kernel is compiled for at most 256, 512 and 1024 threads, which leaves
+// a lane 512, 256 and 128 registers; of these sizes, by its outputs per row, the compiler keeps everything in registers.  Records
+// that ask for neither an LDS patch nor unequal strides (`in_registers`) run in windows of 256 threads whatever they name: their
+// bound, input columns of a thread's outputs times planes per access, only says which of them are records at all, so that stored
+// pools and the counts of a search stand.
 constexpr int dw_block_limit(int wave_m, int wave_n, int planes_per_lane, int stride, bool in_registers)
 {
     const auto built = [](int w) { return w == 1 || w == 2 || w == 4 || w == 7; };
@@ -670,10 +671,13 @@ template <int STR, int VC> int launch_windows_of(DwWindow w, const DwListEntry &
 
 // Records of one stage over a tensor within the 2 GiB offset range, strides 1 or 2: in windows, whose size the launch's own
 // decides, since a record's outputs per thread cost reads that no tile gets back (see dw_window_for).  An LDS patch (two stages)
-// and unequal strides are what the record says.
+// and unequal strides are what the record says.  More windows than they are counted in, which takes padding of many times the
+// image, go to the loop nest.
+bool dw_in_registers(const DwArgs &g) { return g.stages == 1 && g.stride_h == g.stride_w && (g.stride_h == 1 || g.stride_h == 2) && g.x_bytes != 0; }
+
 bool dw_windows(const DwArgs &g, int count, DwListEntry *e, DwWindow *w, int *vc)
 {
-    if (g.stages != 1) return false;
+    if (!dw_in_registers(g)) return false;
     *vc = g.C % 4 == 0 ? 4 : g.C % 2 == 0 ? 2 : 1;
     *w = dw_window_for((int64_t)g.planes / *vc * g.Ho * g.Wo * count, g.stride_h);
     return dw_entry(g, *vc, *w, e);
@@ -691,12 +695,9 @@ int launch_dwconv(const DwArgs &a, const PointerSets &sets, const tt_plan &plan,
         if (a.stride_h == 1) return vc == 4 ? launch_windows_of<1, 4>(w, e, sets, s) : vc == 2 ? launch_windows_of<1, 2>(w, e, sets, s) : launch_windows_of<1, 1>(w, e, sets, s);
         return vc == 4 ? launch_windows_of<2, 4>(w, e, sets, s) : vc == 2 ? launch_windows_of<2, 2>(w, e, sets, s) : launch_windows_of<2, 1>(w, e, sets, s);
     }
+    if (dw_in_registers(a)) return launch_dw_direct(a, sets, kDwLargestDirect, stream);
     const dim3 grid(plan.grid, sets.count), block(plan.block);
     const int lds = plan.lds_bytes;
-    if (a.eff_vec != 1) { // more windows than they are counted in, which takes padding of many times the image
-        const int64_t wgs = ((int64_t)a.planes * a.Ho * a.Wo + 255) / 256;
-        return wgs > INT32_MAX ? TT_ERR_UNSUPPORTED : launch_dw_direct(a, sets, (int)wgs, stream);
-    }
 #define TT_DW_CASE(WM_, WN_)                                                                                         \
     if (a.wave_m == WM_ && a.wave_n == WN_) {                                                                        \
         constexpr int LIMIT = dw_block_limit(WM_, WN_, 1, 1, false);                                                 \

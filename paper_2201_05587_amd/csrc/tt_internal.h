@@ -297,6 +297,10 @@ struct DwList {
     DwListEntry e[kMaxDwListed];
 };
 static_assert(sizeof(DwList) <= 4096, "");
+// Depthwise plans that windows are for, and workgroups of the loop nest for those of them that have too many (2^31 threads: the
+// runtime takes less than 2^32).
+bool dw_in_registers(const DwArgs &g);
+constexpr int kDwLargestDirect = 1 << 23;
 // Whether a launch of `count` entries runs in windows: the entry without its pointers, the window and the channels of a thread.
 bool dw_windows(const DwArgs &g, int count, DwListEntry *e, DwWindow *w, int *vc);
 // Fills in the part of an entry that the launch decides on; false: the entry is not one for a list (C not a multiple of four).

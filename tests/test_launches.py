@@ -27,3 +27,21 @@ def test_lds_is_enabled_for_the_kernel_that_runs():
     assert all(rc == api.TT_OK for rc, _ in done) and len(set(names)) == 2, names
     for rc, made in done:
         assert made[0]["lds"] > ENABLED and made[0]["enabled"] >= made[0]["lds"], done
+
+
+def depthwise(n, c, h, w, stride, pad):
+    return wl.CLS_DWCONV_BIAS_RELU6, wl.ConvShape(n, c, h, w, c, 3, 3, stride, stride, pad, pad, wl.F32)
+
+
+def test_more_windows_than_are_counted():
+    """Padding of many times the image: every record that applies runs, by the loop nest, in a grid that can be launched."""
+    call = depthwise(1, 165, 4, 4, 1, 3700)  # nine thousand million outputs
+    records = [None] + [api.make_schedule(wl.CLS_DWCONV_BIAS_RELU6, api.TT_SK_DWCONV, *r, 0, 1, 0, 1, 1, 1)
+                        for r in ((8, 28, 32, 1, 7), (8, 28, 64, 2, 7), (8, 16, 16, 2, 2))]
+    plans = [api.tt_schedule_apply(r, *call) for r in records if r is not None]
+    assert all(p.runnable() for p in plans) and max(p.block for p in plans) == 1024
+    for rec, (rc, made) in zip(records, launches([call + (r,) for r in records])):
+        plan, _ = api.tt_debug_launch(rec, *call)
+        assert rc == api.TT_OK and "dw_direct_kernel" in made[0]["name"], (rc, made)
+        assert made[0]["grid"] * made[0]["block"] < 1 << 32
+        assert (plan.sketch, plan.grid, plan.block) == (api.TT_SK_DIRECT, made[0]["grid"], made[0]["block"])
