@@ -816,14 +816,15 @@ __device__ __forceinline__ void write_row_piece(float *ws, void *out, const void
 }
 // Up to 8 outputs of such a row, out of line and with everything by value, for kernels that write few of them a thread.
 template <int DT>
-__device__ __noinline__ void write_row_in_pieces(float *ws, void *out, const void *bias, const void *res, bool partial, int act, int64_t at, int first,
-                                                 int count, f32x4 lo, f32x4 hi)
+__device__ __noinline__ void write_row_in_pieces(float *ws, void *out, const void *bias, const void *res, bool partial, bool has_bias, bool has_res, int act,
+                                                 int64_t at, int first, int count, f32x4 lo, f32x4 hi)
 {
-    const bool add = bias && !partial;
+    const bool add = has_bias && !partial;
+    const void *const more = has_res ? res : nullptr;
     const u32x4 none = {0u, 0u, 0u, 0u};
-    write_row_piece<DT>(ws, out, res, partial, act, at, count, lo, hi, add ? load_piece<DT>(bias, first, count) : none);
+    write_row_piece<DT>(ws, out, more, partial, act, at, count, lo, hi, add ? load_piece<DT>(bias, first, count) : none);
     if (DT == TT_F32 && count > 4)
-        write_row_piece<DT>(ws, out, res, partial, act, at + 4, count - 4, hi, hi, add ? load_piece<DT>(bias, first + 4, count - 4) : none);
+        write_row_piece<DT>(ws, out, more, partial, act, at + 4, count - 4, hi, hi, add ? load_piece<DT>(bias, first + 4, count - 4) : none);
 }
 
 // The bias of 8 columns as floats.

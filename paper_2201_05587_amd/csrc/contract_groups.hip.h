@@ -223,8 +223,8 @@ __device__ __forceinline__ void contract_groups_tile(std::conditional_t<LISTED, 
             unpack_bias<DT>(biasf, bias[p]);
             write_row_vector<DT>(g, ws, partial, at[p], first[p], lo, hi, biasf, res[p]);
         } else {
-            write_row_in_pieces<DT>(ws, g.out, g.has_bias ? g.bias : nullptr, g.has_res ? g.res : nullptr, partial, g.act, at[p], first[p],
-                                    g.N - first[p], lo, hi);
+            write_row_in_pieces<DT>(ws, g.out, g.bias, g.res, partial, g.has_bias, g.has_res, g.act, at[p], first[p],
+                                    min(8, g.N - first[p]), lo, hi);
         }
     }
 }
