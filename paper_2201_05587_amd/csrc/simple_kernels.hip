@@ -628,7 +628,7 @@ bool dw_entry(const DwArgs &g, int vc, DwWindow w, DwListEntry *e)
 {
     if (g.C % vc != 0 || g.stride_h != g.stride_w || (g.stride_h != 1 && g.stride_h != 2) || g.x_bytes == 0) return false;
     const int64_t columns = (g.Wo + w.columns - 1) / w.columns, strips = (g.Ho + w.rows - 1) / w.rows, threads = g.planes / vc * columns * strips;
-    if (threads >= 1ll << 30) return false;
+    if (threads >= 1ll << 30 || (int64_t)(g.planes / g.C) * g.Ho >= 1ll << 31) return false; // (rows of outputs, too, are counted in 32 bits)
     e->threads = (int32_t)threads;
     e->C = g.C, e->H = g.H, e->W = g.W, e->Ho = g.Ho, e->Wo = g.Wo, e->pad_h = g.pad_h, e->pad_w = g.pad_w, e->x_bytes = g.x_bytes;
     e->div_c = make_fastdiv((uint32_t)(g.C / vc)), e->div_cols = make_fastdiv((uint32_t)columns), e->div_rows = make_fastdiv((uint32_t)strips);
@@ -638,9 +638,12 @@ bool dw_entry(const DwArgs &g, int vc, DwWindow w, DwListEntry *e)
 // The window of a launch of `pieces` outputs of one thread's channels.  A larger one reads less and a smaller one has more threads,
 // and less code to fetch before the first load: 1 x 1 up to a workgroup per CU, 1 x 2 up to six, 4 x 2 from 80 on.  Unit stride, 1x1 /
 // 1x2 / 2x2 / 4x2 in us, and in rows of the record that a search chose: 57 k pieces 2.7 / 3.0 / 3.6 / 4.8, 3.2; 71 k 3.1 / 3.0 /
-// 3.6 / 4.8, 3.7; 368 k 5.6 / 4.5 / 4.5 / 5.1, 5.3; 442 k 6.1 / 5.1 / 4.5 / 5.1, -; 1.0 M 10.9 / 7.9 / 6.4 / 6.1, 9.7; 4.1 M 41.7 / 30.2
-// / 23.4 / 24.2, 41.6; 5.4 M 56 / 39 / 29.7 / 29.2, 39.5; 6.2 M 67 / 45 / 37.9 / 34.5, 48.3.  Stride 2, 1x1 / 1x2 / 2x2: 76 k 3.1 / 3.2 / 4.1, 3.6;
-// 326 k 5.0 / 4.6 / 4.9, 8.7; 469 k 6.7 / 5.7 / 5.2, 10.9; 1.4 M 21.0 / 19.4 / 19.0, 22.4.
+// 3.6 / 4.8, 3.7; 100 k 3.2 / 3.1 / 3.7 / 4.9; 202 k 4.4 / 3.8 / 3.8 / 5.0; 306 k 5.1 / 4.7 / 4.8 / 5.3; 368 k 5.6 / 4.5 / 4.5 / 5.1, 5.3; 390 k 5.6 /
+// 5.2 / 4.8 / 5.3; 406 k 6.1 / 5.1 / 4.5 / 5.0; 442 k 6.1 / 5.1 / 4.5 / 5.1, -; 609 k 7.8 / 5.8 / 5.4 / 5.8; 1.0 M 10.9 / 7.9 / 6.4 / 6.1, 9.7; 2.1 M
+// 20.3 / 14.9 / 12.0 / 12.4; 4.1 M 41.7 / 30.2 / 23.4 / 24.2, 41.6; 5.4 M 56 / 39 / 29.7 / 29.2, 39.5; 6.2 M 67 / 45 / 37.9 / 34.5, 48.3.  So 1x2 and
+// 2x2 are level from 200 to 370 thousand, and the last workgroup before the line loses 8 %; between 0.8 and 4 million 2x2 and 4x2 are
+// within 5 %, either way.  Stride 2, 1x1 / 1x2 / 2x2: 76 k 3.1 / 3.2 / 4.1, 3.6; 202 k 4.3 / 3.9 / 4.1; 326 k 5.0 / 4.6 / 4.9, 8.7; 390 k 5.6 / 5.5 / 5.2;
+// 469 k 6.7 / 5.7 / 5.2, 10.9; 609 k 9.5 / 8.7 / 8.6; 1.4 M 21.0 / 19.4 / 19.0, 22.4; 2.1 M 24.8 / 25.9 / 25.9, where the memory is the bound.
 DwWindow dw_window_for(int64_t pieces, int stride)
 {
     if (pieces <= 65536) return {1, 1};

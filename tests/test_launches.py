@@ -45,3 +45,13 @@ def test_more_windows_than_are_counted():
         assert rc == api.TT_OK and "dw_direct_kernel" in made[0]["name"], (rc, made)
         assert made[0]["grid"] * made[0]["block"] < 1 << 32
         assert (plan.sketch, plan.grid, plan.block) == (api.TT_SK_DIRECT, made[0]["grid"], made[0]["block"])
+
+
+def test_output_rows_that_no_window_counts():
+    """Rows of outputs beyond 2^31, over all images: a window would write at a negative row."""
+    for n, c, pad, window in ((65536, 1, 16384, True), (65536, 1, 16385, False), (65536, 2, 16385, False)):
+        call = wl.CLS_DWCONV_BIAS_RELU6, wl.ConvShape(n, c, 1, 1, c, 3, 3, 1, 1, pad, 1, wl.F32)
+        assert (n * call[1].ho < 1 << 31) == window
+        rec = api.make_schedule(wl.CLS_DWCONV_BIAS_RELU6, api.TT_SK_DWCONV, 8, 1, 32, 4, 1, 0, 1, 0, 1, 1, 1)
+        (rc, made), = launches([call + (rec,)])
+        assert rc == api.TT_OK and ("window" in made[0]["name"]) == window and ("dw_direct" in made[0]["name"]) != window
