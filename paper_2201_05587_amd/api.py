@@ -538,6 +538,11 @@ def tt_variant_info(variant_id: int):
     return list(info)
 
 
+def _odd_rows(plan: tt_plan, dtype: int) -> str:
+    """Whether the instance for rows of outputs that are no whole vectors runs, as a template argument."""
+    return str(plan.eff_vec_c != 8 if dtype == TT_BF16 else plan.eff_vec_c < 4).lower()
+
+
 def variant_name(plan: tt_plan, shape=None) -> str:
     """Name of the kernel a plan names, spelled like the demangled symbol rocprofv3 reports (launched_name: the one that a
     launch runs on).
@@ -553,7 +558,7 @@ def variant_name(plan: tt_plan, shape=None) -> str:
             return (f"tt::conv3x3_patch_kernel<{info[2]}, {info[3]}, {info[4]}, {info[5]}, {info[6]}, {stride}, "
                     f"{per_thread}>")
         if info[9] == 3:
-            return "tt::gemm_stream_kernel<" + ", ".join(str(info[i]) for i in (0, 2, 3, 4, 5, 6, 7)) + ">"
+            return "tt::gemm_stream_kernel<" + ", ".join(str(info[i]) for i in (0, 2, 3, 4, 5, 6, 7)) + f", {_odd_rows(plan, info[0])}>"
         if info[9]:
             return "tt::contract_async_kernel<" + ", ".join(str(v) for v in info[:8]) + ">"
         return "tt::contract_kernel<" + ", ".join(str(v) for v in info[:9]) + ">"
@@ -578,5 +583,5 @@ def launched_name(sched, cls, shape, count=1) -> str:
     if kernel == TT_LAUNCH_TAPS:
         return f"tt::contract_taps_kernel<{dtype}, {family}, {tm}, {tn}, {tk}, {wm}, {wn}, {mf}>"
     if kernel == TT_LAUNCH_ROWS:
-        return f"tt::conv_rows_kernel<{tm}, {tn}>"
+        return f"tt::conv_rows_kernel<{tm}, {tn}, {_odd_rows(plan, dtype)}>"
     return f"tt::contract_groups_kernel<{dtype}, {family}, {tm}, {tn}, {wm}, {wn}, {mf}>"

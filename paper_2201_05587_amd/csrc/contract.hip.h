@@ -864,6 +864,15 @@ template <int WN, int MF, typename Acc> __device__ __forceinline__ void stage_ba
     asm volatile("" ::: "memory"); // and the reads below stay behind them
 }
 
+// Whether rows of outputs are whole 16-byte vectors long.
+template <int DT> TT_HD bool whole_rows(const ContractArgs &g) { return DT == TT_BF16 ? g.eff_vec_c == 8 : g.eff_vec_c >= 4; }
+
+// Where a wave stages its bands.
+template <int WN, int MF> __device__ __forceinline__ float *staging(unsigned char *smem, int wave)
+{
+    return reinterpret_cast<float *>(smem) + wave * (MF * (WN + (MF == 32 ? 8 : 4)));
+}
+
 // The tile of a matrix whose rows are whole vectors long: the lane's 8 columns (fp32: 4 columns of two rows) need no further
 // checks and no loop.
 template <int DT, int TM, int WM, int WN, int MF, typename Acc, bool ALLOW, bool WAIT_LOADS>
@@ -974,8 +983,8 @@ __device__ __forceinline__ void write_tile(Acc (&acc)[WM / MF][WN / MF], const C
                                            unsigned char *smem, int wave, int lane, const BiasRegs<DT> &bias,
                                            const ResRegs<DT, TM, WM, WN, MF, ALLOW> &early)
 {
-    float *const stage = reinterpret_cast<float *>(smem) + wave * (MF * TileOut<TM, WM, WN, MF>::ESTRIDE);
-    if (__builtin_expect(!ANY_ROWS || (DT == TT_BF16 ? g.eff_vec_c == 8 : g.eff_vec_c >= 4), 1))
+    float *const stage = staging<WN, MF>(smem, wave);
+    if (__builtin_expect(!ANY_ROWS || whole_rows<DT>(g), 1))
         write_tile_whole<DT, TM, WM, WN, MF, Acc, ALLOW, WAIT_LOADS>(acc, g, tc, stage, wave, lane, bias, early);
     else
         write_tile_pieces<DT, TM, WM, WN, MF, Acc, WAIT_LOADS>(acc, g, tc, stage, wave, lane);
@@ -1003,9 +1012,22 @@ template <int DT, int FAM, int TM, int TN, int TK, int MF> struct StageLayout {
     static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
 };
 
+// Waves a SIMD that an instance is compiled for (1: as its workgroup needs).  A SIMD holds 512 vector registers a lane, and scalar
+// ones for eight waves of 80 (the trap handler takes 16 more of every wave).  The epilogue's rolled loop over odd rows keeps more
+// of either than the loops of a few instances do, which then ran a workgroup or a wave less: on whole rows too, without this -> with
+// (us): fp32 3x3, 78 -> 136 channels on 12 x 56x56, 64 x 64 x 16 in waves of 16 x 16 (81 scalars) 310 -> 221; products of 2048 x 512 x 256 (8),
+// 64 x 64 x 64 in such waves (81) 65 -> 51; bf16 3x3, 72 -> 136 on 12 x 56x56, 64 x 64 x 128 (172 registers) 40 -> 34; 32 x 16 x 64 (132), 128 -> 256 on 2 x 56x56, 42 -> 35, but up to 6 % slower in two stages.
+template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int AM> constexpr int waves_kept()
+{
+    constexpr bool SQUARE = TM == 64 && TN == 64;
+    if (DT == TT_F32 && WM * WN == 256) return (FAM == FAM_CONV && AM == 4 && TK == 16) || (FAM == FAM_GEMM_NN && SQUARE && TK == 64) ? 8 : 1;
+    if (DT == TT_BF16 && FAM == FAM_CONV && AM == 16) return SQUARE && WM * WN == 1024 && TK == 128 ? 3 : TM == 32 && TN == 16 && WM == 32 && TK == 64 ? 4 : 1;
+    return DT == TT_BF16 && FAM == FAM_GEMM_TN && SQUARE && WM * WN == 1024 && TK == 32 ? 6 : 1;
+}
+
 // AM = bytes per gathered load of the conv family (16 or the element size); 0 for the others.
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF, int AM>
-__global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) contract_kernel(const ContractArgs args, const PointerSets sets)
+__global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64, (waves_kept<DT, FAM, TM, TN, TK, WM, WN, AM>())) contract_kernel(const ContractArgs args, const PointerSets sets)
 {
     const ContractArgs g = with_set(args, sets, blockIdx.y);
     using E = typename ElemOf<DT>::type;
@@ -1120,8 +1142,8 @@ __global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) contract_kernel(co
     };
 
     // a slice's global loads are held in registers here as well: a smaller budget, and none to spare
-    // for the workgroups of 16 waves (128 registers per lane)
-    constexpr int GROUP = steps_per_group(NI + NJ, NKS, THREADS > 512 ? 16 : 48);
+    // for the workgroups of 16 waves (128 registers per lane; 64 where two of them share a CU)
+    constexpr int GROUP = steps_per_group(NI + NJ, NKS, THREADS > 512 ? (B_KMAJOR && waves_kept<DT, FAM, TM, TN, TK, WM, WN, AM>() == 8 ? 8 : 16) : 48);
     auto k_group = [&](const unsigned char *sr, const unsigned char *sc, int ks0) {
         u32x4 rf[GROUP][NI], cf[GROUP][NJ];
 #pragma unroll
@@ -1521,8 +1543,9 @@ __device__ __forceinline__ void contract_async_tile(const ContractArgs &g, int32
         k_loop(std::false_type{});
     write_tile<DT, TM, WM, WN, MF>(acc, g, tc, smem, wave, lane, bias, res_early);
 }
+// (six waves a SIMD, see waves_kept: 92 registers for 76 without; products of 2048 x 512 x 2048 in tiles of 64 x 32 13.7 -> 13.0 us)
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF>
-__global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) contract_async_kernel(const ContractArgs args, const PointerSets sets)
+__global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64, DT == TT_BF16 && TK == 32 && MF == 32 && WM * WN == 1024 ? 6 : 1) contract_async_kernel(const ContractArgs args, const PointerSets sets)
 {
     contract_async_tile<DT, FAM, TM, TN, TK, WM, WN, MF, false>(with_set(args, sets, blockIdx.y), (int32_t)blockIdx.x);
 }

@@ -45,8 +45,9 @@ __device__ __forceinline__ int entry_of(const ContractList &list, int wg, int *f
     return e;
 }
 
+// (waves a SIMD as without the epilogue of odd rows, see waves_kept: 140 registers for 124 without, 68 for 64)
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF>
-__global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) contract_list_kernel(const ContractList list)
+__global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64, DT == TT_BF16 ? (TM == 64 && TN == 128 && TK == 32 ? 4 : 1) : (TM == 16 && TN == 32 ? 8 : 1)) contract_list_kernel(const ContractList list)
 {
     int first;
     const ListEntry &e = list.e[entry_of(list, (int)blockIdx.x, &first)];

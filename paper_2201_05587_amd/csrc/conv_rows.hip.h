@@ -61,7 +61,9 @@ template <int TM, int TN> TT_HD RowsLayout rows_layout(const ContractArgs &g)
 // product off by less than 2^-22 of n / d.
 __device__ __forceinline__ int divide_small(int n, float inv_d) { return (int)(((float)n + 0.5f) * inv_d); }
 
-template <int TM, int TN>
+// ODD: rows of outputs that are no whole 16-byte vectors.  Two instances: with both epilogues in one, the kernel needs more registers
+// than the workgroups that rows_grid counts on leave it (130 for 512 threads, two of which have 128; 114 and 118 apart).
+template <int TM, int TN, bool ODD>
 __global__ void __launch_bounds__((RowsShape<TM, TN>::THREADS)) conv_rows_kernel(const ContractArgs args, const PointerSets sets)
 {
     const ContractArgs g = with_set(args, sets, blockIdx.y);
@@ -227,8 +229,13 @@ __global__ void __launch_bounds__((RowsShape<TM, TN>::THREADS)) conv_rows_kernel
         else
             k_loop(std::false_type{});
         // (staged where the rows were, from when all waves have read them; the next rows are waited for before the first store)
-        ResRegs<DT, TM, WM, WN, MF, false> no_res;
-        write_tile<DT, TM, WM, WN, MF, typename M::Acc, false, true>(acc, g, tc, patches + buffer * l.buffer, wave, lane, bias, no_res);
+        float *const stage = staging<WN, MF>(patches + buffer * l.buffer, wave);
+        if constexpr (ODD) {
+            write_tile_pieces<DT, TM, WM, WN, MF, typename M::Acc, true>(acc, g, tc, stage, wave, lane);
+        } else {
+            ResRegs<DT, TM, WM, WN, MF, false> no_res;
+            write_tile_whole<DT, TM, WM, WN, MF, typename M::Acc, false, true>(acc, g, tc, stage, wave, lane, bias, no_res);
+        }
     }
 }
 
@@ -259,10 +266,11 @@ template <int TM, int TN> int rows_grid(const ContractArgs &args, int count, int
 template <int TM, int TN> int launch_rows(const ContractArgs &args, const PointerSets &sets, void *stream)
 {
     using S = RowsShape<TM, TN>;
-    auto kern = conv_rows_kernel<TM, TN>;
+    const bool odd = !whole_rows<TT_BF16>(args);
+    auto kern = odd ? conv_rows_kernel<TM, TN, true> : conv_rows_kernel<TM, TN, false>;
     const int lds = rows_lds<TM, TN>(args);
-    static DynamicLdsLimit limit; // per kernel instance
-    if (const int rc = limit.raise_to(reinterpret_cast<const void *>(kern), lds); rc != TT_OK) return rc;
+    static DynamicLdsLimit limits[2]; // per kernel instance
+    if (const int rc = limits[odd].raise_to(reinterpret_cast<const void *>(kern), lds); rc != TT_OK) return rc;
     hipLaunchKernelGGL(kern, dim3(rows_grid<TM, TN>(args, sets.count, lds), sets.count), dim3(S::THREADS), lds, static_cast<hipStream_t>(stream), args, sets);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? TT_OK : note_hip_error((int)e, "conv_rows_kernel launch");

@@ -22,7 +22,9 @@ template <int DT, int TM, int TN, int TK, int WM, int WN, int MF> struct StreamL
     static constexpr int bytes(int k_tiles) { return k_tiles * (TN + 2 * TM) * RB + EPI_BYTES; }
 };
 
-template <int DT, int TM, int TN, int TK, int WM, int WN, int MF>
+// ODD: rows of outputs that are no whole vectors.  Instances of their own: with both epilogues in one the kernel took up to 1.19 times
+// as long on whole rows (fp32, 12544 x 512 x 128 in tiles of 64 x 64 32 -> 27 us apart).
+template <int DT, int TM, int TN, int TK, int WM, int WN, int MF, bool ODD>
 __global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) gemm_stream_kernel(const ContractArgs args, const PointerSets sets)
 {
     const ContractArgs g = with_set(args, sets, blockIdx.y);
@@ -85,7 +87,7 @@ __global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) gemm_stream_kernel
         __syncthreads();
         request_a(tile_m + per, buf ^ 1);
         ResRegs<DT, TM, WM, WN, MF, true> res_early;
-        load_res_early(res_early, g, tc, wave, lane);
+        if constexpr (!ODD) load_res_early(res_early, g, tc, wave, lane);
 
         typename M::Acc acc[NI][NJ];
 #pragma unroll
@@ -112,7 +114,10 @@ __global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) gemm_stream_kernel
         }
         // the staging region is this kernel's own; the requests of the next tile are waited for inside,
         // before the first store (stores issued after a request would hide it from the counter)
-        write_tile<DT, TM, WM, WN, MF, typename M::Acc, true, true>(acc, g, tc, lds_stage, wave, lane, bias, res_early);
+        if constexpr (ODD)
+            write_tile_pieces<DT, TM, WM, WN, MF, typename M::Acc, true>(acc, g, tc, staging<WN, MF>(lds_stage, wave), wave, lane);
+        else
+            write_tile_whole<DT, TM, WM, WN, MF, typename M::Acc, true, true>(acc, g, tc, staging<WN, MF>(lds_stage, wave), wave, lane, bias, res_early);
     }
 }
 
@@ -121,13 +126,14 @@ __global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) gemm_stream_kernel
 template <int DT, int TM, int TN, int TK, int WM, int WN, int MF>
 int launch_gemm_stream(const ContractArgs &args, const PointerSets &sets, int tiles, int lds_bytes, void *stream)
 {
-    auto kern = gemm_stream_kernel<DT, TM, TN, TK, WM, WN, MF>;
+    const bool odd = !whole_rows<DT>(args);
+    auto kern = odd ? gemm_stream_kernel<DT, TM, TN, TK, WM, WN, MF, true> : gemm_stream_kernel<DT, TM, TN, TK, WM, WN, MF, false>;
     (void)tiles;
     if (args.batch != 1 || args.map.eff_split_k != 1 || args.K % TK || args.map.k_tiles != args.K / TK || lds_bytes <= 0 ||
         lds_bytes > 160 * 1024)
         return TT_ERR_UNSUPPORTED;
-    static DynamicLdsLimit limit; // per kernel instance
-    if (const int rc = limit.raise_to(reinterpret_cast<const void *>(kern), lds_bytes); rc != TT_OK) return rc;
+    static DynamicLdsLimit limits[2]; // per kernel instance
+    if (const int rc = limits[odd].raise_to(reinterpret_cast<const void *>(kern), lds_bytes); rc != TT_OK) return rc;
     constexpr int THREADS = (TM / WM) * (TN / WN) * 64;
     const int fit = std::min(4, 160 * 1024 / lds_bytes);
     const int per = std::max(1, std::min(args.map.tiles_m, compute_units() * fit / (args.map.tiles_n * sets.count)));

@@ -55,3 +55,16 @@ def test_output_rows_that_no_window_counts():
         rec = api.make_schedule(wl.CLS_DWCONV_BIAS_RELU6, api.TT_SK_DWCONV, 8, 1, 32, 4, 1, 0, 1, 0, 1, 1, 1)
         (rc, made), = launches([call + (rec,)])
         assert rc == api.TT_OK and ("window" in made[0]["name"]) == window and ("dw_direct" in made[0]["name"]) != window
+
+
+def test_rows_of_outputs_choose_the_instance():
+    """Persistent kernels have an instance for rows that are whole 16-byte vectors and one for all others."""
+    calls, odd = [], []
+    for n in (64, 66, 72, 96, 100, 131):
+        calls.append((1, wl.ConvShape(4, 3, 64, 64, n, 7, 7, 2, 2, 3, 3, wl.BF16), mfma(1, 128, 32, 32, 32, 32, 16, 2, 8)))
+        calls.append((wl.CLS_DENSE_ADD, wl.GemmShape(1, 5000, n, 128, 1, wl.BF16), mfma(wl.CLS_DENSE_ADD, 64, 64, 64, 32, 32, 16, 7, 8)))
+        calls.append((wl.CLS_DENSE_ADD, wl.GemmShape(1, 5000, n, 128, 1, wl.F32), mfma(wl.CLS_DENSE_ADD, 64, 64, 32, 32, 32, 16, 7, 4)))
+        odd += [n % 8 != 0, n % 8 != 0, n % 4 != 0]
+    for (cls, shape, rec), is_odd, (rc, made) in zip(calls, odd, launches(calls)):
+        assert rc == api.TT_OK and made[0]["name"] == api.launched_name(rec, cls, shape)
+        assert made[0]["name"].startswith(("tt::conv_rows_kernel<", "tt::gemm_stream_kernel<")) and made[0]["name"].endswith(f", {str(is_odd).lower()}>")
