@@ -28,7 +28,7 @@ int kernel_contract(const ContractArgs &args, int count, int grid)
         if (rows_shape(args, count).grid > 0) return TT_LAUNCH_ROWS;
     }
     if constexpr (taps_built<DT, FAM, TM, TN, TK, WM, WN, AM>())
-        if (taps_apply<DT, FAM>(args)) return TT_LAUNCH_TAPS;
+        if (taps_apply<DT, FAM>(args, (int64_t)grid * count, DT == TT_F32 && TK == 16 && WM * WN == 256 && TM * TN == 1024)) return TT_LAUNCH_TAPS;
     return TT_LAUNCH_RECORD;
 }
 template <int DT, int FAM, int TM, int TN, int TK, int WM, int WN, int MF>

@@ -68,3 +68,17 @@ def test_rows_of_outputs_choose_the_instance():
     for (cls, shape, rec), is_odd, (rc, made) in zip(calls, odd, launches(calls)):
         assert rc == api.TT_OK and made[0]["name"] == api.launched_name(rec, cls, shape)
         assert made[0]["name"].startswith(("tt::conv_rows_kernel<", "tt::gemm_stream_kernel<")) and made[0]["name"].endswith(f", {str(is_odd).lower()}>")
+
+
+def test_tiles_of_one_item_a_lane_walk_by_taps_where_they_are_few():
+    """Fp32 slices of 16 elements in four waves of 16 x 16: from 768 workgroups on, and long reductions, along the run."""
+    def calls_of(tile, m, n, c, f, split=1, stages=2):
+        cls, shape = (1, wl.ConvShape(1, c, m, 32, n, f, f, 1, 1, f // 2, f // 2, wl.F32)) if f else product(m * 32, n, c, wl.F32)
+        return cls, shape, mfma(cls, *tile, 16, stages, 4, split)
+    few, short = (32, 32, 16, 16, 16), (64, 16, 16, 16, 16)
+    cases = [(calls_of(few, 64, 352, 57, 3), True), (calls_of(few, 64, 384, 57, 3), False), (calls_of(few, 64, 384, 55, 3), True), (calls_of(few, 64, 192, 131, 3, 2), False),
+             (calls_of(few, 64, 192, 109, 3, 2), True), (calls_of(short, 128, 192, 57, 3), False), (calls_of(short, 128, 176, 57, 3), True), (calls_of(few, 64, 384, 131, 0), False),
+             (calls_of(few, 64, 384, 127, 0), True), (calls_of((32, 32, 32, 16, 16), 64, 384, 57, 3), True), (calls_of((16, 16, 16, 16, 16), 64, 384, 57, 3), True)]
+    for (call, taps), (rc, made) in zip(cases, launches([c for c, _ in cases])):
+        assert rc == api.TT_OK and made[0]["name"].startswith("tt::contract_taps_kernel<" if taps else "tt::contract_kernel<"), (call, made)
+        assert (api.tt_debug_launch(call[2], *call[:2])[1] == api.TT_LAUNCH_TAPS) == taps

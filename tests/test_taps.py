@@ -84,7 +84,7 @@ def test_which_tiles_walk_by_taps():
         dtype, family, tm, tn, tk, wm, wn, mf, bytes_, pipeline = api.tt_variant_info(v)[:10]
         if pipeline != 0 or family == 2 or bytes_ == 16:
             continue
-        k = conv(dtype, 8, 511, 28, 28, 256, 3, 1, 1) if family == 0 else product(dtype, 1, 3000, 520, 511)
+        k = conv(dtype, 3, 511, 28, 28, 256, 3, 1, 1) if family == 0 else product(dtype, 1, 1300, 520, 511)
         rec = record(k.cls, dtype, tm, tn, tk, wm, wn, 1, mfma=mf)
         assert api.tt_schedule_apply(rec, k.cls, k.shape).variant_id == v
         waves = tm * tn // (wm * wn)
