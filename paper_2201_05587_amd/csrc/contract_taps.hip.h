@@ -237,10 +237,10 @@ __global__ void __launch_bounds__((TM / WM) * (TN / WN) * 64) contract_taps_kern
 // 22.6, 19 24.8 -> 22.9.  Others, under the record a search chose: bf16 334 -> 176 channels on 3 x 107x107 160 -> 102, 721 -> 236 on
 // 18 x 32x32 222 -> 162, 98 -> 16 on 3 x 10x8 stride 2 21.5 -> 14.8; fp32 842 -> 16 on 10 x 42x55 434 -> 303, 650 -> 384, 5x5, on 2 x
 // 19x15 141 -> 113; products of 26 x 1792 x 220 5.4 -> 4.9, 51 x 3040 x 1722 11.4 -> 10.8.
-// Four waves of 16 x 16 in fp32 slices of 16 elements hold one item a lane and have four products a slice; two slices in flight take
-// the registers of the eighth wave of a SIMD there, which counts from three workgroups a CU and reductions that the walk along the run
-// is not short of on.  Run -> taps: 3x3, 445 -> 16-column tiles, 798 workgroups 222 -> 241, 740 of K = 4302 209 -> 192; 213 -> 1362 of
-// K = 1917 151 -> 178, 1411 of K = 315 33.0 -> 27.7; products of K = 151, 12369 workgroups 78 -> 96, of K = 107, 4140 23.0 -> 22.3.
+// one_item: fp32 tiles of four 16 x 16 waves over slices of 16 elements, one item a lane and four products a wave and slice.  There
+// the second slice in flight costs the eighth wave of a SIMD, which tells from three workgroups a CU on, unless the reduction is short.
+// Run -> taps (us): 3x3 over 478 channels, 740 workgroups 209 -> 192; over 445, 798 222 -> 241; over 213, 1362 151 -> 178; over 35,
+// 1411 33.0 -> 27.7; products over 107, 4140 workgroups 23.0 -> 22.3; over 151, 12369 78 -> 96.
 template <int DT, int FAM> bool taps_apply(const ContractArgs &g, int64_t workgroups, bool one_item)
 {
     if (one_item && workgroups >= 768 && std::min<int64_t>((int64_t)g.map.k_iters * g.map.tile_k, g.K) >= (FAM == FAM_CONV ? 512 : 128)) return false;
